@@ -78,7 +78,7 @@ struct RegionPlan {
     uint32_t stretch;        // stretches of G sorted positions a lane group of R1 walks (1 .. kStretch)
     uint32_t p_quota;        // rows of P per lane group of R1
     float *P;                // [lane groups of R1 * p_quota][d] summed rows of the runs longer than one (d: the widest table's)
-    uint32_t *counts, *starts;   // [NR], [NR + 1]; after R3 counts holds the order of the regions for R5
+    uint32_t *counts, *starts;   // [NR], [NR + 1]; with fullest_first counts holds the order of the regions for R5 after R3
     uint32_t *wg_first;      // [bin_blocks][NR]: R2 -> R4, see region_bin_kernel
     uint2 *rec;              // [<= 2 * n * C] (offset, source block | part flag)
     uint32_t *rec_tg;        // sign on only
@@ -411,109 +411,87 @@ __global__ __launch_bounds__(kBinBlock) void region_bin_kernel(Params p, RegionP
     }
 }
 
-// R3: one workgroup.  starts: exclusive prefix of counts, grand total in starts[NR];
-// then the order in which R5 takes the regions.
-constexpr uint32_t kScanPer = kMaxRegions / 1024u;
+// R3: one workgroup.  starts: exclusive prefix of counts, grand total in starts[NR]; then the order in
+// which R5 takes the regions (it overwrites counts, which nothing reads after this kernel; every thread
+// has its counts in registers by then).
+//
+// A thread owns up to kScanPer consecutive regions, four per load, all requested at once, and adds them
+// up in registers, so that the workgroup scans one value per thread: the kernel is two trips to memory
+// and one block scan.  (One wavefront scan per 64 regions instead, 32 of them in flight per wavefront,
+// spent its time in 192 lane exchanges per thread: 18.9 us for 3052 regions and 16.9 for 30518; now
+// 10.1 and 9.8.)
+constexpr uint32_t kScanThreads = 1024u;
+constexpr uint32_t kScanPer = kMaxRegions / kScanThreads;
+static_assert(kScanPer % 4u == 0, "R3 reads whole vectors of four counts");
 
-// Exclusive prefix sums over kMaxRegions values in index order, by one workgroup of 1024 threads.
-// Thread t holds elements t, t + 1024, ... (coalesced loads, all requested at once); every chunk of
-// 1024 is scanned inside the wavefronts by shuffles, and the 32 x 16 (chunk, wavefront) totals are
-// scanned once more to give every wavefront its base in every chunk.  Returns the grand total.
-__device__ __forceinline__ uint32_t block_scan(const uint32_t (&c)[kScanPer], uint32_t (&excl)[kScanPer],
-                                               uint32_t *base /* [kScanPer * 16] */, uint32_t *upper /* [8] */)
+__global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
 {
+    __shared__ uint32_t wave_sum[kScanThreads / 64u];
+    __shared__ uint32_t cls_n[32], cls_at[32];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    // regions per thread: a multiple of four, the same for all
+    const uint32_t per = (((s.NR + kScanThreads - 1u) / kScanThreads) + 3u) & ~3u;
+    const uint32_t first = t * per;
+    uint32_t c[kScanPer], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kScanPer; k += 4u) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (k < per && first + k < s.NR) v = *reinterpret_cast<const uint4 *>(s.counts + first + k);   // (the array is padded to whole vectors)
+        c[k] = v.x; c[k + 1u] = v.y; c[k + 2u] = v.z; c[k + 3u] = v.w;
+    }
 #pragma unroll
     for (uint32_t k = 0; k < kScanPer; ++k) {
-        uint32_t v = c[k];
-#pragma unroll
-        for (uint32_t off = 1; off < 64u; off <<= 1) {
-            const uint32_t up = __shfl_up(v, off);
-            if (lane >= off) v += up;
-        }
-        excl[k] = v - c[k];
-        if (lane == 63u) base[k * 16u + wave] = v;
+        if (k >= per || first + k >= s.NR) c[k] = 0;
+        sum += c[k];
     }
-    __syncthreads();
-    // exclusive scan of the 512 totals in (chunk, wavefront) order, by the first 512 threads
-    uint32_t x = 0, xi = 0;
-    if (t < kScanPer * 16u) {
-        x = base[t];
-        xi = x;
+    if (t < 32u) cls_n[t] = 0;
+    uint32_t incl = sum;
 #pragma unroll
-        for (uint32_t off = 1; off < 64u; off <<= 1) {
-            const uint32_t up = __shfl_up(xi, off);
-            if (lane >= off) xi += up;
-        }
-        if (lane == 63u) upper[wave] = xi;
+    for (uint32_t off = 1; off < 64u; off <<= 1) {
+        const uint32_t up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
     }
+    if (lane == 63u) wave_sum[wave] = incl;
     __syncthreads();
-    uint32_t before = 0, total = 0;
+    uint32_t at = incl - sum, total = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < 8u; ++w) {
-        const uint32_t u = upper[w];
-        before += w < wave ? u : 0u;
-        total += u;
+    for (uint32_t w = 0; w < kScanThreads / 64u; ++w) {
+        const uint32_t x = wave_sum[w];
+        at += w < wave ? x : 0u;
+        total += x;
     }
-    if (t < kScanPer * 16u) base[t] = before + xi - x;
-    __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < kScanPer; ++k) excl[k] += base[k * 16u + wave];
-    __syncthreads();    // base and upper may be reused
-    return total;
-}
-
-__global__ __launch_bounds__(1024) void region_scan_kernel(RegionPlan s)
-{
-    __shared__ uint32_t base[kScanPer * 16u];
-    __shared__ uint32_t upper[8];
-    const uint32_t t = threadIdx.x;
-    uint32_t c[kScanPer], at[kScanPer];
-#pragma unroll
-    for (uint32_t k = 0; k < kScanPer; ++k) c[k] = k * 1024u + t < s.NR ? s.counts[k * 1024u + t] : 0u;
-    const uint32_t total = block_scan(c, at, base, upper);
-#pragma unroll
-    for (uint32_t k = 0; k < kScanPer; ++k) {
-        const uint32_t i = k * 1024u + t;
-        if (i < s.NR) {
-            s.starts[i] = at[k];
+    for (uint32_t k = 0; k < kScanPer; k += 4u) {
+        const uint4 v = make_uint4(at, at + c[k], at + c[k] + c[k + 1u], at + c[k] + c[k + 1u] + c[k + 2u]);
+        at = v.w + c[k + 3u];
+        if (k < per && first + k < s.NR) {
+            if (first + k + 4u <= s.NR) *reinterpret_cast<uint4 *>(s.starts + first + k) = v;
+            else {
+                s.starts[first + k] = v.x;
+                if (first + k + 1u < s.NR) s.starts[first + k + 1u] = v.y;
+                if (first + k + 2u < s.NR) s.starts[first + k + 2u] = v.z;
+            }
         }
     }
     if (t == 0) s.starts[s.NR] = total;
 
-    // Order in which R5 takes the regions (it overwrites counts, which nothing reads after this
-    // kernel; every thread has its counts in registers by now).  With few regions per workgroup
-    // slot the ones the frequent tokens hit, which take several times the average, must not end up
-    // as the tail of the launch: fullest first, by power-of-two size class.  With many regions per
-    // slot the tails even out and the address order is as good or better.
-    if (!s.fullest_first) {
+    // The order for R5.  With few regions per workgroup slot the ones the frequent tokens hit, which
+    // take several times the average, must not end up as the tail of the launch: fullest first, by
+    // power-of-two size class.  With many regions per slot the tails even out and R5 goes by address.
+    if (!s.fullest_first) return;
 #pragma unroll
-        for (uint32_t k = 0; k < kScanPer; ++k) {
-            if (k * 1024u + t < s.NR) s.counts[k * 1024u + t] = k * 1024u + t;
-        }
-        return;
-    }
-    __shared__ uint32_t cls_n[32], cls_at[32];
-    if (t < 32u) cls_n[t] = 0;
+    for (uint32_t k = 0; k < kScanPer; ++k)
+        if (k < per && first + k < s.NR) atomicAdd(&cls_n[31 - __clz((int)(c[k] | 1u))], 1u);
     __syncthreads();
-#pragma unroll
-    for (uint32_t k = 0; k < kScanPer; ++k) {
-        if (k * 1024u + t < s.NR) atomicAdd(&cls_n[31 - __clz((int)(c[k] | 1u))], 1u);
-    }
-    __syncthreads();
-    if (t == 0) {
+    if (t < 32u) {
         uint32_t a = 0;
-        for (int cls = 31; cls >= 0; --cls) {
-            cls_at[cls] = a;
-            a += cls_n[cls];
-        }
+        for (uint32_t cls = t + 1u; cls < 32u; ++cls) a += cls_n[cls];
+        cls_at[t] = a;
     }
     __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < kScanPer; ++k) {
-        const uint32_t i = k * 1024u + t;
-        if (i < s.NR) s.counts[atomicAdd(&cls_at[31 - __clz((int)(c[k] | 1u))], 1u)] = i;
-    }
+    for (uint32_t k = 0; k < kScanPer; ++k)
+        if (k < per && first + k < s.NR) s.counts[atomicAdd(&cls_at[31 - __clz((int)(c[k] | 1u))], 1u)] = first + k;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -681,7 +659,7 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(8,
     constexpr int kRecBatch = reduce_batch<SIGN, GATHER>();
     constexpr int kPer = (kRecBatch + kReduceBlock - 1) / kReduceBlock;     // records per thread and round
     extern __shared__ float acc[];  // 2^r_shift floats, then the batch staging area
-    const uint32_t r = GATHER ? blockIdx.x : s.counts[blockIdx.x];     // records path, after R3: the regions, fullest first
+    const uint32_t r = (GATHER || !s.fullest_first) ? blockIdx.x : s.counts[blockIdx.x];     // records path, few regions: fullest first (R3)
     if (r >= s.NR) return;
     uint32_t rb = 0, re = 0;
     if constexpr (!GATHER) {
