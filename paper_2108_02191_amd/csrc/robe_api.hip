@@ -404,11 +404,23 @@ int launch_radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint
 // 0.24 ms; no gain from 160 MB on, a loss from 400 MB on).  Larger arrays are streamed.
 const uint64_t kKeepArrayMax = 1ull << 25;
 
+// Regions with few records are taken by region_small_kernel, one wavefront each.  Its time follows the
+// records (0.26 ns each), that of region_reduce_kernel the array (8 ns per 8192 slots) and the records
+// (0.1 ns), so the batch's blocks per 8192 slots decide.  Whole step, small against one workgroup per
+// region, at 17 / 35 / 70 / 102 blocks: 190 / 277 / 426 / 555 against 333 / 396 / 524 / 594 us (250 M
+// slots, d = 128, Z = 32); at 31 / 62 / 124: 131 / 184 / 276 against 147 / 172 / 239 us (70 M slots).
+const uint64_t kSmallMostBlocks = 64;
+// Those regions may then be larger, which makes the record kernels cheaper: up to kSmallFullest blocks a
+// region (two lanes' worth is 128 records) and no fewer regions than there are wavefront slots.  250 M
+// slots, 133 K tokens: 190 us with 2^13 floats, 177 with 2^14, 176 with 2^15; 17 K tokens: 114, 97, 89.
+const uint64_t kSmallFullest = 96, kSmallLeastRegions = 7500;
+
 struct BwdPlan {
     bool dedup;          // sort the tokens and combine identical ones
     bool regions;        // ... and then sort the blocks by destination region instead of using float atomics
     bool spill_rows;     // ... with room in LDS for a row of Z floats per lane group of the reduce kernel
     bool gather;         // ... and the reduce kernel finds its blocks in the sorted token list (no record kernels)
+    uint32_t crowded_most;   // regions only, small_cap: at most this many regions are left to the kernel with one workgroup per region
     bool window_sort;    // atomics route after a sort on few key bits: the combine kernel orders each wavefront's positions itself
     Layout lay;
     robe_hash_t eff;     // the instance the kernels after the key kernel run on: the caller's, or (Z > d) its one-chunk form
@@ -528,6 +540,7 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     // No record kernels, no record storage, any number of regions.  options->region_records asks for
     // either variant.
     uint32_t shift = 0;
+    bool small = false;
     {
         const uint32_t gshift = opt.region_shift ? (uint32_t)opt.region_shift : 13u;
         const uint64_t R = 1ull << gshift, kmax = ((uint64_t)ROBE_PRIME - 1) / h->m, NE = C * (kmax + 3);
@@ -549,6 +562,11 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     }
     if (!pl.gather) {
         shift = pick_region_shift(h, opt.region_shift);
+        small = n * C * 8192u <= h->m * kSmallMostBlocks;
+        if (small && shift != 0 && opt.region_shift == 0) {
+            auto regions_at = [&](uint32_t sh) { return (h->m + (1ull << sh) - 1) >> sh; };
+            while (shift < 15 && regions_at(shift + 1) >= kSmallLeastRegions && n * C <= regions_at(shift + 1) * kSmallFullest) ++shift;
+        }
         if (shift == 0 || shift < grp_shift || (1u << (shift - grp_shift)) < h->Z) return pl;   // a slice of the region must hold one block
     }
     const uint64_t NR = (h->m + (1ull << shift) - 1) >> shift;
@@ -612,6 +630,12 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     r.keep_rows = bags ? 1u : 0u;
     // the slots the tokens can reach, against the array: below a quarter, most 64-byte granules stay untouched
     r.sparse_regions = (uint64_t)n * h->d < h->m / 4 ? 1u : 0u;
+    // few records per region (at most: repeated tokens leave one record per run): one wavefront per region
+    if (small) {
+        r.small_cap = robe::kSmallRegion;
+        const uint64_t crowded = rec_per_block * n * C / (robe::kSmallRegion + 1u);      // no more regions than that can hold more
+        pl.crowded_most = (uint32_t)(crowded < NR ? crowded : NR);
+    }
     pl.spill_rows = (uint64_t)(512u / lg) * h->Z <= robe::kSpillFloats;
     // (the reduce kernel of the gather variant reads keys, src_row and run_tg eight positions at a
     // time: every such array is padded to whole chunks)
@@ -633,7 +657,7 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
         pl.off_dir = off;  off = align_up(off + ((size_t)r.dir_buckets + 1) * 4, 256);
     } else {
         pl.off_counts = off;  off = align_up(off + NR * 4, 256);
-        pl.off_starts = off;  off = align_up(off + (NR + 1) * 4, 256);
+        pl.off_starts = off;  off = align_up(off + (NR + 2) * 4, 256);
         pl.off_wg_first = off; off = align_up(off + (size_t)r.bin_blocks * NR * 4, 256);
         pl.off_rec = off;     off = align_up(off + rec_per_block * n * C * 8, 256);
         pl.off_rec_tg = off;  if (h->use_sign) off = align_up(off + rec_per_block * n * C * 4, 256);
@@ -740,6 +764,8 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         robe::RegionPlan r = pl.rp;
         r.keys = keys_out;
         r.keep_array = (rule != 0 && h->m <= kKeepArrayMax) ? 1u : 0u;
+        const int vec_ok = aligned(grad_array, 16) && (rule != 1 || aligned(state, 16)) ? 1 : 0;
+        if (!vec_ok) r.small_cap = 0;     // region_small_kernel reads and writes whole vectors
         const float scale = rule == 2 ? -lr : (rule == 0 ? 1.0f : lr);    // what the reduce kernel gets as lr
         r.head = pl.gather ? nullptr : reinterpret_cast<uint8_t *>(ws + pl.off_head);
         r.src_row = reinterpret_cast<uint32_t *>(ws + pl.off_src_row);
@@ -807,8 +833,7 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
 
         // R5: one workgroup per region
         const size_t lds_red = robe::reduce_lds_bytes(r.r_shift, sign, pl.gather, pl.spill_rows);
-        const int vec_ok = aligned(grad_array, 16) && (rule != 1 || aligned(state, 16)) ? 1 : 0;
-        const dim3 rgrid(r.NR), rblock(robe::kReduceBlock);
+        const dim3 rgrid(r.small_cap ? pl.crowded_most : r.NR), rblock(robe::kReduceBlock);
         const bool canon = opt.reproducible;
 #define ROBE_REDUCE_G(S_, R_, C_, P_, G_)                                                                             \
     do {                                                                                                              \
@@ -828,6 +853,15 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         else ROBE_REDUCE_C(S_, R_, false, false);                                                                     \
     } while (0)
         if (int rc = probe(opt, ROBE_PROBE_REDUCE, false, stream)) return rc;
+        if (r.small_cap) {
+            const dim3 wgrid((r.NR + robe::kSmallBlock / 64 - 1) / (robe::kSmallBlock / 64)), wblock(robe::kSmallBlock);
+#define ROBE_SMALL(S_, R_) robe::region_small_kernel<S_, R_><<<wgrid, wblock, 0, stream>>>(p, r, grad_out, grad_array, state, scale, eps)
+            if (sign) { if (rule == 1) ROBE_SMALL(true, 1); else ROBE_SMALL(true, 0); }
+            else      { if (rule == 1) ROBE_SMALL(false, 1); else ROBE_SMALL(false, 0); }
+#undef ROBE_SMALL
+            if (int rc = check_launch("backward (reduce, small regions)")) return rc;
+            if (pl.crowded_most == 0) return probe(opt, ROBE_PROBE_REDUCE, true, stream);
+        }
         if (sign) { if (rule == 1) ROBE_REDUCE(true, 1); else ROBE_REDUCE(true, 0); }
         else      { if (rule == 1) ROBE_REDUCE(false, 1); else ROBE_REDUCE(false, 0); }
 #undef ROBE_REDUCE

@@ -62,6 +62,7 @@ struct RegionPlan {
     uint32_t lg_shift;       // log2 of the lanes per record in R5
     uint32_t fullest_first;  // 1: R5 takes the regions by descending size class instead of by address
     uint32_t keep_rows;      // 1: gradient rows are read more than once (bags): R5 loads them with the default cache policy
+    uint32_t small_cap;      // > 0: regions with at most this many records belong to region_small_kernel; R5 takes the others, which R3 lists
     uint32_t sparse_regions; // 1: the tokens reach a small part of the array: R5 writes back by a list of touched granules
     uint32_t keep_array;     // 1: R5 updates the array (Adagrad, SGD) and leaves it in the caches for the next forward pass (small arrays)
     // gather variant of R5 (no R2..R4): the range table has NE = C * epc entries, epc = kmax + 3 with
@@ -78,7 +79,7 @@ struct RegionPlan {
     uint32_t stretch;        // stretches of G sorted positions a lane group of R1 walks (1 .. kStretch)
     uint32_t p_quota;        // rows of P per lane group of R1
     float *P;                // [lane groups of R1 * p_quota][d] summed rows of the runs longer than one (d: the widest table's)
-    uint32_t *counts, *starts;   // [NR], [NR + 1]; with fullest_first counts holds the order of the regions for R5 after R3
+    uint32_t *counts, *starts;   // [NR], [NR + 2]; after R3 counts holds the order of the regions for R5 (fullest_first), or the regions R5 takes (small_cap; how many: starts[NR + 1])
     uint32_t *wg_first;      // [bin_blocks][NR]: R2 -> R4, see region_bin_kernel
     uint2 *rec;              // [<= 2 * n * C] (offset, source block | part flag)
     uint32_t *rec_tg;        // sign on only
@@ -475,6 +476,18 @@ __global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
     }
     if (t == 0) s.starts[s.NR] = total;
 
+    // Most regions hold a handful of records (small_cap): R5 takes only those that hold more, in any order.
+    if (s.small_cap) {
+        if (t == 0) cls_at[0] = 0;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 0; k < kScanPer; ++k)
+            if (c[k] > s.small_cap) s.counts[atomicAdd(&cls_at[0], 1u)] = first + k;
+        __syncthreads();
+        if (t == 0) s.starts[s.NR + 1u] = cls_at[0];
+        return;
+    }
+
     // The order for R5.  With few regions per workgroup slot the ones the frequent tokens hit, which
     // take several times the average, must not end up as the tail of the launch: fullest first, by
     // power-of-two size class.  With many regions per slot the tails even out and R5 goes by address.
@@ -659,7 +672,8 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(8,
     constexpr int kRecBatch = reduce_batch<SIGN, GATHER>();
     constexpr int kPer = (kRecBatch + kReduceBlock - 1) / kReduceBlock;     // records per thread and round
     extern __shared__ float acc[];  // 2^r_shift floats, then the batch staging area
-    const uint32_t r = (GATHER || !s.fullest_first) ? blockIdx.x : s.counts[blockIdx.x];     // records path, few regions: fullest first (R3)
+    if (!GATHER && s.small_cap && blockIdx.x >= s.starts[s.NR + 1u]) return;
+    const uint32_t r = (GATHER || !(s.fullest_first || s.small_cap)) ? blockIdx.x : s.counts[blockIdx.x];     // records path: the order, or the list, of R3
     if (r >= s.NR) return;
     uint32_t rb = 0, re = 0;
     if constexpr (!GATHER) {
@@ -1169,6 +1183,208 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(8,
             adagrad_one(wk, sk, g, lr, eps);
             dst[r0 + i] = wk;
             state[r0 + i] = sk;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// R5 for regions with few records: one wavefront per region, no copy of the region in LDS.
+//
+// A batch that reaches a small part of the array leaves about ten records in each of thirty thousand
+// regions, and region_reduce_kernel is then bound by latency: a workgroup holds 40 KB of LDS, so four fit
+// a CU, and each waits on five dependent trips to memory (7.8 us) to do almost nothing.  Here a wavefront
+// sorts its region's records by the slot they start at (a rank by comparison, one broadcast per record)
+// and then works from the records: 16 lanes per record, four slots a lane.  The 64-byte granules that a
+// record touches and no record before it does are the record's own (all blocks are Z long, so only the
+// record just before it can reach in), their sums are its own elements plus those of the records that
+// follow while they start inside the granule, and the rule is applied to them at once.  Every granule
+// has one owner, nothing is atomic, LDS holds the sorted records only (16 wavefronts per CU more than
+// with the copy), and the trips to memory are three: bounds, records, then rows and slots together.
+// The order of additions is by (slot, source block, sign term), so it is the same in every run.
+//
+// 250 M slots, 133 K tokens (batch 256 of bags of 20, d = 128, Z = 32): 79 us against 229 (3.8 TB/s of the lines it
+// touches).  Two records per 16 lanes in flight; one: 101 us, four: 95 (registers).  Regions that hold
+// more than kSmallRegion records (hot tokens, crowded regions) are left to region_reduce_kernel.
+// ---------------------------------------------------------------------------------------------
+constexpr uint32_t kSmallRegion = 128;     // records of a region, two per lane
+constexpr int kSmallBlock = 256;
+constexpr int kSmallAhead = 2;             // records per 16 lanes whose loads are in flight together
+
+// The rule for one slot; a slot without a gradient keeps its bits.
+template <int RULE>
+__device__ __forceinline__ void small_rule(float &w, float &st, float g, float lr, float eps)
+{
+    if (g == 0.0f) return;
+    if constexpr (RULE == 0) w = __fadd_rn(w, __fmul_rn(g, lr));
+    else adagrad_one(w, st, g, lr, eps);
+}
+
+template <bool SIGN, int RULE>
+__global__ __launch_bounds__(kSmallBlock) void region_small_kernel(Params p, RegionPlan s, const float *__restrict__ grad_out,
+                                                                   float *__restrict__ dst,      // as in region_reduce_kernel
+                                                                   float *__restrict__ state, float lr, float eps)
+{
+    constexpr uint32_t kWaves = kSmallBlock / 64;
+    typedef Vec<4>::A V4;
+    __shared__ int32_t sort_a[kWaves][kSmallRegion];
+    __shared__ uint32_t sort_src[kWaves][kSmallRegion];
+    __shared__ uint32_t sort_tg[SIGN ? kWaves : 1][SIGN ? kSmallRegion : 1];
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t r = blockIdx.x * kWaves + wave;
+    if (r >= s.NR) return;
+    const uint32_t rb = s.starts[r], count = s.starts[r + 1u] - rb;
+    if (count == 0 || count > s.small_cap || count > kSmallRegion) return;     // nothing lands here, or region_reduce_kernel's
+    const uint32_t R = 1u << s.r_shift, r0 = r << s.r_shift;
+    const uint32_t region_len = (p.m - r0) < R ? (p.m - r0) : R;
+
+    // Each lane takes two records.  a: the region slot of the block's element 0, negative when the block
+    // enters at slot 0 with a later element.  Anything that does not belong here cannot occur with
+    // consistent inputs; it sorts last and is dropped.
+    int32_t a[2];
+    uint32_t src[2], tg[2], key[2], rank[2];
+    uint32_t live = 0;
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) {
+        const uint32_t k = lane + 64u * t;
+        a[t] = 0;
+        src[t] = tg[t] = rank[t] = 0;
+        key[t] = 0xFFFFFFFFu;
+        if (k < count) {
+            const uint2 rec = s.rec[rb + k];
+            if constexpr (SIGN) tg[t] = s.rec_tg[rb + k];
+            src[t] = rec.y & ~kPartBit;
+            const RecordSpan sp = span_of(rec.x, (rec.y & kPartBit) != 0, r0, region_len, p.m, p.Z);
+            if (rec.x < p.m && src[t] < s.src_blocks && sp.ok) {
+                a[t] = (int32_t)sp.abase;
+                key[t] = sp.abase + p.Z;                 // >= 1, below 2^16 + Z
+            }
+        }
+        live += (uint32_t)__popcll(__ballot(key[t] != 0xFFFFFFFFu));
+    }
+    // rank of every record among the region's: by slot, then source block, then sign term, then lane
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) {
+        const uint32_t here = count > 64u * t ? (count - 64u * t < 64u ? count - 64u * t : 64u) : 0u;
+        for (uint32_t l = 0; l < here; ++l) {             // uniform over the wavefront
+            const uint32_t key_l = __builtin_amdgcn_readlane(key[t], l), src_l = __builtin_amdgcn_readlane(src[t], l);
+            const uint32_t tg_l = SIGN ? __builtin_amdgcn_readlane(tg[t], l) : 0u;
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u) {
+                const bool tie = key_l == key[u] && src_l == src[u] && (!SIGN || tg_l == tg[u]);
+                const bool before = key_l < key[u] || (key_l == key[u] && (src_l < src[u] || (SIGN && src_l == src[u] && tg_l < tg[u])));
+                rank[u] += before || (tie && l + 64u * t < lane + 64u * u);
+            }
+        }
+    }
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) {
+        if (lane + 64u * t < count) {
+            sort_a[wave][rank[t]] = a[t];
+            sort_src[wave][rank[t]] = src[t];
+            if constexpr (SIGN) sort_tg[wave][rank[t]] = tg[t];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // (a wavefront's LDS accesses are performed in order)
+    __builtin_amdgcn_wave_barrier();
+
+    const uint32_t sub = lane >> 4, q = lane & 15u;
+    const int32_t Z = (int32_t)p.Z, last = (int32_t)region_len - 1;
+    auto block_of = [&](uint32_t j) -> const float * {
+        const uint32_t from = sort_src[wave][j];
+        return from < s.src_own ? grad_out + (uint64_t)from * p.Z : s.P + (uint64_t)(from - s.src_own) * p.Z;
+    };
+    // kSmallAhead records per 16 lanes at a time: the slots and the own elements of all of them are
+    // requested before anything is added (loads of elements outside the block are clamped, not skipped:
+    // a branch per element made four trips of one)
+    for (uint32_t i0 = sub; i0 < live; i0 += 4u * kSmallAhead) {
+        int32_t v0[kSmallAhead], v1[kSmallAhead];               // this lane's first vector of four slots, and the end of the owned ones
+        int32_t most = 0;                                       // passes of 64 slots (one, unless blocks are longer than three granules)
+#pragma unroll
+        for (int u = 0; u < kSmallAhead; ++u) {
+            const uint32_t i = i0 + 4u * (uint32_t)u;
+            v0[u] = v1[u] = 0;
+            if (i < live) {
+                const int32_t ai = sort_a[wave][i];
+                int32_t g0 = (ai > 0 ? ai : 0) >> 4;
+                const int32_t g1 = (ai + Z - 1 < last ? ai + Z - 1 : last) >> 4;
+                if (i > 0) {                                    // granules that the record before touches are not this one's
+                    const int32_t end = sort_a[wave][i - 1u] + Z - 1;
+                    const int32_t taken = (end < last ? end : last) >> 4;
+                    g0 = g0 > taken ? g0 : taken + 1;
+                }
+                v0[u] = 4 * g0 + (int32_t)q;
+                v1[u] = 4 * g1 + 4;
+                const int32_t passes = v1[u] > v0[u] ? (v1[u] - v0[u] + 15) / 16 : 0;
+                most = most > passes ? most : passes;
+            }
+        }
+        for (int32_t pass = 0; pass < most; ++pass) {
+            V4 w[kSmallAhead], st[kSmallAhead];
+            float g[kSmallAhead][4];
+            bool mine[kSmallAhead], whole[kSmallAhead];
+#pragma unroll
+            for (int u = 0; u < kSmallAhead; ++u) {
+                const uint32_t i = i0 + 4u * (uint32_t)u;
+                const int32_t v = v0[u] + 16 * pass, slot = 4 * v;
+                mine[u] = v < v1[u] && slot <= last;
+                whole[u] = mine[u] && slot + 3 <= last;
+                if (whole[u]) {
+                    const uint32_t at = r0 + (uint32_t)slot;
+                    w[u] = s.keep_array ? *reinterpret_cast<const V4 *>(dst + at) : __builtin_nontemporal_load(reinterpret_cast<const V4 *>(dst + at));
+                    if constexpr (RULE == 1) st[u] = __builtin_nontemporal_load(reinterpret_cast<const V4 *>(state + at));
+                }
+                if (mine[u]) {
+                    const int32_t e = slot - sort_a[wave][i];
+                    const float *base = block_of(i);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) g[u][k] = base[e + k < 0 ? 0 : (e + k < Z ? e + k : Z - 1)];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kSmallAhead; ++u) {
+                if (!mine[u]) continue;
+                const uint32_t i = i0 + 4u * (uint32_t)u;
+                const int32_t slot = 4 * (v0[u] + 16 * pass);
+                const int32_t e0 = slot - sort_a[wave][i];
+                const uint32_t tg0 = SIGN ? sort_tg[wave][i] : 0u;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    g[u][k] = e0 + k >= 0 && e0 + k < Z ? signed_block_value<SIGN>(p, g[u][k], tg0, (uint32_t)(e0 + k)) : 0.0f;
+                for (uint32_t j = i + 1u; j < live; ++j) {      // the records that start inside the granule
+                    const int32_t e = slot - sort_a[wave][j];
+                    if (e < -3) break;                          // it and all that follow start past these four slots
+                    const float *base = block_of(j);
+                    float x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) x[k] = base[e + k < 0 ? 0 : (e + k < Z ? e + k : Z - 1)];
+                    const uint32_t tgj = SIGN ? sort_tg[wave][j] : 0u;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (e + k >= 0 && e + k < Z) g[u][k] += signed_block_value<SIGN>(p, x[k], tgj, (uint32_t)(e + k));
+                }
+                const uint32_t at = r0 + (uint32_t)slot;
+                if (whole[u]) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        float wk = w[u][k], sk = RULE == 1 ? st[u][k] : 0.0f;
+                        small_rule<RULE>(wk, sk, g[u][k], lr, eps);
+                        w[u][k] = wk;
+                        if constexpr (RULE == 1) st[u][k] = sk;
+                    }
+                    if (s.keep_array) *reinterpret_cast<V4 *>(dst + at) = w[u];
+                    else __builtin_nontemporal_store(w[u], reinterpret_cast<V4 *>(dst + at));
+                    if constexpr (RULE == 1) __builtin_nontemporal_store(st[u], reinterpret_cast<V4 *>(state + at));
+                } else {                                        // the end of the array: m is no multiple of four
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (slot + k > last) continue;
+                        float wk = dst[at + (uint32_t)k], sk = RULE == 1 ? state[at + (uint32_t)k] : 0.0f;
+                        small_rule<RULE>(wk, sk, g[u][k], lr, eps);
+                        dst[at + (uint32_t)k] = wk;
+                        if constexpr (RULE == 1) state[at + (uint32_t)k] = sk;
+                    }
+                }
+            }
         }
     }
 }
