@@ -224,7 +224,7 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * token per row).  Accumulates onto the caller's grad_array (device float[m]);
  * the order of the float32 additions is not fixed, so results agree with an
  * exact sum only to rounding.  Small scatters issue one float atomic per
- * element (ROBE_ROUTE_DIRECT).  Larger ones first combine the gradient rows of repeated tokens
+ * element (ROBE_ROUTE_DIRECT), up to some million of them or, with bags, some fifty thousand tokens.  Larger ones first combine the gradient rows of repeated tokens
  * (sort by the token part of the hash, run-wise sums) and issue the atomics
  * once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more with 2^21 tokens or
  * more) then collect the blocks by destination region and sum each region in LDS,
@@ -259,7 +259,7 @@ int robe_backward(const robe_hash_t *hash, const float *grad_out,
  * library routine that allocates); its first use on a device looks the buffer's address up once.
  * A problem whose workspace (robe_workspace_bytes with the same options) exceeds the buffer fails with
  * ROBE_EINVAL and launches nothing; problems that scatter directly need no workspace and have no
- * size limit.  The buffer holds nothing between calls that a call relies on.  All calls on one GPU
+ * size limit (one of fewer than 2^25 gradient elements whose sort buffers do not fit goes directly).  The buffer holds nothing between calls that a call relies on.  All calls on one GPU
  * share it: two such calls that overlap in time on one GPU (different streams, or different threads)
  * race and give wrong results - order them on one stream or with events.
  * Errors: as robe_backward, plus ROBE_EHIP if the buffer's address cannot be obtained.

@@ -463,6 +463,20 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
     return 0;
 }
 
+// Whether a scatter of n tokens is worth the sort (about 45 us of launches and passes).  The direct
+// scatter is bound by its atomic requests of 64 bytes, d/Z blocks of 1 + (Z - 1)/16 each a token.
+// Single-hot, whose duplicates it combines tile by tile, the two cross at 1.2 .. 1.4 million requests
+// (us direct / sorted: d = 128, Z = 32, batch 4000 of 26 tables 104 / 108, 8000 176 / 145; d = 16, Z = 4,
+// batch 8000 92 / 98, 16000 148 / 130; uniform ids, which have no duplicates, 118 / 126 and 197 / 180 at
+// d = 128).  With bags it combines nothing, the copies of a frequent token meet at the same addresses,
+// and the line is at some fifty thousand tokens whatever they hold (39 K tokens, d = 100, Z = 10: 89 / 90,
+// 117 K: 222 / 115; d = 20: 39 K 58 / 68, 117 K 122 / 85).
+bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
+{
+    const uint64_t requests = (uint64_t)n * (d / Z) * (Z + 15) / 16;
+    return requests >= 1300000u || (bags && n >= 50000);
+}
+
 uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; return s; }
 
 // Decide between the direct scatter, the combine-duplicates one and the region-sorted one, and lay
@@ -496,8 +510,7 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     if (rows < 1 || n_indices < 1 || rows >= 0x7FFFFFFFll || n_indices >= 0x7FFFFFFFll) return pl;
     if (pick_layout(h, true, grad_out, opt, &pl.lay) != ROBE_OK) return pl;   // the launch reports the bad layout
     if (pl.lay.V == 0 || pl.lay.consec) return pl;   // shapes the sorted routes do not handle
-    // sorting costs about 0.1 ms plus 45 ns per thousand tokens: not worth it for small scatters
-    if (!forced && (uint64_t)n_indices * h->d < (1ull << 25)) return pl;
+    if (!forced && !sorting_pays(n_indices, h->d, h->Z, bags)) return pl;
     // Sorting on the top 24 key bits is one radix pass cheaper; tokens that share those bits merely
     // interleave and are merged less often, which stays rare while there are far fewer tokens than 2^24.
     // (up to 2^18 tokens 16 bits do: a key bucket then holds four tokens at most on average)
@@ -1145,7 +1158,8 @@ static int plan_mixed(const robe_hash_t *hash, const Opt &opt, const uint32_t *d
     if ((uint64_t)batch * (uint64_t)D >= 0xFFFFFFFFull) return ROBE_OK;           // 32-bit row starts in the combine kernels
     const bool forced = regions || opt.bwd_route == ROBE_ROUTE_COMBINE;
     // the same size rule as robe_backward, on the average dimension
-    if (!forced && (uint64_t)n_indices * (uint64_t)(D / n_features) < (1ull << 25)) return ROBE_OK;
+    const uint32_t davg = (uint32_t)(D / n_features) < hash->Z ? hash->Z : (uint32_t)(D / n_features);
+    if (!forced && !sorting_pays(n_indices, davg, hash->Z, bags)) return ROBE_OK;
     const int64_t rows = batch * (int64_t)n_features;
     Opt sorted = opt;
     sorted.bwd_route = regions ? ROBE_ROUTE_REGIONS : ROBE_ROUTE_COMBINE;
@@ -1257,6 +1271,16 @@ int robe_backward_noalloc(const robe_hash_t *hash, const float *grad_out, const 
 {
     size_t need = 0;
     if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, options, &need)) return rc;
+    // Narrow embeddings: many tokens whose sort buffers do not fit, but a scatter small enough to go directly
+    robe_options_t direct;
+    if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES && (uint64_t)n_indices * hash->d < (1ull << 25) &&
+        (options == nullptr || (options->backward_route == ROBE_ROUTE_AUTO && !options->reproducible))) {
+        if (options != nullptr) direct = *options;
+        else memset(&direct, 0, sizeof(direct));
+        direct.backward_route = ROBE_ROUTE_DIRECT;
+        options = &direct;
+        need = 0;
+    }
     if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES)
         return fail(ROBE_EINVAL, "robe_backward_noalloc: this problem needs a workspace of %zu bytes, the built-in one holds %zu; "
                                  "use robe_backward with a workspace of your own, or ROBE_ROUTE_DIRECT",

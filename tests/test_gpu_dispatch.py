@@ -1,0 +1,66 @@
+"""The size rules that pick a backward route by default: results on both sides of each line agree with
+the oracle bit for bit (small-integer gradients), the workspace query covers both kinds of input, and
+the allocation-free call still takes every problem that it can scatter directly."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2108_02191_amd as robe
+from tests import test_gpu_parity as P
+
+DEV = "cuda:0"
+
+
+# (d, Z, tokens) around the line for bags (50000 tokens) and for single-hot lookups (1.3 million requests)
+SIZES = [(16, 4, 49_999), (16, 4, 50_000), (128, 32, 113_200), (128, 32, 113_500), (32, 128, 60_000), (100, 10, 83_000), (100, 10, 84_000)]
+
+
+@pytest.mark.parametrize("d,Z,n", SIZES)
+def test_the_workspace_query_covers_single_hot_and_bags(d, Z, n):
+    h = robe.robe_init_hash(1, 1_000_003, d, Z, 1)
+    single = robe.robe_workspace_bytes(h, n, 1, n)
+    forced = robe.robe_workspace_bytes(h, n, 1, n, robe.options(backward_route=robe.ROUTE_COMBINE))
+    assert single in (0, forced)
+    assert (single > 0) == (n >= 50_000 or n * (d // min(d, Z)) * (min(d, Z) + 15) // 16 >= 1_300_000)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bags", [False, True])
+@pytest.mark.parametrize("d,Z,n", SIZES)
+def test_both_sides_of_the_size_rule_match_the_oracle(d, Z, n, bags):
+    m = 300_007
+    h, H = P.both_hashes(n + d, m, d, Z, 1)
+    rng = np.random.default_rng(n)
+    ids = rng.integers(0, 2000, size=n, dtype=np.int64)
+    ids[rng.random(n) < 0.3] = 7
+    if bags:
+        B, F = n // 6, 2
+        off = np.sort(rng.integers(0, n + 1, size=B * F + 1))
+        off[0], off[-1] = 0, n
+    else:
+        B, F, off = n, 1, None
+    G = rng.integers(-2, 3, size=(B, F, d)).astype(np.float32)
+    ref, _ = oracle.backward(H, G, ids, off, B, F, threads=8)
+    for call in (robe.robe_backward, robe.robe_backward_noalloc):
+        ga = torch.zeros(m, dtype=torch.float32, device=DEV)
+        call(h, P.to_dev(G), P.to_dev(ids), P.to_dev(off), B, F, ga)
+        assert np.array_equal(ga.cpu().numpy().astype(np.float64), ref), call
+
+
+@pytest.mark.gpu
+def test_noalloc_takes_many_narrow_tokens():
+    # 2.2 million tokens need more than the built-in workspace to sort, but go directly
+    m, d, Z, n = 500_009, 4, 2, 2_200_000
+    h, H = P.both_hashes(3, m, d, Z, 0)
+    rng = np.random.default_rng(0)
+    ids = rng.integers(0, 10**6, size=(n // 4, 4), dtype=np.int64)
+    G = rng.integers(-2, 3, size=(n // 4, 4, d)).astype(np.float32)
+    assert robe.robe_workspace_bytes(h, n // 4, 4, n) > robe.lib().robe_noalloc_max_workspace_bytes()
+    ga = torch.zeros(m, dtype=torch.float32, device=DEV)
+    robe.robe_backward_noalloc(h, P.to_dev(G), P.to_dev(ids), None, n // 4, 4, ga)
+    ref, _ = oracle.backward(H, G, ids, None, n // 4, 4, threads=8)
+    assert np.array_equal(ga.cpu().numpy().astype(np.float64), ref)
+    with pytest.raises(robe.RobeError):      # asked for by name, the sorted route is refused as before
+        robe.robe_backward_noalloc(h, P.to_dev(G), P.to_dev(ids), None, n // 4, 4, ga,
+                                   options=robe.options(backward_route=robe.ROUTE_COMBINE))
