@@ -224,7 +224,7 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * token per row).  Accumulates onto the caller's grad_array (device float[m]);
  * the order of the float32 additions is not fixed, so results agree with an
  * exact sum only to rounding.  Small scatters issue one float atomic per
- * element (ROBE_ROUTE_DIRECT), up to some million of them or, with bags, some fifty thousand tokens.  Larger ones first combine the gradient rows of repeated tokens
+ * element (ROBE_ROUTE_DIRECT), up to some million of them or, with bags, some 65 thousand tokens.  Larger ones first combine the gradient rows of repeated tokens
  * (sort by the token part of the hash, run-wise sums) and issue the atomics
  * once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more with 2^21 tokens or
  * more) then collect the blocks by destination region and sum each region in LDS,

@@ -469,12 +469,12 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 // (us direct / sorted: d = 128, Z = 32, batch 4000 of 26 tables 104 / 108, 8000 176 / 145; d = 16, Z = 4,
 // batch 8000 92 / 98, 16000 148 / 130; uniform ids, which have no duplicates, 118 / 126 and 197 / 180 at
 // d = 128).  With bags it combines nothing, the copies of a frequent token meet at the same addresses,
-// and the line is at some fifty thousand tokens whatever they hold (39 K tokens, d = 100, Z = 10: 89 / 90,
+// and the line is at some 65 thousand tokens whatever they hold (39 K tokens, d = 100, Z = 10: 89 / 90,
 // 117 K: 222 / 115; d = 20: 39 K 58 / 68, 117 K 122 / 85).
 bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
 {
     const uint64_t requests = (uint64_t)n * (d / Z) * (Z + 15) / 16;
-    return requests >= 1300000u || (bags && n >= 50000);
+    return requests >= 1300000u || (bags && n >= 65536);
 }
 
 uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; return s; }

@@ -12,8 +12,8 @@ from tests import test_gpu_parity as P
 DEV = "cuda:0"
 
 
-# (d, Z, tokens) around the line for bags (50000 tokens) and for single-hot lookups (1.3 million requests)
-SIZES = [(16, 4, 49_999), (16, 4, 50_000), (128, 32, 113_200), (128, 32, 113_500), (32, 128, 60_000), (100, 10, 83_000), (100, 10, 84_000)]
+# (d, Z, tokens) around the line for bags (65536 tokens) and for single-hot lookups (1.3 million requests)
+SIZES = [(16, 4, 65_535), (16, 4, 65_536), (128, 32, 113_200), (128, 32, 113_500), (32, 128, 60_000), (100, 10, 83_000), (100, 10, 84_000)]
 
 
 @pytest.mark.parametrize("d,Z,n", SIZES)
@@ -22,7 +22,7 @@ def test_the_workspace_query_covers_single_hot_and_bags(d, Z, n):
     single = robe.robe_workspace_bytes(h, n, 1, n)
     forced = robe.robe_workspace_bytes(h, n, 1, n, robe.options(backward_route=robe.ROUTE_COMBINE))
     assert single in (0, forced)
-    assert (single > 0) == (n >= 50_000 or n * (d // min(d, Z)) * (min(d, Z) + 15) // 16 >= 1_300_000)
+    assert (single > 0) == (n >= 65_536 or n * (d // min(d, Z)) * (min(d, Z) + 15) // 16 >= 1_300_000)
 
 
 @pytest.mark.gpu
