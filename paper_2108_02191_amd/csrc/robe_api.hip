@@ -594,13 +594,22 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     // second record), plus every run of the most frequent token (one per walk of a lane group) in one
     // region, against six tenths of the room.  (The gather variant stages its records in an order
     // that is fixed by the sorted list and needs no such split.)
+    // Record kernels, up to 2^21 tokens: two radix passes (16 key bits) instead of three, as on the atomics
+    // route below, and the combine kernel orders the G positions that a lane group looks at by the whole
+    // key.  A frequent token's run is then also cut where other tokens of its key bucket (2^-16 of all
+    // tokens, eight times that for the bound) sit among its copies.
+    // Reproducible step on the 100 MB array, Z = 8: 614 -> 602 us (852 K tokens), Z = 32: 435 -> 421.
+    if (!pl.gather && !opt.key_bits && pl.key_top >= 16 && pl.lay.G >= 16 && n <= (1u << 21)) {
+        pl.key_bits = 16;
+        pl.window_sort = true;
+    }
     auto within_reproducible_bound = [&](uint64_t walk_positions) {
         if (!opt.reproducible || pl.gather) return true;
         const uint64_t batch = h->use_sign ? robe::rec_batch<true>() : robe::rec_batch<false>();
         const uint64_t room = ((batch << robe::kMaxClassShift) * 6) / 10;
         const uint64_t R = 1ull << shift, span = R < h->m ? R : h->m;
         const uint64_t avg = (n * C * (span + h->Z) / span + NR - 1) / NR;
-        const uint64_t worst = avg + avg / 2 + 2ull * C * (n / walk_positions + 1);
+        const uint64_t worst = avg + avg / 2 + 2ull * C * (n / walk_positions + 1) + (pl.window_sort ? 16ull * C * ((n >> 16) + 1) : 0u);
         return worst <= room;
     };
     // rows of P: an eighth of the positions a lane group of the combine kernel walks, for every group
@@ -1361,15 +1370,26 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
     return launch_update(1, hash, array, nullptr, grad_array, lr, 0.0f, stream);
 }
 
-// The fused step uses the region-sorted scatter when it applies and is worth its launches;
-// otherwise a gradient array in the workspace and the two separate steps.  On arrays of 2^26 slots
-// or more the two-step route would fill and sweep all m slots, which alone costs more than the
-// region route's fixed part, so there the region route is taken whatever the batch size.
+// The fused step uses the region-sorted scatter when it applies and is worth its launches; otherwise a
+// gradient array in the workspace and the two separate steps, which fill it, scatter with atomics and
+// sweep all m slots.  From 2^26 slots on the sweeps alone cost more than the region route's fixed part,
+// whatever the batch size.  Below, the region route wins from about 20 M slots on once the tokens are
+// worth sorting, from 2^25 slots on also with somewhat fewer.  Forward + fused step, two steps / regions,
+// us, d = 128, Z = 32, 26 single-hot tables (batch 6000, 24000, 66000): 16 M slots 141 / 134, 312 / 317,
+// 643 / 653; 25 M 158 / 146, 342 / 322, 685 / 667; 60 M 210 / 189, 395 / 366, 792 / 751; batch 3000:
+// 25 M 116 / 120, 60 M 164 / 126.  Bags of 20, 25 M slots, batch 256 and 1000: 173 / 141, 344 / 240.
+static bool fused_regions_pay(const robe_hash_t *hash, int64_t n_indices, uint32_t d, bool bags)
+{
+    const uint32_t Z = hash->Z < d ? hash->Z : d;
+    return hash->m >= (1ull << 26) || (hash->m >= (1ull << 25) && n_indices >= 50000) ||
+           (hash->m >= (5ull << 22) && sorting_pays(n_indices, d, Z, bags));
+}
+
 static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,
                        const void *grad_out, BwdPlan *pl, size_t *scratch_bytes)
 {
     *scratch_bytes = 0;
-    const bool want = opt.fused_route == ROBE_ROUTE_AUTO ? hash->m >= (1ull << 26) : opt.fused_route == ROBE_ROUTE_REGIONS;
+    const bool want = opt.fused_route == ROBE_ROUTE_AUTO ? fused_regions_pay(hash, n_indices, hash->d, bags) : opt.fused_route == ROBE_ROUTE_REGIONS;
     if (opt.reproducible || want) {
         *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out, true);
         if (pl->regions) return true;

@@ -71,7 +71,7 @@ struct RegionPlan {
     uint32_t NE, epc, epc_recip, dir_shift, dir_buckets;   // epc_recip = ceil(2^16 / epc)
     uint32_t key_mask;       // the key bits: 2^31 - 1, or fewer when the keys are array offsets (blocks larger than embeddings)
     uint32_t *dir;
-    const uint32_t *keys;    // sorted keys
+    uint32_t *keys;          // sorted keys (on the bits that the sort looked at; see Geom::window_sort)
     uint8_t *head;           // [n]  1: a run starts here
     uint32_t *src_row;       // [n]  at run starts: the first source block of the run's row (in grad_out, or src_own + row of P * C); else kNoRun
     uint32_t *run_c;         // [n]  at run starts: chunks of the run's embedding; NULL unless tables differ in dimension (then C is the most any has)
@@ -173,6 +173,35 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
                 }
             }
         }
+        // After a sort on few key bits the tokens of a key bucket sit interleaved: the group puts its G
+        // positions in order of the whole key (bitonic network over its lanes, the key made unique by
+        // the lane it came from) and so finds the runs that a full sort would, cut at every G positions
+        // at the most.
+        if (q.window_sort) {
+            uint64_t sk = t.ok ? (((uint64_t)t.th << 6) | grp) : ((1ull << 40) | grp);
+#pragma unroll
+            for (uint32_t kk = 2; kk <= 64u; kk <<= 1) {
+                if (kk > q.G) break;
+#pragma unroll
+                for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
+                    const uint32_t lo = __shfl_xor((uint32_t)sk, (int)j), hi = __shfl_xor((uint32_t)(sk >> 32), (int)j);
+                    const uint64_t other = ((uint64_t)hi << 32) | lo;
+                    const bool take_min = ((grp & j) == 0) == ((grp & kk) == 0);
+                    sk = take_min ? (other < sk ? other : sk) : (other > sk ? other : sk);
+                }
+            }
+            const int from = (int)(base_lane + ((uint32_t)sk & 63u));
+            SortedToken u;
+            u.ok = (sk >> 40) == 0;
+            u.th = u.ok ? (uint32_t)(sk >> 6) : 0u;
+            u.sb = __shfl(t.sb, from);
+            u.dd = mixed ? __shfl(t.dd, from) : q.d;
+            u.e = (SIGN || mixed) ? __shfl(t.e, from) : 0u;
+            u.xlo = SIGN ? __shfl(t.xlo, from) : 0u;
+            u.xhi = SIGN ? __shfl(t.xhi, from) : 0u;
+            u.tg = SIGN ? __shfl(t.tg, from) : 0u;
+            t = u;
+        }
         return t;
     };
 
@@ -262,6 +291,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
 
         if (i0 + grp < n) {
             if (s.head != nullptr) s.head[i0 + grp] = my_lead ? 1 : 0;
+            if (q.window_sort && my_lead) s.keys[i0 + grp] = cur.th;      // (R2 and R4 read the keys of run starts; nobody else reads this position)
             // a run of one reads grad_out in place; the head of a longer run gets its row of P when the run
             // ends; every other position says that no run starts there (the gather variant of R5 reads
             // this array alone to find the runs)

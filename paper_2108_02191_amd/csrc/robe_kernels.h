@@ -47,9 +47,9 @@ struct Geom {
     // first float inside a sample (.x) and its dimension (.y); d above is then the largest dimension.
     // NULL: every table has dimension d and row k starts at float k * d.
     const uint2 *tables;
-    // Sorted backward with float atomics: 1 when the sort looked at few key bits, so that tokens whose
-    // keys agree in those bits sit interleaved; the combine kernel then sorts every wavefront's 64
-    // positions by the whole key before it looks for runs.
+    // Sorted backward: 1 when the sort looked at few key bits, so that tokens whose keys agree in those
+    // bits sit interleaved; the combine kernels then sort the positions they look at together (with
+    // float atomics a wavefront's 64, without a lane group's G) by the whole key before they look for runs.
     uint32_t window_sort;
 };
 
