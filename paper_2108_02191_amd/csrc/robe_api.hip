@@ -19,6 +19,7 @@
 #include "robe_kernels.h"
 #include "robe_backward_dedup.h"
 #include "robe_backward_regions.h"
+#include "robe_backward_elements.h"
 #include "robe_radix_sort.h"
 
 // Workspace of robe_backward_noalloc: device memory that exists from the moment the library is
@@ -418,6 +419,7 @@ const uint64_t kSmallFullest = 96, kSmallLeastRegions = 7500;
 struct BwdPlan {
     bool dedup;          // sort the tokens and combine identical ones
     bool regions;        // ... and then sort the blocks by destination region instead of using float atomics
+    bool elements;       // ... of the (place, value) pairs of small blocks (robe_backward_elements.h)
     bool spill_rows;     // ... with room in LDS for a row of Z floats per lane group of the reduce kernel
     bool gather;         // ... and the reduce kernel finds its blocks in the sorted token list (no record kernels)
     uint32_t crowded_most;   // regions only, small_cap: at most this many regions are left to the kernel with one workgroup per region
@@ -462,6 +464,13 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
         if (fits(shift)) return shift;
     return 0;
 }
+
+// Small blocks take the pairs of robe_backward_elements.h up to this block size and from this many
+// gradient elements on.  Forward + backward on the 100 MB array, d = 128, 852 K lookups, float atomics /
+// pairs: Z = 1 2353 / 1551 us, Z = 2 1266 / 1007, Z = 4 750 / 772 (a block of four is one or two atomic
+// requests).  Z = 1 with 13 K, 52 K, 208 K lookups: 140 / 188, 255 / 251, 725 / 486.
+const uint32_t kElemMostZ = 2;
+const uint64_t kElemLeast = 1u << 23;
 
 // Whether a scatter of n tokens is worth the sort (about 45 us of launches and passes).  The direct
 // scatter is bound by its atomic requests of 64 bytes, d/Z blocks of 1 + (Z - 1)/16 each a token.
@@ -531,7 +540,13 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     pl.bytes = off;
 
     // Region-sorted scatter on top of the combined runs.
-    const bool want_regions = need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
+    // Small blocks: the pairs of every element sorted by region, where nothing else is asked for.
+    const uint64_t elem_regions = (h->m + (1u << robe::kElemShift) - 1) >> robe::kElemShift;
+    const bool elements = h->Z <= kElemMostZ && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
+                          opt.fused_route != ROBE_ROUTE_REGIONS && opt.region_records == 0 && opt.region_shift == 0 &&
+                          elem_regions <= robe::kElemMaxRegions && (uint64_t)n * h->d < 0xFFFFFFFFull &&
+                          (uint64_t)n * h->d >= kElemLeast;
+    const bool want_regions = elements || need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
     if (!want_regions) {
         // Atomics after the sort: up to 2^21 tokens, 16 key bits - two radix passes instead of three,
         // each three launches of 5 to 10 us.  The tokens of a key bucket (2^-16 of them) then sit
@@ -552,9 +567,9 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     // C * ((P - 1) / m + 3) entries, which must fit its LDS: large arrays, few chunks per embedding.
     // No record kernels, no record storage, any number of regions.  options->region_records asks for
     // either variant.
-    uint32_t shift = 0;
+    uint32_t shift = elements ? robe::kElemShift : 0u;
     bool small = false;
-    {
+    if (!elements) {
         const uint32_t gshift = opt.region_shift ? (uint32_t)opt.region_shift : 13u;
         const uint64_t R = 1ull << gshift, kmax = ((uint64_t)ROBE_PRIME - 1) / h->m, NE = C * (kmax + 3);
         const uint32_t cap = h->use_sign ? robe::gather_entries_max<true>() : robe::gather_entries_max<false>();
@@ -573,7 +588,7 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
             shift = gshift;
         }
     }
-    if (!pl.gather) {
+    if (!pl.gather && !elements) {
         shift = pick_region_shift(h, opt.region_shift);
         small = n * C * 8192u <= h->m * kSmallMostBlocks;
         if (small && shift != 0 && opt.region_shift == 0) {
@@ -632,6 +647,7 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     if (src_own + p_rows * C >= 0x7FFFFFFFull) return pl;                // 31-bit source block numbers
 
     pl.regions = true;
+    pl.elements = elements;
     robe::RegionPlan &r = pl.rp;
     r.r_shift = shift;
     r.NR = (uint32_t)NR;
@@ -643,12 +659,13 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     r.stretch = stretch;
     r.key_mask = pl.key_top >= 31 ? (uint32_t)ROBE_PRIME : (1u << pl.key_top) - 1u;
     r.bin_blocks = NR * 4 > 80 * 1024 ? 256u : 512u;      // one or two workgroups per CU by LDS
+    if (elements) r.bin_blocks = robe::kElemBlocks;
     if (n < (size_t)r.bin_blocks * 1024) r.bin_blocks = (uint32_t)((n + 1023) / 1024);
     r.pos_per_block = (uint32_t)((n + r.bin_blocks - 1) / r.bin_blocks);
     r.lg_shift = log2u(lg);
     // measured: it pays below about eight regions per workgroup slot (1024 slots), and in the
     // reproducible mode, whose rounds are longer
-    r.fullest_first = (NR <= 8192 || opt.reproducible) ? 1u : 0u;
+    r.fullest_first = !elements && (NR <= 8192 || opt.reproducible) ? 1u : 0u;
     r.keep_rows = bags ? 1u : 0u;
     // the slots the tokens can reach, against the array: below a quarter, most 64-byte granules stay untouched
     r.sparse_regions = (uint64_t)n * h->d < h->m / 4 ? 1u : 0u;
@@ -681,8 +698,8 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
         pl.off_counts = off;  off = align_up(off + NR * 4, 256);
         pl.off_starts = off;  off = align_up(off + (NR + 2) * 4, 256);
         pl.off_wg_first = off; off = align_up(off + (size_t)r.bin_blocks * NR * 4, 256);
-        pl.off_rec = off;     off = align_up(off + rec_per_block * n * C * 8, 256);
-        pl.off_rec_tg = off;  if (h->use_sign) off = align_up(off + rec_per_block * n * C * 4, 256);
+        pl.off_rec = off;     off = align_up(off + (elements ? (size_t)n * h->d : rec_per_block * n * C) * 8, 256);
+        pl.off_rec_tg = off;  if (h->use_sign && !elements) off = align_up(off + rec_per_block * n * C * 4, 256);
     }
     pl.bytes = off + 256;      // (slack: the padded reads above never leave the workspace)
     return pl;
@@ -834,6 +851,32 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
 #undef ROBE_COMBINE_ROWS
         if (int rc = check_launch("backward (combine rows)")) return rc;
         if (int rc = probe(opt, ROBE_PROBE_COMBINE, true, stream)) return rc;
+
+        if (pl.elements) {
+            // E1, R3, E2, E3 (see robe_backward_elements.h)
+            const dim3 egrid(r.bin_blocks), eblock(robe::kElemBlock);
+            const uint32_t row_shift = ceil_log2(h->d);
+            const size_t lds_count = (size_t)r.NR * 4 + (robe::kElemRuns + robe::kElemBlock) * 8 + 64, lds_scatter = robe::elem_lds_bytes(r.NR, sign);
+            const size_t lds_reduce = (size_t)4 << robe::kElemShift;
+            robe::element_count_kernel<<<egrid, eblock, lds_count, stream>>>(p, r, row_shift);
+            if (int rc = check_launch("backward (count elements)")) return rc;
+            robe::region_scan_kernel<<<dim3(1), dim3(robe::kScanThreads), 0, stream>>>(r);
+            if (int rc = check_launch("backward (scan)")) return rc;
+#define ROBE_ELEMENTS(S_)                                                                                             \
+    do {                                                                                                              \
+        if (int rc = allow_lds(robe::element_scatter_kernel<S_>, lds_scatter, "backward (elements)")) return rc;      \
+        robe::element_scatter_kernel<S_><<<egrid, eblock, lds_scatter, stream>>>(p, r, row_shift, grad_out);                   \
+    } while (0)
+            if (sign) ROBE_ELEMENTS(true);
+            else ROBE_ELEMENTS(false);
+#undef ROBE_ELEMENTS
+            if (int rc = check_launch("backward (elements)")) return rc;
+            if (int rc = probe(opt, ROBE_PROBE_REDUCE, false, stream)) return rc;
+            if (rule == 1) robe::element_reduce_kernel<1><<<dim3(r.NR), eblock, lds_reduce, stream>>>(p, r, grad_array, state, scale, eps, vec_ok);
+            else robe::element_reduce_kernel<0><<<dim3(r.NR), eblock, lds_reduce, stream>>>(p, r, grad_array, state, scale, eps, vec_ok);
+            if (int rc = check_launch("backward (reduce elements)")) return rc;
+            return probe(opt, ROBE_PROBE_REDUCE, true, stream);
+        }
 
         // R2..R4: records sorted by region (the gather variant of R5 does without)
         if (!pl.gather) {
@@ -1280,15 +1323,20 @@ int robe_backward_noalloc(const robe_hash_t *hash, const float *grad_out, const 
 {
     size_t need = 0;
     if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, options, &need)) return rc;
-    // Narrow embeddings: many tokens whose sort buffers do not fit, but a scatter small enough to go directly
-    robe_options_t direct;
-    if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES && (uint64_t)n_indices * hash->d < (1ull << 25) &&
+    // The default route does not fit: the sort alone may (small blocks), and a scatter of few enough
+    // elements goes directly (many narrow tokens).
+    robe_options_t other;
+    if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES &&
         (options == nullptr || (options->backward_route == ROBE_ROUTE_AUTO && !options->reproducible))) {
-        if (options != nullptr) direct = *options;
-        else memset(&direct, 0, sizeof(direct));
-        direct.backward_route = ROBE_ROUTE_DIRECT;
-        options = &direct;
-        need = 0;
+        if (options != nullptr) other = *options;
+        else memset(&other, 0, sizeof(other));
+        other.backward_route = ROBE_ROUTE_COMBINE;
+        if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &other, &need)) return rc;
+        if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES && (uint64_t)n_indices * hash->d < (1ull << 25)) {
+            other.backward_route = ROBE_ROUTE_DIRECT;
+            need = 0;
+        }
+        options = &other;
     }
     if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES)
         return fail(ROBE_EINVAL, "robe_backward_noalloc: this problem needs a workspace of %zu bytes, the built-in one holds %zu; "
@@ -1394,8 +1442,12 @@ static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, in
         *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out, true);
         if (pl->regions) return true;
     }
+    if (opt.fused_route == ROBE_ROUTE_AUTO) {             // small blocks: the pairs' workgroups apply the rule, whatever the array size
+        *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out);
+        if (pl->elements) return true;
+    }
     *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out);
-    if (pl->regions) { pl->regions = false; }            // the two-step fallback adds onto a gradient array
+    if (!pl->elements) pl->regions = false;              // the two-step fallback adds onto a gradient array
     *scratch_bytes = align_up((size_t)hash->m * 4, 256);
     return false;
 }
