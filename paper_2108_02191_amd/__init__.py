@@ -10,6 +10,7 @@ library is not built, importing a function's result fails loudly.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -17,6 +18,7 @@ import torch  # loads the HIP runtime the library binds to
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "librobe.so")
+CALL_PATH = os.path.join(_HERE, "_robe_call.so")
 
 ROBE_OK, ROBE_EINVAL, ROBE_EHIP = 0, -1, -2
 ROBE_PRIME = 2**31 - 1
@@ -67,6 +69,7 @@ EXPORTS = ("robe_init_hash", "robe_offsets", "robe_forward", "robe_workspace_byt
            "robe_last_error")
 
 _lib = None
+_call = None     # see _native()
 
 
 def lib() -> ctypes.CDLL:
@@ -132,6 +135,22 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def _native():
+    """The module that makes the calls of a program's inner loop (csrc/robe_call.cpp), bound to the library."""
+    global _call
+    if _call is None:
+        lib()
+        if not os.path.exists(CALL_PATH):
+            raise ImportError(f"{CALL_PATH} is missing: build it with `python -m paper_2108_02191_amd.build` "
+                              "(there is no fallback path)")
+        spec = importlib.util.spec_from_file_location("_robe_call", CALL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.bind(LIB_PATH, RobeError)
+        _call = module
+    return _call
+
+
 def _check(rc: int) -> None:
     if rc != ROBE_OK:
         raise RobeError(rc, lib().robe_last_error().decode())
@@ -182,18 +201,7 @@ def options(**fields) -> RobeOptions:
 def robe_forward(h: RobeHash, array: torch.Tensor, indices: torch.Tensor, offsets: Optional[torch.Tensor],
                  batch: int, n_features: int, out: Optional[torch.Tensor] = None,
                  options: Optional[RobeOptions] = None) -> torch.Tensor:
-    if array.numel() != h.m:
-        raise ValueError("array length differs from hash.m")
-    if offsets is not None and offsets.numel() != batch * n_features + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    if out is None:
-        out = torch.empty((batch, n_features, h.d), dtype=torch.float32, device=array.device)
-    elif out.numel() != batch * n_features * h.d:
-        raise ValueError("out has the wrong size")
-    _check(lib().robe_forward(ctypes.byref(h), _dev(array, torch.float32, "array"),
-                              _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                              indices.numel(), batch, n_features, _dev(out, torch.float32, "out"), _opt(options), _stream()))
-    return out
+    return (_call or _native()).forward(h, array, indices, offsets, batch, n_features, out, options, False)
 
 
 def robe_workspace_bytes(h: RobeHash, batch: int, n_features: int, n_indices: int,
@@ -203,66 +211,29 @@ def robe_workspace_bytes(h: RobeHash, batch: int, n_features: int, n_indices: in
     return int(need.value)
 
 
-def _workspace(workspace: Optional[torch.Tensor], need: int, device):
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    ws_ptr = None if workspace is None else workspace.data_ptr()
-    ws_len = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    return workspace, ws_ptr, ws_len
-
-
 def robe_backward(h: RobeHash, grad_out: torch.Tensor, indices: torch.Tensor, offsets: Optional[torch.Tensor],
                   batch: int, n_features: int, grad_array: torch.Tensor,
                   workspace: Optional[torch.Tensor] = None, options: Optional[RobeOptions] = None) -> torch.Tensor:
     """grad_array += scatter of grad_out (in place); returns grad_array."""
-    if grad_array.numel() != h.m:
-        raise ValueError("grad_array length differs from hash.m")
-    if grad_out.numel() != batch * n_features * h.d:
-        raise ValueError("grad_out has the wrong size")
-    if offsets is not None and offsets.numel() != batch * n_features + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    need = robe_workspace_bytes(h, batch, n_features, indices.numel(), options) if workspace is None else 0
-    workspace, ws_ptr, ws_len = _workspace(workspace, need, grad_array.device)
-    _check(lib().robe_backward(ctypes.byref(h), _dev(grad_out, torch.float32, "grad_out"),
-                               _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                               indices.numel(), batch, n_features, _dev(grad_array, torch.float32, "grad_array"),
-                               ws_ptr, ws_len, _opt(options), _stream()))
-    return grad_array
+    return (_call or _native()).backward(h, grad_out, indices, offsets, batch, n_features, grad_array, workspace, options, False)
 
 
 def robe_backward_noalloc(h: RobeHash, grad_out: torch.Tensor, indices: torch.Tensor, offsets: Optional[torch.Tensor],
                           batch: int, n_features: int, grad_array: torch.Tensor,
                           options: Optional[RobeOptions] = None) -> torch.Tensor:
     """robe_backward on the library's built-in workspace: nothing is allocated, here or in the library."""
-    if grad_array.numel() != h.m:
-        raise ValueError("grad_array length differs from hash.m")
-    if grad_out.numel() != batch * n_features * h.d:
-        raise ValueError("grad_out has the wrong size")
-    if offsets is not None and offsets.numel() != batch * n_features + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    _check(lib().robe_backward_noalloc(ctypes.byref(h), _dev(grad_out, torch.float32, "grad_out"),
-                                       _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                                       indices.numel(), batch, n_features, _dev(grad_array, torch.float32, "grad_array"),
-                                       _opt(options), _stream()))
-    return grad_array
+    return (_call or _native()).backward(h, grad_out, indices, offsets, batch, n_features, grad_array, None, options, True)
 
 
 def robe_adagrad_update(h: RobeHash, array: torch.Tensor, state: torch.Tensor, grad_array: torch.Tensor,
                         lr: float, eps: float) -> None:
-    for t, name in ((array, "array"), (state, "state"), (grad_array, "grad_array")):
-        if t.numel() != h.m:
-            raise ValueError(f"{name} length differs from hash.m")
-    _check(lib().robe_adagrad_update(ctypes.byref(h), _dev(array, torch.float32, "array"),
-                                     _dev(state, torch.float32, "state"),
-                                     _dev(grad_array, torch.float32, "grad_array"), lr, eps, _stream()))
+    if state is None:
+        raise TypeError("state: need a tensor")
+    (_call or _native()).update(h, array, state, grad_array, lr, eps)
 
 
 def robe_sgd_update(h: RobeHash, array: torch.Tensor, grad_array: torch.Tensor, lr: float) -> None:
-    for t, name in ((array, "array"), (grad_array, "grad_array")):
-        if t.numel() != h.m:
-            raise ValueError(f"{name} length differs from hash.m")
-    _check(lib().robe_sgd_update(ctypes.byref(h), _dev(array, torch.float32, "array"),
-                                 _dev(grad_array, torch.float32, "grad_array"), lr, _stream()))
+    (_call or _native()).update(h, array, None, grad_array, lr, 0.0)
 
 
 def robe_fused_workspace_bytes(h: RobeHash, batch: int, n_features: int, n_indices: int,
@@ -277,37 +248,16 @@ def robe_backward_adagrad(h: RobeHash, grad_out: torch.Tensor, indices: torch.Te
                           lr: float, eps: float, workspace: Optional[torch.Tensor] = None,
                           options: Optional[RobeOptions] = None) -> None:
     """Backward scatter-add and Adagrad update in one call (array and state updated in place)."""
-    for t, name in ((array, "array"), (state, "state")):
-        if t.numel() != h.m:
-            raise ValueError(f"{name} length differs from hash.m")
-    if grad_out.numel() != batch * n_features * h.d:
-        raise ValueError("grad_out has the wrong size")
-    if offsets is not None and offsets.numel() != batch * n_features + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    need = robe_fused_workspace_bytes(h, batch, n_features, indices.numel(), options) if workspace is None else 0
-    workspace, ws_ptr, ws_len = _workspace(workspace, need, array.device)
-    _check(lib().robe_backward_adagrad(ctypes.byref(h), _dev(grad_out, torch.float32, "grad_out"),
-                                       _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                                       indices.numel(), batch, n_features, _dev(array, torch.float32, "array"),
-                                       _dev(state, torch.float32, "state"), lr, eps, ws_ptr, ws_len, _opt(options), _stream()))
+    if state is None:
+        raise TypeError("state: need a tensor")
+    (_call or _native()).fused(h, grad_out, indices, offsets, batch, n_features, array, state, lr, eps, workspace, options)
 
 
 def robe_backward_sgd(h: RobeHash, grad_out: torch.Tensor, indices: torch.Tensor, offsets: Optional[torch.Tensor],
                       batch: int, n_features: int, array: torch.Tensor, lr: float,
                       workspace: Optional[torch.Tensor] = None, options: Optional[RobeOptions] = None) -> None:
     """Backward scatter-add and SGD update in one call (array updated in place)."""
-    if array.numel() != h.m:
-        raise ValueError("array length differs from hash.m")
-    if grad_out.numel() != batch * n_features * h.d:
-        raise ValueError("grad_out has the wrong size")
-    if offsets is not None and offsets.numel() != batch * n_features + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    need = robe_fused_workspace_bytes(h, batch, n_features, indices.numel(), options) if workspace is None else 0
-    workspace, ws_ptr, ws_len = _workspace(workspace, need, array.device)
-    _check(lib().robe_backward_sgd(ctypes.byref(h), _dev(grad_out, torch.float32, "grad_out"),
-                                   _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                                   indices.numel(), batch, n_features, _dev(array, torch.float32, "array"),
-                                   lr, ws_ptr, ws_len, _opt(options), _stream()))
+    (_call or _native()).fused(h, grad_out, indices, offsets, batch, n_features, array, None, lr, 0.0, workspace, options)
 
 
 def _dims_array(dims):
@@ -319,20 +269,7 @@ def robe_forward_mixed(h: RobeHash, dims, array: torch.Tensor, indices: torch.Te
                        offsets: Optional[torch.Tensor], batch: int, out: Optional[torch.Tensor] = None,
                        options: Optional[RobeOptions] = None) -> torch.Tensor:
     """Forward for tables of different dimensions: returns float32[batch, sum(dims)]."""
-    F, D = len(dims), int(sum(dims))
-    if array.numel() != h.m:
-        raise ValueError("array length differs from hash.m")
-    if offsets is not None and offsets.numel() != batch * F + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    if out is None:
-        out = torch.empty((batch, D), dtype=torch.float32, device=array.device)
-    elif out.numel() != batch * D:
-        raise ValueError("out has the wrong size")
-    da = _dims_array(dims)
-    _check(lib().robe_forward_mixed(ctypes.byref(h), ctypes.cast(da, ctypes.c_void_p), _dev(array, torch.float32, "array"),
-                                    _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                                    indices.numel(), batch, F, _dev(out, torch.float32, "out"), _opt(options), _stream()))
-    return out
+    return (_call or _native()).forward_mixed(h, dims, array, indices, offsets, batch, out, options)
 
 
 def robe_mixed_workspace_bytes(h: RobeHash, dims, batch: int, n_indices: int, options: Optional[RobeOptions] = None) -> int:
@@ -347,20 +284,7 @@ def robe_backward_mixed(h: RobeHash, dims, grad_out: torch.Tensor, indices: torc
                         offsets: Optional[torch.Tensor], batch: int, grad_array: torch.Tensor,
                         workspace: Optional[torch.Tensor] = None, options: Optional[RobeOptions] = None) -> None:
     """Backward for tables of different dimensions (accumulates onto grad_array)."""
-    F, D = len(dims), int(sum(dims))
-    if grad_array.numel() != h.m:
-        raise ValueError("grad_array length differs from hash.m")
-    if grad_out.numel() != batch * D:
-        raise ValueError("grad_out has the wrong size")
-    if offsets is not None and offsets.numel() != batch * F + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    need = robe_mixed_workspace_bytes(h, dims, batch, indices.numel(), options) if workspace is None else 0
-    workspace, ws_ptr, ws_len = _workspace(workspace, need, grad_array.device)
-    da = _dims_array(dims)
-    _check(lib().robe_backward_mixed(ctypes.byref(h), ctypes.cast(da, ctypes.c_void_p), _dev(grad_out, torch.float32, "grad_out"),
-                                     _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                                     indices.numel(), batch, F, _dev(grad_array, torch.float32, "grad_array"),
-                                     ws_ptr, ws_len, _opt(options), _stream()))
+    (_call or _native()).backward_mixed(h, dims, grad_out, indices, offsets, batch, grad_array, workspace, options)
 
 
 def robe_fused_mixed_workspace_bytes(h: RobeHash, dims, batch: int, n_indices: int,
@@ -377,21 +301,7 @@ def robe_backward_adagrad_mixed(h: RobeHash, dims, grad_out: torch.Tensor, indic
                                 lr: float, eps: float, workspace: Optional[torch.Tensor] = None,
                                 options: Optional[RobeOptions] = None) -> None:
     """Backward and Adagrad in one call for tables of different dimensions (array and state in place)."""
-    F, D = len(dims), int(sum(dims))
-    if array.numel() != h.m or state.numel() != h.m:
-        raise ValueError("array / state length differs from hash.m")
-    if grad_out.numel() != batch * D:
-        raise ValueError("grad_out has the wrong size")
-    if offsets is not None and offsets.numel() != batch * F + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    need = robe_fused_mixed_workspace_bytes(h, dims, batch, indices.numel(), options) if workspace is None else 0
-    workspace, ws_ptr, ws_len = _workspace(workspace, need, array.device)
-    da = _dims_array(dims)
-    _check(lib().robe_backward_adagrad_mixed(ctypes.byref(h), ctypes.cast(da, ctypes.c_void_p),
-                                             _dev(grad_out, torch.float32, "grad_out"), _dev(indices, torch.int64, "indices"),
-                                             _dev(offsets, torch.int64, "offsets"), indices.numel(), batch, F,
-                                             _dev(array, torch.float32, "array"), _dev(state, torch.float32, "state"),
-                                             lr, eps, ws_ptr, ws_len, _opt(options), _stream()))
+    (_call or _native()).fused_mixed(h, dims, grad_out, indices, offsets, batch, array, state, lr, eps, workspace, options)
 
 
 def robe_array_to_bf16(array: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -409,18 +319,7 @@ def robe_forward_bf16(h: RobeHash, array_bf16: torch.Tensor, indices: torch.Tens
                       batch: int, n_features: int, out: Optional[torch.Tensor] = None,
                       options: Optional[RobeOptions] = None) -> torch.Tensor:
     """robe_forward on an array of bfloat16 bit patterns (int16 tensor of length m)."""
-    if array_bf16.numel() != h.m:
-        raise ValueError("array length differs from hash.m")
-    if offsets is not None and offsets.numel() != batch * n_features + 1:
-        raise ValueError("offsets must hold batch*n_features + 1 entries")
-    if out is None:
-        out = torch.empty((batch, n_features, h.d), dtype=torch.float32, device=array_bf16.device)
-    elif out.numel() != batch * n_features * h.d:
-        raise ValueError("out has the wrong size")
-    _check(lib().robe_forward_bf16(ctypes.byref(h), _dev(array_bf16, torch.int16, "array"),
-                                   _dev(indices, torch.int64, "indices"), _dev(offsets, torch.int64, "offsets"),
-                                   indices.numel(), batch, n_features, _dev(out, torch.float32, "out"), _opt(options), _stream()))
-    return out
+    return (_call or _native()).forward(h, array_bf16, indices, offsets, batch, n_features, out, options, True)
 
 
 def robe_sort_pairs(keys: torch.Tensor, vals: torch.Tensor, lo_bit: int, hi_bit: int):
