@@ -317,7 +317,9 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
 
 #define ROBE_LAUNCH_TILE(V_)                                                                                          \
     do {                                                                                                              \
-        if (sign) robe::single_hot_backward_tile_kernel<V_, true><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);  \
+        if (q.G < 64u && sign) robe::single_hot_backward_window_kernel<V_, true><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);  \
+        else if (q.G < 64u) robe::single_hot_backward_window_kernel<V_, false><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);    \
+        else if (sign) robe::single_hot_backward_tile_kernel<V_, true><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);  \
         else robe::single_hot_backward_tile_kernel<V_, false><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);      \
     } while (0)
     if constexpr (BWD && sizeof(AT) == 4) {

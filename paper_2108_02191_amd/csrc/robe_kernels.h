@@ -474,6 +474,143 @@ __global__ __launch_bounds__(kBlock) void single_hot_backward_tile_kernel(Params
 }
 
 // ---------------------------------------------------------------------------
+// The same for rows of several lane groups to a wavefront (G <= 32, so up to 32 .. 256 floats).
+//
+// At the sizes that come here (some ten thousand lookups) a SIMD holds one wavefront and the kernel is a
+// chain of latencies.  The one above finds the distinct tokens one by one, 64 rounds of dependent lane
+// exchanges where most tokens differ, and its groups then meet unequal sets.  Here the wavefront sorts
+// its 64 lookups by token (bitonic network over the lanes, 21 steps); every group walks the G lookups
+// that its own lanes hold and adds runs in registers; a run that goes on in the next group is handed
+// over, so that a token still costs one row of atomics per tile.  53248 lookups, d = 16, Z = 4: 20.9 us
+// before, 16.7 now; with one group per wavefront (d = 128) the walk is 64 rows long and loses
+// (52000 lookups: 74 against 94 us with the forward), so those keep the kernel above.
+// ---------------------------------------------------------------------------
+constexpr int kWindowRows = 8;          // gradient rows a lane group requests before it adds them
+
+template <int V, bool SIGN>
+__global__ __launch_bounds__(kBlock) void single_hot_backward_window_kernel(Params p, Geom q,
+                                                                          const float *__restrict__ grad_out,
+                                                                          const int64_t *__restrict__ indices,
+                                                                          int64_t rows,
+                                                                          float *__restrict__ grad_array)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    RowWalk w;
+    if (!start_walk(q, rows, 64, w)) return;             // uniform over the wavefront
+    const uint32_t n = (uint32_t)((rows - w.q0) < 64 ? (rows - w.q0) : 64);
+
+    // lane l hashes the l-th lookup of the tile
+    uint32_t th = 0, tg = 0, pl = 0;
+    uint64_t at = 0;                                      // first float of its gradient row
+    if (lane < n) {
+        const RowRef k = walk_row(q, w, lane, p.d);
+        const int64_t x = indices[k.in_row];
+        th = staged_h(p, block_key(p, x, pl), k.e);
+        if constexpr (SIGN) tg = staged_g(p, x, k.e);
+        at = (uint64_t)k.out_off;
+    }
+    const uint32_t grp = lane & (q.G - 1u);
+    const uint32_t base_lane = lane - grp;
+    Lane<V, false, SIGN> L;
+    L.init(p, q, grp);                                    // (while the ids are on their way)
+
+    // Equal (th, place, tg) mean equal offsets and signs.  They are brought side by side by a mix of the
+    // three; what a run is, is decided on all three below.
+    {
+        const uint32_t mix = th + pl * 0x9E3779B1u + (SIGN ? tg * 0x85EBCA6Bu : 0u);
+        uint64_t sk = lane < n ? (((uint64_t)mix << 6) | lane) : ((1ull << 40) | lane);
+#pragma unroll
+        for (uint32_t kk = 2; kk <= 64u; kk <<= 1) {
+#pragma unroll
+            for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
+                const uint32_t lo = __shfl_xor((uint32_t)sk, (int)j), hi = __shfl_xor((uint32_t)(sk >> 32), (int)j);
+                const uint64_t other = ((uint64_t)hi << 32) | lo;
+                const bool take_min = ((lane & j) == 0) == ((lane & kk) == 0);
+                sk = take_min ? (other < sk ? other : sk) : (other > sk ? other : sk);
+            }
+        }
+        const int from = (int)(sk & 63u);                 // (lookups past the end sort last: n of them stay in front)
+        th = __shfl(th, from);
+        if (p.r) pl = __shfl(pl, from);
+        if constexpr (SIGN) tg = __shfl(tg, from);
+        const uint32_t lo = __shfl((uint32_t)at, from), hi = __shfl((uint32_t)(at >> 32), from);
+        at = ((uint64_t)hi << 32) | lo;
+    }
+    // is this token another than the one before?
+    const int prev = (int)(lane ? lane - 1u : 0u);
+    const uint32_t p_th = __shfl(th, prev), p_pl = p.r ? __shfl(pl, prev) : 0u, p_tg = SIGN ? __shfl(tg, prev) : 0u;
+    const bool head = lane == 0 || p_th != th || (p.r && p_pl != pl) || (SIGN && p_tg != tg);
+    const uint64_t heads = __ballot(head && lane < n);
+    const uint64_t mine = (heads >> base_lane) & ((1ull << q.G) - 1ull);    // of this group's lookups (G <= 32)
+    const bool joins = base_lane < n && (mine & 1ull) == 0;                 // the first run began in the group before
+
+    float acc[V], first[V];                               // the open run; the group's first run, if it joins the group before
+#pragma unroll
+    for (int k = 0; k < V; ++k) acc[k] = first[k] = 0.0f;
+    uint32_t run_th = 0, run_tg = 0, run_pl = 0, first_th = 0, first_tg = 0, first_pl = 0;
+    bool open = false, joining = joins;
+    for (uint32_t k0 = 0; k0 < q.G; k0 += kWindowRows) {    // same trip count for every lane
+        uint32_t rth[kWindowRows], rtg[kWindowRows], rpl[kWindowRows];
+        bool ok[kWindowRows], rhead[kWindowRows];
+        float v[kWindowRows][V];
+#pragma unroll
+        for (int u = 0; u < kWindowRows; ++u) {
+            const uint32_t of = base_lane + ((k0 + u) & (q.G - 1u));
+            ok[u] = k0 + u < q.G && of < n;
+            rth[u] = __shfl(th, (int)of);
+            rtg[u] = SIGN ? __shfl(tg, (int)of) : 0u;
+            rpl[u] = p.r ? __shfl(pl, (int)of) : 0u;
+            rhead[u] = __shfl((int)head, (int)of) != 0;
+            const uint32_t lo = __shfl((uint32_t)at, (int)of), hi = __shfl((uint32_t)(at >> 32), (int)of);
+            if (ok[u]) load_row<V, false>(grad_out + (((uint64_t)hi << 32) | lo), q, grp, v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kWindowRows; ++u) {
+            if (!ok[u]) continue;
+            if (rhead[u] && open) {
+                if (joining) {                            // handed over by the group before: it waits for what that one has
+#pragma unroll
+                    for (int k = 0; k < V; ++k) first[k] = acc[k];
+                    first_th = run_th;
+                    first_tg = run_tg;
+                    first_pl = run_pl;
+                    joining = false;
+                } else {
+                    L.scatter(p, grad_array, run_th, run_tg, acc, run_pl);
+                }
+#pragma unroll
+                for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < V; ++k) acc[k] += v[u][k];
+            run_th = rth[u];
+            run_tg = rtg[u];
+            run_pl = rpl[u];
+            open = true;
+        }
+    }
+    // Hand the open runs over, group by group: a group whose lookups are one run adds what it gets to its
+    // own and passes it on, any other finishes its first run with it.
+    const uint32_t sub = lane >> q.g_shift, groups = 64u >> q.g_shift;
+    const bool one_run = joins && (mine == 0);
+    for (uint32_t s = 1; s < groups; ++s) {               // uniform
+        float got[V];
+#pragma unroll
+        for (int k = 0; k < V; ++k) got[k] = __shfl(acc[k], (int)(lane >= q.G ? lane - q.G : lane));
+        if (sub != s || !joins) continue;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            if (one_run) acc[k] += got[k];
+            else first[k] += got[k];
+        }
+    }
+    if (joins && !one_run) L.scatter(p, grad_array, first_th, first_tg, first, first_pl);
+    const uint32_t after = base_lane + q.G;               // the next group's first lookup
+    const bool handed = after < n && after < 64u && ((heads >> (after & 63u)) & 1ull) == 0;
+    if (open && !handed) L.scatter(p, grad_array, run_th, run_tg, acc, run_pl);
+}
+
+// ---------------------------------------------------------------------------
 // Bag-sum forward / bag backward: one group of G lanes per bag, 64/G bags per
 // wavefront.  A group stages up to G of its bag's tokens at a time.
 // ---------------------------------------------------------------------------
