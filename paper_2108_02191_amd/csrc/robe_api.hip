@@ -412,7 +412,13 @@ const uint64_t kKeepArrayMax = 1ull << 25;
 // (0.1 ns), so the batch's blocks per 8192 slots decide.  Whole step, small against one workgroup per
 // region, at 17 / 35 / 70 / 102 blocks: 190 / 277 / 426 / 555 against 333 / 396 / 524 / 594 us (250 M
 // slots, d = 128, Z = 32); at 31 / 62 / 124: 131 / 184 / 276 against 147 / 172 / 239 us (70 M slots).
-const uint64_t kSmallMostBlocks = 64;
+// With fewer regions the latency of their workgroups is hidden less often, so the line moves with the
+// array: 55 blocks at 70 M slots, 100 from 240 M on.
+uint64_t small_most_blocks(uint64_t m)
+{
+    const uint64_t line = 36 + m / 3700000;
+    return line < 100 ? line : 100;
+}
 // Those regions may then be larger, which makes the record kernels cheaper: up to kSmallFullest blocks a
 // region (two lanes' worth is 128 records) and no fewer regions than there are wavefront slots.  250 M
 // slots, 133 K tokens: 190 us with 2^13 floats, 177 with 2^14, 176 with 2^15; 17 K tokens: 114, 97, 89.
@@ -592,11 +598,17 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     }
     if (!pl.gather && !elements) {
         shift = pick_region_shift(h, opt.region_shift);
-        small = n * C * 8192u <= h->m * kSmallMostBlocks;
+        small = n * C * 8192u <= h->m * small_most_blocks(h->m);
         if (small && shift != 0 && opt.region_shift == 0) {
             auto regions_at = [&](uint32_t sh) { return (h->m + (1ull << sh) - 1) >> sh; };
             while (shift < 15 && regions_at(shift + 1) >= kSmallLeastRegions && n * C <= regions_at(shift + 1) * kSmallFullest) ++shift;
         }
+        // Reproducible: a region of more records than one round takes is split into classes, each of which
+        // reads all its records; smaller regions instead where most would be (852 K lookups, d = 128,
+        // Z = 8, 100 MB array, 800 records a region after combining: 600 -> 581 us; Z = 16, half as many: no gain).
+        if (opt.reproducible && !small && shift == 13 && opt.region_shift == 0 && n * C * 8192u > 3200 * h->m &&
+            ((h->m + 4095) >> 12) <= robe::kMaxRegions && 4096u >= 2ull * h->Z && (1u << (12 - grp_shift)) >= h->Z)
+            shift = 12;
         if (shift == 0 || shift < grp_shift || (1u << (shift - grp_shift)) < h->Z) return pl;   // a slice of the region must hold one block
     }
     const uint64_t NR = (h->m + (1ull << shift) - 1) >> shift;
