@@ -380,6 +380,7 @@ int launch_radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint
     robe::SortPass sp;
     sp.n = n;
     sp.tiles = (uint32_t)(((uint64_t)n + robe::kSortTile - 1) / robe::kSortTile);
+    sp.few = sp.tiles <= robe::kFewTiles ? 1u : 0u;
     sp.tile_count = static_cast<uint32_t *>(temp);
     uint32_t *totals = sp.tile_count + (size_t)robe::kDigits * sp.tiles;
     uint32_t *ks = keys_a, *vs = vals_a, *kd = keys_b, *vd = vals_b;
@@ -391,8 +392,10 @@ int launch_radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint
         if (pass == 0) robe::sort_count_kernel<false><<<dim3(sp.tiles), dim3(robe::kSortBlock), 0, stream>>>(sp, ks);
         else robe::sort_count_kernel<true><<<dim3(sp.tiles), dim3(robe::kSortBlock), 0, stream>>>(sp, ks);
         if (int rc = check_launch("sort (count)")) return rc;
-        robe::sort_offsets_kernel<<<dim3(robe::kDigits), dim3(robe::kSortBlock), 0, stream>>>(sp);
-        if (int rc = check_launch("sort (offsets)")) return rc;
+        if (!sp.few) {
+            robe::sort_offsets_kernel<<<dim3(robe::kDigits), dim3(robe::kSortBlock), 0, stream>>>(sp);
+            if (int rc = check_launch("sort (offsets)")) return rc;
+        }
         robe::sort_scatter_kernel<robe::kScatterBlock><<<dim3(sp.tiles), dim3(robe::kScatterBlock), 0, stream>>>(sp, ks, vs, kd, vd);
         if (int rc = check_launch("sort (scatter)")) return rc;
         uint32_t *t = ks; ks = kd; kd = t;

@@ -64,3 +64,14 @@ def test_noalloc_takes_many_narrow_tokens():
     with pytest.raises(robe.RobeError):      # asked for by name, the sorted route is refused as before
         robe.robe_backward_noalloc(h, P.to_dev(G), P.to_dev(ids), None, n // 4, 4, ga,
                                    options=robe.options(backward_route=robe.ROUTE_COMBINE))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [4096, 64 * 4096 - 1, 64 * 4096, 64 * 4096 + 1])
+def test_sort_on_both_sides_of_its_tile_limit(n):
+    from tests import test_gpu_sort as S
+    rng = np.random.default_rng(n)
+    keys = rng.integers(0, 2**31, size=n, dtype=np.uint64).astype(np.uint32)
+    keys[rng.random(n) < 0.3] = 77
+    for lo, hi in ((15, 31), (0, 8), (7, 31)):
+        S.check(keys, lo, hi)
