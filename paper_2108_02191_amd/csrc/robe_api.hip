@@ -227,6 +227,12 @@ struct TableView {
     int64_t row_floats, col0;
 };
 
+// Bags of up to this many tokens on average count as short (see short_bag_kernel), in launches that leave
+// at least this many wavefronts, one for every slot of the GPU.  One bag per lane group / four, us: d = 100,
+// 39 K bags (9.8 K wavefronts of four) of 1, 3, 6, 10 tokens: 24.6 / 15.6, 31.0 / 24.0, 40.1 / 35.9, 51.7 / 51.4;
+// d = 128, bf16, 208 K bags (26 K): 54.9 / 38.0, 73.2 / 66.1, 101 / 102, 140 / 146; 52 K bags (6.5 K) of 3: 21.0 / 23.6.
+const int64_t kShortBagMean = 4, kShortBagWaves = 8192;
+
 template <bool BWD, typename AT = float>
 int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64_t *indices, const int64_t *offsets,
                 int64_t n_indices, int64_t rows, uint32_t F, float *dst, const void *rows_ptr, hipStream_t stream,
@@ -275,7 +281,10 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
     // d = 128: 26624 lookups 27 us plain, 32 us tiled; 53248 lookups 56 us plain, 38 us tiled).
     // options->tile_combine: 1 never, 2 always.
     const bool tile = BWD && !bags && !lay.consec && (opt.tile_combine == 2 || (opt.tile_combine == 0 && rows >= 32768));
-    const int64_t rows_per_wave = tile ? 64 : (bags ? (int64_t)step : (int64_t)q.TL);
+    // short bags: several to a lane group, as long as that leaves a wavefront for every slot of the GPU
+    const bool short_bags = !BWD && bags && lay.G >= robe::kShortBags && n_indices <= kShortBagMean * rows && n_indices < (1ll << 29) &&
+                            rows >= (int64_t)(step * robe::kShortBags) * kShortBagWaves;
+    const int64_t rows_per_wave = tile ? 64 : (short_bags ? (int64_t)(step * robe::kShortBags) : (bags ? (int64_t)step : (int64_t)q.TL));
     const int64_t waves = (rows + rows_per_wave - 1) / rows_per_wave;
     int64_t blocks = (waves + robe::kWavesPerBlock - 1) / robe::kWavesPerBlock;
     // Walk the rows table by table, one eighth of that order per XCD (see RowWalk), unless the launch
@@ -299,7 +308,9 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
 
 #define ROBE_LAUNCH(V_, C_, S_)                                                                                       \
     do {                                                                                                              \
-        if (bags)                                                                                                     \
+        if (short_bags) {                                                                                             \
+            if constexpr (!BWD) robe::short_bag_kernel<V_, C_, S_, AT><<<grid, block, 0, stream>>>(p, q, src, indices, offsets, rows, n_indices, dst); \
+        } else if (bags)                                                                                                     \
             robe::bag_kernel<V_, C_, S_, BWD, AT><<<grid, block, 0, stream>>>(p, q, src, indices, offsets, rows, n_indices, dst); \
         else                                                                                                          \
             robe::single_hot_kernel<V_, C_, S_, BWD, AT><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst); \

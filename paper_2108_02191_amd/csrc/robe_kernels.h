@@ -696,6 +696,129 @@ __global__ __launch_bounds__(kBlock) void bag_kernel(Params p, Geom q,
 }
 
 // ---------------------------------------------------------------------------
+// Bag-sum forward for short bags: a lane group takes kShortBags bags at a time.
+//
+// A bag of a few tokens is four dependent trips to memory (bounds, ids, array, and the store's way out)
+// around almost no work, and a wavefront that did one per lane group and left spent its life in them.
+// The bounds of all its bags are requested together, then their tokens' ids (a lane per token, whatever
+// bag it belongs to), and the array is read kUnroll tokens at a time across the bags' ends.  Tokens are
+// added in their order, so the sums are those of bag_kernel bit for bit.
+// 39013 bags of 3 on average, d = 100, Z = 10, signs: 31.0 us with one bag per group, 24.0 with four.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kShortBags = 4;
+
+template <int V, bool CONSEC, bool SIGN, typename AT>
+__global__ __launch_bounds__(kBlock) void short_bag_kernel(Params p, Geom q,
+                                                           const AT *__restrict__ array,
+                                                           const int64_t *__restrict__ indices,
+                                                           const int64_t *__restrict__ offsets,
+                                                           int64_t rows, int64_t n_indices,
+                                                           float *__restrict__ out)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t step = 64u >> q.g_shift;                 // lane groups per wavefront
+    RowWalk w;
+    if (!start_walk(q, rows, (int64_t)(step * kShortBags), w)) return;     // uniform over the wavefront
+    const uint32_t grp = lane & (q.G - 1u);
+    const uint32_t first = (lane >> q.g_shift) * kShortBags;               // this group's first row of the wavefront's
+    const uint32_t base_lane = lane - grp;
+    const int64_t left = rows - w.q0 - (int64_t)first;
+    const uint32_t bags = left <= 0 ? 0u : (left < (int64_t)kShortBags ? (uint32_t)left : kShortBags);
+
+    // bounds of the bags; cum[k]: tokens in the bags before bag k
+    int64_t t0[kShortBags], to[kShortBags];
+    uint32_t e[kShortBags], cum[kShortBags + 1];
+    {
+        int64_t t1[kShortBags];
+#pragma unroll
+        for (uint32_t k = 0; k < kShortBags; ++k) {
+            const RowRef r = walk_row(q, w, k < bags ? first + k : 0u, p.d);
+            e[k] = r.e;
+            to[k] = r.out_off;
+            t0[k] = offsets[r.in_row];
+            t1[k] = offsets[r.in_row + 1];
+        }
+        cum[0] = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kShortBags; ++k) {
+            t0[k] = t0[k] < 0 ? 0 : (t0[k] > n_indices ? n_indices : t0[k]);
+            t1[k] = t1[k] < t0[k] ? t0[k] : (t1[k] > n_indices ? n_indices : t1[k]);
+            const uint64_t c = k < bags ? (uint64_t)(t1[k] - t0[k]) : 0u;
+            cum[k + 1] = cum[k] + (uint32_t)c;              // (below 2^31: the host takes this kernel below 2^29 tokens)
+        }
+    }
+    const uint32_t total = cum[kShortBags];
+
+    Lane<V, CONSEC, SIGN> L;
+    L.init(p, q, grp);
+
+    float acc[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) acc[k] = 0.0f;
+    uint32_t cur = 0;                                        // the bag that acc belongs to
+    // write the bags up to (not including) `next`: the one being summed, then empty ones
+    auto finish = [&](uint32_t next) {
+#pragma unroll
+        for (uint32_t k = 0; k < kShortBags; ++k) {
+            if (k >= cur && k < next) {
+                store_row<V, CONSEC>(out + to[k], q, grp, acc);
+#pragma unroll
+                for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+            }
+        }
+        cur = next;
+    };
+    for (uint32_t tb = 0; __any(tb < total); tb += q.G) {
+        const uint32_t cnt = tb >= total ? 0u : (total - tb < q.G ? total - tb : q.G);
+        uint32_t th = 0, tg = 0, pl = 0;
+        if (grp < cnt) {
+            const uint32_t j = tb + grp;
+            int64_t at = t0[0];
+            uint32_t ek = e[0], before = 0;
+#pragma unroll
+            for (uint32_t k = 1; k < kShortBags; ++k) {
+                if (j >= cum[k]) {
+                    at = t0[k];
+                    ek = e[k];
+                    before = cum[k];
+                }
+            }
+            const int64_t x = indices[at + (int64_t)(j - before)];
+            th = staged_h(p, block_key(p, x, pl), ek);
+            if constexpr (SIGN) tg = staged_g(p, x, ek);
+        }
+        for (uint32_t u0 = 0; __any(u0 < cnt); u0 += kUnroll) {
+            uint32_t thr[kUnroll], tgr[kUnroll], plr[kUnroll];
+            bool live[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                live[u] = u0 + u < cnt;
+                const uint32_t srcl = base_lane + (live[u] ? u0 + u : 0u);
+                thr[u] = __shfl(th, (int)srcl);
+                tgr[u] = SIGN ? __shfl(tg, (int)srcl) : 0u;
+                plr[u] = p.r ? __shfl(pl, (int)srcl) : 0u;
+            }
+            float v[kUnroll][V];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) L.gather(p, array, thr[u], tgr[u], v[u], plr[u]);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                if (live[u]) {
+                    const uint32_t j = tb + u0 + (uint32_t)u;
+                    uint32_t bag = 0;                        // the last one that starts at or before token j
+#pragma unroll
+                    for (uint32_t k = 1; k < kShortBags; ++k) bag += j >= cum[k] ? 1u : 0u;
+                    if (bag != cur) finish(bag);
+#pragma unroll
+                    for (int k = 0; k < V; ++k) acc[k] += v[u][k];
+                }
+            }
+        }
+    }
+    finish(bags);
+}
+
+// ---------------------------------------------------------------------------
 // Shape-generic fallback (any d, Z with Z | d): one thread per (row, element),
 // every hash evaluated in full by the thread that needs it.
 // ---------------------------------------------------------------------------
