@@ -228,7 +228,10 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * (sort by the token part of the hash, run-wise sums) and issue the atomics
  * once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more with 2^21 tokens or
  * more) then collect the blocks by destination region and sum each region in LDS,
- * with no float atomic at all (ROBE_ROUTE_REGIONS; the route of the reproducible option).  The
+ * with no float atomic at all (ROBE_ROUTE_REGIONS; the route of the reproducible option).  Large
+ * scatters of blocks of one or two floats, on arrays of up to 59 million slots, sort the values
+ * themselves by region instead (nothing asks for that by name; the workspace holds eight bytes per
+ * gradient element then).  The
  * sorted routes need the workspace, rows and n_indices below 2^31 - 1 and d <= 512 (with Z > d,
  * Section 3.3, tokens are sorted by the array offset of their d slots instead of the token hash);
  * ROBE_ROUTE_REGIONS also needs d / Z and the lane group to be powers of two, at most 2^30 array
@@ -299,7 +302,8 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
  * Fused training step: backward scatter-add (Eq. 3) and the Adagrad update in one pass, for a
  * gradient array that would otherwise start from zero.  The result is that of
  *   robe_backward(..., grad_array = zeros, ...) followed by robe_adagrad_update(array, state, grad_array)
- * to the same rounding caveats, but on large arrays the gradient never exists in device memory:
+ * to the same rounding caveats, but on large arrays (by size of array and batch, from 20 million slots
+ * on; always from 2^26) and for small blocks the gradient never exists in device memory:
  * the blocks are collected by destination region, every region of the array is summed in LDS by the
  * one workgroup that owns it, and that workgroup updates array and state directly.  Slots that
  * receive no gradient are left bit-for-bit unchanged, and regions that receive none are not read.

@@ -855,12 +855,17 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         if (int rc = probe(opt, ROBE_PROBE_COMBINE, false, stream)) return rc;
         // R1: combine runs into P, leave one record per run (a lane group walks r.stretch * G positions)
         const dim3 rgrid1((uint32_t)(((uint64_t)n + (uint64_t)robe::kBlock * r.stretch - 1) / ((uint64_t)robe::kBlock * r.stretch)));
+#define ROBE_COMBINE_ROWS_W(V_, M_, W_)                                                                               \
+    do {                                                                                                              \
+        if (sign && bags) robe::combine_rows_kernel<V_, true, true, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);   \
+        else if (sign) robe::combine_rows_kernel<V_, true, false, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
+        else if (bags) robe::combine_rows_kernel<V_, false, true, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
+        else robe::combine_rows_kernel<V_, false, false, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);             \
+    } while (0)
 #define ROBE_COMBINE_ROWS_M(V_, M_)                                                                                   \
     do {                                                                                                              \
-        if (sign && bags) robe::combine_rows_kernel<V_, true, true, M_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);   \
-        else if (sign) robe::combine_rows_kernel<V_, true, false, M_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
-        else if (bags) robe::combine_rows_kernel<V_, false, true, M_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
-        else robe::combine_rows_kernel<V_, false, false, M_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);             \
+        if (pl.window_sort) ROBE_COMBINE_ROWS_W(V_, M_, true);                                                        \
+        else ROBE_COMBINE_ROWS_W(V_, M_, false);                                                                      \
     } while (0)
 #define ROBE_COMBINE_ROWS(V_)                                                                                         \
     do {                                                                                                              \
@@ -875,6 +880,7 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
             case 8: ROBE_COMBINE_ROWS(8); break;
             default: ROBE_COMBINE_ROWS(4); break;
         }
+#undef ROBE_COMBINE_ROWS_W
 #undef ROBE_COMBINE_ROWS_M
 #undef ROBE_COMBINE_ROWS
         if (int rc = check_launch("backward (combine rows)")) return rc;
@@ -1454,11 +1460,15 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
 // us, d = 128, Z = 32, 26 single-hot tables (batch 6000, 24000, 66000): 16 M slots 141 / 134, 312 / 317,
 // 643 / 653; 25 M 158 / 146, 342 / 322, 685 / 667; 60 M 210 / 189, 395 / 366, 792 / 751; batch 3000:
 // 25 M 116 / 120, 60 M 164 / 126.  Bags of 20, 25 M slots, batch 256 and 1000: 173 / 141, 344 / 240.
+// Those are passes on arrays that the last-level cache has lost in between.  Step after step on one array
+// of up to 2^25 slots the update kernel leaves it there for the next forward pass, which the regions'
+// reads of many gradient rows undo: 25 M slots, batch 8192, 24000, 65536 in a training loop 187 / 179,
+// 325 / 305, 632 / 639.  So up to 2^25 slots only up to 2^20 tokens.
 static bool fused_regions_pay(const robe_hash_t *hash, int64_t n_indices, uint32_t d, bool bags)
 {
     const uint32_t Z = hash->Z < d ? hash->Z : d;
-    return hash->m >= (1ull << 26) || (hash->m >= (1ull << 25) && n_indices >= 50000) ||
-           (hash->m >= (5ull << 22) && sorting_pays(n_indices, d, Z, bags));
+    if (hash->m > kKeepArrayMax) return hash->m >= (1ull << 26) || n_indices >= 50000 || sorting_pays(n_indices, d, Z, bags);
+    return hash->m >= (5ull << 22) && n_indices <= (1ll << 20) && sorting_pays(n_indices, d, Z, bags);
 }
 
 static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,

@@ -127,7 +127,8 @@ __device__ __forceinline__ SortedToken shfl_token(const SortedToken &t, int from
     return r;
 }
 
-template <int V, bool SIGN, bool BAGS, bool MIXED>
+// WINDOW: Geom::window_sort (as a run-time flag it cost the others 9 of 448 us on the Multi-hot step).
+template <int V, bool SIGN, bool BAGS, bool MIXED, bool WINDOW>
 __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, RegionPlan s,
                                                               const float *__restrict__ grad_out,
                                                               const int64_t *__restrict__ indices,
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
         // positions in order of the whole key (bitonic network over its lanes, the key made unique by
         // the lane it came from) and so finds the runs that a full sort would, cut at every G positions
         // at the most.
-        if (q.window_sort) {
+        if constexpr (WINDOW) {
             uint64_t sk = t.ok ? (((uint64_t)t.th << 6) | grp) : ((1ull << 40) | grp);
 #pragma unroll
             for (uint32_t kk = 2; kk <= 64u; kk <<= 1) {
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
 
         if (i0 + grp < n) {
             if (s.head != nullptr) s.head[i0 + grp] = my_lead ? 1 : 0;
-            if (q.window_sort && my_lead) s.keys[i0 + grp] = cur.th;      // (R2 and R4 read the keys of run starts; nobody else reads this position)
+            if (WINDOW && my_lead) s.keys[i0 + grp] = cur.th;      // (R2 and R4 read the keys of run starts; nobody else reads this position)
             // a run of one reads grad_out in place; the head of a longer run gets its row of P when the run
             // ends; every other position says that no run starts there (the gather variant of R5 reads
             // this array alone to find the runs)
