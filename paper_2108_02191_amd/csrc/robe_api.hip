@@ -1464,18 +1464,19 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
 // of up to 2^25 slots the update kernel leaves it there for the next forward pass, which the regions'
 // reads of many gradient rows undo: 25 M slots, batch 8192, 24000, 65536 in a training loop 187 / 179,
 // 325 / 305, 632 / 639.  So up to 2^25 slots only up to 2^20 tokens.
-static bool fused_regions_pay(const robe_hash_t *hash, int64_t n_indices, uint32_t d, bool bags)
+// (The same for bags and single-hot lookups: the workspace query does not know which will come.)
+static bool fused_regions_pay(const robe_hash_t *hash, int64_t n_indices, uint32_t d)
 {
     const uint32_t Z = hash->Z < d ? hash->Z : d;
-    if (hash->m > kKeepArrayMax) return hash->m >= (1ull << 26) || n_indices >= 50000 || sorting_pays(n_indices, d, Z, bags);
-    return hash->m >= (5ull << 22) && n_indices <= (1ll << 20) && sorting_pays(n_indices, d, Z, bags);
+    if (hash->m > kKeepArrayMax) return hash->m >= (1ull << 26) || n_indices >= 50000 || sorting_pays(n_indices, d, Z, false);
+    return hash->m >= (5ull << 22) && n_indices <= (1ll << 20) && sorting_pays(n_indices, d, Z, false);
 }
 
 static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,
                        const void *grad_out, BwdPlan *pl, size_t *scratch_bytes)
 {
     *scratch_bytes = 0;
-    const bool want = opt.fused_route == ROBE_ROUTE_AUTO ? fused_regions_pay(hash, n_indices, hash->d, bags) : opt.fused_route == ROBE_ROUTE_REGIONS;
+    const bool want = opt.fused_route == ROBE_ROUTE_AUTO ? fused_regions_pay(hash, n_indices, hash->d) : opt.fused_route == ROBE_ROUTE_REGIONS;
     if (opt.reproducible || want) {
         *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out, true);
         if (pl->regions) return true;

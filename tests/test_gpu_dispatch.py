@@ -25,6 +25,22 @@ def test_the_workspace_query_covers_single_hot_and_bags(d, Z, n):
     assert (single > 0) == (n >= 65_536 or n * (d // min(d, Z)) * (min(d, Z) + 15) // 16 >= 1_300_000)
 
 
+@pytest.mark.parametrize("m", [1_000_003, 20_971_519, 20_971_520, 25_000_000, 2**25, 2**25 + 1, 2**26, 250_000_000])
+@pytest.mark.parametrize("d,Z,sign", [(128, 32, 0), (128, 32, 1), (128, 1, 0), (64, 16, 1), (100, 10, 0), (16, 64, 0)])
+def test_the_fused_query_covers_single_hot_and_bags(m, d, Z, sign):
+    # a call without a workspace says how much it needs and launches nothing
+    import ctypes
+    h = robe.robe_init_hash(1, m, d, Z, sign)
+    L, fake = robe.lib(), ctypes.c_void_p(4096)
+    for n in (1, 49_999, 50_000, 65_535, 65_536, 78_000, 113_000, 114_000, 1 << 18, 1 << 20, (1 << 20) + 1, 1_700_000, 9_000_000):
+        query = robe.robe_fused_workspace_bytes(h, n, 1, n)
+        for offsets in (None, fake):
+            rc = L.robe_backward_adagrad(ctypes.byref(h), fake, fake, offsets, n, n, 1, fake, fake, 0.1, 1e-8, None, 0, None, None)
+            text = L.robe_last_error().decode()
+            assert rc == robe.ROBE_EINVAL and text.startswith("workspace of"), text
+            assert int(text.split()[2]) <= query, (n, offsets)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("bags", [False, True])
 @pytest.mark.parametrize("d,Z,n", SIZES)
