@@ -515,8 +515,10 @@ uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; re
 // need_regions: the caller (the fused step) wants the region-sorted scatter whatever the size.
 // mixed_floats: 0, or (tables of different dimensions, all multiples of Z; the hash is the widest
 // table's) the floats of grad_out, batch * sum(dims).
-BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,
-                      const void *grad_out, bool need_regions = false, uint64_t mixed_floats = 0)
+// tuned: region sizes and key bits by the size of the problem.  A reproducible call that the bound on a
+// region's records refuses with those is planned once more without (see plan_backward).
+BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,
+                           const void *grad_out, bool need_regions, uint64_t mixed_floats)
 {
     BwdPlan pl;
     memset(&pl, 0, sizeof(pl));
@@ -613,14 +615,14 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     if (!pl.gather && !elements) {
         shift = pick_region_shift(h, opt.region_shift);
         small = n * C * 8192u <= h->m * small_most_blocks(h->m);
-        if (small && shift != 0 && opt.region_shift == 0) {
+        if (tuned && small && shift != 0 && opt.region_shift == 0) {
             auto regions_at = [&](uint32_t sh) { return (h->m + (1ull << sh) - 1) >> sh; };
             while (shift < 15 && regions_at(shift + 1) >= kSmallLeastRegions && n * C <= regions_at(shift + 1) * kSmallFullest) ++shift;
         }
         // Reproducible: a region of more records than one round takes is split into classes, each of which
         // reads all its records; smaller regions instead where most would be (852 K lookups, d = 128,
         // Z = 8, 100 MB array, 800 records a region after combining: 600 -> 581 us; Z = 16, half as many: no gain).
-        if (opt.reproducible && !small && shift == 13 && opt.region_shift == 0 && n * C * 8192u > 3200 * h->m &&
+        if (tuned && opt.reproducible && !small && shift == 13 && opt.region_shift == 0 && n * C * 8192u > 3200 * h->m &&
             ((h->m + 4095) >> 12) <= robe::kMaxRegions && 4096u >= 2ull * h->Z && (1u << (12 - grp_shift)) >= h->Z)
             shift = 12;
         if (shift == 0 || shift < grp_shift || (1u << (shift - grp_shift)) < h->Z) return pl;   // a slice of the region must hold one block
@@ -631,21 +633,22 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     const uint64_t last_len = h->m - ((NR - 1) << shift);
     const uint64_t rec_per_block = (NR > 1 && last_len < h->Z) ? 3 : 2;
     if (!pl.gather && rec_per_block * n * C >= 0xFFFFFFFFull) return pl;
+    // Record kernels, up to 2^21 tokens: two radix passes (16 key bits) instead of three, as on the atomics
+    // route above, and the combine kernel orders the G positions that a lane group looks at by the whole
+    // key.  A frequent token's run is then also cut where other tokens of its key bucket (2^-16 of all
+    // tokens, eight times that for the bound) sit among its copies.
+    // Reproducible step on the 100 MB array, Z = 8: 614 -> 602 us (852 K tokens), Z = 32: 435 -> 421.
+    const uint32_t full_key_bits = pl.key_bits;
+    if (tuned && !pl.gather && !opt.key_bits && pl.key_top >= 16 && pl.lay.G >= 16 && n <= (1u << 21)) {
+        pl.key_bits = 16;
+        pl.window_sort = true;
+    }
     // The reproducible order of the record kernels splits an overfull region into at most
     // 2^kMaxClassShift classes of at most one round's records each.  Refuse what could come near that:
     // one and a half times the average region (hashed offsets spread evenly; a block in Z / R leaves a
     // second record), plus every run of the most frequent token (one per walk of a lane group) in one
     // region, against six tenths of the room.  (The gather variant stages its records in an order
     // that is fixed by the sorted list and needs no such split.)
-    // Record kernels, up to 2^21 tokens: two radix passes (16 key bits) instead of three, as on the atomics
-    // route below, and the combine kernel orders the G positions that a lane group looks at by the whole
-    // key.  A frequent token's run is then also cut where other tokens of its key bucket (2^-16 of all
-    // tokens, eight times that for the bound) sit among its copies.
-    // Reproducible step on the 100 MB array, Z = 8: 614 -> 602 us (852 K tokens), Z = 32: 435 -> 421.
-    if (!pl.gather && !opt.key_bits && pl.key_top >= 16 && pl.lay.G >= 16 && n <= (1u << 21)) {
-        pl.key_bits = 16;
-        pl.window_sort = true;
-    }
     auto within_reproducible_bound = [&](uint64_t walk_positions) {
         if (!opt.reproducible || pl.gather) return true;
         const uint64_t batch = h->use_sign ? robe::rec_batch<true>() : robe::rec_batch<false>();
@@ -664,6 +667,10 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     // (as long as the bound above holds: it counts one run of the most frequent token per walk)
     uint32_t stretch = robe::kStretch;
     while (stretch > 1 && n / ((uint64_t)robe::kBlock * stretch) < 2048) stretch >>= 1;
+    if (pl.window_sort && !within_reproducible_bound((uint64_t)stretch * pl.lay.G)) {      // the longer sort cuts fewer runs
+        pl.window_sort = false;
+        pl.key_bits = full_key_bits;
+    }
     while (stretch < (uint32_t)robe::kStretch && !within_reproducible_bound((uint64_t)stretch * pl.lay.G)) stretch <<= 1;
     if (!within_reproducible_bound((uint64_t)stretch * pl.lay.G)) return pl;
     const uint64_t walk = (uint64_t)stretch * pl.lay.G;
@@ -731,6 +738,14 @@ BwdPlan plan_backward(const robe_hash_t *caller_hash, const Opt &opt, int64_t ro
     }
     pl.bytes = off + 256;      // (slack: the padded reads above never leave the workspace)
     return pl;
+}
+
+BwdPlan plan_backward(const robe_hash_t *hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,
+                      const void *grad_out, bool need_regions = false, uint64_t mixed_floats = 0)
+{
+    const BwdPlan pl = plan_backward_with(true, hash, opt, rows, n_indices, bags, grad_out, need_regions, mixed_floats);
+    if (!opt.reproducible || pl.regions) return pl;
+    return plan_backward_with(false, hash, opt, rows, n_indices, bags, grad_out, need_regions, mixed_floats);
 }
 
 template <typename K>

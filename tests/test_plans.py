@@ -1,0 +1,42 @@
+"""What the calls accept, asked through the workspace queries: host arithmetic, no GPU."""
+import math
+import random
+
+import pytest
+
+import paper_2108_02191_amd as robe
+
+
+def accepted(query, *args, **options):
+    try:
+        query(*args, robe.options(**options))
+    except robe.RobeError as e:
+        assert e.code == robe.ROBE_EINVAL
+        return False
+    return True
+
+
+def _reproducible_shapes():
+    yield 376_864_942, 512, 2, 0, 33_910, 11
+    yield 25_000_000, 128, 1, 0, 700_000, 1
+    yield 404_529_294, 512, 2, 0, 13_972, 27
+    yield 133_675_900, 256, 8, 1, 259_352, 8
+    yield 725_339_600, 96, 1, 0, 39_975, 13
+    rng = random.Random(0)
+    for _ in range(4000):
+        d = rng.choice((8, 16, 32, 64, 96, 128, 256, 512))
+        Z = rng.choice([z for z in (1, 2, 4, 8, 16, 32) if d % z == 0])
+        m = int(math.exp(rng.uniform(math.log(10_000), math.log(2**30))))
+        F = rng.randint(1, 40)
+        yield m, d, Z, rng.randint(0, 1), int(math.exp(rng.uniform(math.log(50), math.log(4_000_000 / F)))), F
+
+
+def test_the_default_sort_refuses_no_reproducible_call_that_a_longer_sort_takes():
+    taken = 0
+    for m, d, Z, sign, B, F in _reproducible_shapes():
+        h = robe.robe_init_hash(1, m, d, Z, sign)
+        for query in (robe.robe_workspace_bytes, robe.robe_fused_workspace_bytes):
+            if accepted(query, h, B, F, B * F, reproducible=1, key_bits=24):
+                taken += 1
+                assert accepted(query, h, B, F, B * F, reproducible=1), (query.__name__, m, d, Z, sign, B, F)
+    assert taken > 1000
