@@ -260,11 +260,13 @@ int robe_backward(const robe_hash_t *hash, const float *grad_out,
  * robe_noalloc_max_workspace_bytes() = 32 MiB of device memory per GPU, present from the moment the
  * library is loaded until the process ends.  The call allocates and frees nothing (no hipMalloc, no
  * library routine that allocates); its first use on a device looks the buffer's address up once.
- * A problem whose workspace (robe_workspace_bytes with the same options) exceeds the buffer fails with
- * ROBE_EINVAL and launches nothing; problems that scatter directly need no workspace and have no
- * size limit (one of fewer than 2^25 gradient elements whose sort buffers do not fit goes directly).  The buffer holds nothing between calls that a call relies on.  All calls on one GPU
- * share it: two such calls that overlap in time on one GPU (different streams, or different threads)
- * race and give wrong results - order them on one stream or with events.
+ * When no route is asked for (ROBE_ROUTE_AUTO, not reproducible), fewer than 2^25 gradient elements
+ * (n_indices * d) scatter directly, which needs no workspace, and more of them take ROBE_ROUTE_COMBINE.
+ * A problem whose workspace (robe_workspace_bytes with the route taken) exceeds the buffer fails with
+ * ROBE_EINVAL and launches nothing; there is no other route to fall back on.  The buffer holds nothing
+ * between calls that a call relies on.  All calls on one GPU that sort share it: two such calls that
+ * overlap in time on one GPU (different streams, or different threads) race and give wrong results -
+ * order them on one stream or with events.  Calls that scatter directly do not touch it.
  * Errors: as robe_backward, plus ROBE_EHIP if the buffer's address cannot be obtained.
  */
 size_t robe_noalloc_max_workspace_bytes(void);

@@ -508,6 +508,9 @@ bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
     return requests >= 1300000u || (bags && n >= 65536);
 }
 
+// Whether a scatter of n tokens that asks for no route can do without a workspace: fewer than 2^25 elements.
+bool direct_takes(int64_t n, uint64_t d) { return (uint64_t)n * d < (1ull << 25); }
+
 uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; return s; }
 
 // Decide between the direct scatter, the combine-duplicates one and the region-sorted one, and lay
@@ -1372,20 +1375,16 @@ int robe_backward_noalloc(const robe_hash_t *hash, const float *grad_out, const 
 {
     size_t need = 0;
     if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, options, &need)) return rc;
-    // The default route does not fit: the sort alone may (small blocks), and a scatter of few enough
-    // elements goes directly (many narrow tokens).
-    robe_options_t other;
-    if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES &&
-        (options == nullptr || (options->backward_route == ROBE_ROUTE_AUTO && !options->reproducible))) {
-        if (options != nullptr) other = *options;
-        else memset(&other, 0, sizeof(other));
-        other.backward_route = ROBE_ROUTE_COMBINE;
-        if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &other, &need)) return rc;
-        if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES && (uint64_t)n_indices * hash->d < (1ull << 25)) {
-            other.backward_route = ROBE_ROUTE_DIRECT;
-            need = 0;
-        }
-        options = &other;
+    // Where nothing is asked for, small calls scatter directly whatever sorting would gain: the buffer is
+    // shared by all streams and threads of a GPU, and calls that use it must not overlap.  Larger ones
+    // sort, with atomics (the pairs of small blocks would not fit).
+    robe_options_t routed;
+    if (need > 0 && (options == nullptr || (options->backward_route == ROBE_ROUTE_AUTO && !options->reproducible))) {
+        if (options != nullptr) routed = *options;
+        else memset(&routed, 0, sizeof(routed));
+        routed.backward_route = direct_takes(n_indices, hash->d) ? ROBE_ROUTE_DIRECT : ROBE_ROUTE_COMBINE;
+        if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &routed, &need)) return rc;
+        options = &routed;
     }
     if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES)
         return fail(ROBE_EINVAL, "robe_backward_noalloc: this problem needs a workspace of %zu bytes, the built-in one holds %zu; "

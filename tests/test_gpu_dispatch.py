@@ -83,6 +83,27 @@ def test_noalloc_takes_many_narrow_tokens():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d,Z,n,bags,sorts", [(16, 4, 70_000, True, False), (128, 32, 200_000, False, False), (4, 1, 2**23 - 1, False, False),
+                                              (128, 32, 2**18 - 1, True, False), (128, 32, 2**18, False, True), (128, 1, 2**18, True, True)])
+def test_noalloc_sorts_from_two_to_the_25_elements_on(d, Z, n, bags, sorts):
+    # the built-in workspace is shared by all streams: what scatters directly leaves it alone
+    m = 500_009
+    h = robe.robe_init_hash(1, m, d, Z, 0)
+    begin, end, origin = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+    for e in (origin, begin, end):
+        e.record()
+    torch.cuda.synchronize()
+    first = origin.elapsed_time(begin)
+    opt = robe.options(probe_kernel=robe.PROBE_SORT, probe_begin=begin.cuda_event, probe_end=end.cuda_event)
+    off = torch.arange(n + 1, device=DEV) if bags else None
+    ga = torch.zeros(m, device=DEV)
+    robe.robe_backward_noalloc(h, torch.ones(n, 1, d, device=DEV), torch.arange(n, device=DEV), off, n, 1, ga, options=opt)
+    torch.cuda.synchronize()
+    assert (origin.elapsed_time(begin) != first) == sorts            # recorded anew, just before the sort
+    assert float(ga.sum(dtype=torch.float64)) == n * d
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [4096, 64 * 4096 - 1, 64 * 4096, 64 * 4096 + 1])
 def test_sort_on_both_sides_of_its_tile_limit(n):
     from tests import test_gpu_sort as S
