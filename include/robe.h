@@ -244,7 +244,9 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * call may be captured into a HIP graph.
  *   workspace  device buffer of at least robe_workspace_bytes(...) bytes (same options),
  *              256-byte aligned, contents undefined before and after; may be
- *              NULL when that size is 0
+ *              NULL when that size is 0.  A call that asks for no route and brings less
+ *              scatters directly if it has fewer than 2^25 gradient elements (n_indices * d); a
+ *              larger one of small blocks takes ROBE_ROUTE_COMBINE if that fits
  * Errors: ROBE_EINVAL (also: workspace too small), ROBE_EHIP.
  */
 int robe_backward(const robe_hash_t *hash, const float *grad_out,

@@ -511,6 +511,20 @@ bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
 // Whether a scatter of n tokens that asks for no route can do without a workspace: fewer than 2^25 elements.
 bool direct_takes(int64_t n, uint64_t d) { return (uint64_t)n * d < (1ull << 25); }
 
+// What a call falls back on that asks for no route and brings less workspace than its plan wants: the
+// direct scatter, or (from 2^25 elements on) the sort with atomics.
+Opt with_less_workspace(const Opt &opt, int64_t n, uint64_t d)
+{
+    Opt less = opt;
+    if (opt.bwd_route == ROBE_ROUTE_AUTO && !opt.reproducible) less.bwd_route = direct_takes(n, d) ? ROBE_ROUTE_DIRECT : ROBE_ROUTE_COMBINE;
+    return less;
+}
+
+bool workspace_holds(const void *workspace, size_t given, size_t need)
+{
+    return need == 0 || (workspace != nullptr && given >= need && aligned(workspace, 256));
+}
+
 uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; return s; }
 
 // Decide between the direct scatter, the combine-duplicates one and the region-sorted one, and lay
@@ -1198,7 +1212,12 @@ int robe_backward(const robe_hash_t *hash, const float *grad_out, const int64_t 
     Opt opt;
     if (int rc = read_options(options, &opt)) return rc;
     if (int rc = check_rows(hash, indices, offsets, n_indices, batch, n_features, &rows)) return rc;
-    const BwdPlan pl = plan_backward(hash, opt, rows, n_indices, offsets != nullptr, grad_out);
+    BwdPlan pl = plan_backward(hash, opt, rows, n_indices, offsets != nullptr, grad_out);
+    if (pl.dedup && (pl.elements || direct_takes(n_indices, hash->d)) && !workspace_holds(workspace, workspace_bytes, pl.bytes)) {
+        const Opt less = with_less_workspace(opt, n_indices, hash->d);
+        const BwdPlan small = plan_backward(hash, less, rows, n_indices, offsets != nullptr, grad_out);
+        if (workspace_holds(workspace, workspace_bytes, small.dedup ? small.bytes : 0)) pl = small;
+    }
     if (pl.dedup) {
         if (workspace == nullptr || workspace_bytes < pl.bytes)
             return fail(ROBE_EINVAL, "workspace of %zu bytes needed, %zu given", pl.bytes, workspace_bytes);
@@ -1331,6 +1350,10 @@ int robe_backward_mixed(const robe_hash_t *hash, const uint32_t *dims, const flo
     MixedPlan mp;
     if (int rc = plan_mixed(hash, opt, dims, batch, n_features, n_indices, offsets != nullptr, grad_out, false, &mp)) return rc;
     if (opt.reproducible && rows > 0 && n_indices > 0 && !(mp.sorted && mp.pl.regions)) return fail_not_reproducible();
+    if (mp.sorted && direct_takes(n_indices, (uint64_t)(mp.D / n_features)) && !workspace_holds(workspace, workspace_bytes, mp.bytes)) {
+        const Opt less = with_less_workspace(opt, n_indices, (uint64_t)(mp.D / n_features));
+        if (int rc = plan_mixed(hash, less, dims, batch, n_features, n_indices, offsets != nullptr, grad_out, false, &mp)) return rc;
+    }
     if (!mp.sorted)
         return launch_mixed<true>(hash, opt, dims, grad_out, indices, offsets, n_indices, batch, n_features, grad_array,
                                   grad_out, stream);
@@ -1515,7 +1538,7 @@ int robe_fused_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n
     const int64_t rows = batch * (int64_t)n_features;
     const bool fused = fused_plan(hash, opt, rows, n_indices, true, nullptr, &pl, &scratch);
     if (opt.reproducible && !fused && rows > 0 && n_indices > 0) return fail_not_reproducible();
-    *bytes = scratch + ((pl.dedup || pl.regions) ? pl.bytes : 0);
+    *bytes = scratch + (pl.dedup ? pl.bytes : 0);
     return ROBE_OK;
 }
 
@@ -1539,9 +1562,24 @@ static int fused_step(int rule, const robe_hash_t *hash, const float *grad_out, 
     if (!aligned(grad_out, 4)) return fail(ROBE_EINVAL, "float buffers must be 4-byte aligned");
     BwdPlan pl;
     size_t scratch = 0;
-    const bool fused = fused_plan(hash, opt, rows, n_indices, offsets != nullptr, grad_out, &pl, &scratch);
+    bool fused = fused_plan(hash, opt, rows, n_indices, offsets != nullptr, grad_out, &pl, &scratch);
     if (opt.reproducible && !fused) return fail_not_reproducible();
-    const size_t need = scratch + ((pl.dedup || pl.regions) ? pl.bytes : 0);
+    size_t need = scratch + (pl.dedup ? pl.bytes : 0);
+    if (!workspace_holds(workspace, workspace_bytes, need) && !opt.reproducible &&
+        (!fused || (opt.fused_route == ROBE_ROUTE_AUTO && hash->m < (1ull << 26)))) {      // two steps may need less
+        Opt less = with_less_workspace(opt, n_indices, hash->d);
+        less.fused_route = ROBE_ROUTE_TWO_STEP;
+        BwdPlan two;
+        size_t two_scratch = 0;
+        fused_plan(hash, less, rows, n_indices, offsets != nullptr, grad_out, &two, &two_scratch);
+        const size_t two_need = two_scratch + (two.dedup ? two.bytes : 0);
+        if (workspace_holds(workspace, workspace_bytes, two_need)) {
+            pl = two;
+            scratch = two_scratch;
+            need = two_need;
+            fused = false;
+        }
+    }
     if (need > 0 && (workspace == nullptr || workspace_bytes < need))
         return fail(ROBE_EINVAL, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
     if (need > 0 && !aligned(workspace, 256)) return fail(ROBE_EINVAL, "workspace must be 256-byte aligned");
@@ -1641,6 +1679,11 @@ int robe_backward_adagrad_mixed(const robe_hash_t *hash, const uint32_t *dims, c
     if (grad_out == nullptr) return fail(ROBE_EINVAL, "grad_out is NULL");
     if (!aligned(grad_out, 4)) return fail(ROBE_EINVAL, "float buffers must be 4-byte aligned");
     if (opt.reproducible && !fused) return fail_not_reproducible();
+    if (!fused && !workspace_holds(workspace, workspace_bytes, scratch + (mp.sorted ? mp.bytes : 0))) {      // the direct scatter needs less
+        const Opt less = with_less_workspace(opt, n_indices, (uint64_t)(mp.D / n_features));
+        if (int rc = fused_mixed_plan(hash, less, dims, batch, n_features, n_indices, offsets != nullptr, grad_out, &mp, &fused, &scratch))
+            return rc;
+    }
     const size_t need = scratch + (mp.sorted ? mp.bytes : 0);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need))
         return fail(ROBE_EINVAL, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
