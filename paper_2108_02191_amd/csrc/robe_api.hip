@@ -864,7 +864,6 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         r.keys = keys_out;
         r.keep_array = (rule != 0 && h->m <= kKeepArrayMax) ? 1u : 0u;
         const int vec_ok = aligned(grad_array, 16) && (rule != 1 || aligned(state, 16)) ? 1 : 0;
-        if (!vec_ok) r.small_cap = 0;     // region_small_kernel reads and writes whole vectors
         const float scale = rule == 2 ? -lr : (rule == 0 ? 1.0f : lr);    // what the reduce kernel gets as lr
         r.head = pl.gather ? nullptr : reinterpret_cast<uint8_t *>(ws + pl.off_head);
         r.src_row = reinterpret_cast<uint32_t *>(ws + pl.off_src_row);

@@ -1234,7 +1234,8 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(8,
 // The order of additions is by (slot, source block, sign term), so it is the same in every run.
 //
 // 250 M slots, 133 K tokens (batch 256 of bags of 20, d = 128, Z = 32): 79 us against 229 (3.8 TB/s of the lines it
-// touches).  Two records per 16 lanes in flight; one: 101 us, four: 95 (registers).  Regions that hold
+// touches).  Two records per 16 lanes in flight; one: 101 us, four: 95 (registers).  Array and state one float
+// off their alignment: whole call 158 us against 141 (one workgroup per region of that size: 520).  Regions that hold
 // more than kSmallRegion records (hot tokens, crowded regions) are left to region_reduce_kernel.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kSmallRegion = 128;     // records of a region, two per lane
@@ -1256,7 +1257,7 @@ __global__ __launch_bounds__(kSmallBlock) void region_small_kernel(Params p, Reg
                                                                    float *__restrict__ state, float lr, float eps)
 {
     constexpr uint32_t kWaves = kSmallBlock / 64;
-    typedef Vec<4>::A V4;
+    typedef Vec<4>::U V4;               // array and state at four-byte alignment: the order of additions must not depend on it
     __shared__ int32_t sort_a[kWaves][kSmallRegion];
     __shared__ uint32_t sort_src[kWaves][kSmallRegion];
     __shared__ uint32_t sort_tg[SIGN ? kWaves : 1][SIGN ? kSmallRegion : 1];

@@ -61,7 +61,7 @@ def test_small_regions_match_the_oracle(m, d, Z, sign, shift):
     ga = torch.from_numpy(start).to(DEV)
     robe.robe_backward(h, P.to_dev(G), P.to_dev(ids), P.to_dev(off), B, F, ga, options=opt)
     assert np.array_equal(ga.cpu().numpy().astype(np.float64), ref + 2.0)
-    # an unaligned gradient array takes the other kernel
+    # an unaligned gradient array
     odd = torch.from_numpy(np.concatenate([start[:1], start])).to(DEV)[1:]
     robe.robe_backward(h, P.to_dev(G), P.to_dev(ids), P.to_dev(off), B, F, odd, options=opt)
     assert np.array_equal(odd.cpu().numpy(), ga.cpu().numpy())
@@ -96,3 +96,23 @@ def test_small_regions_mixed_dimensions():
                              options=robe.options(backward_route=robe.ROUTE_REGIONS, region_records=1))
     assert np.array_equal(ga.cpu().numpy().astype(np.float64), ref)
     MD._fused_mixed_check(h, H, dims, G, ids, None, B, m, robe.options(fused_route=robe.ROUTE_REGIONS))
+
+
+@pytest.mark.parametrize("m,d,Z,sign,shift", [(10_000_002, 128, 32, 0, 0), (4_000_001, 32, 32, 1, 10), (2**26 + 3, 128, 32, 1, 0)])
+def test_reproducible_bits_do_not_depend_on_the_buffers_alignment(m, d, Z, sign, shift):
+    h, H, ids, off, B, F, _ = problem(m, d, Z, sign)
+    G = torch.randn(B, F, d, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+    opt = robe.options(reproducible=1, region_records=1, region_shift=shift)
+    start = torch.randn(m, device=DEV, generator=torch.Generator(DEV).manual_seed(2))
+    got = []
+    for pad in (0, 1, 2, 3):
+        bufs = [torch.empty(m + pad, device=DEV)[pad:] for _ in range(3)]
+        bufs[0].zero_()
+        robe.robe_backward(h, G, P.to_dev(ids), P.to_dev(off), B, F, bufs[0], options=opt)
+        bufs[1].copy_(start)
+        bufs[2].fill_(0.5)
+        robe.robe_backward_adagrad(h, G, P.to_dev(ids), P.to_dev(off), B, F, bufs[1], bufs[2], 0.1, 1e-8, options=opt)
+        got.append([b.clone().view(torch.int32) for b in bufs])
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert torch.equal(a, b)
