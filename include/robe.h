@@ -229,7 +229,7 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more with 2^21 tokens or
  * more) then collect the blocks by destination region and sum each region in LDS,
  * with no float atomic at all (ROBE_ROUTE_REGIONS; the route of the reproducible option).  Large
- * scatters of blocks of one or two floats, on arrays of up to 59 million slots, sort the values
+ * scatters of blocks of one or two floats, on arrays of half a million to 59 million slots, sort the values
  * themselves by region instead (nothing asks for that by name; the workspace holds eight bytes per
  * gradient element then).  The
  * sorted routes need the workspace, rows and n_indices below 2^31 - 1 and d <= 512 (with Z > d,

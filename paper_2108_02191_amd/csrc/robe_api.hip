@@ -491,8 +491,17 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 // gradient elements on.  Forward + backward on the 100 MB array, d = 128, 852 K lookups, float atomics /
 // pairs: Z = 1 2353 / 1551 us, Z = 2 1266 / 1007, Z = 4 750 / 772 (a block of four is one or two atomic
 // requests).  Z = 1 with 13 K, 52 K, 208 K lookups: 140 / 188, 255 / 251, 725 / 486.
-const uint32_t kElemMostZ = 2;
-const uint64_t kElemLeast = 1u << 23;
+// Further lines (backward alone, atomics / pairs, us):
+//   the last kernel has one workgroup per 2^14 slots: from 32 of them on.  Z = 2, 858 K lookups of d = 128,
+//   2^16, 2^18, 2^19, 2^22 slots: 672 / 1709, 672 / 688, 679 / 507, 675 / 332;
+//   the first two have one workgroup per 1024 tokens: from 2^16 tokens on.  Z = 1, d = 512, uniform ids,
+//   17.6 K tokens 435 / 515, 78 K 1976 / 602;
+//   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on.  9 M
+//   elements, uniform ids, d = 1, 8, Z = 1: 470 / 975, 443 / 244; d = 2, 4, 8, 16, Z = 2: 258 / 555,
+//   246 / 336, 247 / 297, 240 / 183.
+const uint32_t kElemMostZ = 2, kElemLeastRegions = 32;
+const uint64_t kElemLeast = 1u << 23, kElemLeastTokens = 1u << 16;
+uint32_t elem_least_d(uint32_t Z) { return 8 * Z; }
 
 // Whether a scatter of n tokens is worth the sort (about 45 us of launches and passes).  The direct
 // scatter is bound by its atomic requests of 64 bytes, d/Z blocks of 1 + (Z - 1)/16 each a token.
@@ -583,10 +592,10 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     // Region-sorted scatter on top of the combined runs.
     // Small blocks: the pairs of every element sorted by region, where nothing else is asked for.
     const uint64_t elem_regions = (h->m + (1u << robe::kElemShift) - 1) >> robe::kElemShift;
-    const bool elements = h->Z <= kElemMostZ && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
+    const bool elements = h->Z <= kElemMostZ && h->d >= elem_least_d(h->Z) && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
                           opt.fused_route != ROBE_ROUTE_REGIONS && opt.region_records == 0 && opt.region_shift == 0 &&
-                          elem_regions <= robe::kElemMaxRegions && (uint64_t)n * h->d < 0xFFFFFFFFull &&
-                          (uint64_t)n * h->d >= kElemLeast;
+                          elem_regions <= robe::kElemMaxRegions && elem_regions >= kElemLeastRegions &&
+                          n >= kElemLeastTokens && (uint64_t)n * h->d < 0xFFFFFFFFull && (uint64_t)n * h->d >= kElemLeast;
     const bool want_regions = elements || need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
     if (!want_regions) {
         // Atomics after the sort: up to 2^21 tokens, 16 key bits - two radix passes instead of three,

@@ -59,3 +59,40 @@ def test_small_blocks_match_the_oracle(m, d, Z, sign, bags):
     Md = torch.from_numpy(M.copy()).to(DEV)
     robe.robe_backward_sgd(h, dG, dids, doff, B, F, Md, 1.0)
     assert np.array_equal(Md.cpu().numpy(), M - ref.astype(np.float32))
+
+
+# (m, d, Z, sign, bags): the fewest regions with a last one of five slots, the narrowest rows
+MORE = [
+    (31 * 2**14 + 5, 100, 1, 0, False, 2**23),
+    (1_000_003, 8, 1, 0, False, 2**23),
+    (1_000_003, 16, 2, 1, False, 2**23),
+]
+
+
+@pytest.mark.parametrize("m,d,Z,sign,bags,elems", MORE)
+def test_small_blocks_at_the_edges_of_the_rule(m, d, Z, sign, bags, elems):
+    h, H = P.both_hashes(m + d, m, d, Z, sign)
+    rng = np.random.default_rng(m % 1009 + d)
+    F = 3
+    n = -(-(elems + 1000) // (d * F)) * F
+    ids = rng.permutation(n).astype(np.int64)               # all distinct: a pair for every gradient element
+    ids[:5000] = 7
+    B, off = n // F, None
+    if bags:
+        B = n // (4 * F)
+        off = np.sort(rng.integers(0, n + 1, size=B * F + 1))
+        off[0], off[-1] = 0, n
+    need = robe.robe_workspace_bytes(h, B, F, n)
+    assert need > robe.robe_workspace_bytes(h, B, F, n, robe.options(backward_route=robe.ROUTE_COMBINE))
+    G = rng.integers(-2, 3, size=(B, F, d)).astype(np.float32)
+    dG, dids, doff = P.to_dev(G), P.to_dev(ids), P.to_dev(off)
+    ref, _ = oracle.backward(H, G, ids, off, B, F, threads=8)
+    assert np.abs(ref).max() < 2**24
+    ga = torch.full((m,), 3.0, device=DEV)
+    robe.robe_backward(h, dG, dids, doff, B, F, ga)
+    assert np.array_equal(ga.cpu().numpy().astype(np.float64), ref + 3.0)
+    P._check_fused(h, H, G, ids, off, B, F, m)
+    M = np.random.default_rng(1).standard_normal(m).astype(np.float32)
+    Md = torch.from_numpy(M.copy()).to(DEV)
+    robe.robe_backward_sgd(h, dG, dids, doff, B, F, Md, 1.0)
+    assert np.array_equal(Md.cpu().numpy(), M - ref.astype(np.float32))
