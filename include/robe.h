@@ -229,9 +229,10 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more with 2^21 tokens or
  * more) then collect the blocks by destination region and sum each region in LDS,
  * with no float atomic at all (ROBE_ROUTE_REGIONS; the route of the reproducible option).  Large
- * scatters of blocks of one or two floats, on arrays of half a million to 59 million slots, sort the values
- * themselves by region instead (nothing asks for that by name; the workspace holds eight bytes per
- * gradient element then).  The
+ * scatters of blocks of one or two floats, on arrays of half a million to 59 million slots, sort the
+ * values themselves by region instead (nothing asks for that by name; beside the sort's buffers the
+ * workspace then holds at most three floats per array slot or 384 MiB, whichever is more; what finds no
+ * room there is added with atomics).  The
  * sorted routes need the workspace, rows and n_indices below 2^31 - 1 and d <= 512 (with Z > d,
  * Section 3.3, tokens are sorted by the array offset of their d slots instead of the token hash);
  * ROBE_ROUTE_REGIONS also needs d / Z and the lane group to be powers of two, at most 2^30 array

@@ -442,6 +442,7 @@ struct BwdPlan {
     bool dedup;          // sort the tokens and combine identical ones
     bool regions;        // ... and then sort the blocks by destination region instead of using float atomics
     bool elements;       // ... of the (place, value) pairs of small blocks (robe_backward_elements.h)
+    bool pairs_fit;      // ... with room for every gradient element
     bool spill_rows;     // ... with room in LDS for a row of Z floats per lane group of the reduce kernel
     bool gather;         // ... and the reduce kernel finds its blocks in the sorted token list (no record kernels)
     uint32_t crowded_most;   // regions only, small_cap: at most this many regions are left to the kernel with one workgroup per region
@@ -497,11 +498,17 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 //   the first two have one workgroup per 1024 tokens: from 2^16 tokens on.  Z = 1, d = 512, uniform ids,
 //   17.6 K tokens 435 / 515, 78 K 1976 / 602;
 //   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on.  9 M
-//   elements, uniform ids, d = 1, 8, Z = 1: 470 / 975, 443 / 244; d = 2, 4, 8, 16, Z = 2: 258 / 555,
-//   246 / 336, 247 / 297, 240 / 183.
+//   elements, uniform ids, d = 1, 4, 8, Z = 1: 470 / 975, 445 / 335 (but 110 M, of which few fit in the
+//   room below, 4682 / 5726), 443 / 244; d = 2, 4, 8, 16, Z = 2: 258 / 555, 246 / 336, 247 / 297, 240 / 183.
 const uint32_t kElemMostZ = 2, kElemLeastRegions = 32;
 const uint64_t kElemLeast = 1u << 23, kElemLeastTokens = 1u << 16;
 uint32_t elem_least_d(uint32_t Z) { return 8 * Z; }
+// Room for the pairs: one per array slot, or 2^25.  What does not fit goes by atomics (19.6 M pairs of
+// the 109 M elements above fit).  Where all tokens differ, little of a much larger problem would, and the
+// walk is then in vain, so gradient elements may be eight times the room at the most, four with Z = 2.
+// Half a float of summed rows per element included, that is three floats per array slot, or 384 MiB.
+uint64_t elem_room(uint64_t m) { return m > (1u << 25) ? m : (1u << 25); }
+uint64_t elem_most(uint64_t m, uint32_t Z) { return elem_room(m) * (Z == 1 ? 8 : 4); }
 
 // Whether a scatter of n tokens is worth the sort (about 45 us of launches and passes).  The direct
 // scatter is bound by its atomic requests of 64 bytes, d/Z blocks of 1 + (Z - 1)/16 each a token.
@@ -592,10 +599,11 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     // Region-sorted scatter on top of the combined runs.
     // Small blocks: the pairs of every element sorted by region, where nothing else is asked for.
     const uint64_t elem_regions = (h->m + (1u << robe::kElemShift) - 1) >> robe::kElemShift;
+    const uint64_t elems = (uint64_t)n * h->d, room = elems < elem_room(h->m) ? elems : elem_room(h->m);
     const bool elements = h->Z <= kElemMostZ && h->d >= elem_least_d(h->Z) && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
                           opt.fused_route != ROBE_ROUTE_REGIONS && opt.region_records == 0 && opt.region_shift == 0 &&
                           elem_regions <= robe::kElemMaxRegions && elem_regions >= kElemLeastRegions &&
-                          n >= kElemLeastTokens && (uint64_t)n * h->d < 0xFFFFFFFFull && (uint64_t)n * h->d >= kElemLeast;
+                          n >= kElemLeastTokens && elems >= kElemLeast && elems <= elem_most(h->m, h->Z);
     const bool want_regions = elements || need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
     if (!want_regions) {
         // Atomics after the sort: up to 2^21 tokens, 16 key bits - two radix passes instead of three,
@@ -709,6 +717,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
 
     pl.regions = true;
     pl.elements = elements;
+    pl.pairs_fit = elements && elems <= room;
     robe::RegionPlan &r = pl.rp;
     r.r_shift = shift;
     r.NR = (uint32_t)NR;
@@ -759,7 +768,8 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
         pl.off_counts = off;  off = align_up(off + NR * 4, 256);
         pl.off_starts = off;  off = align_up(off + (NR + 2) * 4, 256);
         pl.off_wg_first = off; off = align_up(off + (size_t)r.bin_blocks * NR * 4, 256);
-        pl.off_rec = off;     off = align_up(off + (elements ? (size_t)n * h->d : rec_per_block * n * C) * 8, 256);
+        pl.off_rec = off;     off = align_up(off + (elements ? room : rec_per_block * n * C) * 8, 256);
+        r.rec_cap = elements ? (uint32_t)room : 0u;
         pl.off_rec_tg = off;  if (h->use_sign && !elements) off = align_up(off + rec_per_block * n * C * 4, 256);
     }
     pl.bytes = off + 256;      // (slack: the padded reads above never leave the workspace)
@@ -939,7 +949,7 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
 #define ROBE_ELEMENTS(S_)                                                                                             \
     do {                                                                                                              \
         if (int rc = allow_lds(robe::element_scatter_kernel<S_>, lds_scatter, "backward (elements)")) return rc;      \
-        robe::element_scatter_kernel<S_><<<egrid, eblock, lds_scatter, stream>>>(p, r, row_shift, grad_out);                   \
+        robe::element_scatter_kernel<S_><<<egrid, eblock, lds_scatter, stream>>>(p, r, row_shift, grad_out, pl.pairs_fit ? nullptr : grad_array); \
     } while (0)
             if (sign) ROBE_ELEMENTS(true);
             else ROBE_ELEMENTS(false);
@@ -1524,13 +1534,11 @@ static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, in
     const bool want = opt.fused_route == ROBE_ROUTE_AUTO ? fused_regions_pay(hash, n_indices, hash->d) : opt.fused_route == ROBE_ROUTE_REGIONS;
     if (opt.reproducible || want) {
         *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out, true);
-        if (pl->regions) return true;
-    }
-    if (opt.fused_route == ROBE_ROUTE_AUTO) {             // small blocks: the pairs' workgroups apply the rule, whatever the array size
-        *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out);
-        if (pl->elements) return true;
+        if (pl->regions && (!pl->elements || pl->pairs_fit)) return true;
     }
     *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out);
+    // small blocks: the pairs' workgroups apply the rule, whatever the array size, if they are sure to get all pairs
+    if (opt.fused_route == ROBE_ROUTE_AUTO && pl->elements && pl->pairs_fit) return true;
     if (!pl->elements) pl->regions = false;              // the two-step fallback adds onto a gradient array
     *scratch_bytes = align_up((size_t)hash->m * 4, 256);
     return false;

@@ -13,6 +13,9 @@
 //                region by LDS counters, put into LDS in region order and written from there, so that
 //                consecutive lanes write consecutive pairs (region_bin_kernel, which writes its eight-byte
 //                records one by one, takes 246 us for as many and reads no rows; E2 170, E1 34).
+//                Pairs past the room for them (RegionPlan::rec_cap: the runs are not known on the host, and
+//                room for every gradient element was seventy times the rest of the workspace) are added
+//                to the gradient array with float atomics, as the other route adds all of them.
 //   E3 reduce    one workgroup per region of 2^14 slots adds its pairs into an LDS copy and applies the
 //                rule to it.  ds_add_f32 runs at 0.33 lanes per clock and CU on this GPU, a compare-and-swap
 //                at 2.2 (random places) to 4.7 (neighbours), but only one lane of those at a place gets
@@ -152,7 +155,8 @@ __global__ __launch_bounds__(kElemBlock) void element_count_kernel(Params p, Reg
 
 template <bool SIGN>
 __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, RegionPlan s, uint32_t row_shift,
-                                                                     const float *__restrict__ grad_out)
+                                                                     const float *__restrict__ grad_out,
+                                                                     float *__restrict__ spill)   // where pairs past rec_cap go; NULL: there are none
 {
     extern __shared__ uint32_t elem_lds[];
     uint2 *staged = reinterpret_cast<uint2 *>(elem_lds);          // kElemTile pairs in region order
@@ -166,7 +170,6 @@ __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, R
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint32_t *mine = s.wg_first + (uint64_t)blockIdx.x * s.NR;
     for (uint32_t r = t; r < s.NR; r += kElemBlock) next[r] = s.starts[r] + mine[r];   // (regions without pairs of this workgroup: never used)
-    const uint32_t cap = s.starts[s.NR];
     __syncthreads();
     const ElemLanes l = elem_lanes(p, row_shift);
     for_each_tile<SIGN>(s, l.runs, run_th, run_src, run_tg, wave_n, [&](uint32_t first, uint32_t count) {
@@ -240,7 +243,8 @@ __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, R
             if (j < items) {
                 const uint2 x = staged[j];
                 const uint32_t to = slot[x.x >> kElemShift] + j;
-                if (to < cap) s.rec[to] = x;                       // always, unless the inputs changed between E1 and E2
+                if (to < s.rec_cap) s.rec[to] = x;
+                else if (spill != nullptr) __hip_atomic_fetch_add(spill + x.x, __uint_as_float(x.y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         __syncthreads();
@@ -259,8 +263,8 @@ __global__ __launch_bounds__(kElemBlock) void element_reduce_kernel(Params p, Re
 {
     extern __shared__ float elem_acc[];
     const uint32_t r = blockIdx.x;
-    const uint32_t rb = s.starts[r], re = s.starts[r + 1u];
-    if (rb >= re) return;                                          // nothing lands in this region
+    const uint32_t rb = s.starts[r], end = s.starts[r + 1u], re = end < s.rec_cap ? end : s.rec_cap;
+    if (rb >= re) return;                                          // nothing lands in this region, or all of it past the room
     const uint32_t r0 = r << kElemShift;
     const uint32_t region_len = (p.m - r0) < (1u << kElemShift) ? (p.m - r0) : (1u << kElemShift);
     uint32_t *bits = reinterpret_cast<uint32_t *>(elem_acc);

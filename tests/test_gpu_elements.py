@@ -61,16 +61,19 @@ def test_small_blocks_match_the_oracle(m, d, Z, sign, bags):
     assert np.array_equal(Md.cpu().numpy(), M - ref.astype(np.float32))
 
 
-# (m, d, Z, sign, bags): the fewest regions with a last one of five slots, the narrowest rows
+# (m, d, Z, sign, bags): the fewest regions with a last one of five slots, the narrowest rows, and more
+# pairs than there is room for (2^25 on arrays this small): the rest is added with atomics
 MORE = [
     (31 * 2**14 + 5, 100, 1, 0, False, 2**23),
+    (31 * 2**14 + 5, 128, 1, 0, False, 2**25 + 2**22),
+    (600_007, 128, 2, 1, True, 2**25 + 2**22),
     (1_000_003, 8, 1, 0, False, 2**23),
     (1_000_003, 16, 2, 1, False, 2**23),
 ]
 
 
 @pytest.mark.parametrize("m,d,Z,sign,bags,elems", MORE)
-def test_small_blocks_at_the_edges_of_the_rule(m, d, Z, sign, bags, elems):
+def test_small_blocks_at_the_edges_of_their_room(m, d, Z, sign, bags, elems):
     h, H = P.both_hashes(m + d, m, d, Z, sign)
     rng = np.random.default_rng(m % 1009 + d)
     F = 3

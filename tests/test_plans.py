@@ -56,3 +56,23 @@ def test_small_blocks_are_sorted_by_value_only_where_it_pays():
                     took += 1
                     assert 2**19 - 2**14 < m <= 3600 * 2**14 and d >= 8 * Z and n >= 65_536 and n * d >= 2**23, (m, d, Z, n)
     assert took > 20
+
+
+def test_small_blocks_take_a_bounded_workspace():
+    """At most three floats per array slot (or 384 MiB) beside the sort's buffers, whatever the batch."""
+    took = 0
+    for m in (5, 16_384, 2**19 - 2**14, 2**19 - 2**14 + 1, 1_000_003, 25_000_000, 3600 * 2**14, 3600 * 2**14 + 1):
+        for d in (2, 4, 8, 16, 100, 128, 512):
+            for Z in (1, 2):
+                h = robe.robe_init_hash(1, m, d, Z, 1) if Z <= m else None
+                for n in (20_000, 65_535, 65_536, 400_000, 852_000, 3_500_000, 8_500_000, 30_000_000):
+                    need = robe.robe_workspace_bytes(h, n, 1, n)
+                    combine = robe.robe_workspace_bytes(h, n, 1, n, robe.options(backward_route=robe.ROUTE_COMBINE))
+                    if need in (0, combine):
+                        continue
+                    took += 1
+                    lists = combine + 9 * n + 2**22               # run starts and sign terms; counts per workgroup and region
+                    assert need <= lists + max(12 * m, 3 * 2**27), (m, d, Z, n)
+                    fused = robe.robe_fused_workspace_bytes(h, n, 1, n)
+                    assert fused <= lists + max(12 * m, 3 * 2**27) + 4 * m + 256
+    assert took > 50
