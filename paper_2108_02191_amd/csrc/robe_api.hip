@@ -233,6 +233,12 @@ struct TableView {
 // d = 128, bf16, 208 K bags (26 K): 54.9 / 38.0, 73.2 / 66.1, 101 / 102, 140 / 146; 52 K bags (6.5 K) of 3: 21.0 / 23.6.
 const int64_t kShortBagMean = 4, kShortBagWaves = 8192;
 
+// Widest rows (lanes times elements per lane) that single_hot_backward_window_kernel takes; wider ones keep the
+// kernel that finds the distinct tokens one by one.  Direct scatter of 34 K and of 60 K lookups, tile / window, us:
+// d = 16, Z = 4 16.9 / 12.7, 21.3 / 16.7; d = 32, Z = 32 22.5 / 19.5, 23.8 / 20.2 (ids without any frequent token
+// 18.1 / 20.0, 18.6 / 20.6); d = 48, Z = 16 20.3 / 17.5, 25.6 / 23.4; d = 96, Z = 32 28.2 / 30.6, 32.3 / 37.7.
+const uint32_t kWindowMostSlots = 48;
+
 template <bool BWD, typename AT = float>
 int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64_t *indices, const int64_t *offsets,
                 int64_t n_indices, int64_t rows, uint32_t F, float *dst, const void *rows_ptr, hipStream_t stream,
@@ -328,8 +334,8 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
 
 #define ROBE_LAUNCH_TILE(V_)                                                                                          \
     do {                                                                                                              \
-        if (q.G < 64u && sign) robe::single_hot_backward_window_kernel<V_, true><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);  \
-        else if (q.G < 64u) robe::single_hot_backward_window_kernel<V_, false><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);    \
+        if (q.G * V_ <= kWindowMostSlots && sign) robe::single_hot_backward_window_kernel<V_, true><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);  \
+        else if (q.G * V_ <= kWindowMostSlots) robe::single_hot_backward_window_kernel<V_, false><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);    \
         else if (sign) robe::single_hot_backward_tile_kernel<V_, true><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);  \
         else robe::single_hot_backward_tile_kernel<V_, false><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst);      \
     } while (0)

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("sign", [0, 1])
-@pytest.mark.parametrize("d,Z", [(8, 8), (16, 4), (20, 5), (32, 1), (16, 64), (48, 16), (128, 32)])
+@pytest.mark.parametrize("d,Z", [(8, 8), (16, 4), (20, 5), (32, 1), (16, 64), (48, 16), (96, 32), (128, 32)])
 def test_tiles_match_the_oracle(d, Z, sign):
     m = 50_021
     h, H = P.both_hashes(d + Z, m, d, Z, sign)
