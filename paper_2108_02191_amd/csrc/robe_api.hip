@@ -516,22 +516,27 @@ uint32_t elem_least_d(uint32_t Z) { return 8 * Z; }
 uint64_t elem_room(uint64_t m) { return m > (1u << 25) ? m : (1u << 25); }
 uint64_t elem_most(uint64_t m, uint32_t Z) { return elem_room(m) * (Z == 1 ? 8 : 4); }
 
-// Whether a scatter of n tokens is worth the sort (about 45 us of launches and passes).  The direct
-// scatter is bound by its atomic requests of 64 bytes, d/Z blocks of 1 + (Z - 1)/16 each a token.
-// Single-hot, whose duplicates it combines tile by tile, the two cross at 1.2 .. 1.4 million requests
-// (us direct / sorted: d = 128, Z = 32, batch 4000 of 26 tables 104 / 108, 8000 176 / 145; d = 16, Z = 4,
-// batch 8000 92 / 98, 16000 148 / 130; uniform ids, which have no duplicates, 118 / 126 and 197 / 180 at
-// d = 128).  With bags it combines nothing, the copies of a frequent token meet at the same addresses,
-// and the line is at some 65 thousand tokens whatever they hold (39 K tokens, d = 100, Z = 10: 89 / 90,
-// 117 K: 222 / 115; d = 20: 39 K 58 / 68, 117 K 122 / 85).
-bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
-{
-    const uint64_t requests = (uint64_t)n * (d / Z) * (Z + 15) / 16;
-    return requests >= 1300000u || (bags && n >= 65536);
-}
-
 // Whether a scatter of n tokens that asks for no route can do without a workspace: fewer than 2^25 elements.
 bool direct_takes(int64_t n, uint64_t d) { return (uint64_t)n * d < (1ull << 25); }
+
+// Whether a scatter of n tokens is worth the sort: always from 2^25 elements on, below by what it saves.
+// The direct scatter is bound by its atomic requests of 64 bytes, d/Z blocks of 1 + (Z - 1)/16 each a
+// token; the sort costs 30 (d = 8) to 75 us (d = 512) and some 0.1 us per thousand tokens.  Backward alone,
+// us, direct / sorted, Zipf ids.  Single-hot, whose duplicates the direct scatter combines tile by tile:
+// d = 128, Z = 32, 66 K lookups 42 / 54, 99 K 59 / 59, 220 K 118 / 80; d = 16, Z = 4, 150 K 36 / 48, 320 K
+// 71 / 68, 500 K 110 / 84; d = 512, Z = 32, 39 K 84 / 80; but d = 16, Z = 16 (two requests a token), 800 K
+// 98 / 111, d = 8, Z = 8, 3 M 300 / 389.  With bags it combines nothing and the copies of a frequent token meet
+// at the same addresses: d = 100, Z = 10, 39 K tokens 50 / 55, 66 K 81 / 58, 320 K 377 / 117; d = 64, Z = 16,
+// 66 K 43 / 50, 99 K 64 / 55; d = 16, Z = 4, 99 K 45 / 46, 150 K 66 / 50; d = 8, Z = 8, 220 K 47 / 48, 320 K 68 / 62.
+// Ids without frequent tokens gain nothing: uniform ones lose the sort's cost, d = 128, Z = 32, 150 K lookups
+// 101 / 123; as many tokens in bags, d = 64, Z = 16, 71 / 92.
+bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
+{
+    if (!direct_takes(n, d)) return true;
+    const uint64_t tokens = (uint64_t)n, requests = tokens * (d / Z) * (Z + 15) / 16;
+    if (bags && n >= 65536 && requests + tokens >= 650000u) return true;
+    return requests >= 1200000u + 1000u * (uint64_t)d && requests >= 1000000u + (d < 16 ? 2u * tokens : tokens + tokens / 4);
+}
 
 // What a call falls back on that asks for no route and brings less workspace than its plan wants: the
 // direct scatter, or (from 2^25 elements on) the sort with atomics.

@@ -12,17 +12,27 @@ from tests import test_gpu_parity as P
 DEV = "cuda:0"
 
 
-# (d, Z, tokens) around the line for bags (65536 tokens) and for single-hot lookups (1.3 million requests)
-SIZES = [(16, 4, 65_535), (16, 4, 65_536), (128, 32, 113_200), (128, 32, 113_500), (32, 128, 60_000), (100, 10, 83_000), (100, 10, 84_000)]
+# (d, Z, tokens) around the lines for bags (65536 tokens, 650 thousand of requests and tokens) and for
+# single-hot lookups (1.2 million requests and a thousand per float of a row, a million more than the tokens cost)
+SIZES = [(16, 4, 65_535), (16, 4, 65_536), (16, 4, 113_043), (16, 4, 113_044), (128, 32, 113_020), (128, 32, 113_030), (32, 128, 60_000),
+         (100, 10, 65_535), (100, 10, 83_199), (100, 10, 83_200), (16, 16, 900_000)]
+MORE_SIZES = [(16, 16, 2**21 - 1), (16, 16, 2**21), (8, 8, 2**22 - 1), (8, 8, 2**22)]        # around 2^25 gradient elements
 
 
-@pytest.mark.parametrize("d,Z,n", SIZES)
+def pays(d, Z, n, bags):
+    Z = min(d, Z)
+    requests = n * (d // Z) * (Z + 15) // 16
+    return (n * d >= 2**25 or (bags and n >= 65_536 and requests + n >= 650_000) or
+            (requests >= 1_200_000 + 1000 * d and requests >= 1_000_000 + (2 * n if d < 16 else n + n // 4)))
+
+
+@pytest.mark.parametrize("d,Z,n", SIZES + MORE_SIZES)
 def test_the_workspace_query_covers_single_hot_and_bags(d, Z, n):
     h = robe.robe_init_hash(1, 1_000_003, d, Z, 1)
     single = robe.robe_workspace_bytes(h, n, 1, n)
     forced = robe.robe_workspace_bytes(h, n, 1, n, robe.options(backward_route=robe.ROUTE_COMBINE))
     assert single in (0, forced)
-    assert (single > 0) == (n >= 65_536 or n * (d // min(d, Z)) * (min(d, Z) + 15) // 16 >= 1_300_000)
+    assert (single > 0) == (pays(d, Z, n, True) or pays(d, Z, n, False))
 
 
 @pytest.mark.parametrize("m", [1_000_003, 20_971_519, 20_971_520, 25_000_000, 2**25, 2**25 + 1, 2**26, 250_000_000])

@@ -36,7 +36,7 @@ def workspaces(size):
     return [buf[:0], buf[:256], buf[4:4 + size]]
 
 
-@pytest.mark.parametrize("d,Z,n,bags", [(16, 4, 70_000, True), (128, 32, 200_000, False), (128, 1, 2**17, False), (128, 2, 2**17, True)])
+@pytest.mark.parametrize("d,Z,n,bags", [(16, 4, 120_000, True), (128, 32, 200_000, False), (128, 1, 2**17, False), (128, 2, 2**17, True)])
 def test_backward_scatters_directly(d, Z, n, bags):
     h, H, ids, off, B, F, G = problem(M, d, Z, n, bags)
     need = robe.robe_workspace_bytes(h, B, F, n)

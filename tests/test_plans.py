@@ -76,3 +76,11 @@ def test_small_blocks_take_a_bounded_workspace():
                     fused = robe.robe_fused_workspace_bytes(h, n, 1, n)
                     assert fused <= lists + max(12 * m, 3 * 2**27) + 4 * m + 256
     assert took > 50
+
+
+def test_few_requests_a_token_are_not_sorted():
+    """Bags and lookups whose direct scatter is quicker than the sort alone, on both sides of 2^25 elements."""
+    for d, Z, n in ((8, 8, 70_000), (8, 8, 200_000), (16, 4, 70_000), (16, 16, 150_000), (32, 32, 100_000), (4, 2, 150_000)):
+        assert robe.robe_workspace_bytes(robe.robe_init_hash(1, 4_000_000, d, Z, 0), n, 1, n) == 0, (d, Z, n)
+    for d, Z, n in ((100, 10, 66_000), (64, 16, 80_000), (16, 4, 120_000), (128, 32, 120_000), (8, 8, 300_000), (4, 2, 2**23)):
+        assert robe.robe_workspace_bytes(robe.robe_init_hash(1, 4_000_000, d, Z, 0), n, 1, n) > 0, (d, Z, n)
