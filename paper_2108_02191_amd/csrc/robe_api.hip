@@ -429,15 +429,22 @@ const uint64_t kKeepArrayMax = 1ull << 25;
 
 // Regions with few records are taken by region_small_kernel, one wavefront each.  Its time follows the
 // records (0.26 ns each), that of region_reduce_kernel the array (8 ns per 8192 slots) and the records
-// (0.1 ns), so the batch's blocks per 8192 slots decide.  Whole step, small against one workgroup per
-// region, at 17 / 35 / 70 / 102 blocks: 190 / 277 / 426 / 555 against 333 / 396 / 524 / 594 us (250 M
-// slots, d = 128, Z = 32); at 31 / 62 / 124: 131 / 184 / 276 against 147 / 172 / 239 us (70 M slots).
-// With fewer regions the latency of their workgroups is hidden less often, so the line moves with the
-// array: 55 blocks at 70 M slots, 100 from 240 M on.
-uint64_t small_most_blocks(uint64_t m)
+// (0.1 ns), so the batch's blocks per 8192 slots decide.  With fewer regions the latency of their
+// workgroups is hidden less often, so the line moves with the array.  Fused call, wavefronts over
+// workgroups, Zipf (tables of a million ids on) / uniform ids, d = 128, Z = 32, blocks per 8192 slots 20, 40, 60, 90:
+//   21 M slots   0.91 / 0.96   1.04 / 1.16   1.15 / 1.32   1.24 / 1.54
+//   68 M         0.78 / 0.83   0.89 / 1.04   1.00 / 1.19   1.07 / 1.40
+//   250 M        0.48 / 0.58   0.63 / 0.85   0.78 / 1.01   0.82 / 1.19
+// Longer blocks take their 16 lanes several passes: Z = 128, 68 M slots, 8, 20, 40 blocks 0.84 / 0.87,
+// 0.95 / 1.08, 1.11 / 1.37.  With one block per token a frequent token leaves records enough at one place that
+// the wavefront adds one after the other: d = 16, Z = 16, tables from ten ids on, 8, 20, 60 blocks 0.89, 1.34, 1.25
+// (68 M slots), 0.67, 0.76, 0.94 (250 M, where the regions are more).  Both count as so many more blocks.
+bool few_records(uint64_t m, uint64_t blocks, uint32_t Z, uint64_t per_token)
 {
-    const uint64_t line = 36 + m / 3700000;
-    return line < 100 ? line : 100;
+    uint64_t weight = Z <= 32 ? 1 : 1 + Z / 64, line = 30 + m / 4000000;
+    if (per_token == 1 && m < 150000000u && weight < 3) weight = 3;
+    if (line > 78) line = 78;
+    return blocks * weight * 8192u <= m * line;
 }
 // Those regions may then be larger, which makes the record kernels cheaper: up to kSmallFullest blocks a
 // region (two lanes' worth is 128 records) and no fewer regions than there are wavefront slots.  250 M
@@ -659,7 +666,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     }
     if (!pl.gather && !elements) {
         shift = pick_region_shift(h, opt.region_shift);
-        small = n * C * 8192u <= h->m * small_most_blocks(h->m);
+        small = few_records(h->m, n * C, h->Z, C);
         if (tuned && small && shift != 0 && opt.region_shift == 0) {
             auto regions_at = [&](uint32_t sh) { return (h->m + (1ull << sh) - 1) >> sh; };
             while (shift < 15 && regions_at(shift + 1) >= kSmallLeastRegions && n * C <= regions_at(shift + 1) * kSmallFullest) ++shift;

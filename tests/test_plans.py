@@ -84,3 +84,16 @@ def test_few_requests_a_token_are_not_sorted():
         assert robe.robe_workspace_bytes(robe.robe_init_hash(1, 4_000_000, d, Z, 0), n, 1, n) == 0, (d, Z, n)
     for d, Z, n in ((100, 10, 66_000), (64, 16, 80_000), (16, 4, 120_000), (128, 32, 120_000), (8, 8, 300_000), (4, 2, 2**23)):
         assert robe.robe_workspace_bytes(robe.robe_init_hash(1, 4_000_000, d, Z, 0), n, 1, n) > 0, (d, Z, n)
+
+
+def test_long_blocks_and_single_ones_count_for_more_in_small_regions():
+    """Regions of few records grow past 2^13 slots: seen in the workspace, which holds counts for each of them."""
+    def grown(m, d, Z, n):
+        h = robe.robe_init_hash(1, m, d, Z, 0)
+        return (robe.robe_fused_workspace_bytes(h, n, 1, n) !=
+                robe.robe_fused_workspace_bytes(h, n, 1, n, robe.options(region_shift=13, region_records=1)))
+    m = 250_000_000
+    for d, Z, blocks in ((128, 32, 40), (128, 16, 20), (128, 64, 30), (128, 128, 20)):
+        assert grown(m, d, Z, blocks * m // 8192 * Z // d), (d, Z, blocks)
+    for d, Z, blocks in ((128, 64, 42), (128, 128, 28)):
+        assert not grown(m, d, Z, blocks * m // 8192 * Z // d), (d, Z, blocks)
