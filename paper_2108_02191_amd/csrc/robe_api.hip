@@ -1528,11 +1528,14 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
 // The fused step uses the region-sorted scatter when it applies and is worth its launches; otherwise a
 // gradient array in the workspace and the two separate steps, which fill it, scatter with atomics and
 // sweep all m slots.  From 2^26 slots on the sweeps alone cost more than the region route's fixed part,
-// whatever the batch size.  Below, the region route wins from about 20 M slots on once the tokens are
-// worth sorting, from 2^25 slots on also with somewhat fewer.  Forward + fused step, two steps / regions,
-// us, d = 128, Z = 32, 26 single-hot tables (batch 6000, 24000, 66000): 16 M slots 141 / 134, 312 / 317,
-// 643 / 653; 25 M 158 / 146, 342 / 322, 685 / 667; 60 M 210 / 189, 395 / 366, 792 / 751; batch 3000:
-// 25 M 116 / 120, 60 M 164 / 126.  Bags of 20, 25 M slots, batch 256 and 1000: 173 / 141, 344 / 240.
+// whatever the batch size.  Below, the region route wins from about 20 M slots on for rows of some length.
+// Fused call alone, two steps / regions, us, Zipf ids, 26 single-hot tables (and uniform ids):
+//   d = 128, Z = 32   25 M slots, 50 K, 100 K, 400 K, 1 M lookups 95 / 99, 112 / 106, 183 / 165, 285 / 290
+//                     (50 K 101 / 102, 100 K 139 / 118, 400 K 367 / 218); 60 M, 50 K 129 / 98
+//   d = 64, Z = 16    25 M, 100 K, 200 K, 400 K 101 / 105, 119 / 116, 153 / 148 (200 K 187 / 139)
+//   d = 32, Z = 4     25 M, 200 K 137 / 119, 1 M 203 / 215; 33 M, 1 M 260 / 238
+//   d = 16, Z = 4     25 M, 100 K 75 / 86, 400 K 135 / 150
+//   d = 128, Z = 128  33 M, 200 K 134 / 123, 1 M 278 / 364 (a frequent token's records all lie in one region)
 // Those are passes on arrays that the last-level cache has lost in between.  Step after step on one array
 // of up to 2^25 slots the update kernel leaves it there for the next forward pass, which the regions'
 // reads of many gradient rows undo: 25 M slots, batch 8192, 24000, 65536 in a training loop 187 / 179,
@@ -1540,9 +1543,14 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
 // (The same for bags and single-hot lookups: the workspace query does not know which will come.)
 static bool fused_regions_pay(const robe_hash_t *hash, int64_t n_indices, uint32_t d)
 {
+    const uint64_t m = hash->m;
+    if (m >= (1ull << 26)) return true;
+    if (m < (5ull << 22) || d < 32) return false;
+    if (m <= kKeepArrayMax && n_indices > (1ll << 20)) return false;
+    if (n_indices > (1ll << 18) && ((d < 64 && m < 33000000u) || (d >= 128 && hash->Z >= d && m < 40000000u))) return false;
     const uint32_t Z = hash->Z < d ? hash->Z : d;
-    if (hash->m > kKeepArrayMax) return hash->m >= (1ull << 26) || n_indices >= 50000 || sorting_pays(n_indices, d, Z, false);
-    return hash->m >= (5ull << 22) && n_indices <= (1ll << 20) && sorting_pays(n_indices, d, Z, false);
+    const uint64_t requests = (uint64_t)n_indices * (d / Z) * (Z + 15) / 16;      // as in sorting_pays
+    return requests >= (m >= 50000000u ? 500000u : 1000000u);
 }
 
 static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, int64_t n_indices, bool bags,

@@ -97,3 +97,17 @@ def test_long_blocks_and_single_ones_count_for_more_in_small_regions():
         assert grown(m, d, Z, blocks * m // 8192 * Z // d), (d, Z, blocks)
     for d, Z, blocks in ((128, 64, 42), (128, 128, 28)):
         assert not grown(m, d, Z, blocks * m // 8192 * Z // d), (d, Z, blocks)
+
+
+def test_the_fused_step_takes_regions_by_rows_and_requests():
+    def regions(m, d, Z, n):
+        h = robe.robe_init_hash(1, m, d, Z, 0)
+        need = [robe.robe_fused_workspace_bytes(h, n, 1, n, robe.options(fused_route=r)) for r in (robe.ROUTE_AUTO, robe.ROUTE_REGIONS, robe.ROUTE_TWO_STEP)]
+        assert need[0] in need[1:] and need[1] != need[2]
+        return need[0] == need[1]
+    for m, d, Z, n in ((25_000_000, 128, 32, 100_000), (25_000_000, 64, 16, 200_000), (25_000_000, 32, 4, 200_000), (60_000_000, 128, 32, 50_000),
+                       (33_000_000, 128, 128, 200_000), (40_000_000, 128, 32, 1_700_000), (2**26, 16, 16, 100)):
+        assert regions(m, d, Z, n), (m, d, Z, n)
+    for m, d, Z, n in ((20_000_000, 128, 32, 400_000), (25_000_000, 128, 32, 50_000), (25_000_000, 16, 4, 400_000), (25_000_000, 32, 4, 400_000),
+                       (33_000_000, 128, 128, 400_000), (25_000_000, 128, 32, 2**20 + 1), (34_000_000, 16, 16, 150_000), (34_000_000, 64, 64, 100_000)):
+        assert not regions(m, d, Z, n), (m, d, Z, n)
