@@ -231,7 +231,11 @@ struct TableView {
 // at least this many wavefronts, one for every slot of the GPU.  One bag per lane group / four, us: d = 100,
 // 39 K bags (9.8 K wavefronts of four) of 1, 3, 6, 10 tokens: 24.6 / 15.6, 31.0 / 24.0, 40.1 / 35.9, 51.7 / 51.4;
 // d = 128, bf16, 208 K bags (26 K): 54.9 / 38.0, 73.2 / 66.1, 101 / 102, 140 / 146; 52 K bags (6.5 K) of 3: 21.0 / 23.6.
+// Narrow rows have the bags of a wavefront side by side already, so from lane groups of 16 on: 338 K bags of 2,
+// 25 M slots, d = 32, Z = 8 (groups of 8) 43.3 / 49.9, d = 64, Z = 16 72.2 / 59.7.
 const int64_t kShortBagMean = 4, kShortBagWaves = 8192;
+const uint32_t kShortBagLanes = 16;
+static_assert(kShortBagLanes >= robe::kShortBags, "a wavefront walks at most 64 rows");
 
 // Widest rows (lanes times elements per lane) that single_hot_backward_window_kernel takes; wider ones keep the
 // kernel that finds the distinct tokens one by one.  Direct scatter of 34 K and of 60 K lookups, tile / window, us:
@@ -288,7 +292,7 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
     // options->tile_combine: 1 never, 2 always.
     const bool tile = BWD && !bags && !lay.consec && (opt.tile_combine == 2 || (opt.tile_combine == 0 && rows >= 32768));
     // short bags: several to a lane group, as long as that leaves a wavefront for every slot of the GPU
-    const bool short_bags = !BWD && bags && lay.G >= robe::kShortBags && n_indices <= kShortBagMean * rows && n_indices < (1ll << 29) &&
+    const bool short_bags = !BWD && bags && lay.G >= kShortBagLanes && n_indices <= kShortBagMean * rows && n_indices < (1ll << 29) &&
                             rows >= (int64_t)(step * robe::kShortBags) * kShortBagWaves;
     const int64_t rows_per_wave = tile ? 64 : (short_bags ? (int64_t)(step * robe::kShortBags) : (bags ? (int64_t)step : (int64_t)q.TL));
     const int64_t waves = (rows + rows_per_wave - 1) / rows_per_wave;

@@ -15,11 +15,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("d,Z,sign", [(100, 10, 1), (128, 32, 0), (32, 4, 1), (16, 64, 0), (200, 100, 0)])
+@pytest.mark.parametrize("d,Z,sign", [(100, 10, 1), (128, 32, 0), (32, 4, 1), (16, 64, 0), (200, 100, 0), (64, 16, 1), (48, 16, 0)])
 def test_short_bags(d, Z, sign):
     m, F = 30_011, 3
     h, H = P.both_hashes(d, m, d, Z, sign)
-    G = {100: 64, 128: 32, 32: 8, 16: 4, 200: 64}[d]
+    G = {100: 64, 128: 32, 32: 8, 16: 4, 200: 64, 64: 16, 48: 16}[d]     # (below 16 lanes: the one-bag kernel)
     rows = 8192 * 4 * (64 // G) + 5                  # a few past the least that the kernel takes
     B = -(-rows // F)
     rng = np.random.default_rng(d)
