@@ -21,11 +21,11 @@ CASES = [
     (25_000_001, 128, 1, 1, True),
     (3600 * 2**14, 128, 2, 0, False),      # the most regions the route takes, and one slot more
     (3600 * 2**14 + 1, 128, 2, 0, False),
-    (5, 100, 1, 0, False),                 # a region of five slots
+    (5, 100, 1, 0, False),                 # (too small an array for the route: sorted atomics)
     (700_001, 100, 2, 1, False),           # lanes past the row stay idle
     (700_002, 512, 1, 0, True),            # the widest rows
-    (300_007, 16, 2, 1, False),
-    (300_006, 2, 8, 0, False),             # blocks larger than embeddings: pairs of two slots
+    (300_007, 16, 2, 1, False),            # (the same)
+    (300_006, 2, 8, 0, False),             # (the same, blocks larger than embeddings)
 ]
 
 
