@@ -224,10 +224,11 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * token per row).  Accumulates onto the caller's grad_array (device float[m]);
  * the order of the float32 additions is not fixed, so results agree with an
  * exact sum only to rounding.  Small scatters issue one float atomic per
- * element (ROBE_ROUTE_DIRECT), up to some million of them or, with bags, some 65 thousand tokens.  Larger ones first combine the gradient rows of repeated tokens
- * (sort by the token part of the hash, run-wise sums) and issue the atomics
- * once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more with 2^21 tokens or
- * more) then collect the blocks by destination region and sum each region in LDS,
+ * element (ROBE_ROUTE_DIRECT): up to some million atomic requests of 64 bytes, with bags up to
+ * some 65 thousand tokens or more of narrow ones, and only below 2^25 elements.  Larger ones first
+ * combine the gradient rows of repeated tokens (sort by the token part of the hash, run-wise sums)
+ * and issue the atomics once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more
+ * with 2^21 tokens or more) then collect the blocks by destination region and sum each region in LDS,
  * with no float atomic at all (ROBE_ROUTE_REGIONS; the route of the reproducible option).  Large
  * scatters of blocks of one or two floats, on arrays of half a million to 59 million slots, sort the
  * values themselves by region instead (nothing asks for that by name; beside the sort's buffers the
@@ -307,8 +308,8 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
  * Fused training step: backward scatter-add (Eq. 3) and the Adagrad update in one pass, for a
  * gradient array that would otherwise start from zero.  The result is that of
  *   robe_backward(..., grad_array = zeros, ...) followed by robe_adagrad_update(array, state, grad_array)
- * to the same rounding caveats, but on large arrays (by size of array and batch, from 20 million slots
- * on; always from 2^26) and for small blocks the gradient never exists in device memory:
+ * to the same rounding caveats, but on large arrays (from 20 million slots on by the size of array,
+ * rows and batch; always from 2^26) and for small blocks the gradient never exists in device memory:
  * the blocks are collected by destination region, every region of the array is summed in LDS by the
  * one workgroup that owns it, and that workgroup updates array and state directly.  Slots that
  * receive no gradient are left bit-for-bit unchanged, and regions that receive none are not read.

@@ -463,7 +463,7 @@ struct BwdPlan {
     bool spill_rows;     // ... with room in LDS for a row of Z floats per lane group of the reduce kernel
     bool gather;         // ... and the reduce kernel finds its blocks in the sorted token list (no record kernels)
     uint32_t crowded_most;   // regions only, small_cap: at most this many regions are left to the kernel with one workgroup per region
-    bool window_sort;    // atomics route after a sort on few key bits: the combine kernel orders each wavefront's positions itself
+    bool window_sort;    // after a sort on few key bits the combine kernel orders the positions it looks at together itself (Geom::window_sort)
     Layout lay;
     robe_hash_t eff;     // the instance the kernels after the key kernel run on: the caller's, or (Z > d) its one-chunk form
     uint32_t key_top;    // keys are below 2^key_top
@@ -1668,7 +1668,7 @@ int robe_backward_sgd(const robe_hash_t *hash, const float *grad_out, const int6
 }
 
 // The fused step over tables of mixed dimensions: the region route when the plan has one (and the
-// array is large, or it is asked for), else two steps through a gradient array at the front of the
+// array is large, or it is asked for; the finer line of fused_regions_pay was not measured for it), else two steps through a gradient array at the front of the
 // workspace, like robe_backward_adagrad.
 static int fused_mixed_plan(const robe_hash_t *hash, const Opt &opt, const uint32_t *dims, int64_t batch, int32_t n_features,
                             int64_t n_indices, bool bags, const void *grad_out, MixedPlan *mp, bool *fused, size_t *scratch_bytes)

@@ -474,7 +474,7 @@ __global__ __launch_bounds__(kBlock) void single_hot_backward_tile_kernel(Params
 }
 
 // ---------------------------------------------------------------------------
-// The same for rows of several lane groups to a wavefront (G <= 32, so up to 32 .. 256 floats).
+// The same for rows of several lane groups to a wavefront (G <= 32; taken for rows of up to 48 floats).
 //
 // At the sizes that come here (some ten thousand lookups) a SIMD holds one wavefront and the kernel is a
 // chain of latencies.  The one above finds the distinct tokens one by one, 64 rounds of dependent lane
