@@ -723,12 +723,18 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     // (as long as the bound above holds: it counts one run of the most frequent token per walk)
     uint32_t stretch = robe::kStretch;
     while (stretch > 1 && n / ((uint64_t)robe::kBlock * stretch) < 2048) stretch >>= 1;
-    if (pl.window_sort && !within_reproducible_bound((uint64_t)stretch * pl.lay.G)) {      // the longer sort cuts fewer runs
-        pl.window_sort = false;
+    const uint32_t wanted = stretch;
+    auto lengthen = [&] {
+        stretch = wanted;
+        while (stretch < (uint32_t)robe::kStretch && !within_reproducible_bound((uint64_t)stretch * pl.lay.G)) stretch <<= 1;
+        return within_reproducible_bound((uint64_t)stretch * pl.lay.G);
+    };
+    if (!lengthen()) {
+        if (!pl.window_sort) return pl;
+        pl.window_sort = false;                            // the longer sort cuts fewer runs
         pl.key_bits = full_key_bits;
+        if (!lengthen()) return pl;
     }
-    while (stretch < (uint32_t)robe::kStretch && !within_reproducible_bound((uint64_t)stretch * pl.lay.G)) stretch <<= 1;
-    if (!within_reproducible_bound((uint64_t)stretch * pl.lay.G)) return pl;
     const uint64_t walk = (uint64_t)stretch * pl.lay.G;
     const uint32_t p_quota = walk / 8 ? (uint32_t)(walk / 8) : 1u;
     const uint64_t combine_blocks = (n + (uint64_t)robe::kBlock * stretch - 1) / ((uint64_t)robe::kBlock * stretch);
