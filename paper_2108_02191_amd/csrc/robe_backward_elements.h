@@ -167,6 +167,7 @@ __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, R
     uint32_t *run_tg = run_src + kElemRuns + kElemBlock;
     uint32_t *wave_n = run_tg + (SIGN ? kElemRuns + kElemBlock : 0u);
     uint32_t *wave_sum = wave_n + 16;
+    uint32_t *spills = wave_sum + 16;                             // 1: pairs of the tile lie past rec_cap
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint32_t *mine = s.wg_first + (uint64_t)blockIdx.x * s.NR;
     for (uint32_t r = t; r < s.NR; r += kElemBlock) next[r] = s.starts[r] + mine[r];   // (regions without pairs of this workgroup: never used)
@@ -175,6 +176,7 @@ __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, R
     for_each_tile<SIGN>(s, l.runs, run_th, run_src, run_tg, wave_n, [&](uint32_t first, uint32_t count) {
         const uint32_t items = count * p.d;
         for (uint32_t r = t; r < s.NR; r += kElemBlock) cnt[r] = 0;
+        if (t == 0) *spills = 0;
         __syncthreads();
         uint32_t at[kElemPer], rank[kElemPer];
         float v[kElemPer];
@@ -226,6 +228,7 @@ __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, R
                 cnt[r] = a;
                 slot[r] = out - a;                                 // (wraps; the sum below is the slot)
                 next[r] = out + c[q];
+                if (c[q] && out + c[q] > s.rec_cap) *spills = 1;
             }
             a += c[q];
         }
@@ -237,10 +240,17 @@ __global__ __launch_bounds__(kElemBlock) void element_scatter_kernel(Params p, R
                 staged[cnt[at[u] >> kElemShift] + rank[u]] = make_uint2(at[u], __float_as_uint(v[u]));
             }
         __syncthreads();
+        if (*spills == 0) {                                       // (its own loop: the check inside it cost 6 us of 170)
 #pragma unroll
-        for (uint32_t u = 0; u < kElemPer; ++u) {
-            const uint32_t j = t + u * kElemBlock;
-            if (j < items) {
+            for (uint32_t u = 0; u < kElemPer; ++u) {
+                const uint32_t j = t + u * kElemBlock;
+                if (j < items) {
+                    const uint2 x = staged[j];
+                    s.rec[slot[x.x >> kElemShift] + j] = x;
+                }
+            }
+        } else {
+            for (uint32_t j = t; j < items; j += kElemBlock) {
                 const uint2 x = staged[j];
                 const uint32_t to = slot[x.x >> kElemShift] + j;
                 if (to < s.rec_cap) s.rec[to] = x;
