@@ -514,18 +514,22 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 //   2^16, 2^18, 2^19, 2^22 slots: 672 / 1709, 672 / 688, 679 / 507, 675 / 332;
 //   the first two have one workgroup per 1024 tokens: from 2^16 tokens on.  Z = 1, d = 512, uniform ids,
 //   17.6 K tokens 435 / 515, 78 K 1976 / 602;
-//   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on.  9 M
-//   elements, uniform ids, d = 1, 4, 8, Z = 1: 470 / 975, 445 / 335 (but 110 M, of which few fit in the
-//   room below, 4682 / 5726), 443 / 244; d = 2, 4, 8, 16, Z = 2: 258 / 555, 246 / 336, 247 / 297, 240 / 183.
+//   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on, from four
+//   on arrays of up to 2^25 slots if all pairs are sure to fit in the room below.  9 M elements, uniform ids,
+//   d = 1, 4, 8, Z = 1: 470 / 975, 445 / 335 (110 M elements, most without room: 4682 / 5726), 443 / 244;
+//   d = 2, 4, 8, 16, Z = 2: 258 / 555, 246 / 336, 243 / 240 (58 M slots: 247 / 297), 240 / 183.
 const uint32_t kElemMostZ = 2, kElemLeastRegions = 32;
 const uint64_t kElemLeast = 1u << 23, kElemLeastTokens = 1u << 16;
-uint32_t elem_least_d(uint32_t Z) { return 8 * Z; }
 // Room for the pairs: one per array slot, or 2^25.  What does not fit goes by atomics (19.6 M pairs of
 // the 109 M elements above fit).  Where all tokens differ, little of a much larger problem would, and the
 // walk is then in vain, so gradient elements may be eight times the room at the most, four with Z = 2.
 // Half a float of summed rows per element included, that is three floats per array slot, or 384 MiB.
 uint64_t elem_room(uint64_t m) { return m > (1u << 25) ? m : (1u << 25); }
-uint64_t elem_most(uint64_t m, uint32_t Z) { return elem_room(m) * (Z == 1 ? 8 : 4); }
+uint64_t elem_most(uint64_t m, uint32_t d, uint32_t Z)
+{
+    if (d / Z >= 8) return elem_room(m) * (Z == 1 ? 8 : 4);
+    return d / Z >= 4 && m <= (1u << 25) ? elem_room(m) : 0;
+}
 
 // Whether a scatter of n tokens that asks for no route can do without a workspace: fewer than 2^25 elements.
 bool direct_takes(int64_t n, uint64_t d) { return (uint64_t)n * d < (1ull << 25); }
@@ -622,10 +626,10 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     // Small blocks: the pairs of every element sorted by region, where nothing else is asked for.
     const uint64_t elem_regions = (h->m + (1u << robe::kElemShift) - 1) >> robe::kElemShift;
     const uint64_t elems = (uint64_t)n * h->d, room = elems < elem_room(h->m) ? elems : elem_room(h->m);
-    const bool elements = h->Z <= kElemMostZ && h->d >= elem_least_d(h->Z) && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
+    const bool elements = h->Z <= kElemMostZ && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
                           opt.fused_route != ROBE_ROUTE_REGIONS && opt.region_records == 0 && opt.region_shift == 0 &&
                           elem_regions <= robe::kElemMaxRegions && elem_regions >= kElemLeastRegions &&
-                          n >= kElemLeastTokens && elems >= kElemLeast && elems <= elem_most(h->m, h->Z);
+                          n >= kElemLeastTokens && elems >= kElemLeast && elems <= elem_most(h->m, h->d, h->Z);
     const bool want_regions = elements || need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
     if (!want_regions) {
         // Atomics after the sort: up to 2^21 tokens, 16 key bits - two radix passes instead of three,

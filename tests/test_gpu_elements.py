@@ -67,7 +67,8 @@ MORE = [
     (31 * 2**14 + 5, 100, 1, 0, False, 2**23),
     (31 * 2**14 + 5, 128, 1, 0, False, 2**25 + 2**22),
     (600_007, 128, 2, 1, True, 2**25 + 2**22),
-    (1_000_003, 8, 1, 0, False, 2**23),
+    (1_000_003, 4, 1, 0, False, 2**23),
+    (1_000_003, 8, 2, 1, True, 2**23),
     (1_000_003, 16, 2, 1, False, 2**23),
 ]
 

@@ -43,18 +43,20 @@ def test_the_default_sort_refuses_no_reproducible_call_that_a_longer_sort_takes(
 
 
 def test_small_blocks_are_sorted_by_value_only_where_it_pays():
-    """Arrays of 32 regions of 2^14 slots or more, rows of eight blocks, 2^16 tokens, 2^23 gradient elements."""
+    """Arrays of 32 regions of 2^14 slots or more, rows of eight blocks (four if all is sure to fit), 2^16 tokens,
+    2^23 gradient elements."""
     took = 0
     for m in (5, 16_384, 2**19 - 2**14, 2**19 - 2**14 + 1, 1_000_003, 25_000_000, 3600 * 2**14, 3600 * 2**14 + 1):
         for d in (2, 4, 8, 16, 100, 128, 512):
             for Z in (1, 2):
                 h = robe.robe_init_hash(1, m, d, Z, 1)
-                for n in (20_000, 65_535, 65_536, 400_000, 852_000):
+                for n in (20_000, 65_535, 65_536, 400_000, 852_000, 2_200_000, 9_000_000):
                     need = robe.robe_workspace_bytes(h, n, 1, n)
                     if need in (0, robe.robe_workspace_bytes(h, n, 1, n, robe.options(backward_route=robe.ROUTE_COMBINE))):
                         continue
                     took += 1
-                    assert 2**19 - 2**14 < m <= 3600 * 2**14 and d >= 8 * Z and n >= 65_536 and n * d >= 2**23, (m, d, Z, n)
+                    assert 2**19 - 2**14 < m <= 3600 * 2**14 and n >= 65_536 and n * d >= 2**23, (m, d, Z, n)
+                    assert d >= 8 * Z or (d >= 4 * Z and m <= 2**25 and n * d <= 2**25), (m, d, Z, n)
     assert took > 20
 
 
