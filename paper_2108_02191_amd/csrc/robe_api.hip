@@ -543,14 +543,16 @@ bool direct_takes(int64_t n, uint64_t d) { return (uint64_t)n * d < (1ull << 25)
 // 98 / 111, d = 8, Z = 8, 3 M 300 / 389.  With bags it combines nothing and the copies of a frequent token meet
 // at the same addresses: d = 100, Z = 10, 39 K tokens 50 / 55, 66 K 81 / 58, 320 K 377 / 117; d = 64, Z = 16,
 // 66 K 43 / 50, 99 K 64 / 55; d = 16, Z = 4, 99 K 45 / 46, 150 K 66 / 50; d = 8, Z = 8, 220 K 47 / 48, 320 K 68 / 62.
+// Lane groups of four and less move few bytes a step: bags, d = 4, Z = 4, 350 K tokens 68 / 68, d = 3, Z = 3 199 / 317,
+// d = 6, Z = 2 109 / 118; single-hot d = 10, Z = 2, 350 K 84 / 111, d = 12, Z = 4, 700 K 129 / 152, d = 4, Z = 1, 1.5 M 282 / 285.
 // Ids without frequent tokens gain nothing: uniform ones lose the sort's cost, d = 128, Z = 32, 150 K lookups
 // 101 / 123; as many tokens in bags, d = 64, Z = 16, 71 / 92.
-bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags)
+bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags, uint32_t lanes)
 {
     if (!direct_takes(n, d)) return true;
     const uint64_t tokens = (uint64_t)n, requests = tokens * (d / Z) * (Z + 15) / 16;
-    if (bags && n >= 65536 && requests + tokens >= 650000u) return true;
-    return requests >= 1200000u + 1000u * (uint64_t)d && requests >= 1000000u + (d < 16 ? 2u * tokens : tokens + tokens / 4);
+    if (bags && lanes >= 4 && n >= 65536 && requests + tokens >= 650000u) return true;
+    return lanes >= 8 && requests >= 1200000u + 1000u * (uint64_t)d && requests >= 1000000u + (d < 16 ? 2u * tokens : tokens + tokens / 4);
 }
 
 // What a call falls back on that asks for no route and brings less workspace than its plan wants: the
@@ -602,7 +604,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     if (rows < 1 || n_indices < 1 || rows >= 0x7FFFFFFFll || n_indices >= 0x7FFFFFFFll) return pl;
     if (pick_layout(h, true, grad_out, opt, &pl.lay) != ROBE_OK) return pl;   // the launch reports the bad layout
     if (pl.lay.V == 0 || pl.lay.consec) return pl;   // shapes the sorted routes do not handle
-    if (!forced && !sorting_pays(n_indices, h->d, h->Z, bags)) return pl;
+    if (!forced && !sorting_pays(n_indices, h->d, h->Z, bags, pl.lay.G)) return pl;
     // Sorting on the top 24 key bits is one radix pass cheaper; tokens that share those bits merely
     // interleave and are merged less often, which stays rare while there are far fewer tokens than 2^24.
     // (up to 2^18 tokens 16 bits do: a key bucket then holds four tokens at most on average)
@@ -1332,7 +1334,9 @@ static int plan_mixed(const robe_hash_t *hash, const Opt &opt, const uint32_t *d
     const bool forced = regions || opt.bwd_route == ROBE_ROUTE_COMBINE;
     // the same size rule as robe_backward, on the average dimension
     const uint32_t davg = (uint32_t)(D / n_features) < hash->Z ? hash->Z : (uint32_t)(D / n_features);
-    if (!forced && !sorting_pays(n_indices, davg, hash->Z, bags)) return ROBE_OK;
+    Layout lay;
+    if (pick_layout(&mp->widest, true, grad_out, opt, &lay) != ROBE_OK) return ROBE_OK;      // the launch reports the bad layout
+    if (!forced && !sorting_pays(n_indices, davg, hash->Z, bags, lay.G)) return ROBE_OK;
     const int64_t rows = batch * (int64_t)n_features;
     Opt sorted = opt;
     sorted.bwd_route = regions ? ROBE_ROUTE_REGIONS : ROBE_ROUTE_COMBINE;
