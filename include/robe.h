@@ -317,7 +317,10 @@ int robe_sgd_update(const robe_hash_t *hash, float *array, float *grad_array, fl
  *   workspace      device buffer of at least robe_fused_workspace_bytes(...) bytes (same options),
  *                  256-byte aligned (it holds the sort buffers, the summed rows of repeated tokens and
  *                  the block records; for problems too small or shapes too odd for the sorted path it
- *                  holds a gradient array instead and the two steps run one after the other)
+ *                  holds a gradient array instead and the two steps run one after the other).  A call
+ *                  that asks for no route and brings less runs in two steps, scattering directly below
+ *                  2^25 gradient elements, if that fits and the array has fewer than 2^26 slots (or the
+ *                  two steps were its plan)
  * robe_fused_workspace_bytes is host arithmetic like robe_workspace_bytes and fails the same way.
  * Errors: ROBE_EINVAL (null pointers, eps <= 0, non-finite lr/eps, workspace too small), ROBE_EHIP.
  * Like robe_backward it records kernels only and may be captured into a HIP graph.
@@ -367,7 +370,9 @@ int robe_backward_sgd(const robe_hash_t *hash, const float *grad_out,
  * robe_backward_mixed with robe_adagrad_update / robe_sgd_update.
  *   workspace  device buffer of at least robe_mixed_workspace_bytes(...) bytes
  *              (robe_fused_mixed_workspace_bytes for the fused call; same dims and options),
- *              256-byte aligned; may be NULL when that size is 0
+ *              256-byte aligned; may be NULL when that size is 0.  Calls that ask for no route and
+ *              bring less scatter directly below 2^25 gradient elements (n_indices times the average
+ *              dimension), the fused call where two steps are its plan
  * Errors: ROBE_EINVAL (also: a dims entry that is zero or neither a multiple nor a divisor of Z;
  * workspace too small), ROBE_EHIP.
  */

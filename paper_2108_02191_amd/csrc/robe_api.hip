@@ -540,7 +540,8 @@ bool direct_takes(int64_t n, uint64_t d) { return (uint64_t)n * d < (1ull << 25)
 // us, direct / sorted, Zipf ids.  Single-hot, whose duplicates the direct scatter combines tile by tile:
 // d = 128, Z = 32, 66 K lookups 42 / 54, 99 K 59 / 59, 220 K 118 / 80; d = 16, Z = 4, 150 K 36 / 48, 320 K
 // 71 / 68, 500 K 110 / 84; d = 512, Z = 32, 39 K 84 / 80; but d = 16, Z = 16 (two requests a token), 800 K
-// 98 / 111, d = 8, Z = 8, 3 M 300 / 389.  With bags it combines nothing and the copies of a frequent token meet
+// 98 / 111, d = 8, Z = 8, 3 M 300 / 389; blocks of one or two floats leave the sorted route as many requests: d = 16,
+// Z = 1, 69 K 48 / 55, 119 K 75 / 70 (uniform ids 98 / 127), d = 32, Z = 2, 69 K 49 / 54, 119 K 79 / 69.  With bags it combines nothing and the copies of a frequent token meet
 // at the same addresses: d = 100, Z = 10, 39 K tokens 50 / 55, 66 K 81 / 58, 320 K 377 / 117; d = 64, Z = 16,
 // 66 K 43 / 50, 99 K 64 / 55; d = 16, Z = 4, 99 K 45 / 46, 150 K 66 / 50; d = 8, Z = 8, 220 K 47 / 48, 320 K 68 / 62.
 // Lane groups of four and less move few bytes a step: bags, d = 4, Z = 4, 350 K tokens 68 / 68, d = 3, Z = 3 199 / 317,
@@ -552,7 +553,8 @@ bool sorting_pays(int64_t n, uint32_t d, uint32_t Z, bool bags, uint32_t lanes)
     if (!direct_takes(n, d)) return true;
     const uint64_t tokens = (uint64_t)n, requests = tokens * (d / Z) * (Z + 15) / 16;
     if (bags && lanes >= 4 && n >= 65536 && requests + tokens >= 650000u) return true;
-    return lanes >= 8 && requests >= 1200000u + 1000u * (uint64_t)d && requests >= 1000000u + (d < 16 ? 2u * tokens : tokens + tokens / 4);
+    const uint64_t least = 1200000u + 1000u * (uint64_t)d + (Z <= 2 ? 300000u : 0u);
+    return lanes >= 8 && requests >= least && requests >= 1000000u + (d < 16 ? 2u * tokens : tokens + tokens / 4);
 }
 
 // What a call falls back on that asks for no route and brings less workspace than its plan wants: the

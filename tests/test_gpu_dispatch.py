@@ -17,7 +17,7 @@ DEV = "cuda:0"
 SIZES = [(16, 4, 65_535), (16, 4, 65_536), (16, 4, 113_043), (16, 4, 113_044), (128, 32, 113_020), (128, 32, 113_030), (32, 128, 60_000),
          (100, 10, 65_535), (100, 10, 83_199), (100, 10, 83_200), (16, 16, 900_000)]
 MORE_SIZES = [(16, 16, 2**21 - 1), (16, 16, 2**21), (8, 8, 2**22 - 1), (8, 8, 2**22),
-              (4, 1, 125_000), (4, 1, 135_000), (6, 2, 900_000), (12, 4, 140_000), (12, 4, 145_000), (3, 3, 2_000_000), (3, 3, 12_000_000)]        # around 2^25 gradient elements
+              (16, 1, 90_000), (16, 1, 95_000), (16, 1, 64_000), (4, 1, 125_000), (4, 1, 135_000), (6, 2, 900_000), (12, 4, 140_000), (12, 4, 145_000), (3, 3, 2_000_000), (3, 3, 12_000_000)]        # around 2^25 gradient elements
 
 
 def pays(d, Z, n, bags):
@@ -25,7 +25,7 @@ def pays(d, Z, n, bags):
     requests = n * (d // Z) * (Z + 15) // 16
     lanes = {3: 1, 4: 4, 6: 2, 8: 8, 12: 4}.get(d, 16)
     return (n * d >= 2**25 or (bags and lanes >= 4 and n >= 65_536 and requests + n >= 650_000) or
-            (lanes >= 8 and requests >= 1_200_000 + 1000 * d and requests >= 1_000_000 + (2 * n if d < 16 else n + n // 4)))
+            (lanes >= 8 and requests >= 1_200_000 + 1000 * d + (300_000 if Z <= 2 else 0) and requests >= 1_000_000 + (2 * n if d < 16 else n + n // 4)))
 
 
 @pytest.mark.parametrize("d,Z,n", SIZES + MORE_SIZES)
