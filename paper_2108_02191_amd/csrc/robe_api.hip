@@ -79,15 +79,22 @@ int check_hash(const robe_hash_t *h)
     return ROBE_OK;
 }
 
+// min(floor(2^32 / x), 2^32 - 1), x >= 1: see mod_m
+uint32_t reciprocal(uint32_t x)
+{
+    const uint64_t r = (1ull << 32) / x;
+    return r > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)r;
+}
+
 robe::Params to_params(const robe_hash_t *h)
 {
     robe::Params p;
     p.m = (uint32_t)h->m;
-    const uint64_t recip = (1ull << 32) / h->m;
-    p.m_recip = recip > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)recip;
+    p.m_recip = reciprocal(p.m);
     p.d = h->d;
     p.Z = h->Z;
     p.C = h->Z <= h->d ? h->d / h->Z : 1u;
+    p.z_recip = p.C == 1 || h->Z == 1 ? 0u : (uint32_t)(((1ull << 32) + h->Z - 1) / h->Z);
     p.r = h->Z <= h->d ? 0u : h->Z / h->d;
     p.Ah = h->Ah; p.Bh = h->Bh; p.Ch = h->Ch; p.Dh = h->Dh;
     p.Ag = h->Ag; p.Bg = h->Bg; p.Cg = h->Cg; p.Dg = h->Dg;
@@ -263,6 +270,10 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
     q.e0 = view ? view->e0 : 0u;
     q.row_floats = view ? view->row_floats : (int64_t)F * h->d;
     q.col0 = view ? view->col0 : 0;
+    q.F_recip = reciprocal(F);
+    q.narrow = rows < (1ll << 31) && q.row_floats <= (1ll << 23) && q.F_in <= (1u << 23) ? 1u : 0u;
+    q.batch_recip = q.narrow && q.batch > 0 ? reciprocal((uint32_t)q.batch) : 0u;
+    q.plain = q.F_in == F && q.e0 == 0 && q.col0 == 0 && q.row_floats == (int64_t)F * h->d ? 1u : 0u;
 
     if (lay.V == 0) {
         uint32_t rpb = robe::kBlock / h->d;
@@ -296,7 +307,7 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
                             rows >= (int64_t)(step * robe::kShortBags) * kShortBagWaves;
     const int64_t rows_per_wave = tile ? 64 : (short_bags ? (int64_t)(step * robe::kShortBags) : (bags ? (int64_t)step : (int64_t)q.TL));
     const int64_t waves = (rows + rows_per_wave - 1) / rows_per_wave;
-    int64_t blocks = (waves + robe::kWavesPerBlock - 1) / robe::kWavesPerBlock;
+    int64_t blocks = (waves + robe::kRowWaves - 1) / robe::kRowWaves;
     // Walk the rows table by table, one eighth of that order per XCD (see RowWalk), unless the launch
     // is too small to matter.  options->row_order overrides.
     q.bpx = 0;
@@ -309,16 +320,27 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
     // many copies of that table's frequent tokens.
     int order = opt.row_order;
     if (order == ROBE_ROWS_AUTO) order = ((!BWD && (bags || h->Z * 4 <= 64)) || tile) ? ROBE_ROWS_BY_TABLE : ROBE_ROWS_MEMORY;
-    if (F >= 2 && ((order == ROBE_ROWS_BY_TABLE && blocks >= 64) || order == ROBE_ROWS_BY_TABLE_ALWAYS)) {
+    if (F >= 2 && ((order == ROBE_ROWS_BY_TABLE && blocks * robe::kRowWaves >= 256) || order == ROBE_ROWS_BY_TABLE_ALWAYS)) {
         q.bpx = (uint32_t)((blocks + robe::kXcds - 1) / robe::kXcds);
         blocks = (int64_t)q.bpx * robe::kXcds;
     }
     if (blocks > 0x7FFFFFFFll) return fail(ROBE_EINVAL, "too many rows for one launch");
-    const dim3 grid((uint32_t)blocks), block(robe::kBlock);
+    const dim3 grid((uint32_t)blocks), block(robe::kRowBlock);
+
+    // blocks that several lanes read: one lane hashes their offset for all of them
+    const bool blocks_of_lanes = !BWD && !short_bags && lay.consec && h->Z >= (uint32_t)(robe::kUnroll * lay.V);
+    if (blocks_of_lanes) {
+        q.z_shift = h->Z <= h->d ? log2u(h->Z) : 0u;       // (Z > d: one chunk)
+        q.c_shift = log2u(p.C);
+    }
 
 #define ROBE_LAUNCH(V_, C_, S_)                                                                                       \
     do {                                                                                                              \
-        if (short_bags) {                                                                                             \
+        if (blocks_of_lanes && bags) {                                                                                \
+            if constexpr (!BWD && C_) robe::bag_block_kernel<V_, S_, AT><<<grid, block, 0, stream>>>(p, q, src, indices, offsets, rows, n_indices, dst); \
+        } else if (blocks_of_lanes) {                                                                                 \
+            if constexpr (!BWD && C_) robe::single_hot_block_kernel<V_, S_, AT><<<grid, block, 0, stream>>>(p, q, src, indices, rows, dst); \
+        } else if (short_bags) {                                                                                             \
             if constexpr (!BWD) robe::short_bag_kernel<V_, C_, S_, AT><<<grid, block, 0, stream>>>(p, q, src, indices, offsets, rows, n_indices, dst); \
         } else if (bags)                                                                                                     \
             robe::bag_kernel<V_, C_, S_, BWD, AT><<<grid, block, 0, stream>>>(p, q, src, indices, offsets, rows, n_indices, dst); \

@@ -6,6 +6,9 @@
 //   * a sum of residues is reduced again before it can reach 2^64.
 //   * r mod m for r < 2^31 uses a 32-bit reciprocal estimate that is low by at
 //     most one, corrected by a single conditional subtraction.
+//   * s in [0, 2P) is reduced by min(s, s - P): below P the subtraction wraps to more than s.
+// The kernels that gather are bound by instruction issue as much as by memory (quarter-rate integer
+// multiplies above all), so these are written for the fewest instructions.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -19,6 +22,7 @@ struct Params {
     uint32_t m;        // array length, 1 <= m <= 2^31 - 1
     uint32_t m_recip;  // min(floor(2^32 / m), 2^32 - 1)
     uint32_t d, Z, C;  // C = d / Z chunks per embedding (1 when Z > d)
+    uint32_t z_recip;  // ceil(2^32 / Z): floor(i / Z) = mulhi(i, z_recip) for i < 2^16; 0 where C = 1; Z = 1: see chunk_of
     uint32_t r;        // Z / d embeddings per chunk when Z > d, else 0
     uint32_t Ah, Bh, Ch, Dh;
     uint32_t Ag, Bg, Cg, Dg;
@@ -35,36 +39,55 @@ __device__ __forceinline__ uint32_t mod_p(uint64_t t)
 // (a + b) mod P for a, b in [0, P).
 __device__ __forceinline__ uint32_t add_p(uint32_t a, uint32_t b)
 {
-    uint32_t s = a + b;                              // < 2^32 - 2
-    return s >= kP ? s - kP : s;
+    const uint32_t s = a + b;                        // < 2^32 - 2
+    return min(s, s - kP);
 }
 
-// (a * b) mod P for a, b < 2^31 (product < 2^62).
-__device__ __forceinline__ uint32_t mul_p(uint32_t a, uint32_t b)
+// (a * b + c) mod P for a, c < P and b <= P: the sum is at most P^2 - 1 < 2^62, so its upper part is
+// at most P - 1 and the two parts add up to less than 2P.
+__device__ __forceinline__ uint32_t mul_add_p(uint32_t a, uint32_t b, uint32_t c)
 {
-    return mod_p((uint64_t)a * (uint64_t)b);
+    const uint64_t t = (uint64_t)a * b + c;
+    const uint32_t s = ((uint32_t)t & kP) + (uint32_t)(t >> 31);
+    return min(s, s - kP);
+}
+
+// (a * b) mod P for a < P, b <= P.
+__device__ __forceinline__ uint32_t mul_p(uint32_t a, uint32_t b) { return mul_add_p(a, b, 0u); }
+
+// x mod P, possibly P itself for 0 (a factor of mul_p), for any 64-bit x: its three parts of 31, 31 and
+// 2 bits added up.
+__device__ __forceinline__ uint32_t fold_p(uint64_t x)
+{
+    uint32_t s = ((uint32_t)x & kP) + ((uint32_t)(x >> 31) & kP);     // <= 2P
+    s = min(s, s - kP) + (uint32_t)(x >> 62);                         // <= P + 3
+    return min(s, s - kP);
 }
 
 // r mod m for r < 2^31.  q = floor(r * recip / 2^32) is floor(r/m) or one less.
 __device__ __forceinline__ uint32_t mod_m(uint32_t r, uint32_t m, uint32_t recip)
 {
-    uint32_t q = __umulhi(r, recip);
-    uint32_t rem = r - q * m;                        // in [0, 2m), fits since m < 2^31
-    return rem >= m ? rem - m : rem;
+    const uint32_t rem = r - __umulhi(r, recip) * m; // in [0, 2m), fits since m < 2^31
+    return min(rem, rem - m);
+}
+
+// floor(r / m) by the same reciprocal, for r < 2^31.
+__device__ __forceinline__ uint32_t div_m(uint32_t r, uint32_t m, uint32_t recip)
+{
+    const uint32_t q = __umulhi(r, recip);
+    return q + (r - q * m >= m ? 1u : 0u);
+}
+
+// The chunk of element i < d <= 2^16 of an embedding.
+__device__ __forceinline__ uint32_t chunk_of(const Params &p, uint32_t i)
+{
+    return p.Z == 1u ? i : __umulhi(i, p.z_recip);
 }
 
 // Token part of a hash: (B * x) mod P with x read as an unsigned 64-bit integer.
 __device__ __forceinline__ uint32_t token_term(uint32_t B, int64_t x)
 {
-    return mul_p(B, mod_p((uint64_t)x));
-}
-
-// Table-and-position part: (A*e + C*k + D) mod P for e < 2^31, k < 2^32.
-__device__ __forceinline__ uint32_t static_term(uint32_t A, uint32_t C, uint32_t D, uint32_t e, uint32_t k)
-{
-    uint32_t te = mod_p((uint64_t)A * e + D);        // < 2^62 + 2^31
-    uint32_t tk = mod_p((uint64_t)C * k);            // < 2^63
-    return add_p(te, tk);
+    return mul_p(B, fold_p((uint64_t)x));
 }
 
 // h(e,x,c) from the two parts.
@@ -76,13 +99,22 @@ __device__ __forceinline__ uint32_t offset_of(const Params &p, uint32_t tok_h, u
 // (o + j) mod m for o < m, j < Z <= m.
 __device__ __forceinline__ uint32_t wrap(uint32_t pos, uint32_t m)
 {
-    return pos >= m ? pos - m : pos;
+    return min(pos, pos - m);                        // (pos < 2m < 2^32; below m the subtraction wraps past pos)
 }
 
 // Sign bit mask of g: 0x80000000 when g == -1 (hash residue even), else 0.
 __device__ __forceinline__ uint32_t sign_mask(uint32_t residue)
 {
     return ((residue & 1u) ^ 1u) << 31;
+}
+
+// The same for the residue (a + b) mod P, given a and b + 1 (a, b < P).  With s = a + b + 1 < 2^32: a + b reaches P
+// exactly where s has bit 31, and taking the odd P off changes the parity, so the residue is even
+// where bit 0 and bit 31 of s differ.
+__device__ __forceinline__ uint32_t sign_mask_of_sum(uint32_t a, uint32_t b_plus_1)
+{
+    const uint32_t s = a + b_plus_1;
+    return ((s << 31) ^ s) & 0x80000000u;
 }
 
 __device__ __forceinline__ float apply_sign(float v, uint32_t mask)
