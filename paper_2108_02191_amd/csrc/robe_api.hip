@@ -439,13 +439,67 @@ int launch_radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint
             robe::sort_offsets_kernel<<<dim3(robe::kDigits), dim3(robe::kSortBlock), 0, stream>>>(sp);
             if (int rc = check_launch("sort (offsets)")) return rc;
         }
-        robe::sort_scatter_kernel<robe::kScatterBlock><<<dim3(sp.tiles), dim3(robe::kScatterBlock), 0, stream>>>(sp, ks, vs, kd, vd);
+        robe::sort_scatter_kernel<robe::kScatterBlock><<<dim3(robe::tile_blocks(sp.tiles)), dim3(robe::kScatterBlock), 0, stream>>>(sp, ks, vs, kd, vd);
         if (int rc = check_launch("sort (scatter)")) return rc;
         uint32_t *t = ks; ks = kd; kd = t;
         t = vs; vs = vd; vd = t;
     }
     *in_b = (passes & 1u) != 0;
     return ROBE_OK;
+}
+
+// Up to this many tokens the grouping sort places by 8 bits (a few hundred tokens a bucket), above by 10.
+const uint64_t kGroupSmall = 1u << 18, kGroupMost = (uint64_t)robe::kGroupMostTiles * robe::kSortTile;
+
+size_t group_sort_temp_bytes(uint64_t n)
+{
+    const uint64_t tiles = (n + robe::kSortTile - 1) / robe::kSortTile, digits = n <= kGroupSmall ? 256 : 1024;
+    return (size_t)((tiles + 1) * digits * 4);
+}
+
+// The grouping sort of robe_radix_sort.h: n <= 2^21 pairs by the `bits` key bits [lo, lo + bits), nearly.  Keys
+// from the ids (single-hot: indices != NULL, the values are the positions), or from (keys_a, vals_a).  `words`: n
+// eight-byte words of scratch; the result is in (keys_a, vals_a).
+int launch_group_sort(const robe::Params &p, const int64_t *indices, uint32_t F, uint32_t *keys_a, uint32_t *vals_a, uint2 *words,
+                      uint32_t n, uint32_t lo, uint32_t bits, void *temp, hipStream_t stream,
+                      const robe::TableArgs &tab, uint32_t n_tab, uint2 *tables)
+{
+    robe::GroupPlan g;
+    g.n = n;
+    g.tiles = (uint32_t)(((uint64_t)n + robe::kSortTile - 1) / robe::kSortTile);
+    const bool wide = n > kGroupSmall;
+    const uint32_t digit_bits = wide ? 10u : 8u, digits = 1u << digit_bits;
+    if (g.tiles > robe::kGroupMostTiles || bits <= digit_bits) return fail(ROBE_EINVAL, "internal: grouping sort");
+    g.few = !wide && g.tiles <= robe::kFewTiles ? 1u : 0u;
+    g.shift = lo + bits - digit_bits;
+    g.local_shift = g.shift > 8 ? g.shift - 8 : 0u;
+    g.local_mask = (1u << (g.shift - g.local_shift)) - 1u;
+    g.tile_count = static_cast<uint32_t *>(temp);
+    g.totals = g.tile_count + (size_t)g.tiles * digits;
+    g.F = F;
+    g.F_recip = reciprocal(F);
+    const dim3 block(robe::kGroupBlock), tiles(g.tiles), spread(robe::tile_blocks(g.tiles));
+#define ROBE_GROUP(D_, I_)                                                                                            \
+    do {                                                                                                              \
+        robe::group_count_kernel<D_, I_><<<tiles, block, 0, stream>>>(g, p, indices, keys_a, tab, n_tab, tables);     \
+        if (int rc = check_launch("sort (count)")) return rc;                                                         \
+        if (!g.few) {                                                                                                 \
+            robe::group_offsets_kernel<D_><<<dim3(D_ / 64), dim3(robe::kGroupOffsetsBlock), 0, stream>>>(g);          \
+            if (int rc = check_launch("sort (offsets)")) return rc;                                                   \
+        }                                                                                                             \
+        robe::group_scatter_kernel<D_, I_, false><<<spread, block, 0, stream>>>(g, p, indices, keys_a, vals_a, words, nullptr, nullptr); \
+        if (int rc = check_launch("sort (scatter)")) return rc;                                                       \
+    } while (0)
+    if (indices != nullptr) {
+        if (wide) ROBE_GROUP(1024, true);
+        else ROBE_GROUP(256, true);
+    } else {
+        if (wide) ROBE_GROUP(1024, false);
+        else ROBE_GROUP(256, false);
+    }
+#undef ROBE_GROUP
+    robe::group_scatter_kernel<256, false, true><<<tiles, block, 0, stream>>>(g, p, nullptr, nullptr, nullptr, words, keys_a, vals_a);
+    return check_launch("sort (local)");
 }
 
 // An array of up to 128 MiB written with the default cache policy is still in the 256 MB last-level
@@ -636,12 +690,13 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     if (pl.key_bits > pl.key_top) pl.key_bits = pl.key_top;
 
     const size_t n = (size_t)n_indices;
-    const size_t temp = radix_sort_temp_bytes(n);
+    const size_t grouping = n <= kGroupMost && !opt.key_bits ? group_sort_temp_bytes(n) : 0;      // (where the plan says window_sort below)
+    const size_t temp = grouping > radix_sort_temp_bytes(n) ? grouping : radix_sort_temp_bytes(n);
     pl.dedup = true;
     size_t off = 0;
     pl.off_keys_in = off;  off = align_up(off + (n + 8) * 4, 256);
-    pl.off_keys_out = off; off = align_up(off + (n + 8) * 4, 256);
     pl.off_vals_in = off;  off = align_up(off + n * 4, 256);
+    pl.off_keys_out = off; off = align_up(off + (n + 8) * 4, 256);     // keys_out and vals_out together: the words of the grouping sort
     pl.off_vals_out = off; off = align_up(off + n * 4, 256);
     pl.off_tok_bag = off;  if (bags && h->use_sign) off = align_up(off + n * 4, 256);   // sign off: the sorted value is the row
     pl.off_temp = off;     off = align_up(off + temp, 256);
@@ -658,10 +713,10 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
                           n >= kElemLeastTokens && elems >= kElemLeast && elems <= elem_most(h->m, h->d, h->Z);
     const bool want_regions = elements || need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
     if (!want_regions) {
-        // Atomics after the sort: up to 2^21 tokens, 16 key bits - two radix passes instead of three,
-        // each three launches of 5 to 10 us.  The tokens of a key bucket (2^-16 of them) then sit
+        // Atomics after the sort: up to 2^21 tokens the grouping sort (on the top 18 or 16 key bits, or the 16
+        // that the caller's choice of bits below leaves).  Tokens that share those bits then sit
         // interleaved, and the combine kernel sorts every wavefront's 64 positions by the whole key.
-        if (!opt.key_bits && pl.key_bits >= 16 && n_indices <= (1ll << 21)) {
+        if (!opt.key_bits && pl.key_bits >= 16 && n <= kGroupMost) {
             pl.key_bits = 16;
             pl.window_sort = true;
         }
@@ -719,13 +774,12 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     const uint64_t last_len = h->m - ((NR - 1) << shift);
     const uint64_t rec_per_block = (NR > 1 && last_len < h->Z) ? 3 : 2;
     if (!pl.gather && rec_per_block * n * C >= 0xFFFFFFFFull) return pl;
-    // Record kernels, up to 2^21 tokens: two radix passes (16 key bits) instead of three, as on the atomics
-    // route above, and the combine kernel orders the G positions that a lane group looks at by the whole
-    // key.  A frequent token's run is then also cut where other tokens of its key bucket (2^-16 of all
-    // tokens, eight times that for the bound) sit among its copies.
-    // Reproducible step on the 100 MB array, Z = 8: 614 -> 602 us (852 K tokens), Z = 32: 435 -> 421.
+    // Record kernels, up to 2^21 tokens: the grouping sort, as on the atomics route above, and the combine
+    // kernel orders the G positions that a lane group looks at by the whole key.  A frequent token's run is
+    // then also cut where others of its group sit among its copies: 2^-16 of all tokens, and at the two ends of
+    // its bucket those of a tile that share the lower digit, sixteen; eight times that for the bound.
     const uint32_t full_key_bits = pl.key_bits;
-    if (tuned && !pl.gather && !opt.key_bits && pl.key_top >= 16 && pl.lay.G >= 16 && n <= (1u << 21)) {
+    if (tuned && !pl.gather && !opt.key_bits && pl.key_top >= 16 && pl.lay.G >= 16 && n <= kGroupMost) {
         pl.key_bits = 16;
         pl.window_sort = true;
     }
@@ -741,7 +795,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
         const uint64_t room = ((batch << robe::kMaxClassShift) * 6) / 10;
         const uint64_t R = 1ull << shift, span = R < h->m ? R : h->m;
         const uint64_t avg = (n * C * (span + h->Z) / span + NR - 1) / NR;
-        const uint64_t worst = avg + avg / 2 + 2ull * C * (n / walk_positions + 1) + (pl.window_sort ? 16ull * C * ((n >> 16) + 1) : 0u);
+        const uint64_t worst = avg + avg / 2 + 2ull * C * (n / walk_positions + 1) + (pl.window_sort ? 16ull * C * ((n >> 16) + 32) : 0u);
         return worst <= room;
     };
     // rows of P: an eighth of the positions a lane group of the combine kernel walks, for every group
@@ -899,7 +953,10 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         }
     }
     // sign off: the sorted value is the token's row of grad_out and positions are never needed again
-    if (bags && sign) robe::token_keys_kernel<true, false><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
+    // (single-hot: row and position are the same, and the grouping sort hashes the ids itself)
+    const bool keys_from_ids = pl.window_sort && !bags;
+    if (keys_from_ids) {
+    } else if (bags && sign) robe::token_keys_kernel<true, false><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
     else if (bags) robe::token_keys_kernel<true, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
     else robe::token_keys_kernel<false, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
     if (int rc = check_launch("backward (keys)")) return rc;
@@ -914,9 +971,14 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         // significant bits, which put far-apart pieces next to each other.  (The region route needs
         // the order of the whole key for its directory.)
         const uint32_t lo = (!pl.regions && pl.key_top < 31) ? 0u : pl.key_top - pl.key_bits;
-        if (int rc = launch_radix_sort(keys_in, vals_in, keys_out, vals_out, n, lo, lo + pl.key_bits, ws + pl.off_temp,
-                                       stream, &in_b))
+        if (pl.window_sort) {
+            if (int rc = launch_group_sort(p_keys, keys_from_ids ? indices : nullptr, F, keys_in, vals_in, reinterpret_cast<uint2 *>(keys_out),
+                                           n, lo, pl.key_bits, ws + pl.off_temp, stream, tab, n_tab, tables))
+                return rc;
+        } else if (int rc = launch_radix_sort(keys_in, vals_in, keys_out, vals_out, n, lo, lo + pl.key_bits, ws + pl.off_temp,
+                                              stream, &in_b)) {
             return rc;
+        }
         if (int rc = probe(opt, ROBE_PROBE_SORT, true, stream)) return rc;
         if (!in_b) {        // an even number of passes leaves the result in the first pair of buffers
             keys_out = keys_in;
@@ -1484,6 +1546,14 @@ int robe_backward_noalloc(const robe_hash_t *hash, const float *grad_out, const 
         if (options != nullptr) routed = *options;
         else memset(&routed, 0, sizeof(routed));
         routed.backward_route = direct_takes(n_indices, hash->d) ? ROBE_ROUTE_DIRECT : ROBE_ROUTE_COMBINE;
+        if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &routed, &need)) return rc;
+        options = &routed;
+    }
+    if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES && (options == nullptr || options->key_bits == 0)) {
+        // (the plain sort's counts take three quarters of a byte less per token than the grouping sort's)
+        if (options != nullptr) routed = *options;
+        else memset(&routed, 0, sizeof(routed));
+        routed.key_bits = 24;
         if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &routed, &need)) return rc;
         options = &routed;
     }

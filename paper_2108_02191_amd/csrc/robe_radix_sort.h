@@ -21,10 +21,10 @@
 // ballot per digit bit), plus what the wavefronts before it hold.
 //
 // It records nothing but kernels on the stream (no fill operations), and for the sizes met here
-// (10^5 .. 10^7 pairs) it is shorter on launches than the device library's sort.
+// (10^5 .. 10^7 pairs) it is shorter on launches than the device library's sort.  Up to 2^21 pairs the backward
+// mostly needs less than a sort: see the grouping at the end of this file.
 #pragma once
-#include <hip/hip_runtime.h>
-#include <stdint.h>
+#include "robe_backward_dedup.h"
 
 namespace robe {
 
@@ -143,6 +143,41 @@ __global__ __launch_bounds__(kSortBlock) void sort_offsets_kernel(SortPass s)
     if (t == 0) s.totals[digit] = carry;
 }
 
+// Rank of this lane's digit (below 2^BITS) among those that the wavefront has met so far, in order of rounds
+// and lanes; count: the wavefront's counters in LDS, which the call moves on.  Lanes that hold nothing
+// (`have` false) are not counted.  The lanes of equal digit are found with one ballot per bit: lane masks as
+// two words that lose, bit by bit, the lanes that differ (one three-operand instruction per word; written with
+// 64-bit selects and populations under a mask a tile of 1.7 M pairs took 15.4 us a pass, now 14.2).
+template <int BITS>
+__device__ __forceinline__ uint32_t rank_in_tile(uint32_t digit, bool have, uint32_t *count)
+{
+    const uint64_t live = __ballot(have);
+    uint32_t lo = (uint32_t)live, hi = (uint32_t)(live >> 32);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const uint32_t mine = 0u - ((digit >> b) & 1u);
+        const uint64_t bit = __ballot(mine != 0u);
+        lo &= ~((uint32_t)bit ^ mine);
+        hi &= ~((uint32_t)(bit >> 32) ^ mine);
+    }
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    const uint32_t so_far = count[digit];                   // every lane reads before the first lane of a set adds
+    __builtin_amdgcn_wave_barrier();
+    if (have && below == 0) count[digit] = so_far + (uint32_t)(__popc(lo) + __popc(hi));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return so_far + below;
+}
+
+// Which tile a scattering workgroup takes: every XCD an eighth of the tiles, in order, so that what neighbouring
+// tiles write of a digit meets in one L2 instead of leaving eight of them in halves of a line.  8.5 M pairs:
+// 44 us a pass -> 35.  Launched with tile_blocks() workgroups; those past the last tile end at once.
+__host__ __device__ inline uint32_t tile_blocks(uint32_t tiles) { return (tiles + 7u) / 8u * 8u; }
+__device__ __forceinline__ uint32_t tile_of_block(uint32_t tiles)
+{
+    return (blockIdx.x & 7u) * ((tiles + 7u) / 8u) + (blockIdx.x >> 3);
+}
+
 // BLOCK threads take a tile of kSortTile pairs, kSortTile / BLOCK rounds of 64 per wavefront.
 // Measured on 8.5 M pairs: 512 threads (74 registers, six wavefronts per SIMD) 2 us per pass faster
 // than 256 (128 registers, four per SIMD); 1024 slower again.
@@ -161,7 +196,8 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
     __shared__ uint2 staged[kSortTile];               // the tile in digit order
     __shared__ uint32_t wave_total[WAVES];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    const uint32_t tile = blockIdx.x;
+    const uint32_t tile = tile_of_block(s.tiles);
+    if (tile >= s.tiles) return;
     const uint64_t base = (uint64_t)tile * kSortTile + (uint64_t)wave * (ROUNDS * 64u);
     for (uint32_t d = t; d < (uint32_t)WAVES * kDigits; d += BLOCK) (&wave_count[0][0])[d] = 0;
     {   // a digit's pairs start after all pairs of the smaller digits, then after the digit's pairs in the tiles before
@@ -202,26 +238,9 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
         key[i] = at < s.n ? keys_in[at] : 0xFFFFFFFFu;
         val[i] = at < s.n ? vals_in[at] : 0u;
     }
-    const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
-    for (int i = 0; i < ROUNDS; ++i) {
-        const uint64_t at = base + (uint32_t)i * 64u + lane;
-        const bool have = at < s.n;
-        const uint32_t digit = (key[i] >> s.shift) & s.mask;
-        // the lanes of this round that hold the same digit
-        uint64_t same = __ballot(have);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t bit = __ballot((digit >> b) & 1u);
-            same &= ((digit >> b) & 1u) ? bit : ~bit;
-        }
-        const uint32_t so_far = wave_count[wave][digit];        // every lane reads before the first lane of a set adds
-        rank[i] = so_far + (uint32_t)__popcll(same & below);
-        __builtin_amdgcn_wave_barrier();
-        if (have && (same & below) == 0) wave_count[wave][digit] = so_far + (uint32_t)__popcll(same);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
+    for (int i = 0; i < ROUNDS; ++i)
+        rank[i] = rank_in_tile<8>((key[i] >> s.shift) & s.mask, base + (uint32_t)i * 64u + lane < s.n, wave_count[wave]);
     __syncthreads();
     // per digit: the tile's count, every wavefront's base inside the digit, the digit's first slot
     uint32_t in_digit = 0;
@@ -265,6 +284,255 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
             const uint32_t slot = digit_slot[digit] + j;      // wraps like the subtraction above: the sum is the slot
             keys_out[slot] = kv.x;
             vals_out[slot] = kv.y;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Grouping: equal keys side by side, or nearly so, for up to 2^21 pairs.
+//
+// The kernels that sum runs of equal keys put the positions they look at in order of the whole key
+// themselves (Geom::window_sort), so that all they need is that the copies of a key are close together.  Two
+// radix passes of 8 bits gave them that, six kernels of 5 to 10 us that a small input cannot fill.
+// Here one pass places the pairs by their top GroupPlan::bits key bits, and then every tile of kSortTile
+// places, which holds a bucket or a few, is ordered by the next eight bits inside LDS, with no counts of other tiles:
+// a key's copies are split where a tile ends.  Runs, of 1704 K Zipf tokens (294 K distinct): 322 K after 16
+// sorted bits, 333 K here with 10 bits (375 K with 8); of 118 K tokens (23.0 K) 24.5 K, and 24.9 K with 8 bits.
+// The keys of single-hot lookups are hashed where they are needed: no kernel writes them first.
+//   count    as above, the counts tile by tile; IDS: keys from the ids
+//   offsets  one wavefront per 64 digits and sixteenth of the tiles (left out up to kFewTiles tiles)
+//   scatter  as above, writing (key, value) words
+//   local    a tile by the next bits
+// Keys and sort, us: 1704 K lookups 61 -> 41, 852 K 46 -> 29; bags, 118 K tokens 33 -> 24.  Tiles of 8192: 1 to
+// 3 us longer for as many runs less.  Ordered by the whole span of their keys instead of the bits below the
+// bucket's: the same for the atomics, and the regions' kernel 10 us longer (neighbours then write the same
+// regions at a time).  Every step is stable.
+// ---------------------------------------------------------------------------------------------
+struct GroupPlan {
+    uint32_t n, tiles, few;      // as in SortPass
+    uint32_t shift;              // first key bit of the digit; it has log2(DIG) bits, the topmost that matter
+    uint32_t local_shift, local_mask;
+    uint32_t *tile_count;        // [tiles][DIG]
+    uint32_t *totals;            // [DIG]
+    uint32_t F, F_recip;         // IDS: tables
+};
+
+constexpr int kGroupBlock = 512;
+constexpr uint32_t kGroupMostTiles = 512;     // 2^21 pairs
+constexpr int kGroupOffsetsBlock = 1024;
+constexpr int kGroupOffsetsRows = (int)kGroupMostTiles / (kGroupOffsetsBlock / 64);
+
+template <int DIG, bool IDS>
+__global__ __launch_bounds__(kGroupBlock) void group_count_kernel(GroupPlan s, Params p, const int64_t *__restrict__ indices,
+                                                                  const uint32_t *__restrict__ keys,
+                                                                  TableArgs tab, uint32_t n_tab, uint2 *__restrict__ tables)
+{
+    constexpr int ROUNDS = (int)kSortTile / kGroupBlock;
+    __shared__ uint32_t h[DIG];
+    if (IDS && blockIdx.x == 0 && threadIdx.x < n_tab) tables[threadIdx.x] = make_uint2(tab.col[threadIdx.x], tab.dim[threadIdx.x]);
+    for (uint32_t d = threadIdx.x; d < (uint32_t)DIG; d += kGroupBlock) h[d] = 0;
+    __syncthreads();
+    const uint32_t base = blockIdx.x * kSortTile;              // (at most 2^21)
+    uint32_t k[ROUNDS];
+    if constexpr (IDS) {
+        int64_t x[ROUNDS];
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const uint32_t at = base + (uint32_t)i * kGroupBlock + threadIdx.x;
+            x[i] = at < s.n ? indices[at] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i)
+            k[i] = sort_key(p, x[i], mod_m(base + (uint32_t)i * kGroupBlock + threadIdx.x, s.F, s.F_recip));
+    } else {
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const uint32_t at = base + (uint32_t)i * kGroupBlock + threadIdx.x;
+            k[i] = at < s.n ? keys[at] : 0u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i)
+        if (base + (uint32_t)i * kGroupBlock + threadIdx.x < s.n) atomicAdd(&h[(k[i] >> s.shift) & (DIG - 1u)], 1u);
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < (uint32_t)DIG; d += kGroupBlock) s.tile_count[(uint64_t)blockIdx.x * DIG + d] = h[d];
+}
+
+// counts -> the digit's pairs in the tiles before; the digit's total.  Launched with DIG / 64 workgroups.
+template <int DIG>
+__global__ __launch_bounds__(kGroupOffsetsBlock) void group_offsets_kernel(GroupPlan s)
+{
+    constexpr uint32_t WAVES = kGroupOffsetsBlock / 64;
+    __shared__ uint32_t part[WAVES][64];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, digit = blockIdx.x * 64u + lane;
+    const uint32_t rows = (s.tiles + WAVES - 1u) / WAVES, first = wave * rows;        // rows <= kGroupOffsetsRows
+    uint32_t c[kGroupOffsetsRows], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kGroupOffsetsRows; ++k) {
+        c[k] = k < rows && first + k < s.tiles ? s.tile_count[(uint64_t)(first + k) * DIG + digit] : 0u;
+        sum += c[k];
+    }
+    part[wave][lane] = sum;
+    __syncthreads();
+    uint32_t at = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < WAVES; ++w) at += w < wave ? part[w][lane] : 0u;
+    if (wave == WAVES - 1u) s.totals[digit] = at + sum;
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kGroupOffsetsRows; ++k) {
+        if (k < rows && first + k < s.tiles) s.tile_count[(uint64_t)(first + k) * DIG + digit] = at;
+        at += c[k];
+    }
+}
+
+// LOCAL: the tile stays where it is, by the bits below; pairs come as words and leave in two arrays.
+// Otherwise pairs come from two arrays, or (IDS) the key is hashed and the value is the position, and leave
+// as words.
+template <int DIG, bool IDS, bool LOCAL>
+__global__ __launch_bounds__(kGroupBlock) void group_scatter_kernel(GroupPlan s, Params p, const int64_t *__restrict__ indices,
+                                                                    const uint32_t *__restrict__ keys_in,
+                                                                    const uint32_t *__restrict__ vals_in,
+                                                                    uint2 *__restrict__ words,
+                                                                    uint32_t *__restrict__ keys_out,
+                                                                    uint32_t *__restrict__ vals_out)
+{
+    constexpr int BLOCK = kGroupBlock, ROUNDS = (int)kSortTile / BLOCK, WAVES = BLOCK / 64;
+    constexpr int BITS = DIG == 256 ? 8 : 10;
+    static_assert(DIG == 256 || DIG == 1024, "digits of 8 or 10 bits");
+    static_assert(!(LOCAL && (IDS || DIG != 256)), "the local step has one form");
+    constexpr uint32_t PER = (DIG + BLOCK - 1) / BLOCK;         // digits per thread (threads past DIG have none)
+    __shared__ uint32_t wave_count[WAVES][DIG];
+    __shared__ uint32_t digit_slot[LOCAL ? 1 : DIG];
+    __shared__ uint2 staged[kSortTile];
+    __shared__ uint32_t wave_total[WAVES];
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    const uint32_t tile = LOCAL ? blockIdx.x : tile_of_block(s.tiles);
+    if (tile >= s.tiles) return;
+    const uint32_t base = tile * kSortTile + wave * (ROUNDS * 64u);
+    const uint32_t shift = LOCAL ? s.local_shift : s.shift, mask = LOCAL ? s.local_mask : DIG - 1u;
+
+    uint32_t key[ROUNDS], val[ROUNDS], rank[ROUNDS];
+    if constexpr (IDS) {
+        int64_t x[ROUNDS];
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const uint32_t at = base + (uint32_t)i * 64u + lane;
+            x[i] = at < s.n ? indices[at] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            val[i] = base + (uint32_t)i * 64u + lane;
+            key[i] = sort_key(p, x[i], mod_m(val[i], s.F, s.F_recip));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const uint32_t at = base + (uint32_t)i * 64u + lane;
+            uint2 w = make_uint2(0u, 0u);
+            if (at < s.n) {
+                if constexpr (LOCAL) w = words[at];
+                else w = make_uint2(keys_in[at], vals_in[at]);
+            }
+            key[i] = w.x;
+            val[i] = w.y;
+        }
+    }
+    for (uint32_t d = t; d < (uint32_t)(WAVES * DIG); d += BLOCK) (&wave_count[0][0])[d] = 0;
+    if constexpr (!LOCAL) {   // a digit's pairs start after all pairs of the smaller digits, then after the digit's pairs in the tiles before
+        uint32_t before_tiles[PER], digit_total[PER], all, sum = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) before_tiles[q] = digit_total[q] = 0;
+        if (s.few) {
+            static_assert(BLOCK % 256 == 0, "two threads per digit of eight bits");
+            if constexpr (DIG == 256) {
+                uint32_t *half = reinterpret_cast<uint32_t *>(staged);         // (free until the tile is put in order)
+                const uint32_t digit = t & 255u;
+#pragma unroll 8
+                for (uint32_t k = t >> 8; k < s.tiles; k += 2u) {
+                    const uint32_t c = s.tile_count[(uint64_t)k * DIG + digit];
+                    before_tiles[0] += k < tile ? c : 0u;
+                    digit_total[0] += c;
+                }
+                if (t >= 256u) {
+                    half[digit] = before_tiles[0];
+                    half[256u + digit] = digit_total[0];
+                }
+                __syncthreads();
+                if (t < 256u) {
+                    before_tiles[0] += half[t];
+                    digit_total[0] += half[256u + t];
+                }
+            }
+        } else if (t * PER < (uint32_t)DIG) {
+#pragma unroll
+            for (uint32_t q = 0; q < PER; ++q) {
+                before_tiles[q] = s.tile_count[(uint64_t)tile * DIG + t * PER + q];
+                digit_total[q] = s.totals[t * PER + q];
+            }
+        }
+        if (t * PER < (uint32_t)DIG) {
+#pragma unroll
+            for (uint32_t q = 0; q < PER; ++q) sum += digit_total[q];
+        }
+        uint32_t at = exclusive_scan_block<BLOCK>(sum, wave_total, all);
+        if (t * PER < (uint32_t)DIG) {
+#pragma unroll
+            for (uint32_t q = 0; q < PER; ++q) {
+                digit_slot[t * PER + q] = at + before_tiles[q];
+                at += digit_total[q];
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i)
+        rank[i] = rank_in_tile<BITS>((key[i] >> shift) & mask, base + (uint32_t)i * 64u + lane < s.n, wave_count[wave]);
+    __syncthreads();
+    // as in sort_scatter_kernel: every wavefront's first tile-local slot of a digit, and the distance from a
+    // digit's tile-local slots to its output slots
+    uint32_t in_digit[PER], sum = 0, all;
+    if (t * PER < (uint32_t)DIG) {
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            in_digit[q] = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const uint32_t c = wave_count[w][t * PER + q];
+                wave_count[w][t * PER + q] = in_digit[q];
+                in_digit[q] += c;
+            }
+            sum += in_digit[q];
+        }
+    }
+    uint32_t start = exclusive_scan_block<BLOCK>(sum, wave_total, all);
+    if (t * PER < (uint32_t)DIG) {
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) wave_count[w][t * PER + q] += start;
+            if constexpr (!LOCAL) digit_slot[t * PER + q] -= start;
+            start += in_digit[q];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i)
+        if (base + (uint32_t)i * 64u + lane < s.n)
+            staged[wave_count[wave][(key[i] >> shift) & mask] + rank[i]] = make_uint2(key[i], val[i]);
+    __syncthreads();
+    const uint32_t tile_base = tile * kSortTile;
+    const uint32_t in_tile = s.n - tile_base < kSortTile ? s.n - tile_base : kSortTile;
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const uint32_t j = (uint32_t)i * BLOCK + t;
+        if (j < in_tile) {
+            const uint2 kv = staged[j];
+            if constexpr (LOCAL) {
+                keys_out[tile_base + j] = kv.x;
+                vals_out[tile_base + j] = kv.y;
+            } else {
+                words[digit_slot[(kv.x >> shift) & mask] + j] = kv;      // wraps like the subtraction above: the sum is the slot
+            }
         }
     }
 }
