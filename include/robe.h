@@ -198,7 +198,8 @@ int robe_offsets(const robe_hash_t *hash, const int64_t *indices, int64_t n, int
  *                    float32 in token order.  Bag bounds are clamped to
  *                    [0, n_indices] on the device, so a malformed CSR cannot
  *                    read outside `indices`.
- *   out        device float[batch][n_features][d], fully overwritten
+ *   out        device float[batch][n_features][d], fully overwritten (large lookups of blocks of up to
+ *              four floats keep their lists in it until the rows are written)
  *   options    NULL or host robe_options_t (fwd_elems, fwd_strided, tile_lookups, row_order are read)
  * Errors: ROBE_EINVAL, ROBE_EHIP.  batch == 0 is a no-op.
  */

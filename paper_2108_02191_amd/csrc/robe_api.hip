@@ -17,6 +17,7 @@
 
 #include "../../include/robe.h"
 #include "robe_kernels.h"
+#include "robe_forward_distinct.h"
 #include "robe_backward_dedup.h"
 #include "robe_backward_regions.h"
 #include "robe_backward_elements.h"
@@ -250,6 +251,33 @@ static_assert(kShortBagLanes >= robe::kShortBags, "a wavefront walks at most 64 
 // 18.1 / 20.0, 18.6 / 20.6); d = 48, Z = 16 20.3 / 17.5, 25.6 / 23.4; d = 96, Z = 32 28.2 / 30.6, 32.3 / 37.7.
 const uint32_t kWindowMostSlots = 48;
 
+int launch_fill(uint32_t *dst, uint64_t n, uint32_t v, hipStream_t stream, const char *what)      // n < 2^33
+{
+    const uint64_t per_block = 4ull * robe::kBlock * robe::kFillVecs;
+    robe::fill_u32_kernel<<<dim3((uint32_t)((n + per_block - 1) / per_block)), dim3(robe::kBlock), 0, stream>>>(dst, n, v);
+    return check_launch(what);
+}
+
+// Whether a single-hot lookup gathers every distinct token once (robe_forward_distinct.h): blocks of up to four
+// floats, and enough lines of 128 bytes to read, d / Z blocks of 1 + (Z - 1) / 32 a lookup.  Its five launches cost
+// some 45 us and a copied row what four lines cost.  Forward, us, plain / distinct, Zipf ids, d = 128, millions of lines:
+//   Z = 1   109 1112 / 570   27 278 / 203   13.3 143 / 128   6.7 76 / 94
+//   Z = 2    56  568 / 372   14 144 / 133
+//   Z = 4    30  323 / 268   18 200 / 185    7.3 83 / 107
+//   d = 32  Z = 1 27 248 / 179, Z = 2 14 137 / 125, Z = 4 7.5 87 / 100;  d = 64, Z = 4 15 165 / 154;  d = 16, Z = 1 27 250 / 202
+// (Z = 8: 852 K lookups 226 / 214, but 520 K 141 / 149, and 367 / 436 where no id repeats: not taken.)
+bool distinct_pays(const robe_hash_t *h, const Opt &opt, int64_t rows)
+{
+    if (opt.fwd_elems != 0 || opt.tile_lookups != 0 || opt.row_order != ROBE_ROWS_AUTO) return false;
+    if (h->Z > 4 || h->d < 16 || rows >= (1ll << 28)) return false;
+    return (uint64_t)rows * (h->d / h->Z) * (31 + h->Z) / 32 >= 12500000u + 400000u * h->Z;
+}
+
+// The four steps.  *taken: whether this call went that way.
+template <typename AT>
+int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, const robe::Geom &q, const AT *array, const int64_t *indices,
+                    int64_t rows, uint32_t F, float *out, hipStream_t stream, bool *taken);
+
 template <bool BWD, typename AT = float>
 int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64_t *indices, const int64_t *offsets,
                 int64_t n_indices, int64_t rows, uint32_t F, float *dst, const void *rows_ptr, hipStream_t stream,
@@ -289,6 +317,13 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
 
     q.G = lay.G;
     q.g_shift = log2u(lay.G);
+    if constexpr (!BWD) {
+        if (!bags && view == nullptr && distinct_pays(h, opt, rows)) {
+            bool taken = false;
+            if (int rc = launch_distinct(h, opt, lay, q, src, indices, rows, F, dst, stream, &taken)) return rc;
+            if (taken) return ROBE_OK;
+        }
+    }
     const uint32_t step = 64u / lay.G;
     // one pass of the gather loop per wavefront tile measured best (more, shorter wavefronts)
     q.TL = step * robe::kUnroll >= 64u ? 64u : step * robe::kUnroll;
@@ -399,6 +434,74 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
     return check_launch(BWD ? "backward" : "forward");
 }
 
+
+template <typename AT>
+int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, const robe::Geom &q, const AT *array, const int64_t *indices,
+                    int64_t rows, uint32_t F, float *out, hipStream_t stream, bool *taken)
+{
+    // the last samples, whose rows hold rep: at least rows / d of them
+    const int64_t batch = rows / (int64_t)F, last = (rows + h->d - 1) / h->d, keep = batch - (last + F - 1) / F;
+    uint64_t places = 1;
+    while (places < 2ull * (uint64_t)rows) places <<= 1;
+    // table at the front, aligned for its words; rep behind it
+    const uint64_t skip = aligned(out, 8) ? 0 : 1;
+    if (keep < 1 || (skip + 2 * places) > (uint64_t)keep * F * h->d) return ROBE_OK;
+    *taken = true;
+    const robe::Params p = to_params(h);
+    robe::DistinctPlan s;
+    s.batch = (uint32_t)keep;
+    s.batch_recip = reciprocal(s.batch);
+    s.F = F;
+    s.n = (uint32_t)(keep * F);
+    s.table = reinterpret_cast<uint64_t *>(out + skip);
+    s.mask = (uint32_t)(places - 1);
+    s.rep = reinterpret_cast<uint32_t *>(out + (uint64_t)s.n * h->d);
+    const bool sign = h->use_sign != 0;
+    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(s.table), 2 * places, 0u, stream, "forward (clear table)")) return rc;
+    const dim3 tiles((s.n + robe::kDistinctTile - 1) / robe::kDistinctTile), find(robe::kDistinctBlock);
+    if (sign) robe::distinct_find_kernel<true><<<tiles, find, 0, stream>>>(p, s, indices);
+    else robe::distinct_find_kernel<false><<<tiles, find, 0, stream>>>(p, s, indices);
+    if (int rc = check_launch("forward (find)")) return rc;
+    const uint32_t waves = (s.n + robe::kDistinctRows - 1) / robe::kDistinctRows;
+    const dim3 grid(waves), block(robe::kRowBlock);
+#define ROBE_DISTINCT(V_, C_)                                                                                         \
+    do {                                                                                                              \
+        if (sign) robe::distinct_gather_kernel<V_, C_, true, AT><<<grid, block, 0, stream>>>(p, q, s, array, indices, out);   \
+        else robe::distinct_gather_kernel<V_, C_, false, AT><<<grid, block, 0, stream>>>(p, q, s, array, indices, out);       \
+    } while (0)
+    if (lay.consec) {
+        switch (lay.V) {
+            case 1: ROBE_DISTINCT(1, true); break;
+            case 2: ROBE_DISTINCT(2, true); break;
+            default: ROBE_DISTINCT(4, true); break;
+        }
+    } else {
+        switch (lay.V) {
+            case 1: ROBE_DISTINCT(1, false); break;
+            case 2: ROBE_DISTINCT(2, false); break;
+            case 3: ROBE_DISTINCT(3, false); break;
+            case 6: ROBE_DISTINCT(6, false); break;
+            case 8: ROBE_DISTINCT(8, false); break;
+            default: ROBE_DISTINCT(4, false); break;
+        }
+    }
+#undef ROBE_DISTINCT
+    if (int rc = check_launch("forward (distinct)")) return rc;
+    const uint32_t per_xcd = (waves + robe::kXcds - 1) / robe::kXcds;
+    const dim3 spread(per_xcd * robe::kXcds);
+    if (h->d % 4 == 0 && aligned(out, 16)) {
+        const uint32_t g = log2u(h->d / 4) < 6 ? log2u(h->d / 4) : 6u;
+        robe::distinct_copy_kernel<4><<<spread, block, 0, stream>>>(s, h->d, g, per_xcd, out);
+    } else {
+        const uint32_t g = log2u(h->d) < 6 ? log2u(h->d) : 6u;
+        robe::distinct_copy_kernel<1><<<spread, block, 0, stream>>>(s, h->d, g, per_xcd, out);
+    }
+    if (int rc = check_launch("forward (copy)")) return rc;
+    // the last samples (a requested layout keeps this call off the path above)
+    Opt plain = opt;
+    plain.row_order = ROBE_ROWS_BY_TABLE;
+    return launch_rows<false, AT>(h, plain, array, indices + s.n, nullptr, rows - s.n, rows - s.n, F, out + (uint64_t)s.n * h->d, out + (uint64_t)s.n * h->d, stream);
+}
 
 // ---------------------------------------------------------------------------
 // Backward with duplicate tokens combined: plan (shared by robe_workspace_bytes
@@ -1744,10 +1847,7 @@ static int fused_step(int rule, const robe_hash_t *hash, const float *grad_out, 
     // two steps through a gradient array at the front of the workspace
     float *grad = static_cast<float *>(workspace);
     const uint64_t m = hash->m;
-    uint64_t fill_blocks = (m + 255) / 256;
-    if (fill_blocks > 65536) fill_blocks = 65536;
-    robe::fill_u32_kernel<<<dim3((uint32_t)fill_blocks), dim3(256), 0, s>>>(reinterpret_cast<uint32_t *>(grad), (uint32_t)m, 0u);
-    if (int rc = check_launch("fused step (clear gradient)")) return rc;
+    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(grad), m, 0u, s, "fused step (clear gradient)")) return rc;
     char *rest = static_cast<char *>(workspace) + scratch;
     int rc;
     if (pl.dedup)
@@ -1849,10 +1949,7 @@ int robe_backward_adagrad_mixed(const robe_hash_t *hash, const uint32_t *dims, c
     // two steps through a gradient array at the front of the workspace
     float *grad = static_cast<float *>(workspace);
     const uint64_t m = hash->m;
-    uint64_t fill_blocks = (m + 255) / 256;
-    if (fill_blocks > 65536) fill_blocks = 65536;
-    robe::fill_u32_kernel<<<dim3((uint32_t)fill_blocks), dim3(256), 0, s>>>(reinterpret_cast<uint32_t *>(grad), (uint32_t)m, 0u);
-    if (int rc = check_launch("fused step (clear gradient)")) return rc;
+    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(grad), m, 0u, s, "fused step (clear gradient)")) return rc;
     char *rest = static_cast<char *>(workspace) + scratch;
     int rc;
     if (mp.sorted)

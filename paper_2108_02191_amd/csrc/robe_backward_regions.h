@@ -86,11 +86,6 @@ struct RegionPlan {
     uint32_t *rec_tg;        // sign on only
 };
 
-__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *dst, uint32_t n, uint32_t v)
-{
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) dst[i] = v;
-}
-
 // ---------------------------------------------------------------------------------------------
 // R1.  Lane layout as in the direct scatter: G lanes per row, lane `grp` owns elements grp + k*G.
 // A group walks s.stretch * G consecutive sorted positions, G at a time; a run is cut only where the

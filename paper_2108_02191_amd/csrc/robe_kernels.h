@@ -1268,4 +1268,25 @@ __global__ __launch_bounds__(kBlock) void update_kernel(float *__restrict__ arra
     }
 }
 
+// Whole vectors of four words by a thread each, what is left in front of and behind them by single threads.
+// 100 MB: one word a thread and step 20.9 us, so 14.3.
+constexpr uint32_t kFillVecs = 4;      // vectors per thread
+
+__global__ __launch_bounds__(kBlock) void fill_u32_kernel(uint32_t *__restrict__ dst, uint64_t n, uint32_t v)
+{
+    const uint64_t skip = (4u - (((uintptr_t)dst >> 2) & 3u)) & 3u, head = skip < n ? skip : n, vecs = (n - head) / 4u;
+    typedef uint32_t V4 __attribute__((ext_vector_type(4)));
+    V4 *at = reinterpret_cast<V4 *>(dst + head);
+    const V4 v4 = {v, v, v, v};
+    const uint64_t first = (uint64_t)blockIdx.x * (kBlock * kFillVecs) + threadIdx.x;
+#pragma unroll
+    for (uint32_t k = 0; k < kFillVecs; ++k)
+        if (first + k * kBlock < vecs) at[first + k * kBlock] = v4;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < head) dst[threadIdx.x] = v;
+        const uint64_t tail = head + 4u * vecs + threadIdx.x;
+        if (threadIdx.x < 4u && tail < n) dst[tail] = v;
+    }
+}
+
 }  // namespace robe
