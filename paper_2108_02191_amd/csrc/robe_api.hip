@@ -1128,12 +1128,17 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         if (int rc = probe(opt, ROBE_PROBE_COMBINE, false, stream)) return rc;
         // R1: combine runs into P, leave one record per run (a lane group walks r.stretch * G positions)
         const dim3 rgrid1((uint32_t)(((uint64_t)n + (uint64_t)robe::kBlock * r.stretch - 1) / ((uint64_t)robe::kBlock * r.stretch)));
+#define ROBE_COMBINE_ROWS_G(V_, M_, W_, G_)                                                                               \
+    do {                                                                                                              \
+        if (sign && bags) robe::combine_rows_kernel<V_, true, true, M_, W_, G_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);   \
+        else if (sign) robe::combine_rows_kernel<V_, true, false, M_, W_, G_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
+        else if (bags) robe::combine_rows_kernel<V_, false, true, M_, W_, G_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
+        else robe::combine_rows_kernel<V_, false, false, M_, W_, G_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);             \
+    } while (0)
 #define ROBE_COMBINE_ROWS_W(V_, M_, W_)                                                                               \
     do {                                                                                                              \
-        if (sign && bags) robe::combine_rows_kernel<V_, true, true, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);   \
-        else if (sign) robe::combine_rows_kernel<V_, true, false, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
-        else if (bags) robe::combine_rows_kernel<V_, false, true, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);    \
-        else robe::combine_rows_kernel<V_, false, false, M_, W_><<<rgrid1, block, 0, stream>>>(p, q, r, grad_out, indices, vals_out, tok_bag);             \
+        if (W_ && pl.lay.G == 64) ROBE_COMBINE_ROWS_G(V_, M_, W_, W_);                                                \
+        else ROBE_COMBINE_ROWS_G(V_, M_, W_, false);                                                                  \
     } while (0)
 #define ROBE_COMBINE_ROWS_M(V_, M_)                                                                                   \
     do {                                                                                                              \
@@ -1153,6 +1158,7 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
             case 8: ROBE_COMBINE_ROWS(8); break;
             default: ROBE_COMBINE_ROWS(4); break;
         }
+#undef ROBE_COMBINE_ROWS_G
 #undef ROBE_COMBINE_ROWS_W
 #undef ROBE_COMBINE_ROWS_M
 #undef ROBE_COMBINE_ROWS
@@ -1247,12 +1253,19 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
     if (int rc = probe(opt, ROBE_PROBE_COMBINE, false, stream)) return rc;
     // S3: combine runs and scatter with float atomics (a lane group walks kWalk * G positions)
     const dim3 sgrid((uint32_t)(((uint64_t)n + (uint64_t)robe::kBlock * robe::kWalk - 1) / ((uint64_t)robe::kBlock * robe::kWalk)));
+#define ROBE_COMBINE_G(V_, M_, G_)                                                                                              \
+    do {                                                                                                              \
+        if (sign && bags) robe::combine_scatter_kernel<V_, true, true, M_, G_><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);   \
+        else if (sign) robe::combine_scatter_kernel<V_, true, false, M_, G_><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);    \
+        else if (bags) robe::combine_scatter_kernel<V_, false, true, M_, G_><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);    \
+        else robe::combine_scatter_kernel<V_, false, false, M_, G_><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);             \
+    } while (0)
 #define ROBE_COMBINE(V_)                                                                                              \
     do {                                                                                                              \
-        if (sign && bags) robe::combine_scatter_kernel<V_, true, true><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);   \
-        else if (sign) robe::combine_scatter_kernel<V_, true, false><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);    \
-        else if (bags) robe::combine_scatter_kernel<V_, false, true><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);    \
-        else robe::combine_scatter_kernel<V_, false, false><<<grid, block, 0, stream>>>(p, q, grad_out, indices, keys_out, vals_out, tok_bag, urows, n, grad_array);             \
+        if (tables != nullptr && pl.lay.G == 64) ROBE_COMBINE_G(V_, true, true);                                      \
+        else if (tables != nullptr) ROBE_COMBINE_G(V_, true, false);                                                  \
+        else if (pl.lay.G == 64) ROBE_COMBINE_G(V_, false, true);                                                     \
+        else ROBE_COMBINE_G(V_, false, false);                                                                        \
     } while (0)
     switch (pl.lay.V) {
         case 1: ROBE_COMBINE(1); break;
@@ -1263,6 +1276,7 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         default: ROBE_COMBINE(4); break;
     }
 #undef ROBE_COMBINE
+#undef ROBE_COMBINE_G
     if (int rc = check_launch("backward (combine and scatter)")) return rc;
     return probe(opt, ROBE_PROBE_COMBINE, true, stream);
 }

@@ -124,7 +124,10 @@ __device__ __forceinline__ SortedToken shfl_token(const SortedToken &t, int from
 }
 
 // WINDOW: Geom::window_sort (as a run-time flag it cost the others 9 of 448 us on the Multi-hot step).
-template <int V, bool SIGN, bool BAGS, bool MIXED, bool WINDOW>
+// WAVE: G = 64, see combine_scatter_kernel; here the rows of runs of one are not even looked at.  852 K lookups,
+// d = 128: 98 -> 92 us, 133 K tokens 16.0 -> 13.1.  Only with WINDOW: 8.5 M tokens of 218 MB of rows, which is what
+// comes without, take 457 us instead of 447 (lane masks are then not what they wait for).
+template <int V, bool SIGN, bool BAGS, bool MIXED, bool WINDOW, bool WAVE>
 __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, RegionPlan s,
                                                               const float *__restrict__ grad_out,
                                                               const int64_t *__restrict__ indices,
@@ -132,7 +135,8 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
                                                               const uint32_t *__restrict__ tok_bag)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t grp = lane & (q.G - 1u);
+    const uint32_t G = WAVE ? 64u : q.G;
+    const uint32_t grp = WAVE ? lane : lane & (G - 1u);
     const uint32_t base_lane = lane - grp;
     const uint32_t n = s.n;
     const uint64_t thread_id = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
             uint64_t sk = t.ok ? (((uint64_t)t.th << 6) | grp) : ((1ull << 40) | grp);
 #pragma unroll
             for (uint32_t kk = 2; kk <= 64u; kk <<= 1) {
-                if (kk > q.G) break;
+                if (kk > G) break;
 #pragma unroll
                 for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
                     const uint32_t lo = __shfl_xor((uint32_t)sk, (int)j), hi = __shfl_xor((uint32_t)(sk >> 32), (int)j);
@@ -209,7 +213,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
     // Rows of P: every lane group owns p_quota of them, at row (group number) * p_quota, and hands
     // them to the runs longer than one that start in its walk, in order.  A group that meets more
     // such runs leaves the rest uncombined: each of their tokens becomes a run of its own.
-    const uint32_t p_first = (uint32_t)((thread_id - grp) >> q.g_shift) * s.p_quota;
+    const uint32_t p_first = (uint32_t)((thread_id - grp) >> (WAVE ? 6u : q.g_shift)) * s.p_quota;
     uint32_t n_multi = 0, run_slot = 0;        // multi-token runs started so far; slot of the run being summed
     uint32_t open_slot = 0;                    // slot of the run that the stretch before left open, if it has one
     bool open_over = false;                    // ... or whether that run found the quota used up
@@ -220,11 +224,11 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
     carry.ok = false;
     if (s.dir != nullptr && i_first > 0 && i_first <= n) carry.th = s.keys[i_first - 1];   // its key only: the directory needs it
     for (uint32_t st = 0; st < s.stretch; ++st) {
-        const uint64_t i0 = i_first + (uint64_t)st * q.G;
+        const uint64_t i0 = i_first + (uint64_t)st * G;
         if (__all(i0 >= n)) break;                          // every group of the wavefront is past the end
         SortedToken nxt;
         if (st + 1u < s.stretch) {
-            nxt = fetch(i0 + q.G + grp);
+            nxt = fetch(i0 + G + grp);
         } else {
             nxt = carry;
             nxt.ok = false;
@@ -234,9 +238,9 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
         SortedToken before = shfl_token<SIGN>(cur, (int)(base_lane + (grp ? grp - 1u : 0u)), mixed);
         if (grp == 0) before = carry;
         const bool my_head = cur.ok && (!before.ok || !same_token<SIGN>(before, cur, mixed));
-        SortedToken after = shfl_token<SIGN>(cur, (int)(base_lane + (grp + 1u < q.G ? grp + 1u : grp)), mixed);
+        SortedToken after = shfl_token<SIGN>(cur, (int)(base_lane + (grp + 1u < G ? grp + 1u : grp)), mixed);
         const SortedToken first_of_next = shfl_token<SIGN>(nxt, (int)base_lane, mixed);
-        if (grp + 1u >= q.G) after = first_of_next;
+        if (grp + 1u >= G) after = first_of_next;
         const bool my_end = cur.ok && (!after.ok || !same_token<SIGN>(after, cur, mixed));
         bool my_single = my_head && my_end;
         // the slot of the run every position belongs to: the run of the last head at or before it (none:
@@ -244,7 +248,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
         uint32_t my_slot = open_slot;
         bool my_over = open_over;
         {
-            const uint64_t gmask = q.G >= 64u ? ~0ull : ((1ull << q.G) - 1ull);
+            const uint64_t gmask = G >= 64u ? ~0ull : ((1ull << G) - 1ull);
             const uint64_t heads = (__ballot(my_head) >> base_lane) & gmask;
             const uint64_t multi = (__ballot(my_head && !my_end) >> base_lane) & gmask;
             const uint64_t upto = heads & ((2ull << grp) - 1ull);
@@ -301,7 +305,41 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
         }
 
         // runs longer than one: sum their rows into P (a run may have begun in an earlier stretch)
-        for (uint32_t k0 = 0; k0 < q.G; k0 += kRowsAhead) {     // same trip count for every lane of the wavefront
+        if constexpr (WAVE) {
+            const uint64_t heads = __ballot(my_head), ends = __ballot(my_end);
+            uint64_t todo = __ballot(cur.ok && !my_single);
+            while (todo) {
+                uint32_t k[kRowsAhead];
+                float v[kRowsAhead][V];
+                const uint32_t count = (uint32_t)__popcll(todo);
+#pragma unroll
+                for (int u = 0; u < kRowsAhead; ++u) {        // past the last row: that one again, not added
+                    k[u] = todo ? (uint32_t)__builtin_ctzll(todo) : k[u ? u - 1 : 0];
+                    todo &= todo - 1ull;                      // (0 stays 0)
+                    const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)cur.sb, (int)k[u]);
+                    const uint32_t dd = mixed ? (uint32_t)__builtin_amdgcn_readlane((int)cur.dd, (int)k[u]) : q.d;
+                    load_row_of<V, BAGS>(grad_out + (uint64_t)sb * p.Z, G, dd, lane, v[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < kRowsAhead; ++u) {
+                    if ((uint32_t)u >= count) break;
+                    if (((heads >> k[u]) & 1ull) != 0) {
+                        head_pos = (uint32_t)i0 + k[u];
+                        run_slot = (uint32_t)__builtin_amdgcn_readlane((int)my_slot, (int)k[u]);
+#pragma unroll
+                        for (int j = 0; j < V; ++j) acc[j] = 0.0f;
+                    }
+#pragma unroll
+                    for (int j = 0; j < V; ++j) acc[j] += v[u][j];
+                    if (((ends >> k[u]) & 1ull) != 0) {
+                        const uint32_t prow = p_first + run_slot;
+                        store_row<V, false>(s.P + (uint64_t)prow * p.d, q, lane, acc);
+                        if (lane == 0) s.src_row[head_pos] = s.src_own + prow * p.C;
+                    }
+                }
+            }
+        }
+        for (uint32_t k0 = 0; !WAVE && k0 < G; k0 += kRowsAhead) {     // same trip count for every lane of the wavefront
             uint32_t sb[kRowsAhead], dd[kRowsAhead], slot[kRowsAhead];
             bool use[kRowsAhead], head[kRowsAhead], end[kRowsAhead];
             // what the loop below needs of a position, in one word: its run's slot, whether the position
@@ -309,8 +347,8 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
             const uint32_t mine = (my_slot << 3) | ((cur.ok && !my_single) ? 4u : 0u) | (my_head ? 2u : 0u) | (my_end ? 1u : 0u);
 #pragma unroll
             for (int u = 0; u < kRowsAhead; ++u) {
-                const int from = (int)(base_lane + ((k0 + u) & (q.G - 1u)));
-                const bool in = k0 + u < q.G;
+                const int from = (int)(base_lane + ((k0 + u) & (G - 1u)));
+                const bool in = k0 + u < G;
                 const uint32_t theirs = __shfl(mine, from);
                 sb[u] = __shfl(cur.sb, from);
                 dd[u] = mixed ? __shfl(cur.dd, from) : q.d;
@@ -322,7 +360,7 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
             float v[kRowsAhead][V];
 #pragma unroll
             for (int u = 0; u < kRowsAhead; ++u) {
-                if (use[u]) load_row_of<V, BAGS>(grad_out + (uint64_t)sb[u] * p.Z, q.G, dd[u], grp, v[u]);
+                if (use[u]) load_row_of<V, BAGS>(grad_out + (uint64_t)sb[u] * p.Z, G, dd[u], grp, v[u]);
             }
 #pragma unroll
             for (int u = 0; u < kRowsAhead; ++u) {
@@ -342,9 +380,9 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
                 }
             }
         }
-        carry = shfl_token<SIGN>(cur, (int)(base_lane + q.G - 1u), mixed);
-        open_slot = __shfl(my_slot, (int)(base_lane + q.G - 1u));
-        open_over = __shfl((int)my_over, (int)(base_lane + q.G - 1u)) != 0;
+        carry = shfl_token<SIGN>(cur, (int)(base_lane + G - 1u), mixed);
+        open_slot = __shfl(my_slot, (int)(base_lane + G - 1u));
+        open_over = __shfl((int)my_over, (int)(base_lane + G - 1u)) != 0;
         cur = nxt;
     }
 }
