@@ -487,6 +487,26 @@ __global__ __launch_bounds__(kBinBlock) void region_bin_kernel(Params p, RegionP
 // spent its time in 192 lane exchanges per thread: 18.9 us for 3052 regions and 16.9 for 30518; now
 // 10.1 and 9.8.)
 constexpr uint32_t kScanThreads = 1024u;
+
+// Count the lanes with `have` in their classes' counters in LDS, a lane's place in its class back.  Nearly all
+// regions are of one or two classes, and additions to one word go one by one: once per class and wavefront
+// instead of once per region, 6104 regions take 12.2 us instead of 14.4.
+__device__ __forceinline__ uint32_t add_to_class(uint32_t *counter, uint32_t cls, bool have)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t to = 0;
+    for (uint64_t todo = __ballot(have); todo;) {
+        const int lead = __builtin_ctzll(todo);
+        const bool mine = have && cls == (uint32_t)__builtin_amdgcn_readlane((int)cls, lead);
+        const uint64_t same = __ballot(mine);
+        uint32_t base = 0;
+        if ((int)lane == lead) base = atomicAdd(&counter[cls], (uint32_t)__popcll(same));
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, lead);
+        if (mine) to = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        todo &= ~same;
+    }
+    return to;
+}
 constexpr uint32_t kScanPer = kMaxRegions / kScanThreads;
 static_assert(kScanPer % 4u == 0, "R3 reads whole vectors of four counts");
 
@@ -559,7 +579,7 @@ __global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
     if (!s.fullest_first) return;
 #pragma unroll
     for (uint32_t k = 0; k < kScanPer; ++k)
-        if (k < per && first + k < s.NR) atomicAdd(&cls_n[31 - __clz((int)(c[k] | 1u))], 1u);
+        if (k < per) add_to_class(cls_n, 31u - (uint32_t)__clz((int)(c[k] | 1u)), first + k < s.NR);
     __syncthreads();
     if (t < 32u) {
         uint32_t a = 0;
@@ -568,8 +588,11 @@ __global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
     }
     __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < kScanPer; ++k)
-        if (k < per && first + k < s.NR) s.counts[atomicAdd(&cls_at[31 - __clz((int)(c[k] | 1u))], 1u)] = first + k;
+    for (uint32_t k = 0; k < kScanPer; ++k) {
+        if (k >= per) continue;
+        const uint32_t to = add_to_class(cls_at, 31u - (uint32_t)__clz((int)(c[k] | 1u)), first + k < s.NR);
+        if (first + k < s.NR) s.counts[to] = first + k;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
