@@ -561,11 +561,11 @@ size_t group_sort_temp_bytes(uint64_t n)
 }
 
 // The grouping sort of robe_radix_sort.h: n <= 2^21 pairs by the `bits` key bits [lo, lo + bits), nearly.  Keys
-// from the ids (single-hot: indices != NULL, the values are the positions), or from (keys_a, vals_a).  `words`: n
+// from the ids (single-hot: indices != NULL, the values are the positions; `clear`: cleared by the way), or from (keys_a, vals_a).  `words`: n
 // eight-byte words of scratch; the result is in (keys_a, vals_a).
 int launch_group_sort(const robe::Params &p, const int64_t *indices, uint32_t F, uint32_t *keys_a, uint32_t *vals_a, uint2 *words,
                       uint32_t n, uint32_t lo, uint32_t bits, void *temp, hipStream_t stream,
-                      const robe::TableArgs &tab, uint32_t n_tab, uint2 *tables)
+                      const robe::TableArgs &tab, uint32_t n_tab, uint2 *tables, robe::Clear clear)
 {
     robe::GroupPlan g;
     g.n = n;
@@ -582,9 +582,11 @@ int launch_group_sort(const robe::Params &p, const int64_t *indices, uint32_t F,
     g.F = F;
     g.F_recip = reciprocal(F);
     const dim3 block(robe::kGroupBlock), tiles(g.tiles), spread(robe::tile_blocks(g.tiles));
+    clear.work = g.tiles;
+    const dim3 counting(g.tiles + robe::fill_blocks(clear.n, robe::kGroupBlock));
 #define ROBE_GROUP(D_, I_)                                                                                            \
     do {                                                                                                              \
-        robe::group_count_kernel<D_, I_><<<tiles, block, 0, stream>>>(g, p, indices, keys_a, tab, n_tab, tables);     \
+        robe::group_count_kernel<D_, I_><<<counting, block, 0, stream>>>(g, p, indices, keys_a, tab, n_tab, tables, clear); \
         if (int rc = check_launch("sort (count)")) return rc;                                                         \
         if (!g.few) {                                                                                                 \
             robe::group_offsets_kernel<D_><<<dim3(D_ / 64), dim3(robe::kGroupOffsetsBlock), 0, stream>>>(g);          \
@@ -1011,11 +1013,13 @@ int allow_lds(K kernel, size_t bytes, const char *what)
 
 // rule 0: grad_array += scatter.  Regions only: rule 1, Adagrad on (array = dst, state) with the scatter
 // as gradient; rule 2, SGD on array = dst (the scatter rule of the reduce kernel with the scale -lr).
+// clear_words: so many words of grad_array are cleared first (see robe::Clear).
 int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &pl, const float *grad_out, const int64_t *indices,
                           const int64_t *offsets, int64_t n_indices, int64_t rows, uint32_t F,
                           float *grad_array, void *workspace, hipStream_t stream,
                           int rule = 0, float *state = nullptr, float lr = 0.0f, float eps = 0.0f,
-                          uint2 *tables = nullptr, int64_t sample_floats = 0, const uint32_t *dims = nullptr)
+                          uint2 *tables = nullptr, int64_t sample_floats = 0, const uint32_t *dims = nullptr,
+                          uint64_t clear_words = 0)
 {
     const robe::Params p_keys = to_params(h);     // the caller's instance: S1 hashes the ids with it
     h = &pl.eff;                                  // everything after S1 (see plan_backward)
@@ -1041,7 +1045,8 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
     const uint64_t key_threads = bags ? (((uint64_t)rows + robe::kKeyBags - 1) / robe::kKeyBags) << g_shift : (uint64_t)rows;
     uint64_t key_blocks = (key_threads + 255) / 256;
     if (key_blocks > 65536) key_blocks = 65536;
-    const dim3 kgrid((uint32_t)key_blocks), kblock(256);
+    robe::Clear clear = {reinterpret_cast<uint32_t *>(grad_array), clear_words, (uint32_t)key_blocks};
+    const dim3 kgrid((uint32_t)key_blocks + robe::fill_blocks(clear_words, 256)), kblock(256);
     // tables of mixed dimensions: the key kernel also writes the per-table map (its first kTableArgs entries)
     robe::TableArgs tab;
     memset(&tab, 0, sizeof(tab));
@@ -1059,9 +1064,9 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
     // (single-hot: row and position are the same, and the grouping sort hashes the ids itself)
     const bool keys_from_ids = pl.window_sort && !bags;
     if (keys_from_ids) {
-    } else if (bags && sign) robe::token_keys_kernel<true, false><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
-    else if (bags) robe::token_keys_kernel<true, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
-    else robe::token_keys_kernel<false, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables);
+    } else if (bags && sign) robe::token_keys_kernel<true, false><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables, clear);
+    else if (bags) robe::token_keys_kernel<true, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables, clear);
+    else robe::token_keys_kernel<false, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables, clear);
     if (int rc = check_launch("backward (keys)")) return rc;
 
     // S2: sort (key, value) pairs by the top key_bits bits of the key
@@ -1076,7 +1081,8 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         const uint32_t lo = (!pl.regions && pl.key_top < 31) ? 0u : pl.key_top - pl.key_bits;
         if (pl.window_sort) {
             if (int rc = launch_group_sort(p_keys, keys_from_ids ? indices : nullptr, F, keys_in, vals_in, reinterpret_cast<uint2 *>(keys_out),
-                                           n, lo, pl.key_bits, ws + pl.off_temp, stream, tab, n_tab, tables))
+                                           n, lo, pl.key_bits, ws + pl.off_temp, stream, tab, n_tab, tables,
+                                           keys_from_ids ? clear : robe::Clear{nullptr, 0, 0}))
                 return rc;
         } else if (int rc = launch_radix_sort(keys_in, vals_in, keys_out, vals_out, n, lo, lo + pl.key_bits, ws + pl.off_temp,
                                               stream, &in_b)) {
@@ -1561,7 +1567,7 @@ static int plan_mixed(const robe_hash_t *hash, const Opt &opt, const uint32_t *d
 static int launch_mixed_sorted(const MixedPlan &mp, const Opt &opt, const uint32_t *dims, const float *grad_out,
                                const int64_t *indices, const int64_t *offsets, int64_t n_indices, int64_t rows,
                                int32_t n_features, float *dst, void *workspace, hipStream_t s,
-                               int rule = 0, float *state = nullptr, float lr = 0.0f, float eps = 0.0f)
+                               int rule = 0, float *state = nullptr, float lr = 0.0f, float eps = 0.0f, uint64_t clear_words = 0)
 {
     uint2 *tables = reinterpret_cast<uint2 *>(static_cast<char *>(workspace) + mp.off_tables);
     // the per-table map: its first kTableArgs entries travel with the key kernel, the rest go here
@@ -1580,7 +1586,7 @@ static int launch_mixed_sorted(const MixedPlan &mp, const Opt &opt, const uint32
         if (int rc = check_launch("backward (table map)")) return rc;
     }
     return launch_dedup_backward(&mp.widest, opt, mp.pl, grad_out, indices, offsets, n_indices, rows, (uint32_t)n_features,
-                                 dst, workspace, s, rule, state, lr, eps, tables, mp.D, dims);
+                                 dst, workspace, s, rule, state, lr, eps, tables, mp.D, dims, clear_words);
 }
 
 int robe_mixed_workspace_bytes(const robe_hash_t *hash, const uint32_t *dims, int64_t batch, int32_t n_features,
@@ -1861,11 +1867,13 @@ static int fused_step(int rule, const robe_hash_t *hash, const float *grad_out, 
     // two steps through a gradient array at the front of the workspace
     float *grad = static_cast<float *>(workspace);
     const uint64_t m = hash->m;
-    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(grad), m, 0u, s, "fused step (clear gradient)")) return rc;
+    if (!pl.dedup)
+        if (int rc = launch_fill(reinterpret_cast<uint32_t *>(grad), m, 0u, s, "fused step (clear gradient)")) return rc;
     char *rest = static_cast<char *>(workspace) + scratch;
     int rc;
     if (pl.dedup)
-        rc = launch_dedup_backward(hash, opt, pl, grad_out, indices, offsets, n_indices, rows, (uint32_t)n_features, grad, rest, s);
+        rc = launch_dedup_backward(hash, opt, pl, grad_out, indices, offsets, n_indices, rows, (uint32_t)n_features, grad, rest, s,
+                                   0, nullptr, 0.0f, 0.0f, nullptr, 0, nullptr, m);
     else
         rc = launch_rows<true>(hash, opt, grad_out, indices, offsets, n_indices, rows, (uint32_t)n_features, grad, grad_out, s);
     if (rc) return rc;
@@ -1963,11 +1971,13 @@ int robe_backward_adagrad_mixed(const robe_hash_t *hash, const uint32_t *dims, c
     // two steps through a gradient array at the front of the workspace
     float *grad = static_cast<float *>(workspace);
     const uint64_t m = hash->m;
-    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(grad), m, 0u, s, "fused step (clear gradient)")) return rc;
+    if (!mp.sorted)
+        if (int rc = launch_fill(reinterpret_cast<uint32_t *>(grad), m, 0u, s, "fused step (clear gradient)")) return rc;
     char *rest = static_cast<char *>(workspace) + scratch;
     int rc;
     if (mp.sorted)
-        rc = launch_mixed_sorted(mp, opt, dims, grad_out, indices, offsets, n_indices, rows, n_features, grad, rest, s);
+        rc = launch_mixed_sorted(mp, opt, dims, grad_out, indices, offsets, n_indices, rows, n_features, grad, rest, s,
+                                 0, nullptr, 0.0f, 0.0f, m);
     else
         rc = launch_mixed<true>(hash, opt, dims, grad_out, indices, offsets, n_indices, batch, n_features, grad, grad_out, stream);
     if (rc) return rc;

@@ -75,12 +75,17 @@ __global__ __launch_bounds__(256) void token_keys_kernel(Params p, uint32_t F, u
                                                          uint32_t rows, uint32_t n_indices,
                                                          uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
                                                          uint32_t *__restrict__ tok_bag,
-                                                         TableArgs tab, uint32_t n_tab, uint2 *__restrict__ tables)
+                                                         TableArgs tab, uint32_t n_tab, uint2 *__restrict__ tables,
+                                                         Clear clear)
 {
+    if (blockIdx.x >= clear.work) {
+        fill_u32<256>(clear.dst, clear.n, 0u, blockIdx.x - clear.work);
+        return;
+    }
     if (blockIdx.x == 0 && threadIdx.x < n_tab) tables[threadIdx.x] = make_uint2(tab.col[threadIdx.x], tab.dim[threadIdx.x]);
     const uint32_t G = 1u << g_shift;
     const uint32_t lane = threadIdx.x & (G - 1u);
-    const uint64_t groups = ((uint64_t)gridDim.x * 256u) >> g_shift;
+    const uint64_t groups = ((uint64_t)clear.work * 256u) >> g_shift;
     const uint64_t group = ((uint64_t)blockIdx.x * 256u + threadIdx.x) >> g_shift;
     if constexpr (!BAGS) {
         for (uint64_t k = group; k < rows; k += groups) {      // G = 1: one lookup per lane

@@ -325,10 +325,15 @@ constexpr int kGroupOffsetsRows = (int)kGroupMostTiles / (kGroupOffsetsBlock / 6
 template <int DIG, bool IDS>
 __global__ __launch_bounds__(kGroupBlock) void group_count_kernel(GroupPlan s, Params p, const int64_t *__restrict__ indices,
                                                                   const uint32_t *__restrict__ keys,
-                                                                  TableArgs tab, uint32_t n_tab, uint2 *__restrict__ tables)
+                                                                  TableArgs tab, uint32_t n_tab, uint2 *__restrict__ tables,
+                                                                  Clear clear)
 {
     constexpr int ROUNDS = (int)kSortTile / kGroupBlock;
     __shared__ uint32_t h[DIG];
+    if (IDS && blockIdx.x >= clear.work) {
+        fill_u32<kGroupBlock>(clear.dst, clear.n, 0u, blockIdx.x - clear.work);
+        return;
+    }
     if (IDS && blockIdx.x == 0 && threadIdx.x < n_tab) tables[threadIdx.x] = make_uint2(tab.col[threadIdx.x], tab.dim[threadIdx.x]);
     for (uint32_t d = threadIdx.x; d < (uint32_t)DIG; d += kGroupBlock) h[d] = 0;
     __syncthreads();
