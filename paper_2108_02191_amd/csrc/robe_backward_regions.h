@@ -175,26 +175,14 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
             }
         }
         // After a sort on few key bits the tokens of a key bucket sit interleaved: the group puts its G
-        // positions in order of the whole key (bitonic network over its lanes, the key made unique by
-        // the lane it came from) and so finds the runs that a full sort would, cut at every G positions
+        // positions in order of the key (made unique by the lane it came from) and so finds the runs that a full sort would, cut at every G positions
         // at the most.
         if constexpr (WINDOW) {
-            uint64_t sk = t.ok ? (((uint64_t)t.th << 6) | grp) : ((1ull << 40) | grp);
-#pragma unroll
-            for (uint32_t kk = 2; kk <= 64u; kk <<= 1) {
-                if (kk > G) break;
-#pragma unroll
-                for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-                    const uint32_t lo = __shfl_xor((uint32_t)sk, (int)j), hi = __shfl_xor((uint32_t)(sk >> 32), (int)j);
-                    const uint64_t other = ((uint64_t)hi << 32) | lo;
-                    const bool take_min = ((grp & j) == 0) == ((grp & kk) == 0);
-                    sk = take_min ? (other < sk ? other : sk) : (other > sk ? other : sk);
-                }
-            }
-            const int from = (int)(base_lane + ((uint32_t)sk & 63u));
+            const uint32_t sk = sort_lanes(window_key(t.ok, t.th, grp), G);
+            const int from = (int)(base_lane + (sk & 63u));
             SortedToken u;
-            u.ok = (sk >> 40) == 0;
-            u.th = u.ok ? (uint32_t)(sk >> 6) : 0u;
+            u.ok = window_key_ok(sk);
+            u.th = __shfl(t.th, from);
             u.sb = __shfl(t.sb, from);
             u.dd = mixed ? __shfl(t.dd, from) : q.d;
             u.e = (SIGN || mixed) ? __shfl(t.e, from) : 0u;

@@ -327,6 +327,83 @@ struct Lane {
     }
 };
 
+// The value of lane `lane ^ J`.  Inside rows of 16 lanes by DPP moves, which cost no trip through LDS.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+}
+template <int J>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t v)
+{
+    if constexpr (J == 1) return dpp_move<0xB1>(v);                       // quad_perm [1,0,3,2]
+    else if constexpr (J == 2) return dpp_move<0x4E>(v);                  // quad_perm [2,3,0,1]
+    else if constexpr (J == 3) return dpp_move<0x1B>(v);                  // quad_perm [3,2,1,0]
+    else if constexpr (J == 4) return dpp_move<0x1B>(dpp_move<0x141>(v));
+    else if constexpr (J == 7) return dpp_move<0x141>(v);                 // row_half_mirror
+    else if constexpr (J == 8) return dpp_move<0x128>(v);                 // row_ror:8
+    else if constexpr (J == 15) return dpp_move<0x140>(v);                // row_mirror
+    else if constexpr (J == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
+    else if constexpr (J == 31) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x7C1F);
+    else return (uint32_t)__shfl_xor((int)v, J);
+}
+
+template <int J, int HALF>
+__device__ __forceinline__ uint32_t keep_ordered(uint32_t key, uint32_t lane)
+{
+    const uint32_t other = xor_lane<J>(key), low = min(key, other), high = max(key, other);
+    return (lane & HALF) == 0u ? low : high;
+}
+
+// The keys of G = 1, 2, 4 .. 64 lanes in ascending order (every group of G lanes on its own; all lanes take part): a bitonic network whose
+// stages begin with a comparison against the mirrored lane, so that all go upwards.  18 of its 21 exchanges are
+// DPP moves.  The sort of a window was 42 exchanges through LDS with 37-bit keys.  Direct scatter of 53 K lookups of
+// d = 16 16.4 -> 15.5 us; combining 117 K tokens 31.2 -> 29.8, 133 K 13.1 -> 12.4, 852 K lookups 92 -> 87.
+__device__ __forceinline__ uint32_t sort_lanes(uint32_t key, uint32_t G)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    if (G >= 2u) key = keep_ordered<1, 1>(key, lane);
+    if (G >= 4u) {
+        key = keep_ordered<3, 2>(key, lane);
+        key = keep_ordered<1, 1>(key, lane);
+    }
+    if (G >= 8u) {
+        key = keep_ordered<7, 4>(key, lane);
+        key = keep_ordered<2, 2>(key, lane);
+        key = keep_ordered<1, 1>(key, lane);
+    }
+    if (G >= 16u) {
+        key = keep_ordered<15, 8>(key, lane);
+        key = keep_ordered<4, 4>(key, lane);
+        key = keep_ordered<2, 2>(key, lane);
+        key = keep_ordered<1, 1>(key, lane);
+    }
+    if (G >= 32u) {
+        key = keep_ordered<31, 16>(key, lane);
+        key = keep_ordered<8, 8>(key, lane);
+        key = keep_ordered<4, 4>(key, lane);
+        key = keep_ordered<2, 2>(key, lane);
+        key = keep_ordered<1, 1>(key, lane);
+    }
+    if (G >= 64u) {
+        key = keep_ordered<63, 32>(key, lane);
+        key = keep_ordered<16, 16>(key, lane);
+        key = keep_ordered<8, 8>(key, lane);
+        key = keep_ordered<4, 4>(key, lane);
+        key = keep_ordered<2, 2>(key, lane);
+        key = keep_ordered<1, 1>(key, lane);
+    }
+    return key;
+}
+
+// What a window is ordered by: 26 bits of the token's key and the lane it came from; positions without a token last.
+// Tokens that differ in the other bits alone may interleave: runs are found by the whole key, so that only cuts some.
+__device__ __forceinline__ uint32_t window_key(bool ok, uint32_t key, uint32_t lane)
+{
+    return ((ok ? min(key & 0x3FFFFFFu, 0x3FFFFFEu) : 0x3FFFFFFu) << 6) | lane;
+}
+__device__ __forceinline__ bool window_key_ok(uint32_t k) { return k < 0xFFFFFFC0u; }
+
 // Load / store the V owned elements of one output row.
 template <int V, bool CONSEC>
 __device__ __forceinline__ void store_row(float *__restrict__ row, const Geom &q, uint32_t grp, const float (&v)[V])
@@ -649,7 +726,7 @@ __global__ __launch_bounds__(kRowBlock) void single_hot_backward_tile_kernel(Par
 // At the sizes that come here (some ten thousand lookups) a SIMD holds one wavefront and the kernel is a
 // chain of latencies.  The one above finds the distinct tokens one by one, 64 rounds of dependent lane
 // exchanges where most tokens differ, and its groups then meet unequal sets.  Here the wavefront sorts
-// its 64 lookups by token (bitonic network over the lanes, 21 steps); every group walks the G lookups
+// its 64 lookups by token (sort_lanes); every group walks the G lookups
 // that its own lanes hold and adds runs in registers; a run that goes on in the next group is handed
 // over, so that a token still costs one row of atomics per tile.  53248 lookups, d = 16, Z = 4: 20.9 us
 // before, 16.7 now; with one group per wavefront (d = 128) the walk is 64 rows long and loses
@@ -688,17 +765,7 @@ __global__ __launch_bounds__(kRowBlock) void single_hot_backward_window_kernel(P
     // three; what a run is, is decided on all three below.
     {
         const uint32_t mix = th + pl * 0x9E3779B1u + (SIGN ? tg * 0x85EBCA6Bu : 0u);
-        uint64_t sk = lane < n ? (((uint64_t)mix << 6) | lane) : ((1ull << 40) | lane);
-#pragma unroll
-        for (uint32_t kk = 2; kk <= 64u; kk <<= 1) {
-#pragma unroll
-            for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-                const uint32_t lo = __shfl_xor((uint32_t)sk, (int)j), hi = __shfl_xor((uint32_t)(sk >> 32), (int)j);
-                const uint64_t other = ((uint64_t)hi << 32) | lo;
-                const bool take_min = ((lane & j) == 0) == ((lane & kk) == 0);
-                sk = take_min ? (other < sk ? other : sk) : (other > sk ? other : sk);
-            }
-        }
+        const uint32_t sk = sort_lanes(window_key(lane < n, mix, lane), 64u);
         const int from = (int)(sk & 63u);                 // (lookups past the end sort last: n of them stay in front)
         th = __shfl(th, from);
         if (p.r) pl = __shfl(pl, from);
