@@ -199,7 +199,9 @@ int robe_offsets(const robe_hash_t *hash, const int64_t *indices, int64_t n, int
  *                    [0, n_indices] on the device, so a malformed CSR cannot
  *                    read outside `indices`.
  *   out        device float[batch][n_features][d], fully overwritten (large lookups of blocks of up to
- *              four floats keep their lists in it until the rows are written)
+ *              four floats, some 25 million 128-byte lines or more, keep their lists in it until the
+ *              rows are written: repeated tokens' rows are then copied, which costs up to a tenth
+ *              where ids hardly repeat; a row_order other than ROBE_ROWS_AUTO gathers every row)
  *   options    NULL or host robe_options_t (fwd_elems, fwd_strided, tile_lookups, row_order are read)
  * Errors: ROBE_EINVAL, ROBE_EHIP.  batch == 0 is a no-op.
  */

@@ -259,18 +259,21 @@ int launch_fill(uint32_t *dst, uint64_t n, uint32_t v, hipStream_t stream, const
 }
 
 // Whether a single-hot lookup gathers every distinct token once (robe_forward_distinct.h): blocks of up to four
-// floats, and enough lines of 128 bytes to read, d / Z blocks of 1 + (Z - 1) / 32 a lookup.  Its five launches cost
-// some 45 us and a copied row what four lines cost.  Forward, us, plain / distinct, Zipf ids, d = 128, millions of lines:
-//   Z = 1   109 1112 / 570   27 278 / 203   13.3 143 / 128   6.7 76 / 94
-//   Z = 2    56  568 / 372   14 144 / 133
-//   Z = 4    30  323 / 268   18 200 / 185    7.3 83 / 107
-//   d = 32  Z = 1 27 248 / 179, Z = 2 14 137 / 125, Z = 4 7.5 87 / 100;  d = 64, Z = 4 15 165 / 154;  d = 16, Z = 1 27 250 / 202
-// (Z = 8: 852 K lookups 226 / 214, but 520 K 141 / 149, and 367 / 436 where no id repeats: not taken.)
+// floats, and many lines of 128 bytes to read, d / Z blocks of 1 + (Z - 1) / 32 a lookup.  A million lines take 18 to
+// 20 us to gather, the lists 20 us and 17 more a million rows, which ids that never repeat pay for nothing: the line
+// lies where that is a twentieth.  Forward, us, plain / distinct, Zipf ids and (ids that never repeat), millions of lines:
+//   Z = 1   109 1092 / 574 (1976 / 2007)   53 539 / 333 (970 / 1000)   25 254 / 196 (451 / 474)
+//   Z = 2    56  543 / 373 (1060 / 1086)   30 292 / 231 (561 / 589)
+//   Z = 4    60  563 / 474 (1185 / 1235)   46 432 / 379 (909 / 954)
+//   d = 32, Z = 1 51 417 / 294 (949 / 1008);  d = 512, Z = 4 25 299 / 266 (499 / 525)
+// not taken: Z = 1 19 202 / 163 (355 / 378), Z = 2 20 197 / 175 (377 / 406), Z = 4 30 288 / 270 (596 / 631), 14 142 / 155
+// (286 / 315);  d = 32, Z = 2 14 121 / 127 (279 / 312), Z = 4 15 141 / 177 (323 / 382).
+// Uniform ids of which an eighth repeats lose most: 1966 / 2004 (Z = 1, 109), 539 / 587 (Z = 2, 30), 485 / 522 (d = 512).
 bool distinct_pays(const robe_hash_t *h, const Opt &opt, int64_t rows)
 {
     if (opt.fwd_elems != 0 || opt.tile_lookups != 0 || opt.row_order != ROBE_ROWS_AUTO) return false;
     if (h->Z > 4 || h->d < 16 || rows >= (1ll << 28)) return false;
-    return (uint64_t)rows * (h->d / h->Z) * (31 + h->Z) / 32 >= 12500000u + 400000u * h->Z;
+    return (uint64_t)rows * (h->d / h->Z) * (31 + h->Z) / 32 >= 21000000u + 18u * (uint64_t)rows;
 }
 
 // The four steps.  *taken: whether this call went that way.
@@ -456,6 +459,7 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
     s.table = reinterpret_cast<uint64_t *>(out + skip);
     s.mask = (uint32_t)(places - 1);
     s.rep = reinterpret_cast<uint32_t *>(out + (uint64_t)s.n * h->d);
+    s.least_repeats = robe::distinct_least_repeats((uint64_t)batch);
     const bool sign = h->use_sign != 0;
     if (int rc = launch_fill(reinterpret_cast<uint32_t *>(s.table), 2 * places, 0u, stream, "forward (clear table)")) return rc;
     const dim3 tiles((s.n + robe::kDistinctTile - 1) / robe::kDistinctTile), find(robe::kDistinctBlock);

@@ -7,7 +7,8 @@
 //
 //   D1 find    lookups table by table, a tile of kDistinctTile per workgroup: equal tokens of a tile are found by
 //              a hash table in LDS; the first of each enters a hash table in memory, or finds there who
-//              came first in another tile.  rep[position]: the row that gathers for it.
+//              came first in another tile (where the tile has repeats enough).  rep[position]: the row that
+//              gathers for it.
 //   D2 gather  the rows that gather for themselves, as single_hot_kernel does.
 //   D3 copy    the others.
 //   D4         the last samples' rows, plainly: rep lies there until now.
@@ -16,9 +17,10 @@
 // rep at its end until D4, whose rows no other lookup copies from.  Tokens are the same when the token part of h
 // is (and of g, with the sign on): then every offset and every sign is.
 //
-// 852 K Zipf lookups over 26 tables, d = 128, 100 MB array: Z = 1 1112 -> 570 us (gather 443, 2.5 GB of lines at
-// 5.6 TB/s; copy 99, find 25, the last samples 14, clearing the table 6), Z = 2 568 -> 372, Z = 4 323 -> 268.
-// Ids that never repeat pay D1 and the empty D3: 1969 -> 2038, 598 -> 668 at Z = 4.  Tiles of 2048 lookups: of 4096
+// 852 K Zipf lookups over 26 tables, d = 128, 100 MB array: Z = 1 1092 -> 574 us (gather 433, 2.5 GB of lines at
+// 5.6 TB/s; copy 98, find 23, the last samples 14, clearing the table 6), Z = 2 543 -> 373.
+// Ids that never repeat pay D1 and the empty D3: Z = 1 1976 -> 2007, Z = 2 1060 -> 1086 (2054 and 1130 with every token
+// entered in memory, see distinct_least_repeats).  Tiles of 2048 lookups: of 4096
 // 208 K lookups take 212 us instead of 203, of 1024 852 K 576 instead of 570.
 #pragma once
 #include "robe_kernels.h"
@@ -38,7 +40,18 @@ struct DistinctPlan {
     uint64_t *table;           // (th + 1) << 32 | row; 0: free
     uint32_t mask;             // its places - 1, a power of two and at least 2n places
     uint32_t *rep;             // [n]
+    uint32_t least_repeats;    // see distinct_least_repeats
 };
+
+// A tile with fewer repeated lookups than this stays out of the table in memory, whose atomics are most of what the
+// lists cost where hardly any id repeats (D1 of 852 K lookups that differ 58 us).  If the pairs of a whole table are
+// equal as often as those of a tile, the share of its lookups that repeat is repeats * batch / kDistinctTile^2: a
+// quarter, below which they gain nothing, Z = 4 least of all.  Up to tiles a quarter of whose own lookups repeat.
+__host__ __device__ inline uint32_t distinct_least_repeats(uint64_t batch)
+{
+    const uint64_t least = (uint64_t)kDistinctTile * kDistinctTile / 4u / batch;
+    return least < kDistinctTile / 4u ? (uint32_t)least : kDistinctTile / 4u;
+}
 
 // The row b * F + f of a position, and its table.
 __device__ __forceinline__ uint32_t distinct_row(const DistinctPlan &s, uint32_t q, uint32_t &f)
@@ -53,7 +66,9 @@ __global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p,
     __shared__ uint32_t place[kDistinctSlots];               // tile-local lookup + 1; 0: free
     __shared__ uint32_t th[kDistinctTile], rep[kDistinctTile];
     __shared__ uint32_t tg[SIGN ? kDistinctTile : 1];
+    __shared__ uint32_t repeats;                             // lookups of the tile whose token another one of it has
     const uint32_t t = threadIdx.x, base = blockIdx.x * kDistinctTile;
+    if (t == 0) repeats = 0;
     for (uint32_t i = t; i < kDistinctSlots; i += kDistinctBlock) place[i] = 0;
     uint32_t row[kDistinctPer], f[kDistinctPer];
     int64_t x[kDistinctPer];
@@ -93,12 +108,20 @@ __global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p,
                 }
             }
         }
+        const uint64_t again = __ballot(lead[i] != j);
+        if ((t & 63u) == 0) atomicAdd(&repeats, (uint32_t)__popcll(again));
     }
+    __syncthreads();
+    const bool enter = repeats >= s.least_repeats;          // uniform over the workgroup
 #pragma unroll
     for (uint32_t i = 0; i < kDistinctPer; ++i) {
         const uint32_t j = i * kDistinctBlock + t;
         if (base + j >= s.n || lead[i] != j) continue;
         uint32_t mine = row[i];
+        if (!enter) {
+            rep[j] = mine;
+            continue;
+        }
         const uint64_t entry = ((uint64_t)(h[i] + 1u) << 32) | row[i];
         uint32_t at = ((h[i] ^ (g[i] << 7)) * 0x85EBCA6Bu) ^ (h[i] >> 13);
         for (uint32_t tries = 0; tries < kDistinctProbes; ++tries, ++at) {
