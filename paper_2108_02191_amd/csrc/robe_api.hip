@@ -555,59 +555,61 @@ int launch_radix_sort(uint32_t *keys_a, uint32_t *vals_a, uint32_t *keys_b, uint
     return ROBE_OK;
 }
 
-// Up to this many tokens the grouping sort places by 8 bits (a few hundred tokens a bucket), above by 10.
-const uint64_t kGroupSmall = 1u << 18, kGroupMost = (uint64_t)robe::kGroupMostTiles * robe::kSortTile;
+// Up to this many tokens the grouping sort places by 8 bits (a few hundred tokens a bucket), above by 10.  Bags keep 8
+// bits for longer: their keys are then hashed by the bags' kernel, with 10 bits twice in the sort (see below).
+// Backward, d = 128, Z = 32, 300 K, 400 K, 520 K, 560 K tokens with 8 / 10 bits: 89.0 / 89.7, 104.5 / 105.1, 124.2 / 127.1,
+// 133.4 / 133.9 us; d = 100, Z = 10 with the sign 109.2 / 110.2, 131.6 / 130.8, 159.4 / 155.3, - / 164.2.
+const uint64_t kGroupSmall = 1u << 18, kGroupSmallBags = 450000, kGroupMost = (uint64_t)robe::kGroupMostTiles * robe::kSortTile;
 
-size_t group_sort_temp_bytes(uint64_t n)
-{
-    const uint64_t tiles = (n + robe::kSortTile - 1) / robe::kSortTile, digits = n <= kGroupSmall ? 256 : 1024;
-    return (size_t)((tiles + 1) * digits * 4);
-}
+bool group_wide(uint64_t n, bool bags) { return n > (bags ? kGroupSmallBags : kGroupSmall); }
 
-// The grouping sort of robe_radix_sort.h: n <= 2^21 pairs by the `bits` key bits [lo, lo + bits), nearly.  Keys
-// from the ids (single-hot: indices != NULL, the values are the positions; `clear`: cleared by the way), or from (keys_a, vals_a).  `words`: n
-// eight-byte words of scratch; the result is in (keys_a, vals_a).
-int launch_group_sort(const robe::Params &p, const int64_t *indices, uint32_t F, uint32_t *keys_a, uint32_t *vals_a, uint2 *words,
-                      uint32_t n, uint32_t lo, uint32_t bits, void *temp, hipStream_t stream,
+// The grouping sort of robe_radix_sort.h: n <= 2^21 tokens by the `bits` key bits [lo, lo + bits), nearly.  Tokens come as
+// (keys, vals) pairs (indices == NULL), or the keys are hashed from the ids; bag_rows: every token's row then (NULL:
+// single-hot, its position; `clear` is cleared by the way), and the values are rows (row_values) or positions.
+// `words`: n eight-byte words of scratch; the result is in (keys, vals).  Its counts are 1 or 4 KB a tile of 4096 tokens.
+// Those of 1 KB fit `temp`, radix_sort_temp_bytes(n) bytes; the others lie in `keys`, which the last step alone
+// writes where keys are hashed: no workspace is larger for this sort.
+int launch_group_sort(const robe::Params &p, const int64_t *indices, const uint32_t *bag_rows, bool row_values, bool wide, uint32_t F,
+                      uint32_t *keys, uint32_t *vals, uint2 *words, uint32_t n, uint32_t lo, uint32_t bits, void *temp, hipStream_t stream,
                       const robe::TableArgs &tab, uint32_t n_tab, uint2 *tables, robe::Clear clear)
 {
     robe::GroupPlan g;
     g.n = n;
     g.tiles = (uint32_t)(((uint64_t)n + robe::kSortTile - 1) / robe::kSortTile);
-    const bool wide = n > kGroupSmall;
     const uint32_t digit_bits = wide ? 10u : 8u, digits = 1u << digit_bits;
-    if (g.tiles > robe::kGroupMostTiles || bits <= digit_bits) return fail(ROBE_EINVAL, "internal: grouping sort");
+    if (g.tiles > robe::kGroupMostTiles || bits <= digit_bits || (wide && (indices == nullptr || n <= kGroupSmall))) return fail(ROBE_EINVAL, "internal: grouping sort");
     g.few = !wide && g.tiles <= robe::kFewTiles ? 1u : 0u;
     g.shift = lo + bits - digit_bits;
     g.local_shift = g.shift > 8 ? g.shift - 8 : 0u;
     g.local_mask = (1u << (g.shift - g.local_shift)) - 1u;
-    g.tile_count = static_cast<uint32_t *>(temp);
+    g.tile_count = wide ? keys : static_cast<uint32_t *>(temp);      // (tiles + 1 rows of 4 KB are less than n > kGroupSmall words)
     g.totals = g.tile_count + (size_t)g.tiles * digits;
+    g.row_values = row_values ? 1u : 0u;
     g.F = F;
     g.F_recip = reciprocal(F);
     const dim3 block(robe::kGroupBlock), tiles(g.tiles), spread(robe::tile_blocks(g.tiles));
     clear.work = g.tiles;
     const dim3 counting(g.tiles + robe::fill_blocks(clear.n, robe::kGroupBlock));
-#define ROBE_GROUP(D_, I_)                                                                                            \
+#define ROBE_GROUP(D_, S_)                                                                                            \
     do {                                                                                                              \
-        robe::group_count_kernel<D_, I_><<<counting, block, 0, stream>>>(g, p, indices, keys_a, tab, n_tab, tables, clear); \
+        robe::group_count_kernel<D_, S_><<<counting, block, 0, stream>>>(g, p, indices, bag_rows, keys, tab, n_tab, tables, clear); \
         if (int rc = check_launch("sort (count)")) return rc;                                                         \
         if (!g.few) {                                                                                                 \
             robe::group_offsets_kernel<D_><<<dim3(D_ / 64), dim3(robe::kGroupOffsetsBlock), 0, stream>>>(g);          \
             if (int rc = check_launch("sort (offsets)")) return rc;                                                   \
         }                                                                                                             \
-        robe::group_scatter_kernel<D_, I_, false><<<spread, block, 0, stream>>>(g, p, indices, keys_a, vals_a, words, nullptr, nullptr); \
+        robe::group_scatter_kernel<D_, S_><<<spread, block, 0, stream>>>(g, p, indices, bag_rows, keys, vals, words); \
         if (int rc = check_launch("sort (scatter)")) return rc;                                                       \
     } while (0)
-    if (indices != nullptr) {
-        if (wide) ROBE_GROUP(1024, true);
-        else ROBE_GROUP(256, true);
+    if (wide) {
+        if (bag_rows == nullptr) ROBE_GROUP(1024, robe::GROUP_LOOKUPS);
+        else ROBE_GROUP(1024, robe::GROUP_BAGS);
     } else {
-        if (wide) ROBE_GROUP(1024, false);
-        else ROBE_GROUP(256, false);
+        if (indices != nullptr) ROBE_GROUP(256, robe::GROUP_LOOKUPS);
+        else ROBE_GROUP(256, robe::GROUP_PAIRS);
     }
 #undef ROBE_GROUP
-    robe::group_scatter_kernel<256, false, true><<<tiles, block, 0, stream>>>(g, p, nullptr, nullptr, nullptr, words, keys_a, vals_a);
+    robe::group_scatter_kernel<256, robe::GROUP_LOCAL><<<tiles, block, 0, stream>>>(g, p, nullptr, nullptr, keys, vals, words);
     return check_launch("sort (local)");
 }
 
@@ -799,8 +801,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     if (pl.key_bits > pl.key_top) pl.key_bits = pl.key_top;
 
     const size_t n = (size_t)n_indices;
-    const size_t grouping = n <= kGroupMost && !opt.key_bits ? group_sort_temp_bytes(n) : 0;      // (where the plan says window_sort below)
-    const size_t temp = grouping > radix_sort_temp_bytes(n) ? grouping : radix_sort_temp_bytes(n);
+    const size_t temp = radix_sort_temp_bytes(n);
     pl.dedup = true;
     size_t off = 0;
     pl.off_keys_in = off;  off = align_up(off + (n + 8) * 4, 256);
@@ -1065,12 +1066,17 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         }
     }
     // sign off: the sorted value is the token's row of grad_out and positions are never needed again
-    // (single-hot: row and position are the same, and the grouping sort hashes the ids itself)
-    const bool keys_from_ids = pl.window_sort && !bags;
-    if (keys_from_ids) {
-    } else if (bags && sign) robe::token_keys_kernel<true, false><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables, clear);
-    else if (bags) robe::token_keys_kernel<true, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables, clear);
-    else robe::token_keys_kernel<false, true><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, tok_bag, tab, n_tab, tables, clear);
+    // (single-hot: row and position are the same, and the grouping sort hashes the ids itself; many tokens in bags:
+    // it needs their rows)
+    const bool grouping = pl.window_sort, wide = group_wide(n, bags), hashed = grouping && (wide || !bags);
+    uint32_t *bag_rows = !bags ? nullptr : (sign ? tok_bag : vals_in);
+#define ROBE_KEYS(B_, R_, K_, BAG_) robe::token_keys_kernel<B_, R_, K_><<<kgrid, kblock, 0, stream>>>(p_keys, F, g_shift, indices, offsets, urows, n, keys_in, vals_in, BAG_, tab, n_tab, tables, clear)
+    if (hashed && bags) ROBE_KEYS(true, false, false, bag_rows);
+    else if (hashed) {
+    } else if (bags && sign) ROBE_KEYS(true, false, true, tok_bag);
+    else if (bags) ROBE_KEYS(true, true, true, tok_bag);
+    else ROBE_KEYS(false, true, true, tok_bag);
+#undef ROBE_KEYS
     if (int rc = check_launch("backward (keys)")) return rc;
 
     // S2: sort (key, value) pairs by the top key_bits bits of the key
@@ -1083,10 +1089,9 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         // significant bits, which put far-apart pieces next to each other.  (The region route needs
         // the order of the whole key for its directory.)
         const uint32_t lo = (!pl.regions && pl.key_top < 31) ? 0u : pl.key_top - pl.key_bits;
-        if (pl.window_sort) {
-            if (int rc = launch_group_sort(p_keys, keys_from_ids ? indices : nullptr, F, keys_in, vals_in, reinterpret_cast<uint2 *>(keys_out),
-                                           n, lo, pl.key_bits, ws + pl.off_temp, stream, tab, n_tab, tables,
-                                           keys_from_ids ? clear : robe::Clear{nullptr, 0, 0}))
+        if (grouping) {
+            if (int rc = launch_group_sort(p_keys, hashed ? indices : nullptr, bag_rows, !sign, wide, F, keys_in, vals_in, reinterpret_cast<uint2 *>(keys_out),
+                                           n, lo, pl.key_bits, ws + pl.off_temp, stream, tab, n_tab, tables, bags ? robe::Clear{nullptr, 0, 0} : clear))
                 return rc;
         } else if (int rc = launch_radix_sort(keys_in, vals_in, keys_out, vals_out, n, lo, lo + pl.key_bits, ws + pl.off_temp,
                                               stream, &in_b)) {
@@ -1673,14 +1678,6 @@ int robe_backward_noalloc(const robe_hash_t *hash, const float *grad_out, const 
         if (options != nullptr) routed = *options;
         else memset(&routed, 0, sizeof(routed));
         routed.backward_route = direct_takes(n_indices, hash->d) ? ROBE_ROUTE_DIRECT : ROBE_ROUTE_COMBINE;
-        if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &routed, &need)) return rc;
-        options = &routed;
-    }
-    if (need > (size_t)ROBE_STATIC_SCRATCH_BYTES && (options == nullptr || options->key_bits == 0)) {
-        // (the plain sort's counts take three quarters of a byte less per token than the grouping sort's)
-        if (options != nullptr) routed = *options;
-        else memset(&routed, 0, sizeof(routed));
-        routed.key_bits = 24;
         if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, &routed, &need)) return rc;
         options = &routed;
     }

@@ -68,7 +68,8 @@ __global__ __launch_bounds__(64) void table_map_kernel(TableArgs a, uint32_t fir
     if (threadIdx.x < count) tables[first + threadIdx.x] = make_uint2(a.col[threadIdx.x], a.dim[threadIdx.x]);
 }
 
-template <bool BAGS, bool ROWVAL>
+// KEYS false: bags only, every token's bag and nothing else (the grouping sort of robe_radix_sort.h hashes the ids itself).
+template <bool BAGS, bool ROWVAL, bool KEYS>
 __global__ __launch_bounds__(256) void token_keys_kernel(Params p, uint32_t F, uint32_t g_shift,
                                                          const int64_t *__restrict__ indices,
                                                          const int64_t *__restrict__ offsets,
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256) void token_keys_kernel(Params p, uint32_t F, u
                 t0[j] = t0[j] < 0 ? 0 : (t0[j] > (int64_t)n_indices ? (int64_t)n_indices : t0[j]);
                 t1[j] = t1[j] < t0[j] ? t0[j] : (t1[j] > (int64_t)n_indices ? (int64_t)n_indices : t1[j]);
                 if (bag0 + j >= rows) t1[j] = t0[j];           // past the last bag: nothing to do
-                x[j] = t0[j] + lane < t1[j] ? indices[t0[j] + lane] : 0;
+                x[j] = KEYS && t0[j] + lane < t1[j] ? indices[t0[j] + lane] : 0;
             }
 #pragma unroll
             for (int j = 0; j < kKeyBags; ++j) {
@@ -115,13 +116,17 @@ __global__ __launch_bounds__(256) void token_keys_kernel(Params p, uint32_t F, u
                 const uint32_t e = bag % F;
                 int64_t t = t0[j] + lane;
                 if (t < t1[j]) {
-                    keys[t] = sort_key(p, x[j], e);
-                    vals[t] = ROWVAL ? bag : (uint32_t)t;
+                    if constexpr (KEYS) {
+                        keys[t] = sort_key(p, x[j], e);
+                        vals[t] = ROWVAL ? bag : (uint32_t)t;
+                    }
                     if constexpr (!ROWVAL) tok_bag[t] = bag;
                 }
                 for (t += G; t < t1[j]; t += G) {              // bags longer than the lane group
-                    keys[t] = sort_key(p, indices[t], e);
-                    vals[t] = ROWVAL ? bag : (uint32_t)t;
+                    if constexpr (KEYS) {
+                        keys[t] = sort_key(p, indices[t], e);
+                        vals[t] = ROWVAL ? bag : (uint32_t)t;
+                    }
                     if constexpr (!ROWVAL) tok_bag[t] = bag;
                 }
             }

@@ -298,8 +298,9 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
 // places, which holds a bucket or a few, is ordered by the next eight bits inside LDS, with no counts of other tiles:
 // a key's copies are split where a tile ends.  Runs, of 1704 K Zipf tokens (294 K distinct): 322 K after 16
 // sorted bits, 333 K here with 10 bits (375 K with 8); of 118 K tokens (23.0 K) 24.5 K, and 24.9 K with 8 bits.
-// The keys of single-hot lookups are hashed where they are needed: no kernel writes them first.
-//   count    as above, the counts tile by tile; IDS: keys from the ids
+// The keys of single-hot lookups, and of bags of many tokens, are hashed where they are needed: no kernel writes them
+// first, and their array has room for counts of 10 bits.
+//   count    as above, the counts tile by tile
 //   offsets  one wavefront per 64 digits and sixteenth of the tiles (left out up to kFewTiles tiles)
 //   scatter  as above, writing (key, value) words
 //   local    a tile by the next bits
@@ -314,7 +315,8 @@ struct GroupPlan {
     uint32_t local_shift, local_mask;
     uint32_t *tile_count;        // [tiles][DIG]
     uint32_t *totals;            // [DIG]
-    uint32_t F, F_recip;         // IDS: tables
+    uint32_t F, F_recip;         // tables
+    uint32_t row_values;         // 1: the values are the tokens' rows, 0: their positions
 };
 
 constexpr int kGroupBlock = 512;
@@ -322,40 +324,50 @@ constexpr uint32_t kGroupMostTiles = 512;     // 2^21 pairs
 constexpr int kGroupOffsetsBlock = 1024;
 constexpr int kGroupOffsetsRows = (int)kGroupMostTiles / (kGroupOffsetsBlock / 64);
 
-template <int DIG, bool IDS>
+// Where a kernel has its pairs from: single-hot ids (the row is the position), ids and their rows, two arrays, or
+// (the local step) the words that the step before wrote.
+enum GroupSource { GROUP_LOOKUPS, GROUP_BAGS, GROUP_PAIRS, GROUP_LOCAL };
+
+// The keys of a thread's ROUNDS tokens base, base + step, .. and, unless they come from an array, their rows.
+template <GroupSource FROM, int ROUNDS>
+__device__ __forceinline__ void group_keys(const GroupPlan &s, const Params &p, const int64_t *__restrict__ indices,
+                                           const uint32_t *__restrict__ bag_rows, const uint32_t *__restrict__ keys, uint32_t base, uint32_t step,
+                                           uint32_t (&key)[ROUNDS], uint32_t (&row)[ROUNDS])
+{
+    if constexpr (FROM == GROUP_PAIRS) {
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) key[i] = base + (uint32_t)i * step < s.n ? keys[base + (uint32_t)i * step] : 0u;
+    } else {
+        int64_t x[ROUNDS];
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const uint32_t at = base + (uint32_t)i * step;
+            x[i] = at < s.n ? indices[at] : 0;
+            row[i] = FROM == GROUP_LOOKUPS ? at : (at < s.n ? bag_rows[at] : 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) key[i] = sort_key(p, x[i], mod_m(row[i], s.F, s.F_recip));
+    }
+}
+
+template <int DIG, GroupSource FROM>
 __global__ __launch_bounds__(kGroupBlock) void group_count_kernel(GroupPlan s, Params p, const int64_t *__restrict__ indices,
-                                                                  const uint32_t *__restrict__ keys,
+                                                                  const uint32_t *__restrict__ bag_rows, const uint32_t *keys,
                                                                   TableArgs tab, uint32_t n_tab, uint2 *__restrict__ tables,
                                                                   Clear clear)
 {
     constexpr int ROUNDS = (int)kSortTile / kGroupBlock;
     __shared__ uint32_t h[DIG];
-    if (IDS && blockIdx.x >= clear.work) {
+    if (FROM == GROUP_LOOKUPS && blockIdx.x >= clear.work) {
         fill_u32<kGroupBlock>(clear.dst, clear.n, 0u, blockIdx.x - clear.work);
         return;
     }
-    if (IDS && blockIdx.x == 0 && threadIdx.x < n_tab) tables[threadIdx.x] = make_uint2(tab.col[threadIdx.x], tab.dim[threadIdx.x]);
+    if (FROM == GROUP_LOOKUPS && blockIdx.x == 0 && threadIdx.x < n_tab) tables[threadIdx.x] = make_uint2(tab.col[threadIdx.x], tab.dim[threadIdx.x]);
     for (uint32_t d = threadIdx.x; d < (uint32_t)DIG; d += kGroupBlock) h[d] = 0;
     __syncthreads();
     const uint32_t base = blockIdx.x * kSortTile;              // (at most 2^21)
-    uint32_t k[ROUNDS];
-    if constexpr (IDS) {
-        int64_t x[ROUNDS];
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            const uint32_t at = base + (uint32_t)i * kGroupBlock + threadIdx.x;
-            x[i] = at < s.n ? indices[at] : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i)
-            k[i] = sort_key(p, x[i], mod_m(base + (uint32_t)i * kGroupBlock + threadIdx.x, s.F, s.F_recip));
-    } else {
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            const uint32_t at = base + (uint32_t)i * kGroupBlock + threadIdx.x;
-            k[i] = at < s.n ? keys[at] : 0u;
-        }
-    }
+    uint32_t k[ROUNDS], row[ROUNDS];
+    group_keys<FROM, ROUNDS>(s, p, indices, bag_rows, keys, base + threadIdx.x, kGroupBlock, k, row);
 #pragma unroll
     for (int i = 0; i < ROUNDS; ++i)
         if (base + (uint32_t)i * kGroupBlock + threadIdx.x < s.n) atomicAdd(&h[(k[i] >> s.shift) & (DIG - 1u)], 1u);
@@ -390,21 +402,19 @@ __global__ __launch_bounds__(kGroupOffsetsBlock) void group_offsets_kernel(Group
     }
 }
 
-// LOCAL: the tile stays where it is, by the bits below; pairs come as words and leave in two arrays.
-// Otherwise pairs come from two arrays, or (IDS) the key is hashed and the value is the position, and leave
-// as words.
-template <int DIG, bool IDS, bool LOCAL>
+// The local step: the tile stays where it is, by the bits below; pairs come as words and leave in two arrays.
+// Otherwise they leave as words.
+template <int DIG, GroupSource FROM>
 __global__ __launch_bounds__(kGroupBlock) void group_scatter_kernel(GroupPlan s, Params p, const int64_t *__restrict__ indices,
-                                                                    const uint32_t *__restrict__ keys_in,
-                                                                    const uint32_t *__restrict__ vals_in,
-                                                                    uint2 *__restrict__ words,
-                                                                    uint32_t *__restrict__ keys_out,
-                                                                    uint32_t *__restrict__ vals_out)
+                                                                    const uint32_t *__restrict__ bag_rows,
+                                                                    uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
+                                                                    uint2 *__restrict__ words)
 {
+    constexpr bool LOCAL = FROM == GROUP_LOCAL;
     constexpr int BLOCK = kGroupBlock, ROUNDS = (int)kSortTile / BLOCK, WAVES = BLOCK / 64;
     constexpr int BITS = DIG == 256 ? 8 : 10;
     static_assert(DIG == 256 || DIG == 1024, "digits of 8 or 10 bits");
-    static_assert(!(LOCAL && (IDS || DIG != 256)), "the local step has one form");
+    static_assert(!LOCAL || DIG == 256, "the local step has one form");
     constexpr uint32_t PER = (DIG + BLOCK - 1) / BLOCK;         // digits per thread (threads past DIG have none)
     __shared__ uint32_t wave_count[WAVES][DIG];
     __shared__ uint32_t digit_slot[LOCAL ? 1 : DIG];
@@ -417,29 +427,21 @@ __global__ __launch_bounds__(kGroupBlock) void group_scatter_kernel(GroupPlan s,
     const uint32_t shift = LOCAL ? s.local_shift : s.shift, mask = LOCAL ? s.local_mask : DIG - 1u;
 
     uint32_t key[ROUNDS], val[ROUNDS], rank[ROUNDS];
-    if constexpr (IDS) {
-        int64_t x[ROUNDS];
+    if constexpr (LOCAL) {
 #pragma unroll
         for (int i = 0; i < ROUNDS; ++i) {
             const uint32_t at = base + (uint32_t)i * 64u + lane;
-            x[i] = at < s.n ? indices[at] : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            val[i] = base + (uint32_t)i * 64u + lane;
-            key[i] = sort_key(p, x[i], mod_m(val[i], s.F, s.F_recip));
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            const uint32_t at = base + (uint32_t)i * 64u + lane;
-            uint2 w = make_uint2(0u, 0u);
-            if (at < s.n) {
-                if constexpr (LOCAL) w = words[at];
-                else w = make_uint2(keys_in[at], vals_in[at]);
-            }
+            const uint2 w = at < s.n ? words[at] : make_uint2(0u, 0u);
             key[i] = w.x;
             val[i] = w.y;
+        }
+    } else {
+        group_keys<FROM, ROUNDS>(s, p, indices, bag_rows, keys, base + lane, 64u, key, val);
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const uint32_t at = base + (uint32_t)i * 64u + lane;
+            if constexpr (FROM == GROUP_PAIRS) val[i] = at < s.n ? vals[at] : 0u;
+            else if (FROM == GROUP_BAGS && !s.row_values) val[i] = at;
         }
     }
     for (uint32_t d = t; d < (uint32_t)(WAVES * DIG); d += BLOCK) (&wave_count[0][0])[d] = 0;
@@ -533,8 +535,8 @@ __global__ __launch_bounds__(kGroupBlock) void group_scatter_kernel(GroupPlan s,
         if (j < in_tile) {
             const uint2 kv = staged[j];
             if constexpr (LOCAL) {
-                keys_out[tile_base + j] = kv.x;
-                vals_out[tile_base + j] = kv.y;
+                keys[tile_base + j] = kv.x;
+                vals[tile_base + j] = kv.y;
             } else {
                 words[digit_slot[(kv.x >> shift) & mask] + j] = kv;      // wraps like the subtraction above: the sum is the slot
             }

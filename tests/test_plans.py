@@ -113,3 +113,14 @@ def test_the_fused_step_takes_regions_by_rows_and_requests():
     for m, d, Z, n in ((20_000_000, 128, 32, 400_000), (25_000_000, 128, 32, 50_000), (25_000_000, 16, 4, 400_000), (25_000_000, 32, 4, 400_000),
                        (33_000_000, 128, 128, 400_000), (25_000_000, 128, 32, 2**20 + 1), (34_000_000, 16, 16, 150_000), (34_000_000, 64, 64, 100_000)):
         assert not regions(m, d, Z, n), (m, d, Z, n)
+
+
+def test_the_shorter_sort_takes_the_plain_sorts_workspace():
+    """Tokens are sorted on 16 bits up to 2^21 of them: a caller whose buffer holds the 24-bit sort has room enough."""
+    for m, d, Z in ((25_000_000, 128, 32), (1_000_003, 16, 4), (25_000_000, 100, 10), (25_000_000, 128, 1), (2**26, 64, 16)):
+        for n in (1000, 2**18, 2**18 + 1, 300_000, 852_000, 2**21, 2**21 + 1):
+            for sign in (0, 1):
+                h = robe.robe_init_hash(1, m, d, Z, sign)
+                for asked in ({}, {"backward_route": robe.ROUTE_COMBINE}, {"backward_route": robe.ROUTE_COMBINE, "fused_route": robe.ROUTE_TWO_STEP}):
+                    for query in (robe.robe_workspace_bytes, robe.robe_fused_workspace_bytes):
+                        assert query(h, n, 1, n, robe.options(**asked)) == query(h, n, 1, n, robe.options(key_bits=24, **asked)), (m, d, Z, n, sign, asked)
