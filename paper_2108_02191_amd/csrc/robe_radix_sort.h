@@ -291,7 +291,7 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
 // ---------------------------------------------------------------------------------------------
 // Grouping: equal keys side by side, or nearly so, for up to 2^21 pairs.
 //
-// The kernels that sum runs of equal keys put the positions they look at in order of the whole key
+// The kernels that sum runs of equal keys put the positions they look at in order of 26 key bits
 // themselves (Geom::window_sort), so that all they need is that the copies of a key are close together.  Two
 // radix passes of 8 bits gave them that, six kernels of 5 to 10 us that a small input cannot fill.
 // Here one pass places the pairs by their top GroupPlan::bits key bits, and then every tile of kSortTile
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
 // regions at a time).  Every step is stable.
 // ---------------------------------------------------------------------------------------------
 struct GroupPlan {
-    uint32_t n, tiles, few;      // as in SortPass
+    uint32_t n, tiles, few;      // as in SortPass (few: with 256 digits only)
     uint32_t shift;              // first key bit of the digit; it has log2(DIG) bits, the topmost that matter
     uint32_t local_shift, local_mask;
     uint32_t *tile_count;        // [tiles][DIG]
@@ -449,26 +449,24 @@ __global__ __launch_bounds__(kGroupBlock) void group_scatter_kernel(GroupPlan s,
         uint32_t before_tiles[PER], digit_total[PER], all, sum = 0;
 #pragma unroll
         for (uint32_t q = 0; q < PER; ++q) before_tiles[q] = digit_total[q] = 0;
-        if (s.few) {
-            static_assert(BLOCK % 256 == 0, "two threads per digit of eight bits");
-            if constexpr (DIG == 256) {
-                uint32_t *half = reinterpret_cast<uint32_t *>(staged);         // (free until the tile is put in order)
-                const uint32_t digit = t & 255u;
+        if (DIG == 256 && s.few) {
+            static_assert(BLOCK == 512, "two threads per digit of eight bits");
+            uint32_t *half = reinterpret_cast<uint32_t *>(staged);             // (free until the tile is put in order)
+            const uint32_t digit = t & 255u;
 #pragma unroll 8
-                for (uint32_t k = t >> 8; k < s.tiles; k += 2u) {
-                    const uint32_t c = s.tile_count[(uint64_t)k * DIG + digit];
-                    before_tiles[0] += k < tile ? c : 0u;
-                    digit_total[0] += c;
-                }
-                if (t >= 256u) {
-                    half[digit] = before_tiles[0];
-                    half[256u + digit] = digit_total[0];
-                }
-                __syncthreads();
-                if (t < 256u) {
-                    before_tiles[0] += half[t];
-                    digit_total[0] += half[256u + t];
-                }
+            for (uint32_t k = t >> 8; k < s.tiles; k += 2u) {
+                const uint32_t c = s.tile_count[(uint64_t)k * DIG + digit];
+                before_tiles[0] += k < tile ? c : 0u;
+                digit_total[0] += c;
+            }
+            if (t >= 256u) {
+                half[digit] = before_tiles[0];
+                half[256u + digit] = digit_total[0];
+            }
+            __syncthreads();
+            if (t < 256u) {
+                before_tiles[0] += half[t];
+                digit_total[0] += half[256u + t];
             }
         } else if (t * PER < (uint32_t)DIG) {
 #pragma unroll
