@@ -825,7 +825,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     if (!want_regions) {
         // Atomics after the sort: up to 2^21 tokens the grouping sort (on the top 18 or 16 key bits, or the 16
         // that the caller's choice of bits below leaves).  Tokens that share those bits then sit
-        // interleaved, and the combine kernel sorts every wavefront's 64 positions by the whole key.
+        // interleaved, and the combine kernel sorts every wavefront's 64 positions by 26 key bits.
         if (!opt.key_bits && pl.key_bits >= 16 && n <= kGroupMost) {
             pl.key_bits = 16;
             pl.window_sort = true;
@@ -885,9 +885,10 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     const uint64_t rec_per_block = (NR > 1 && last_len < h->Z) ? 3 : 2;
     if (!pl.gather && rec_per_block * n * C >= 0xFFFFFFFFull) return pl;
     // Record kernels, up to 2^21 tokens: the grouping sort, as on the atomics route above, and the combine
-    // kernel orders the G positions that a lane group looks at by the whole key.  A frequent token's run is
+    // kernel orders the G positions that a lane group looks at by 26 key bits.  A frequent token's run is
     // then also cut where others of its group sit among its copies: 2^-16 of all tokens, and at the two ends of
-    // its bucket those of a tile that share the lower digit, sixteen; eight times that for the bound.
+    // its bucket those of a tile that share the lower digit, sixteen; eight times that for the bound.  (Those that
+    // agree in all 26 bits are among the former.)
     const uint32_t full_key_bits = pl.key_bits;
     if (tuned && !pl.gather && !opt.key_bits && pl.key_top >= 16 && pl.lay.G >= 16 && n <= kGroupMost) {
         pl.key_bits = 16;

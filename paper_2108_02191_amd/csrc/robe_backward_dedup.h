@@ -201,9 +201,9 @@ __global__ __launch_bounds__(kBlock) void combine_scatter_kernel(Params p, Geom 
             }
         }
         // A coarse sort (few key bits) leaves the tokens of one key bucket interleaved.  A lane group's
-        // run never outlives its walk anyway, so putting the wavefront's 64 positions in key order
-        // here (the key is made unique by the lane it came from, which also says where to fetch the rest of
-        // the token) finds the same runs a full sort would.
+        // run never outlives its walk anyway, so putting the wavefront's 64 positions in order of 26 key bits
+        // here (made unique by the lane it came from, which also says where to fetch the rest of the token)
+        // finds the runs a full sort would, but for tokens that agree in those bits: they may cut each other's.
         if (q.window_sort) {
             const uint32_t sk = sort_lanes(window_key(my_ok, my_th, lane), 64u);
             const int from = (int)(sk & 63u);

@@ -175,8 +175,8 @@ __global__ __launch_bounds__(kBlock) void combine_rows_kernel(Params p, Geom q, 
             }
         }
         // After a sort on few key bits the tokens of a key bucket sit interleaved: the group puts its G
-        // positions in order of the key (made unique by the lane it came from) and so finds the runs that a full sort would, cut at every G positions
-        // at the most.
+        // positions in order of 26 key bits (made unique by the lane it came from) and so finds the runs that a
+        // full sort would, cut at every G positions and, rarely, by tokens that agree in those bits.
         if constexpr (WINDOW) {
             const uint32_t sk = sort_lanes(window_key(t.ok, t.th, grp), G);
             const int from = (int)(base_lane + (sk & 63u));

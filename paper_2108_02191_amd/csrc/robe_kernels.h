@@ -59,7 +59,8 @@ struct Geom {
     const uint2 *tables;
     // Sorted backward: 1 when the sort looked at few key bits, so that tokens whose keys agree in those
     // bits sit interleaved; the combine kernels then sort the positions they look at together (with
-    // float atomics a wavefront's 64, without a lane group's G) by the whole key before they look for runs.
+    // float atomics a wavefront's 64, without a lane group's G) by 26 bits of the key (window_key) before they
+    // look for runs.
     uint32_t window_sort;
 };
 
