@@ -1,6 +1,7 @@
 """The fused step in two steps clears its gradient array beside the first kernel of the sort: parity with the oracle,
 exact on small integers, from a workspace full of NaN, for keys hashed in the sort and keys written before it, both
-sorts, arrays that are no whole number of vectors or shorter than a workgroup's share, mixed dimensions."""
+sorts, arrays that are no whole number of vectors or shorter than a workgroup's share, mixed dimensions, and small
+blocks sorted by value whose pairs do not all fit."""
 import numpy as np
 import pytest
 import torch
@@ -48,3 +49,23 @@ def test_two_steps_of_mixed_dimensions_clear_their_gradient():
     need = robe.robe_fused_mixed_workspace_bytes(h, list(dims), B, ids.size, opt)
     robe.robe_backward_adagrad_mixed(h, list(dims), P.to_dev(G), P.to_dev(ids), None, B, array, state, 0.01, 1e-8, workspace=_nan(need), options=opt)
     assert np.array_equal(state.cpu().numpy(), np.float32(ref) * np.float32(ref))       # (integers below 2^12: squares are exact)
+
+
+@pytest.mark.parametrize("n,d,bags", [(270_000, 128, False), (270_000, 128, True), (2**21 + 4, 32, False)])
+def test_pairs_without_room_clear_their_gradient(n, d, bags):
+    """More than 2^25 elements of blocks of one float on a small array: what finds no room among the pairs is added with
+    atomics, so the step goes through a gradient array."""
+    m, F = 600_011, 2
+    h, H = P.both_hashes(n, m, d, 1, 0)
+    rng = np.random.default_rng(n)
+    B = n // F
+    ids = rng.integers(0, 10**9, size=n).astype(np.int64)
+    off = np.concatenate([[0], np.sort(rng.integers(0, n + 1, size=n - 1)), [n]]).astype(np.int64) if bags else None
+    use = ids if bags else ids.reshape(B, F)
+    G = rng.integers(-2, 3, size=(B, F, d)).astype(np.float32)
+    need = robe.robe_fused_workspace_bytes(h, B, F, n)
+    assert need > robe.robe_fused_workspace_bytes(h, B, F, n, robe.options(backward_route=robe.ROUTE_COMBINE))      # the pairs' route
+    ref, _ = oracle.backward(H, G, use, off, B, F, threads=8)
+    array = torch.zeros(m, device="cuda:0")
+    robe.robe_backward_sgd(h, P.to_dev(G), P.to_dev(use), P.to_dev(off) if bags else None, B, F, array, 1.0, workspace=_nan(need))
+    assert np.array_equal(array.cpu().numpy().astype(np.float64), -ref)
