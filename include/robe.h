@@ -198,10 +198,12 @@ int robe_offsets(const robe_hash_t *hash, const int64_t *indices, int64_t n, int
  *                    float32 in token order.  Bag bounds are clamped to
  *                    [0, n_indices] on the device, so a malformed CSR cannot
  *                    read outside `indices`.
- *   out        device float[batch][n_features][d], fully overwritten (large lookups of blocks of up to
- *              four floats, some 25 million 128-byte lines or more, keep their lists in it until the
- *              rows are written: repeated tokens' rows are then copied, which costs up to a tenth
- *              where ids hardly repeat; a row_order other than ROBE_ROWS_AUTO gathers every row)
+ *   out        device float[batch][n_features][d], fully overwritten.  Large single-hot lookups of blocks
+ *              of up to four floats (some 25 million 128-byte lines or more) keep their lists in it
+ *              until the rows are written, with 64-bit atomics, and copy the rows of repeated tokens
+ *              out of it: memory that is slow to read back, or takes no such atomics, wants a
+ *              row_order other than ROBE_ROWS_AUTO, which gathers every row.  So do ids that hardly
+ *              repeat, which pay up to a tenth for the lists
  *   options    NULL or host robe_options_t (fwd_elems, fwd_strided, tile_lookups, row_order are read)
  * Errors: ROBE_EINVAL, ROBE_EHIP.  batch == 0 is a no-op.
  */
