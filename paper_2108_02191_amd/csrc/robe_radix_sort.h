@@ -170,8 +170,11 @@ __device__ __forceinline__ uint32_t rank_in_tile(uint32_t digit, bool have, uint
 }
 
 // Which tile a scattering workgroup takes: every XCD an eighth of the tiles, in order, so that what neighbouring
-// tiles write of a digit meets in one L2 instead of leaving eight of them in halves of a line.  8.5 M pairs:
-// 44 us a pass -> 35.  Launched with tile_blocks() workgroups; those past the last tile end at once.
+// tiles write of a digit meets in one L2 instead of leaving eight of them in halves of a line.  Launched with
+// tile_blocks() workgroups; those past the last tile end at once.  The radix sort gains by it from some
+// 3 M pairs on and loses below (why was not looked into).  24 bits, us, in turn / by eighths: 852 K pairs 57.2 / 58.4, 1.7 M 66.5 / 72.5, 2.5 M 77.4 / 79.4, 3.5 M 101.0 / 94.6, 8.5 M 188 / 160.  (The grouping
+// below writes words: 852 K tokens with their atomics 71.3 / 70.2.)
+constexpr uint32_t kSpreadTiles = 700;
 __host__ __device__ inline uint32_t tile_blocks(uint32_t tiles) { return (tiles + 7u) / 8u * 8u; }
 __device__ __forceinline__ uint32_t tile_of_block(uint32_t tiles)
 {
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
     __shared__ uint2 staged[kSortTile];               // the tile in digit order
     __shared__ uint32_t wave_total[WAVES];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    const uint32_t tile = tile_of_block(s.tiles);
+    const uint32_t tile = s.tiles < kSpreadTiles ? blockIdx.x : tile_of_block(s.tiles);
     if (tile >= s.tiles) return;
     const uint64_t base = (uint64_t)tile * kSortTile + (uint64_t)wave * (ROUNDS * 64u);
     for (uint32_t d = t; d < (uint32_t)WAVES * kDigits; d += BLOCK) (&wave_count[0][0])[d] = 0;

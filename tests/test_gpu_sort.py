@@ -59,6 +59,11 @@ def test_key_distributions(kind):
         check(keys, lo, hi)
 
 
+@pytest.mark.parametrize("n", [699 * 4096, 699 * 4096 + 1, 700 * 4096 + 1])
+def test_sorts_around_the_change_of_the_tiles_order(n):
+    check(np.random.default_rng(n).integers(0, 2**31, size=n, dtype=np.uint64).astype(np.uint32), 7, 31)
+
+
 def test_large_sort_and_bad_arguments():
     n = 9_000_001
     keys = np.random.default_rng(1).integers(0, 2**31, size=n, dtype=np.uint64).astype(np.uint32)
