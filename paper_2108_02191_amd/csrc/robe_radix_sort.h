@@ -172,8 +172,9 @@ __device__ __forceinline__ uint32_t rank_in_tile(uint32_t digit, bool have, uint
 // Which tile a scattering workgroup takes: every XCD an eighth of the tiles, in order, so that what neighbouring
 // tiles write of a digit meets in one L2 instead of leaving eight of them in halves of a line.  Launched with
 // tile_blocks() workgroups; those past the last tile end at once.  The radix sort gains by it from some
-// 3 M pairs on and loses below (why was not looked into).  24 bits, us, in turn / by eighths: 852 K pairs 57.2 / 58.4, 1.7 M 66.5 / 72.5, 2.5 M 77.4 / 79.4, 3.5 M 101.0 / 94.6, 8.5 M 188 / 160.  (The grouping
-// below writes words: 852 K tokens with their atomics 71.3 / 70.2.)
+// 3 M pairs on and loses below (why was not looked into).  24 bits, us, in turn / by eighths: 852 K pairs
+// 57.2 / 58.4, 1.7 M 66.5 / 72.5, 2.5 M 77.4 / 79.4, 3.5 M 101.0 / 94.6, 8.5 M 188 / 160.  (The grouping below, 852 K
+// tokens with their atomics: 71.3 / 70.2.)
 constexpr uint32_t kSpreadTiles = 700;
 __host__ __device__ inline uint32_t tile_blocks(uint32_t tiles) { return (tiles + 7u) / 8u * 8u; }
 __device__ __forceinline__ uint32_t tile_of_block(uint32_t tiles)
@@ -300,7 +301,8 @@ __global__ __launch_bounds__(BLOCK) void sort_scatter_kernel(SortPass s, const u
 // Here one pass places the pairs by their top GroupPlan::bits key bits, and then every tile of kSortTile
 // places, which holds a bucket or a few, is ordered by the next eight bits inside LDS, with no counts of other tiles:
 // a key's copies are split where a tile ends.  Runs, of 1704 K Zipf tokens (294 K distinct): 322 K after 16
-// sorted bits, 333 K here with 10 bits (375 K with 8); of 118 K tokens (23.0 K) 24.5 K, and 24.9 K with 8 bits.
+// sorted bits, 333 K here with 10 bits (375 K with 8); of 118 K tokens (23.0 K) 24.5 K, and 24.9 K with 8 bits.  (What more runs
+// and their order cost the atomics: see combine_scatter_kernel.)
 // The keys of single-hot lookups, and of bags of many tokens, are hashed where they are needed: no kernel writes them
 // first, and their array has room for counts of 10 bits.
 //   count    as above, the counts tile by tile
