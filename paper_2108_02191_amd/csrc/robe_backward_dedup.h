@@ -142,8 +142,8 @@ __global__ __launch_bounds__(256) void token_keys_kernel(Params p, uint32_t F, u
 // four words through LDS for every position and works under a mask.  On the order that the grouping sort leaves, 1.7 M
 // lookups, d = 128: 259 -> 244 us; 117 K tokens in bags, d = 100: 33 -> 31.  Sixteen rows ahead instead of eight: 258.
 // That order costs about what this form gains: 1.7 M lookups with it 242, the groups' form on 16 sorted bits 245,
-// this one on 24 sorted bits 236; 852 K of mixed dimensions 122, 120, 115.  Keys and sort take 38, 53 and 75 us
-// before the first three.
+// this one on 24 sorted bits 236; 852 K of mixed dimensions 122, 120, 115.  What is gained is the sort's, 61 -> 41 us
+// with the keys (1.7 M lookups).
 template <int V, bool SIGN, bool BAGS, bool MIXED, bool WAVE>
 __global__ __launch_bounds__(kBlock) void combine_scatter_kernel(Params p, Geom q,
                                                                  const float *__restrict__ grad_out,

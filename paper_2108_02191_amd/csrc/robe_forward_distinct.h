@@ -17,8 +17,8 @@
 // rep at its end until D4, whose rows no other lookup copies from.  Tokens are the same when the token part of h
 // is (and of g, with the sign on): then every offset and every sign is.
 //
-// 852 K Zipf lookups over 26 tables, d = 128, 100 MB array: Z = 1 1092 -> 574 us (gather 433, 2.5 GB of lines at
-// 5.6 TB/s; copy 98, find 23, the last samples 14, clearing the table 6), Z = 2 543 -> 373.
+// 852 K Zipf lookups over 26 tables, d = 128, 100 MB array: Z = 1 1092 -> 574 us (gather 433, 2.9 GB of lines read
+// and 0.1 GB written at 6.9 TB/s; copy 98, find 23, the last samples 14, clearing the table 6), Z = 2 543 -> 373.
 // Ids that never repeat pay D1 and the empty D3: Z = 1 1976 -> 2007, Z = 2 1060 -> 1086 (2054 and 1130 with every token
 // entered in memory, see distinct_least_repeats).  Tiles of 2048 lookups: of 4096
 // 208 K lookups take 212 us instead of 203, of 1024 852 K 576 instead of 570.
@@ -50,7 +50,7 @@ struct DistinctPlan {
 __host__ __device__ inline uint32_t distinct_least_repeats(uint64_t batch)
 {
     const uint64_t least = (uint64_t)kDistinctTile * kDistinctTile / 4u / batch;
-    return least < kDistinctTile / 4u ? (uint32_t)least : kDistinctTile / 4u;
+    return least < 1u ? 1u : (least < kDistinctTile / 4u ? (uint32_t)least : kDistinctTile / 4u);
 }
 
 // The row b * F + f of a position, and its table.
