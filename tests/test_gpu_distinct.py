@@ -38,7 +38,7 @@ def _first_batch(d, Z, F):
 
 @pytest.mark.parametrize("d,Z,F,kind,sign", [(512, 1, 3, "zipf", 0), (512, 4, 1, "zipf", 1), (128, 1, 26, "zipf", 1), (128, 2, 7, "congruent", 0),
                                              (100, 1, 5, "congruent", 1), (64, 1, 2, "zipf", 0), (192, 1, 40, "same", 0), (384, 2, 9, "distinct", 1),
-                                             (33, 1, 4, "zipf", 0), (128, 1, 4, "patches", 1), (384, 4, 3, "distinct", 0), (512, 2, 1, "patches", 0)])
+                                             (33, 1, 4, "zipf", 0), (512, 1, 100, "zipf", 1), (128, 1, 4, "patches", 1), (384, 4, 3, "distinct", 0), (512, 2, 1, "patches", 0)])
 def test_copied_rows_have_the_gathered_bits(d, Z, F, kind, sign):
     m = 777_777
     h, _ = P.both_hashes(d, m, d, Z, sign)
