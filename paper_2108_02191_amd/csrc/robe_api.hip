@@ -20,6 +20,7 @@
 #include "robe_forward_distinct.h"
 #include "robe_backward_dedup.h"
 #include "robe_backward_regions.h"
+#include "robe_forward_places.h"
 #include "robe_backward_elements.h"
 #include "robe_radix_sort.h"
 
@@ -103,6 +104,7 @@ robe::Params to_params(const robe_hash_t *h)
 }
 
 bool is_pow2(uint32_t v) { return v && !(v & (v - 1)); }
+uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; return s; }
 uint32_t log2u(uint32_t v) { uint32_t s = 0; while ((1u << s) < v) ++s; return s; }
 bool aligned(const void *ptr, size_t a) { return ((uintptr_t)ptr % a) == 0; }
 
@@ -438,17 +440,87 @@ int launch_rows(const robe_hash_t *h, const Opt &opt, const AT *src, const int64
 }
 
 
+template <typename K>
+int allow_lds(K kernel, size_t bytes, const char *what)
+{
+    if (bytes <= 64 * 1024) return ROBE_OK;
+    hipError_t st = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (st != hipSuccess) return fail(ROBE_EHIP, "%s: cannot reserve %zu bytes of LDS: %s", what, bytes, hipGetErrorString(st));
+    return ROBE_OK;
+}
+
+// Whether the distinct tokens of such a lookup are served region by region of the array (robe_forward_places.h): where
+// its lines are many and one L2 does not hold much of it, and the array is not so large that reading it all costs what its lines
+// do.  Forward, us, gathered / by place, Zipf ids of 10 M a table and (ids that never repeat), d = 128, Z = 1:
+//   9 M slots, 208 K lookups 304 / 228 (460 / 475);  25 M, 198 K 316 / 249 (486 / 501), 852 K 1074 / 600 (2007 / 2047)
+//   60 M, 312 K 473 / 400 (773 / 796);  120 M, 852 K 1133 / 824 (2089 / 2143);  250 M, 1040 K 1435 / 1213 (2764 / 2823)
+//   Z = 2, 25 M, 468 K 384 / 301 (610 / 637);  d = 64, 9 M, 520 K 345 / 243 (578 / 608);  d = 512, 25 M, 78 K 532 / 497 (744 / 762)
+bool places_pay(const robe_hash_t *h, int64_t rows, const float *out)
+{
+    if (h->Z > 2 || h->d % 64 != 0 || h->d > robe::kPlaceMostD || !aligned(out, 16) || rows * (int64_t)h->d >= (1ll << 30)) return false;
+    return h->m >= (1u << 23) && h->m < (1u << 29) && (uint64_t)rows * (h->d / h->Z) >= h->m / 3;
+}
+
+// Sizes of its lists for `rows` lookups, in words: what lies in the last samples' rows beside rep, what behind the table.
+void plan_places(const robe_hash_t *h, int64_t rows, robe::PlacePlan *s, uint64_t *list_words, uint64_t *count_words)
+{
+    while (((h->m + (1ull << s->bucket_shift) - 1) >> s->bucket_shift) > robe::kMaxRegions) ++s->bucket_shift;
+    s->buckets = (uint32_t)((h->m + (1ull << s->bucket_shift) - 1) >> s->bucket_shift);
+    s->r_bits = ceil_log2(h->m);
+    s->r_mask = (1u << s->r_bits) - 1u;
+    s->most = (uint32_t)(rows / 2) & ~63u;
+    // fewer are gathered: a million lines take 19 us so, 4 by place, which costs some 35 before the first one at 25 M slots
+    s->least = (uint32_t)(h->m / 8 / (h->d / h->Z)) + 1;
+    // a list for at least sixteen workgroups of D1, whose additions to a list's counter go one by one
+    s->segments = 1;
+    while (s->segments < robe::kPlaceMostSegments && (uint64_t)rows >= 32ull * s->segments * robe::kDistinctTile) s->segments <<= 1;
+    s->segment_shift = log2u(s->segments);
+    s->segment_rows = (s->most / 64 + s->segments - 1) / s->segments * 64;
+    s->page_elems = h->d / 64;
+    s->page_recip = (65536 + s->page_elems - 1) / s->page_elems;
+    s->out_bytes = (uint32_t)(rows * (int64_t)h->d * 4);
+    *list_words = (((uint64_t)s->buckets + 4) & ~3ull) + 4 + 2ull * s->most + (uint64_t)s->segments * s->segment_rows + 2 * robe::kPlacePad;
+    *count_words = (((uint64_t)s->buckets + 3) & ~3ull) + s->segments;
+}
+
+void lay_out_places(uint32_t *counts, uint32_t *lists, robe::PlacePlan *s)
+{
+    s->counts = counts;
+    s->free_count = counts + (((uint64_t)s->buckets + 3) & ~3ull);
+    s->starts = lists;
+    s->used = lists + (((uint64_t)s->buckets + 4) & ~3ull);
+    s->entries = s->used + 4;
+    s->row = s->entries + s->most + robe::kPlacePad;
+    s->pages = s->row + s->most;
+}
+
 template <typename AT>
 int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, const robe::Geom &q, const AT *array, const int64_t *indices,
                     int64_t rows, uint32_t F, float *out, hipStream_t stream, bool *taken)
 {
-    // the last samples, whose rows hold rep: at least rows / d of them
-    const int64_t batch = rows / (int64_t)F, last = (rows + h->d - 1) / h->d, keep = batch - (last + F - 1) / F;
+    robe::PlacePlan lists;
+    memset(&lists, 0, sizeof(lists));
+    uint64_t list_words = 0, count_words = 0;        // beside rep, in the last samples' rows; behind the table
+    bool by_place = places_pay(h, rows, out);
+    if (by_place) plan_places(h, rows, &lists, &list_words, &count_words);
+    // the last samples, whose rows hold rep and the lists
+    const int64_t batch = rows / (int64_t)F;
     uint64_t places = 1;
     while (places < 2ull * (uint64_t)rows) places <<= 1;
     // table at the front, aligned for its words; rep behind it
     const uint64_t skip = aligned(out, 8) ? 0 : 1;
-    if (keep < 1 || (skip + 2 * places) > (uint64_t)keep * F * h->d) return ROBE_OK;
+    int64_t keep = 0;
+    auto fits = [&] {
+        const int64_t last = ((int64_t)list_words + rows + h->d - 1) / h->d;
+        keep = batch - (last + F - 1) / F;
+        return keep >= 1 && skip + 2 * places + count_words <= (uint64_t)keep * F * h->d;
+    };
+    if (by_place && !fits()) {
+        by_place = false;
+        list_words = count_words = 0;
+    }
+    if (!by_place && !fits()) return ROBE_OK;
     *taken = true;
     const robe::Params p = to_params(h);
     robe::DistinctPlan s;
@@ -458,20 +530,34 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
     s.n = (uint32_t)(keep * F);
     s.table = reinterpret_cast<uint64_t *>(out + skip);
     s.mask = (uint32_t)(places - 1);
-    s.rep = reinterpret_cast<uint32_t *>(out + (uint64_t)s.n * h->d);
+    uint32_t *lists_at = reinterpret_cast<uint32_t *>(out + (uint64_t)s.n * h->d);
+    s.rep = lists_at + list_words;
     s.least_repeats = robe::distinct_least_repeats((uint64_t)batch);
+    if (by_place) lay_out_places(reinterpret_cast<uint32_t *>(s.table) + 2 * places, lists_at, &lists);
     const bool sign = h->use_sign != 0;
-    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(s.table), 2 * places, 0u, stream, "forward (clear table)")) return rc;
+    if (int rc = launch_fill(reinterpret_cast<uint32_t *>(s.table), 2 * places + count_words, 0u, stream, "forward (clear table)")) return rc;
     const dim3 tiles((s.n + robe::kDistinctTile - 1) / robe::kDistinctTile), find(robe::kDistinctBlock);
-    if (sign) robe::distinct_find_kernel<true><<<tiles, find, 0, stream>>>(p, s, indices);
-    else robe::distinct_find_kernel<false><<<tiles, find, 0, stream>>>(p, s, indices);
+    if (by_place && sign) robe::distinct_find_kernel<true, true><<<tiles, find, 0, stream>>>(p, s, lists, indices);
+    else if (by_place) robe::distinct_find_kernel<false, true><<<tiles, find, 0, stream>>>(p, s, lists, indices);
+    else if (sign) robe::distinct_find_kernel<true, false><<<tiles, find, 0, stream>>>(p, s, lists, indices);
+    else robe::distinct_find_kernel<false, false><<<tiles, find, 0, stream>>>(p, s, lists, indices);
     if (int rc = check_launch("forward (find)")) return rc;
     const uint32_t waves = (s.n + robe::kDistinctRows - 1) / robe::kDistinctRows;
     const dim3 grid(waves), block(robe::kRowBlock);
+    if (by_place) {
+        robe::place_scan_kernel<<<dim3(1), dim3(robe::kScanThreads), 0, stream>>>(lists);
+        if (int rc = check_launch("forward (scan)")) return rc;
+    }
+    const dim3 pgrid((s.n + robe::kRowBlock - 1) / robe::kRowBlock);
+#define ROBE_DISTINCT_S(V_, C_, S_)                                                                                   \
+    do {                                                                                                              \
+        if (by_place) robe::place_tokens_kernel<V_, C_, S_, AT><<<pgrid, block, 0, stream>>>(p, q, s, lists, array, indices, out); \
+        else robe::distinct_gather_kernel<V_, C_, S_, AT><<<grid, block, 0, stream>>>(p, q, s, array, indices, out);  \
+    } while (0)
 #define ROBE_DISTINCT(V_, C_)                                                                                         \
     do {                                                                                                              \
-        if (sign) robe::distinct_gather_kernel<V_, C_, true, AT><<<grid, block, 0, stream>>>(p, q, s, array, indices, out);   \
-        else robe::distinct_gather_kernel<V_, C_, false, AT><<<grid, block, 0, stream>>>(p, q, s, array, indices, out);       \
+        if (sign) ROBE_DISTINCT_S(V_, C_, true);                                                                      \
+        else ROBE_DISTINCT_S(V_, C_, false);                                                                          \
     } while (0)
     if (lay.consec) {
         switch (lay.V) {
@@ -490,7 +576,26 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
         }
     }
 #undef ROBE_DISTINCT
+#undef ROBE_DISTINCT_S
     if (int rc = check_launch("forward (distinct)")) return rc;
+    if (by_place) {
+        const size_t lds = robe::kPlaceLds;
+        const uint32_t regions = (uint32_t)((h->m + (1u << robe::kPlaceShift) - 1) >> robe::kPlaceShift);
+        const dim3 rgrid(regions), rblock(robe::kPlaceBlock);
+#define ROBE_PLACE_REGIONS(Z_)                                                                                        \
+    do {                                                                                                              \
+        if (int rc = allow_lds(robe::place_regions_kernel<Z_, AT>, lds, "forward (regions)")) return rc;              \
+        robe::place_regions_kernel<Z_, AT><<<rgrid, rblock, lds, stream>>>(p, lists, array, lists.entries, lists.pages, out); \
+    } while (0)
+        if (h->Z == 1) ROBE_PLACE_REGIONS(1);
+        else ROBE_PLACE_REGIONS(2);
+#undef ROBE_PLACE_REGIONS
+        if (int rc = check_launch("forward (regions)")) return rc;
+        const dim3 turns(lists.most / 64u), turn(256);
+        if (sign) robe::place_rows_kernel<true><<<turns, turn, 0, stream>>>(p, lists, F, reciprocal(F), indices, out);
+        else robe::place_rows_kernel<false><<<turns, turn, 0, stream>>>(p, lists, F, reciprocal(F), indices, out);
+        if (int rc = check_launch("forward (rows)")) return rc;
+    }
     const uint32_t per_xcd = (waves + robe::kXcds - 1) / robe::kXcds;
     const dim3 spread(per_xcd * robe::kXcds);
     if (h->d % 4 == 0 && aligned(out, 16)) {
@@ -758,8 +863,6 @@ bool workspace_holds(const void *workspace, size_t given, size_t need)
     return need == 0 || (workspace != nullptr && given >= need && aligned(workspace, 256));
 }
 
-uint32_t ceil_log2(uint64_t v) { uint32_t s = 0; while ((1ull << s) < v) ++s; return s; }
-
 // Decide between the direct scatter, the combine-duplicates one and the region-sorted one, and lay
 // out the workspace.  Host arithmetic only, so that the workspace queries and the calls agree.
 // need_regions: the caller (the fused step) wants the region-sorted scatter whatever the size.
@@ -1005,16 +1108,6 @@ BwdPlan plan_backward(const robe_hash_t *hash, const Opt &opt, int64_t rows, int
     const BwdPlan pl = plan_backward_with(true, hash, opt, rows, n_indices, bags, grad_out, need_regions, mixed_floats);
     if (!opt.reproducible || pl.regions) return pl;
     return plan_backward_with(false, hash, opt, rows, n_indices, bags, grad_out, need_regions, mixed_floats);
-}
-
-template <typename K>
-int allow_lds(K kernel, size_t bytes, const char *what)
-{
-    if (bytes <= 64 * 1024) return ROBE_OK;
-    hipError_t st = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (st != hipSuccess) return fail(ROBE_EHIP, "%s: cannot reserve %zu bytes of LDS: %s", what, bytes, hipGetErrorString(st));
-    return ROBE_OK;
 }
 
 // rule 0: grad_array += scatter.  Regions only: rule 1, Adagrad on (array = dst, state) with the scatter

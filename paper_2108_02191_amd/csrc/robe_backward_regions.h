@@ -498,27 +498,29 @@ __device__ __forceinline__ uint32_t add_to_class(uint32_t *counter, uint32_t cls
 constexpr uint32_t kScanPer = kMaxRegions / kScanThreads;
 static_assert(kScanPer % 4u == 0, "R3 reads whole vectors of four counts");
 
-__global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
+// Regions per thread: a multiple of four, the same for all.
+__device__ __forceinline__ uint32_t scan_per(uint32_t n) { return (((n + kScanThreads - 1u) / kScanThreads) + 3u) & ~3u; }
+
+// starts: exclusive prefix of n <= kMaxRegions counts, the total in starts[n], and returned.  c: this thread's counts,
+// those from thread * scan_per(n) on.  Both arrays are padded to whole vectors of four words.
+__device__ __forceinline__ uint32_t scan_counts(const uint32_t *__restrict__ counts, uint32_t *__restrict__ starts, uint32_t n,
+                                                uint32_t (&c)[kScanPer], uint32_t *wave_sum)
 {
-    __shared__ uint32_t wave_sum[kScanThreads / 64u];
-    __shared__ uint32_t cls_n[32], cls_at[32];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    // regions per thread: a multiple of four, the same for all
-    const uint32_t per = (((s.NR + kScanThreads - 1u) / kScanThreads) + 3u) & ~3u;
+    const uint32_t per = scan_per(n);
     const uint32_t first = t * per;
-    uint32_t c[kScanPer], sum = 0;
+    uint32_t sum = 0;
 #pragma unroll
     for (uint32_t k = 0; k < kScanPer; k += 4u) {
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (k < per && first + k < s.NR) v = *reinterpret_cast<const uint4 *>(s.counts + first + k);   // (the array is padded to whole vectors)
+        if (k < per && first + k < n) v = *reinterpret_cast<const uint4 *>(counts + first + k);   // (the array is padded to whole vectors)
         c[k] = v.x; c[k + 1u] = v.y; c[k + 2u] = v.z; c[k + 3u] = v.w;
     }
 #pragma unroll
     for (uint32_t k = 0; k < kScanPer; ++k) {
-        if (k >= per || first + k >= s.NR) c[k] = 0;
+        if (k >= per || first + k >= n) c[k] = 0;
         sum += c[k];
     }
-    if (t < 32u) cls_n[t] = 0;
     uint32_t incl = sum;
 #pragma unroll
     for (uint32_t off = 1; off < 64u; off <<= 1) {
@@ -538,16 +540,27 @@ __global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
     for (uint32_t k = 0; k < kScanPer; k += 4u) {
         const uint4 v = make_uint4(at, at + c[k], at + c[k] + c[k + 1u], at + c[k] + c[k + 1u] + c[k + 2u]);
         at = v.w + c[k + 3u];
-        if (k < per && first + k < s.NR) {
-            if (first + k + 4u <= s.NR) *reinterpret_cast<uint4 *>(s.starts + first + k) = v;
+        if (k < per && first + k < n) {
+            if (first + k + 4u <= n) *reinterpret_cast<uint4 *>(starts + first + k) = v;
             else {
-                s.starts[first + k] = v.x;
-                if (first + k + 1u < s.NR) s.starts[first + k + 1u] = v.y;
-                if (first + k + 2u < s.NR) s.starts[first + k + 2u] = v.z;
+                starts[first + k] = v.x;
+                if (first + k + 1u < n) starts[first + k + 1u] = v.y;
+                if (first + k + 2u < n) starts[first + k + 2u] = v.z;
             }
         }
     }
-    if (t == 0) s.starts[s.NR] = total;
+    if (t == 0) starts[n] = total;
+    return total;
+}
+
+__global__ __launch_bounds__(kScanThreads) void region_scan_kernel(RegionPlan s)
+{
+    __shared__ uint32_t wave_sum[kScanThreads / 64u];
+    __shared__ uint32_t cls_n[32], cls_at[32];
+    const uint32_t t = threadIdx.x, per = scan_per(s.NR), first = t * per;
+    if (t < 32u) cls_n[t] = 0;
+    uint32_t c[kScanPer];
+    scan_counts(s.counts, s.starts, s.NR, c, wave_sum);
 
     // Most regions hold a handful of records (small_cap): R5 takes only those that hold more, in any order.
     if (s.small_cap) {

@@ -53,6 +53,26 @@ __host__ __device__ inline uint32_t distinct_least_repeats(uint64_t batch)
     return least < 1u ? 1u : (least < kDistinctTile / 4u ? (uint32_t)least : kDistinctTile / 4u);
 }
 
+// The lists of robe_forward_places.h, which D1 begins.
+struct PlacePlan {
+    uint32_t buckets, bucket_shift;      // of r = th mod m; bucket_shift: log2 of the slots of one
+    uint32_t *counts, *starts;           // [buckets], [buckets + 1]: entries of a bucket, entries before it
+    uint32_t most;                       // entries there is room for, a multiple of 64
+    uint32_t least;                      // fewer entries are gathered
+    uint32_t *entries;                   // [most + kPlacePad] the entries by bucket, see place_entry
+    uint32_t r_bits, r_mask;             // bits of r; 2^r_bits - 1
+    uint32_t *row;                       // [most] their rows of out
+    uint32_t segments, segment_shift;    // the free rows lie in so many lists (a power of two), by D1's workgroups in turn; tile t has the
+    uint32_t segment_rows;               // next 64 of list t mod segments.  Room of each list, a multiple of 64
+    uint32_t *free_count;                // [segments] rows of each list
+    uint32_t *pages;                     // [tiles][64] the free rows, as multiples of 64 floats: row * page_elems
+    uint32_t out_bytes;
+    uint32_t page_elems, page_recip;     // d / 64; ceil(2^16 / page_elems): i / page_elems = i * page_recip >> 16 for i < 512
+    uint32_t *used;                      // entries that have room and whose tiles find free rows; the others' rows are gathered
+};
+constexpr uint32_t kPlacePad = 256;            // words past the end of the lists that F3 may read
+constexpr uint32_t kPlaceSelf = 0x80000000u;   // in rep: the row gathers for itself, and the lower bits say which of its bucket it is
+
 // The row b * F + f of a position, and its table.
 __device__ __forceinline__ uint32_t distinct_row(const DistinctPlan &s, uint32_t q, uint32_t &f)
 {
@@ -60,8 +80,8 @@ __device__ __forceinline__ uint32_t distinct_row(const DistinctPlan &s, uint32_t
     return (q - f * s.batch) * s.F + f;
 }
 
-template <bool SIGN>
-__global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p, DistinctPlan s, const int64_t *__restrict__ indices)
+template <bool SIGN, bool PLACES>
+__global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p, DistinctPlan s, PlacePlan lists, const int64_t *__restrict__ indices)
 {
     __shared__ uint32_t place[kDistinctSlots];               // tile-local lookup + 1; 0: free
     __shared__ uint32_t th[kDistinctTile], rep[kDistinctTile];
@@ -140,10 +160,48 @@ __global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p,
         rep[j] = mine;
     }
     __syncthreads();
+    if constexpr (!PLACES) {
 #pragma unroll
-    for (uint32_t i = 0; i < kDistinctPer; ++i) {
-        const uint32_t q = base + i * kDistinctBlock + t;
-        if (q < s.n) s.rep[q] = rep[lead[i]];
+        for (uint32_t i = 0; i < kDistinctPer; ++i) {
+            const uint32_t q = base + i * kDistinctBlock + t;
+            if (q < s.n) s.rep[q] = rep[lead[i]];
+        }
+    } else {
+        __shared__ uint32_t free_n[kDistinctPer * kDistinctBlock / 64u], free_first;
+        const uint32_t lane = t & 63u, wave = t >> 6;
+        bool free[kDistinctPer];
+        uint32_t before[kDistinctPer];
+#pragma unroll
+        for (uint32_t i = 0; i < kDistinctPer; ++i) {
+            const uint32_t q = base + i * kDistinctBlock + t;
+            free[i] = false;
+            if (q < s.n) {
+                uint32_t w = rep[lead[i]];
+                free[i] = w != row[i];
+                if (!free[i]) w = kPlaceSelf | atomicAdd(&lists.counts[mod_m(h[i], p.m, p.m_recip) >> lists.bucket_shift], 1u);
+                s.rep[q] = w;
+            }
+            const uint64_t mask = __ballot(free[i]);
+            before[i] = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (lane == 0) free_n[i * (kDistinctBlock / 64u) + wave] = (uint32_t)__popcll(mask);
+        }
+        __syncthreads();
+        const uint32_t seg = blockIdx.x & (lists.segments - 1u);
+        uint32_t all = 0, mine[kDistinctPer];
+#pragma unroll
+        for (uint32_t k = 0; k < kDistinctPer * kDistinctBlock / 64u; ++k) {
+#pragma unroll
+            for (uint32_t i = 0; i < kDistinctPer; ++i)
+                if (k == i * (kDistinctBlock / 64u) + wave) mine[i] = all;
+            all += free_n[k];
+        }
+        if (t == 0) free_first = atomicAdd(&lists.free_count[seg], all);
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < kDistinctPer; ++i) {
+            const uint32_t k = free_first + mine[i] + before[i];
+            if (free[i] && k < lists.segment_rows) lists.pages[(((k >> 6) << lists.segment_shift) + seg) * 64u + (k & 63u)] = row[i] * lists.page_elems;
+        }
     }
 }
 
@@ -160,24 +218,13 @@ __device__ __forceinline__ uint32_t to_front(bool yes, uint64_t mask, uint32_t &
     return count;
 }
 
+// The rows of the lanes with `self` (mask: their ballot).
 template <int V, bool CONSEC, bool SIGN, typename AT>
-__global__ __launch_bounds__(kRowBlock) void distinct_gather_kernel(Params p, Geom q, DistinctPlan s, const AT *__restrict__ array,
-                                                                    const int64_t *__restrict__ indices, float *__restrict__ out)
+__device__ __forceinline__ void gather_rows(const Params &p, const Geom &q, bool self, uint64_t mask, uint32_t row, uint32_t th, uint32_t tg,
+                                            const AT *__restrict__ array, float *__restrict__ out)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t at = blockIdx.x * kDistinctRows + lane;
-    uint32_t f = 0, row = 0, th = 0, tg = 0;
-    bool self = false;
-    if (lane < kDistinctRows && at < s.n) {
-        row = distinct_row(s, at, f);
-        self = s.rep[at] == row;
-        if (self) {
-            const int64_t x = indices[row];
-            th = staged_h(p, x, f);
-            if constexpr (SIGN) tg = staged_g(p, x, f);
-        }
-    }
-    const uint32_t n = to_front(self, __ballot(self), row, th, tg);
+    const uint32_t n = to_front(self, mask, row, th, tg);
     const uint32_t grp = lane & (q.G - 1u), sub = lane >> q.g_shift, step = 64u >> q.g_shift;
     Lane<V, CONSEC, SIGN> L;
     L.init(p, q, grp);
@@ -197,6 +244,26 @@ __global__ __launch_bounds__(kRowBlock) void distinct_gather_kernel(Params p, Ge
         for (int u = 0; u < kUnroll; ++u)
             if (live[u]) store_row<V, CONSEC>(out + (uint64_t)k[u] * p.d, q, grp, v[u]);
     }
+}
+
+template <int V, bool CONSEC, bool SIGN, typename AT>
+__global__ __launch_bounds__(kRowBlock) void distinct_gather_kernel(Params p, Geom q, DistinctPlan s, const AT *__restrict__ array,
+                                                                    const int64_t *__restrict__ indices, float *__restrict__ out)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t at = blockIdx.x * kDistinctRows + lane;
+    uint32_t f = 0, row = 0, th = 0, tg = 0;
+    bool self = false;
+    if (lane < kDistinctRows && at < s.n) {
+        row = distinct_row(s, at, f);
+        self = s.rep[at] == row;
+        if (self) {
+            const int64_t x = indices[row];
+            th = staged_h(p, x, f);
+            if constexpr (SIGN) tg = staged_g(p, x, f);
+        }
+    }
+    gather_rows<V, CONSEC, SIGN>(p, q, self, __ballot(self), row, th, tg, array, out);
 }
 
 // W: floats per lane and access (4 where rows are aligned for it).  A row is G lanes' work, in several steps if longer.
