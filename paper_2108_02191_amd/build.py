@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librobe.so")
 CALL = os.path.join(HERE, "_robe_call.so")      # the Python side of a call (csrc/robe_call.cpp)
 SOURCES = ["robe_api.hip"]
-HEADERS = ["robe_device.h", "robe_kernels.h", "robe_forward_distinct.h", "robe_forward_places.h", "robe_backward_dedup.h", "robe_backward_regions.h", "robe_backward_elements.h", "robe_radix_sort.h", os.path.join("..", "..", "include", "robe.h")]
+HEADERS = ["robe_device.h", "robe_kernels.h", "robe_forward_distinct.h", "robe_forward_places.h", "robe_backward_dedup.h", "robe_backward_regions.h", "robe_backward_places.h", "robe_radix_sort.h", os.path.join("..", "..", "include", "robe.h")]
 
 
 def hipcc_command(out: str = LIB) -> list:

@@ -21,7 +21,7 @@
 #include "robe_backward_dedup.h"
 #include "robe_backward_regions.h"
 #include "robe_forward_places.h"
-#include "robe_backward_elements.h"
+#include "robe_backward_places.h"
 #include "robe_radix_sort.h"
 
 // Workspace of robe_backward_noalloc: device memory that exists from the moment the library is
@@ -462,13 +462,19 @@ bool places_pay(const robe_hash_t *h, int64_t rows, const float *out)
     return h->m >= (1u << 23) && h->m < (1u << 29) && (uint64_t)rows * (h->d / h->Z) >= h->m / 3;
 }
 
+// The buckets of r = th mod m, and the form of an entry (see place_entry).
+void plan_buckets(uint64_t m, robe::PlacePlan *s)
+{
+    while (((m + (1ull << s->bucket_shift) - 1) >> s->bucket_shift) > robe::kMaxRegions) ++s->bucket_shift;
+    s->buckets = (uint32_t)((m + (1ull << s->bucket_shift) - 1) >> s->bucket_shift);
+    s->r_bits = ceil_log2(m);
+    s->r_mask = (1u << s->r_bits) - 1u;
+}
+
 // Sizes of its lists for `rows` lookups, in words: what lies in the last samples' rows beside rep, what behind the table.
 void plan_places(const robe_hash_t *h, int64_t rows, robe::PlacePlan *s, uint64_t *list_words, uint64_t *count_words)
 {
-    while (((h->m + (1ull << s->bucket_shift) - 1) >> s->bucket_shift) > robe::kMaxRegions) ++s->bucket_shift;
-    s->buckets = (uint32_t)((h->m + (1ull << s->bucket_shift) - 1) >> s->bucket_shift);
-    s->r_bits = ceil_log2(h->m);
-    s->r_mask = (1u << s->r_bits) - 1u;
+    plan_buckets(h->m, s);
     s->most = (uint32_t)(rows / 2) & ~63u;
     // fewer are gathered: a million lines take 19 us so, 4 by place, which costs some 35 before the first one at 25 M slots
     s->least = (uint32_t)(h->m / 8 / (h->d / h->Z)) + 1;
@@ -750,8 +756,8 @@ const uint64_t kSmallFullest = 96, kSmallLeastRegions = 7500;
 struct BwdPlan {
     bool dedup;          // sort the tokens and combine identical ones
     bool regions;        // ... and then sort the blocks by destination region instead of using float atomics
-    bool elements;       // ... of the (place, value) pairs of small blocks (robe_backward_elements.h)
-    bool pairs_fit;      // ... with room for every gradient element
+    bool elements;       // ... of the elements of small blocks (robe_backward_places.h)
+    bool all_fit;        // ... with room for the row of every run
     bool spill_rows;     // ... with room in LDS for a row of Z floats per lane group of the reduce kernel
     bool gather;         // ... and the reduce kernel finds its blocks in the sorted token list (no record kernels)
     uint32_t crowded_most;   // regions only, small_cap: at most this many regions are left to the kernel with one workgroup per region
@@ -763,6 +769,7 @@ struct BwdPlan {
     size_t off_keys_in, off_keys_out, off_vals_in, off_vals_out, off_tok_bag, off_temp, temp_bytes, bytes;
     // regions only
     robe::RegionPlan rp;
+    robe::RunPlan runs;      // places only
     size_t off_head, off_src_row, off_run_tg, off_run_c, off_P, off_counts, off_starts, off_wg_first, off_rec, off_rec_tg, off_dir;
 };
 
@@ -797,25 +804,27 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
     return 0;
 }
 
-// Small blocks take the pairs of robe_backward_elements.h up to this block size and from this many
-// gradient elements on.  Forward + backward on the 100 MB array, d = 128, 852 K lookups, float atomics /
-// pairs: Z = 1 2353 / 1551 us, Z = 2 1266 / 1007, Z = 4 750 / 772 (a block of four is one or two atomic
-// requests).  Z = 1 with 13 K, 52 K, 208 K lookups: 140 / 188, 255 / 251, 725 / 486.
-// Further lines (backward alone, atomics / pairs, us):
+// Small blocks take the route of robe_backward_places.h up to this block size and from this many gradient elements on.
+// Its lines were drawn for the kernels it replaced, which sorted (place, value) pairs and were slower at every size measured
+// since (below), against float atomics, us: forward + backward on the 100 MB array, d = 128, 852 K lookups, atomics / pairs
+// Z = 1 2353 / 1551, Z = 2 1266 / 1007, Z = 4 750 / 772; Z = 1 with 13 K, 52 K, 208 K lookups 140 / 188, 255 / 251, 725 / 486.
+// Backward alone, atomics / pairs:
 //   the last kernel has one workgroup per 2^14 slots: from 32 of them on.  Z = 2, 858 K lookups of d = 128,
 //   2^16, 2^18, 2^19, 2^22 slots: 672 / 1709, 672 / 688, 679 / 507, 675 / 332;
-//   the first two have one workgroup per 1024 tokens: from 2^16 tokens on.  Z = 1, d = 512, uniform ids,
-//   17.6 K tokens 435 / 515, 78 K 1976 / 602;
+//   few tokens leave its windows empty: from 2^16 tokens on.  Z = 1, d = 512, uniform ids, 17.6 K tokens 435 / 515, 78 K 1976 / 602;
 //   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on, from four
-//   on arrays of up to 2^25 slots if all pairs are sure to fit in the room below.  9 M elements, uniform ids,
-//   d = 1, 4, 8, Z = 1: 470 / 975, 445 / 335 (110 M elements, most without room: 4682 / 5726), 443 / 244;
-//   d = 2, 4, 8, 16, Z = 2: 258 / 555, 246 / 336, 243 / 240 (58 M slots: 247 / 297), 240 / 183.
-const uint32_t kElemMostZ = 2, kElemLeastRegions = 32;
+//   on arrays of up to 2^25 slots if the rows of all tokens are sure to fit in the room below.  9 M elements, uniform ids,
+//   d = 1, 4, 8, Z = 1: 470 / 975, 445 / 335, 443 / 244; d = 2, 4, 8, 16, Z = 2: 258 / 555, 246 / 336, 243 / 240, 240 / 183.
+// Backward alone, pairs / places, Zipf ids of 10 M a table (and ids that never repeat):
+//   d = 128, Z = 1, 852 K lookups, 0.6, 2.1, 8.4, 25 (signs), 58 M slots 1449 / 934 (4387 / 3391), 1198 / 405 (3853 / 2527), 1163 / 333,
+//   1190 / 361 (3762 / 2401), 746 / 412 (2694 / 603);  104 K lookups, 4.2, 25 M 152 / 95 (178 / 102), 179 / 137 (205 / 133)
+//   Z = 2, 852 K, 25 M 770 / 342 (2110 / 1435);  208 K, 25, 58 M 207 / 158 (264 / 185), 276 / 249 (384 / 265)
+//   d = 16, Z = 1, 852 K, 25 M 177 / 144 (207 / 175);  d = 8, 1.4 M 230 / 199 (252 / 229);  d = 512, 208 K 1615 / 437 (3662 / 2366)
+const uint32_t kElemMostZ = 2, kElemLeastRegions = 32, kElemMostRegions = 3600;
 const uint64_t kElemLeast = 1u << 23, kElemLeastTokens = 1u << 16;
-// Room for the pairs: one per array slot, or 2^25.  What does not fit goes by atomics (19.6 M pairs of
-// the 109 M elements above fit).  Where all tokens differ, little of a much larger problem would, and the
-// walk is then in vain, so gradient elements may be eight times the room at the most, four with Z = 2.
-// Half a float of summed rows per element included, that is three floats per array slot, or 384 MiB.
+// Room for the runs' rows: two floats per array slot, or 2^26.  What does not fit goes by atomics.  Where all tokens differ,
+// little of a much larger problem would, and the walk is then in vain, so gradient elements may be eight times half of it at
+// the most, four with Z = 2.  Half a float of summed rows per element included, that is three floats per array slot, or 384 MiB.
 uint64_t elem_room(uint64_t m) { return m > (1u << 25) ? m : (1u << 25); }
 uint64_t elem_most(uint64_t m, uint32_t d, uint32_t Z)
 {
@@ -918,11 +927,11 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
 
     // Region-sorted scatter on top of the combined runs.
     // Small blocks: the pairs of every element sorted by region, where nothing else is asked for.
-    const uint64_t elem_regions = (h->m + (1u << robe::kElemShift) - 1) >> robe::kElemShift;
+    const uint64_t elem_regions = (h->m + (1u << robe::kPlaceShift) - 1) >> robe::kPlaceShift;
     const uint64_t elems = (uint64_t)n * h->d, room = elems < elem_room(h->m) ? elems : elem_room(h->m);
     const bool elements = h->Z <= kElemMostZ && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
                           opt.fused_route != ROBE_ROUTE_REGIONS && opt.region_records == 0 && opt.region_shift == 0 &&
-                          elem_regions <= robe::kElemMaxRegions && elem_regions >= kElemLeastRegions &&
+                          elem_regions <= kElemMostRegions && elem_regions >= kElemLeastRegions &&
                           n >= kElemLeastTokens && elems >= kElemLeast && elems <= elem_most(h->m, h->d, h->Z);
     const bool want_regions = elements || need_regions || (route == ROBE_ROUTE_AUTO ? regions_by_default(h, n_indices) : route == ROBE_ROUTE_REGIONS);
     if (!want_regions) {
@@ -945,7 +954,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     // C * ((P - 1) / m + 3) entries, which must fit its LDS: large arrays, few chunks per embedding.
     // No record kernels, no record storage, any number of regions.  options->region_records asks for
     // either variant.
-    uint32_t shift = elements ? robe::kElemShift : 0u;
+    uint32_t shift = elements ? robe::kPlaceShift : 0u;
     bool small = false;
     if (!elements) {
         const uint32_t gshift = opt.region_shift ? (uint32_t)opt.region_shift : 13u;
@@ -1043,10 +1052,16 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
 
     pl.regions = true;
     pl.elements = elements;
-    pl.pairs_fit = elements && elems <= room;
     robe::RegionPlan &r = pl.rp;
     r.r_shift = shift;
     r.NR = (uint32_t)NR;
+    if (elements) {
+        plan_buckets(h->m, &pl.runs.place);
+        r.NR = pl.runs.place.buckets;                                  // (what the scan goes over)
+        const uint64_t rows_fit = room * 2 / h->d & ~63ull, whole = (n + 63) & ~63ull;
+        pl.runs.place.most = (uint32_t)(rows_fit < whole ? rows_fit : whole);
+        pl.all_fit = n <= pl.runs.place.most;
+    }
     r.n = (uint32_t)n;
     r.rows = (uint32_t)rows;
     r.src_own = (uint32_t)src_own;
@@ -1055,7 +1070,6 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     r.stretch = stretch;
     r.key_mask = pl.key_top >= 31 ? (uint32_t)ROBE_PRIME : (1u << pl.key_top) - 1u;
     r.bin_blocks = NR * 4 > 80 * 1024 ? 256u : 512u;      // one or two workgroups per CU by LDS
-    if (elements) r.bin_blocks = robe::kElemBlocks;
     if (n < (size_t)r.bin_blocks * 1024) r.bin_blocks = (uint32_t)((n + 1023) / 1024);
     r.pos_per_block = (uint32_t)((n + r.bin_blocks - 1) / r.bin_blocks);
     r.lg_shift = log2u(lg);
@@ -1091,12 +1105,16 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
         r.epc_recip = (65536u + r.epc - 1) / r.epc;
         pl.off_dir = off;  off = align_up(off + ((size_t)r.dir_buckets + 1) * 4, 256);
     } else {
-        pl.off_counts = off;  off = align_up(off + NR * 4, 256);
-        pl.off_starts = off;  off = align_up(off + (NR + 2) * 4, 256);
-        pl.off_wg_first = off; off = align_up(off + (size_t)r.bin_blocks * NR * 4, 256);
+        pl.off_counts = off;  off = align_up(off + (size_t)r.NR * 4, 256);
+        pl.off_starts = off;  off = align_up(off + ((size_t)r.NR + 2) * 4, 256);
+        pl.off_wg_first = off; if (!elements) off = align_up(off + (size_t)r.bin_blocks * NR * 4, 256);
         pl.off_rec = off;     off = align_up(off + (elements ? room : rec_per_block * n * C) * 8, 256);
-        r.rec_cap = elements ? (uint32_t)room : 0u;
-        pl.off_rec_tg = off;  if (h->use_sign && !elements) off = align_up(off + rec_per_block * n * C * 4, 256);
+        pl.off_rec_tg = off;
+        if (h->use_sign && elements) {                                // (the tokens' bags are not needed any more by then)
+            if (bags) pl.off_rec_tg = pl.off_tok_bag;
+            else off = align_up(off + n * 4, 256);
+        }
+        if (h->use_sign && !elements) off = align_up(off + rec_per_block * n * C * 4, 256);
     }
     pl.bytes = off + 256;      // (slack: the padded reads above never leave the workspace)
     return pl;
@@ -1275,28 +1293,37 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
         if (int rc = probe(opt, ROBE_PROBE_COMBINE, true, stream)) return rc;
 
         if (pl.elements) {
-            // E1, R3, E2, E3 (see robe_backward_elements.h)
-            const dim3 egrid(r.bin_blocks), eblock(robe::kElemBlock);
-            const uint32_t row_shift = ceil_log2(h->d);
-            const size_t lds_count = (size_t)r.NR * 4 + (robe::kElemRuns + robe::kElemBlock) * 8 + 64, lds_scatter = robe::elem_lds_bytes(r.NR, sign);
-            const size_t lds_reduce = (size_t)4 << robe::kElemShift;
-            robe::element_count_kernel<<<egrid, eblock, lds_count, stream>>>(p, r, row_shift);
-            if (int rc = check_launch("backward (count elements)")) return rc;
+            // S1, R3, S2, S3, S4 (see robe_backward_places.h).  The sort's other arrays are free by now, and so are the sorted values.
+            const bool first = keys_out == reinterpret_cast<uint32_t *>(ws + pl.off_keys_in);
+            robe::RunPlan l = pl.runs;
+            l.place.counts = r.counts;
+            l.place.starts = r.starts;
+            l.place.entries = reinterpret_cast<uint32_t *>(ws + (first ? pl.off_keys_out : pl.off_keys_in));
+            l.place.row = vals_out;
+            l.rank = reinterpret_cast<uint32_t *>(ws + (first ? pl.off_vals_out : pl.off_vals_in));
+            l.tg = r.rec_tg;
+            l.tiles = reinterpret_cast<float *>(r.rec);
+            const dim3 ngrid((n + robe::kRunBlock - 1) / robe::kRunBlock), nblock(robe::kRunBlock), tgrid(l.place.most / 64u);
+            const uint32_t walk = r.stretch * pl.lay.G, starts = (uint32_t)(((n + walk - 1u) / walk + robe::kRunBlock - 1u) / robe::kRunBlock);
+            robe::run_count_kernel<<<dim3(ngrid.x + starts), nblock, 0, stream>>>(p, r, l, walk, starts);
+            if (int rc = check_launch("backward (count runs)")) return rc;
             robe::region_scan_kernel<<<dim3(1), dim3(robe::kScanThreads), 0, stream>>>(r);
             if (int rc = check_launch("backward (scan)")) return rc;
-#define ROBE_ELEMENTS(S_)                                                                                             \
-    do {                                                                                                              \
-        if (int rc = allow_lds(robe::element_scatter_kernel<S_>, lds_scatter, "backward (elements)")) return rc;      \
-        robe::element_scatter_kernel<S_><<<egrid, eblock, lds_scatter, stream>>>(p, r, row_shift, grad_out, pl.pairs_fit ? nullptr : grad_array); \
-    } while (0)
-            if (sign) ROBE_ELEMENTS(true);
-            else ROBE_ELEMENTS(false);
-#undef ROBE_ELEMENTS
-            if (int rc = check_launch("backward (elements)")) return rc;
+            float *spill = pl.all_fit ? nullptr : grad_array;
+            if (sign) robe::run_place_kernel<true><<<ngrid, nblock, 0, stream>>>(p, r, l, grad_out, spill);
+            else robe::run_place_kernel<false><<<ngrid, nblock, 0, stream>>>(p, r, l, grad_out, spill);
+            if (int rc = check_launch("backward (place runs)")) return rc;
+            if (sign) robe::run_turn_kernel<true><<<tgrid, nblock, 0, stream>>>(p, r, l, grad_out);
+            else robe::run_turn_kernel<false><<<tgrid, nblock, 0, stream>>>(p, r, l, grad_out);
+            if (int rc = check_launch("backward (turn runs)")) return rc;
             if (int rc = probe(opt, ROBE_PROBE_REDUCE, false, stream)) return rc;
-            if (rule == 1) robe::element_reduce_kernel<1><<<dim3(r.NR), eblock, lds_reduce, stream>>>(p, r, grad_array, state, scale, eps, vec_ok);
-            else robe::element_reduce_kernel<0><<<dim3(r.NR), eblock, lds_reduce, stream>>>(p, r, grad_array, state, scale, eps, vec_ok);
-            if (int rc = check_launch("backward (reduce elements)")) return rc;
+            const dim3 pgrid((uint32_t)((h->m + (1u << robe::kPlaceShift) - 1) >> robe::kPlaceShift)), pblock(robe::kPlaceBlock);
+            const size_t lds = (size_t)4 * robe::kRunSlots;
+            if (int rc = allow_lds(robe::run_reduce_kernel<0>, lds, "backward (reduce runs)")) return rc;
+            if (int rc = allow_lds(robe::run_reduce_kernel<1>, lds, "backward (reduce runs)")) return rc;
+            if (rule == 1) robe::run_reduce_kernel<1><<<pgrid, pblock, lds, stream>>>(p, r, l, l.place.entries, l.tiles, grad_array, state, scale, eps, vec_ok);
+            else robe::run_reduce_kernel<0><<<pgrid, pblock, lds, stream>>>(p, r, l, l.place.entries, l.tiles, grad_array, state, scale, eps, vec_ok);
+            if (int rc = check_launch("backward (reduce runs)")) return rc;
             return probe(opt, ROBE_PROBE_REDUCE, true, stream);
         }
 
@@ -1890,11 +1917,11 @@ static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, in
     const bool want = opt.fused_route == ROBE_ROUTE_AUTO ? fused_regions_pay(hash, n_indices, hash->d) : opt.fused_route == ROBE_ROUTE_REGIONS;
     if (opt.reproducible || want) {
         *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out, true);
-        if (pl->regions && (!pl->elements || pl->pairs_fit)) return true;
+        if (pl->regions && (!pl->elements || pl->all_fit)) return true;
     }
     *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out);
     // small blocks: the pairs' workgroups apply the rule, whatever the array size, if they are sure to get all pairs
-    if (opt.fused_route == ROBE_ROUTE_AUTO && pl->elements && pl->pairs_fit) return true;
+    if (opt.fused_route == ROBE_ROUTE_AUTO && pl->elements && pl->all_fit) return true;
     if (!pl->elements) pl->regions = false;              // the two-step fallback adds onto a gradient array
     *scratch_bytes = align_up((size_t)hash->m * 4, 256);
     return false;

@@ -81,8 +81,7 @@ struct RegionPlan {
     float *P;                // [lane groups of R1 * p_quota][d] summed rows of the runs longer than one (d: the widest table's)
     uint32_t *counts, *starts;   // [NR], [NR + 2]; after R3 counts holds the order of the regions for R5 (fullest_first), or the regions R5 takes (small_cap; how many: starts[NR + 1])
     uint32_t *wg_first;      // [bin_blocks][NR]: R2 -> R4, see region_bin_kernel
-    uint2 *rec;              // (offset, source block | part flag), up to three per token and chunk; or pairs (see robe_backward_elements.h)
-    uint32_t rec_cap;        // pairs only: how many there is room for
+    uint2 *rec;              // (offset, source block | part flag), up to three per token and chunk; or rows (see robe_backward_places.h)
     uint32_t *rec_tg;        // sign on only
 };
 
