@@ -226,7 +226,6 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
     const uint32_t my_base = my_w & 1u ? least : 0u, my_width = my_w & 1u ? 0u - least : least;
     uint32_t my_shift = wrap(mod_m(my_cc, p.m, p.m_recip) + (my_live ? my_i - my_c * p.Z : 0u), p.m);
     if (my_w & 1u) my_shift = wrap(my_shift + p.m - mod_m(kP, p.m, p.m_recip), p.m);
-    const uint32_t windows = wave < 2u * p.d ? (2u * p.d - wave + kWaves - 1u) / kWaves : 0u;        // <= 64 of this wavefront
     const uint32_t r0 = blockIdx.x << kPlaceShift, len = min(1u << kPlaceShift, p.m - r0), len4 = 4u * len;
     const PlaceWindow my = place_window(p, l.place, used, r0, len, my_shift, my_live);
     if (!__syncthreads_or((int)(my.count | my.over))) return;     // nothing lands here
@@ -269,33 +268,33 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
                 __hip_atomic_fetch_add(&acc[at[u]], b.v[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     };
-    if (windows != 0) {
-        uint32_t w = 0, n = 0, first = of_lane(my.first, 0), count = of_lane(my.count, 0);
-        auto fetch = [&](RunBatch &b) {                          // past the last window: a batch of nothing
-            if (n >= count && w + 1u < windows) {
-                ++w;
-                n = 0;
-                first = of_lane(my.first, w);
-                count = of_lane(my.count, w);
-            }
-            const uint32_t left = n < count ? count - n : 0u;
-            load(b, w, first + (left ? n : 0u), left, of_lane(my.delta, w));
-            n += kRunAhead;
-            return left != 0 || w + 1u < windows;
-        };
-        RunBatch even, odd;
-        for (bool more = fetch(even); more;) {
-            fetch(odd);
-            serve(even);
-            more = fetch(even);
-            serve(odd);
+    uint64_t todo = __ballot(my.count != 0);                      // windows to come
+    uint32_t w = 0, n = 0, first = 0, count = 0;
+    auto fetch = [&](RunBatch &b) {                              // past the last window: a batch of nothing
+        if (n >= count && todo != 0) {
+            w = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1ull;
+            n = 0;
+            first = of_lane(my.first, w);
+            count = of_lane(my.count, w);
         }
-        for (uint64_t wrapped = __ballot(my.over != 0); wrapped != 0; wrapped &= wrapped - 1ull) {
-            const uint32_t x = (uint32_t)__builtin_ctzll(wrapped), end = of_lane(my.over, x);
-            for (n = 0; n < end; n += kRunAhead) {
-                load(even, x, n, end - n, of_lane(my.delta, x) + 4u * p.m);
-                serve(even);
-            }
+        const uint32_t left = n < count ? count - n : 0u;
+        load(b, w, first + (left ? n : 0u), left, of_lane(my.delta, w));
+        n += kRunAhead;
+        return left != 0;
+    };
+    RunBatch even, odd;
+    for (bool more = todo != 0 && fetch(even); more;) {
+        fetch(odd);
+        serve(even);
+        more = fetch(even);
+        serve(odd);
+    }
+    for (uint64_t wrapped = __ballot(my.over != 0); wrapped != 0; wrapped &= wrapped - 1ull) {
+        const uint32_t x = (uint32_t)__builtin_ctzll(wrapped), end = of_lane(my.over, x);
+        for (n = 0; n < end; n += kRunAhead) {
+            load(even, x, n, end - n, of_lane(my.delta, x) + 4u * p.m);
+            serve(even);
         }
     }
     __syncthreads();

@@ -36,7 +36,6 @@ namespace robe {
 constexpr uint32_t kPlaceShift = 14;          // floats of a region: 64 KB of LDS, two workgroups per CU
 constexpr uint32_t kPlaceBlock = 1024;
 constexpr uint32_t kPlaceAhead = 3;           // tiles whose loads are requested together
-constexpr uint32_t kPlaceDeep = 2;            // batches of these per wavefront on their way (three, four: level)
 constexpr uint32_t kPlaceMostSegments = 32;
 constexpr uint32_t kPlaceTurn = 128;          // elements of a tile turned round at a time
 constexpr uint32_t kPlaceMostD = 512;
@@ -179,7 +178,6 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void place_regions_kernel(Params p,
         my_page[j] = (i * s.page_recip) >> 16;
         my_in_page[j] = i - my_page[j] * s.page_elems;
     }
-    const uint32_t windows = uniform(my_w) < 2u * p.C ? (2u * p.C - uniform(my_w) + kPlaceBlock / 64u - 1u) / (kPlaceBlock / 64u) : 0u;    // <= 64 of this wavefront
     // A lane that has nothing to store points past the end of the buffer: every store is issued, so that the compiler knows
     // how many are in flight and lets a wait for loads leave the stores before them alone.
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)s.out_bytes, 0x00027000);
@@ -192,7 +190,6 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void place_regions_kernel(Params p,
         if (t == 0) slots[len] = widen(array[wrap(r0 + len, p.m)]);
         __syncthreads();
     }
-    if (windows == 0) return;
     // tiles [first, first + count) of window w
     auto load = [&](PlaceBatch<Z> &b, uint32_t w, uint32_t first, uint32_t count, uint32_t delta) {
         const uint32_t width = of_lane(my_width, w);
@@ -228,11 +225,13 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void place_regions_kernel(Params p,
                 __builtin_amdgcn_raw_buffer_store_b32((int)__float_as_uint(x[u][j]), rows, at, (int)((of_lane(b.page[j], u) << 8) + b.in_page[j]), 0);
         }
     };
-    // the walk: window w of the wavefront, from its entry n on
-    uint32_t w = 0, n = 0, first = of_lane(my.first, 0), count = of_lane(my.count, 0);
-    auto fetch = [&](PlaceBatch<Z> &b) {                     // past the last window: a batch of nothing
-        if (n >= count && w + 1u < windows) {
-            ++w;
+    // the walk: window w of the wavefront, from its tile n on; todo: windows to come
+    uint64_t todo = __ballot(my.count != 0);
+    uint32_t w = 0, n = 0, first = 0, count = 0;
+    auto fetch = [&](PlaceBatch<Z> &b) {                         // past the last window: a batch of nothing
+        if (n >= count && todo != 0) {
+            w = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1ull;
             n = 0;
             first = of_lane(my.first, w);
             count = of_lane(my.count, w);
@@ -240,27 +239,24 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void place_regions_kernel(Params p,
         const uint32_t left = n < count ? count - n : 0u;
         load(b, w, first + (left ? n : 0u), left, of_lane(my.delta, w));
         n += kPlaceAhead;
-        return left != 0 || w + 1u < windows;
+        return left != 0;
     };
     // Loads and stores of a wavefront complete in the order they were issued, so that a wait for loads waits for all
-    // stores before them too: a batch's loads are requested before the stores of the batch before it.  (Each batch in registers
+    // stores before them too: a batch's loads are requested before the stores of the batch before it (three
+    // or four batches on their way: level).  (Each batch in registers
     // of its own: a copy would wait for its loads.  No way out of the loop between a batch's loads and its use, or they would move there.)
-    PlaceBatch<Z> b[kPlaceDeep];
-#pragma unroll
-    for (uint32_t i = 0; i + 1u < kPlaceDeep; ++i) fetch(b[i]);
-    for (bool more = true; more;) {
-#pragma unroll
-        for (uint32_t i = 0; i < kPlaceDeep; ++i) {
-            const bool some = fetch(b[(i + kPlaceDeep - 1u) % kPlaceDeep]);
-            if (i == 1) more = some;                         // (nothing in b[0]: nor in those after it)
-            serve(b[i]);
-        }
+    PlaceBatch<Z> even, odd;
+    for (bool more = todo != 0 && fetch(even); more;) {
+        fetch(odd);
+        serve(even);
+        more = fetch(even);
+        serve(odd);
     }
     for (uint64_t wrapped = __ballot(my.over != 0); wrapped != 0; wrapped &= wrapped - 1ull) {      // a few windows of the launch
         const uint32_t l = (uint32_t)__builtin_ctzll(wrapped), end = of_lane(my.over, l);
         for (n = 0; n < end; n += kPlaceAhead) {
-            load(b[0], l, n, end - n, of_lane(my.delta, l) + 4u * p.m);
-            serve(b[0]);
+            load(even, l, n, end - n, of_lane(my.delta, l) + 4u * p.m);
+            serve(even);
         }
     }
 }
