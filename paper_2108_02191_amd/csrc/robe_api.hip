@@ -451,15 +451,18 @@ int allow_lds(K kernel, size_t bytes, const char *what)
 }
 
 // Whether the distinct tokens of such a lookup are served region by region of the array (robe_forward_places.h): where
-// its lines are many and one L2 does not hold much of it, and the array is not so large that reading it all costs what its lines
-// do.  Forward, us, gathered / by place, Zipf ids of 10 M a table and (ids that never repeat), d = 128, Z = 1:
-//   9 M slots, 208 K lookups 304 / 228 (460 / 475);  25 M, 198 K 316 / 249 (486 / 501), 852 K 1074 / 600 (2007 / 2047)
-//   60 M, 312 K 473 / 400 (773 / 796);  120 M, 852 K 1133 / 824 (2089 / 2143);  250 M, 1040 K 1435 / 1213 (2764 / 2823)
-//   Z = 2, 25 M, 468 K 384 / 301 (610 / 637);  d = 64, 9 M, 520 K 345 / 243 (578 / 608);  d = 512, 25 M, 78 K 532 / 497 (744 / 762)
+// one L2 does not hold much of it, and the lookups read as many blocks as it has slots, or reading it all is not worth it.
+// Forward, us, gathered / by place, d = 128, Zipf ids of 10 M a table and (ids that never repeat):
+//   Z = 1, 9 M slots, 208 K lookups 304 / 189 (460 / 474);  25 M, 198 K 316 / 249 (486 / 501), 852 K 1074 / 421 (2007 / 2057)
+//   Z = 2, 25 M, 468 K 384 / 239 (610 / 630);  d = 64, 9 M, 520 K 345 / 243 (578 / 608);  d = 512, 25 M, 78 K 532 / 497 (744 / 762)
+// 26 tables, spaced evenly on a log scale, of 10 ids and up to 100 K, to 3 M, to 40 M:
+//   Z = 1, 10 M slots, 208 K 138 / 104, 169 / 108, 193 / 113;  25 M, 208 K 144 / 131, 180 / 135, 203 / 137, 852 K 323 / 224, 471 / 243,
+//   571 / 265;  50 M, 416 K 209 / 243, 288 / 228, 337 / 238;  Z = 2, 10 M, 468 K 151 / 131, 196 / 149, 224 / 164;  50 M, 858 K 238 / 270, 320 / 271
+// Blocks of four (where this was not kept): 25 M, 852 K, to 40 M 311 / 242, never repeating 600 / 671; 520 K 191 / 174, 367 / 419.
 bool places_pay(const robe_hash_t *h, int64_t rows, const float *out)
 {
     if (h->Z > 2 || h->d % 64 != 0 || h->d > robe::kPlaceMostD || !aligned(out, 16) || rows * (int64_t)h->d >= (1ll << 30)) return false;
-    return h->m >= (1u << 23) && h->m < (1u << 29) && (uint64_t)rows * (h->d / h->Z) >= h->m / 3;
+    return h->m >= (1u << 23) && h->m < (1u << 29) && (uint64_t)rows * (h->d / h->Z) >= h->m;
 }
 
 // The buckets of r = th mod m, and the form of an entry (see place_entry).
@@ -815,7 +818,11 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 //   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on, from four
 //   on arrays of up to 2^25 slots if the rows of all tokens are sure to fit in the room below.  9 M elements, uniform ids,
 //   d = 1, 4, 8, Z = 1: 470 / 975, 445 / 335, 443 / 244; d = 2, 4, 8, 16, Z = 2: 258 / 555, 246 / 336, 243 / 240, 240 / 183.
-// Backward alone, pairs / places, Zipf ids of 10 M a table (and ids that never repeat):
+// Backward alone, pairs / places, 26 tables spaced evenly on a log scale of 10 ids and up to 100 K, to 40 M, d = 128:
+//   Z = 1, 208 K lookups, 10, 25, 50 M slots 124 / 111, 145 / 117; 142 / 135, 169 / 141; 176 / 176, 218 / 193;  852 K, 25 M 353 / 242, 434 / 275
+//   Z = 2, 208 K, 25, 50 M 137 / 131, 168 / 140; 162 / 169, 205 / 188;  858 K, 50 M 377 / 299, 495 / 337
+//   Z = 4 (atomics / places, where it was not kept), 25 M, 208 K 97 / 141, 153 / 149;  852 K 221 / 257, 403 / 277
+// Zipf ids of 10 M a table (and ids that never repeat):
 //   d = 128, Z = 1, 852 K lookups, 0.6, 2.1, 8.4, 25 (signs), 58 M slots 1449 / 934 (4387 / 3391), 1198 / 405 (3853 / 2527), 1163 / 333,
 //   1190 / 361 (3762 / 2401), 746 / 412 (2694 / 603);  104 K lookups, 4.2, 25 M 152 / 95 (178 / 102), 179 / 137 (205 / 133)
 //   Z = 2, 852 K, 25 M 770 / 342 (2110 / 1435);  208 K, 25, 58 M 207 / 158 (264 / 185), 276 / 249 (384 / 265)

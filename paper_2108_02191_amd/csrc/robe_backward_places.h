@@ -33,6 +33,7 @@ constexpr uint32_t kRunBlock = 256;
 constexpr uint32_t kRunWb = 4;             // vectors per thread in flight in the write-back
 constexpr uint32_t kRunTurn = 64;           // elements of a tile turned round at a time
 constexpr uint32_t kRunSlots = (1u << kPlaceShift) + 64u;      // of S4 in LDS: the region, a word per lane
+constexpr uint32_t kRunShort = 96;           // entries a window on average up to which S4 takes one tile at a time
 constexpr uint32_t kRunAhead = 3;            // tiles whose loads are requested together
 
 struct RunPlan {
@@ -149,12 +150,95 @@ __global__ __launch_bounds__(kRunBlock) void run_turn_kernel(Params p, RegionPla
     }
 }
 
-// Up to kRunAhead tiles of a window, see PlaceBatch.
+// Up to A tiles of a window, see PlaceBatch.
+template <uint32_t A>
 struct RunBatch {
-    uint32_t entry[kRunAhead];
-    float v[kRunAhead];
-    uint32_t delta, base, width[kRunAhead];
+    uint32_t entry[A];
+    float v[A];
+    uint32_t delta, base, width[A];
 };
+
+// What S4's walk needs of its region and wavefront: see run_reduce_kernel.
+struct RunWalk {
+    PlaceWindow my;
+    uint32_t my_base, my_width, wave, len4, last_tile, r_mask;
+};
+
+// A: tiles whose loads are requested together.
+template <uint32_t A>
+__device__ __forceinline__ void run_walk(const Params &p, const RunWalk &k, const uint32_t *__restrict__ entries, const float *__restrict__ tiles, float *acc)
+{
+    const uint32_t lane = threadIdx.x & 63u, len4 = k.len4;
+    auto of_lane = [](uint32_t v, uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)x); };
+    // tiles [first, first + count) of window w
+    auto load = [&](RunBatch<A> &b, uint32_t w, uint32_t first, uint32_t count, uint32_t delta) {
+        const uint32_t width = of_lane(k.my_width, w), i = (k.wave + w * (kPlaceBlock / 64u)) >> 1;
+        b.delta = delta;
+        b.base = of_lane(k.my_base, w);
+#pragma unroll
+        for (uint32_t u = 0; u < A; ++u) {
+            const uint32_t tile = min(first + u, k.last_tile);
+            b.width[u] = u < count ? width : 0u;
+            b.entry[u] = entries[tile * 64u + lane];
+            b.v[u] = tiles[(uint64_t)(tile * p.d + i) * 64u + lane];
+        }
+    };
+    uint32_t *bits = reinterpret_cast<uint32_t *>(acc);
+    // One compare-and-swap per value, all on their way together; a lane that has nothing to add tries a word of its own.  The
+    // few that find another value in between go on alone.
+    auto serve = [&](const RunBatch<A> &b) {
+        uint32_t at[A], old[A], got[A];
+        bool on[A], again = false;
+#pragma unroll
+        for (uint32_t u = 0; u < A; ++u) {
+            const uint32_t rel = ((b.entry[u] & k.r_mask) << 2) + b.delta;
+            on[u] = (rel < len4) & (b.entry[u] - b.base < b.width[u]);
+            at[u] = on[u] ? rel >> 2 : (1u << kPlaceShift) + lane;
+            old[u] = bits[at[u]];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < A; ++u) got[u] = atomicCAS(&bits[at[u]], old[u], __float_as_uint(__uint_as_float(old[u]) + b.v[u]));
+#pragma unroll
+        for (uint32_t u = 0; u < A; ++u) again |= on[u] && got[u] != old[u];
+        if (!__any(again)) return;
+#pragma unroll
+        for (uint32_t u = 0; u < A; ++u) {
+            if (!on[u] || got[u] == old[u]) continue;
+            if (!__hip_atomic_compare_exchange_strong(&bits[at[u]], &got[u], __float_as_uint(__uint_as_float(got[u]) + b.v[u]), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_WORKGROUP))
+                __hip_atomic_fetch_add(&acc[at[u]], b.v[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    };
+    uint64_t todo = __ballot(k.my.count != 0);                      // windows to come
+    uint32_t w = 0, n = 0, first = 0, count = 0;
+    auto fetch = [&](RunBatch<A> &b) {                              // past the last window: a batch of nothing
+        if (n >= count && todo != 0) {
+            w = (uint32_t)__builtin_ctzll(todo);
+            todo &= todo - 1ull;
+            n = 0;
+            first = of_lane(k.my.first, w);
+            count = of_lane(k.my.count, w);
+        }
+        const uint32_t left = n < count ? count - n : 0u;
+        load(b, w, first + (left ? n : 0u), left, of_lane(k.my.delta, w));
+        n += A;
+        return left != 0;
+    };
+    RunBatch<A> even, odd;
+    for (bool more = todo != 0 && fetch(even); more;) {
+        fetch(odd);
+        serve(even);
+        more = fetch(even);
+        serve(odd);
+    }
+    for (uint64_t wrapped = __ballot(k.my.over != 0); wrapped != 0; wrapped &= wrapped - 1ull) {
+        const uint32_t x = (uint32_t)__builtin_ctzll(wrapped), end = of_lane(k.my.over, x);
+        for (n = 0; n < end; n += A) {
+            load(even, x, n, end - n, of_lane(k.my.delta, x) + 4u * p.m);
+            serve(even);
+        }
+    }
+}
 
 // The rule applied to region_len slots from r0 on, acc their gradient; kPlaceBlock threads.
 template <int RULE>
@@ -216,7 +300,6 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
     const uint32_t t = threadIdx.x, lane = t & 63u, last_tile = (used - 1u) >> 6;
     constexpr uint32_t kWaves = kPlaceBlock / 64u;
     auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
-    auto of_lane = [](uint32_t v, uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)x); };
     for (uint32_t i = t; i < kRunSlots; i += kPlaceBlock) acc[i] = 0.0f;
     // a lane's window: element and class (see place_regions_kernel; every element has windows of its own, since a block may end in the next region)
     const uint32_t wave = uniform(t >> 6), my_w = wave + lane * kWaves, my_i = my_w >> 1;
@@ -226,77 +309,22 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
     const uint32_t my_base = my_w & 1u ? least : 0u, my_width = my_w & 1u ? 0u - least : least;
     uint32_t my_shift = wrap(mod_m(my_cc, p.m, p.m_recip) + (my_live ? my_i - my_c * p.Z : 0u), p.m);
     if (my_w & 1u) my_shift = wrap(my_shift + p.m - mod_m(kP, p.m, p.m_recip), p.m);
-    const uint32_t r0 = blockIdx.x << kPlaceShift, len = min(1u << kPlaceShift, p.m - r0), len4 = 4u * len;
+    const uint32_t r0 = blockIdx.x << kPlaceShift, len = min(1u << kPlaceShift, p.m - r0);
     const PlaceWindow my = place_window(p, l.place, used, r0, len, my_shift, my_live);
     if (!__syncthreads_or((int)(my.count | my.over))) return;     // nothing lands here
-    // tiles [first, first + count) of window w
-    auto load = [&](RunBatch &b, uint32_t w, uint32_t first, uint32_t count, uint32_t delta) {
-        const uint32_t width = of_lane(my_width, w), i = (wave + w * kWaves) >> 1;
-        b.delta = delta;
-        b.base = of_lane(my_base, w);
-#pragma unroll
-        for (uint32_t u = 0; u < kRunAhead; ++u) {
-            const uint32_t tile = min(first + u, last_tile);
-            b.width[u] = u < count ? width : 0u;
-            b.entry[u] = entries[tile * 64u + lane];
-            b.v[u] = tiles[(uint64_t)(tile * p.d + i) * 64u + lane];
-        }
-    };
-    uint32_t *bits = reinterpret_cast<uint32_t *>(acc);
-    // One compare-and-swap per value, all on their way together; a lane that has nothing to add tries a word of its own.  The
-    // few that find another value in between go on alone.
-    auto serve = [&](const RunBatch &b) {
-        uint32_t at[kRunAhead], old[kRunAhead], got[kRunAhead];
-        bool on[kRunAhead], again = false;
-#pragma unroll
-        for (uint32_t u = 0; u < kRunAhead; ++u) {
-            const uint32_t rel = ((b.entry[u] & l.place.r_mask) << 2) + b.delta;
-            on[u] = (rel < len4) & (b.entry[u] - b.base < b.width[u]);
-            at[u] = on[u] ? rel >> 2 : (1u << kPlaceShift) + lane;
-            old[u] = bits[at[u]];
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < kRunAhead; ++u) got[u] = atomicCAS(&bits[at[u]], old[u], __float_as_uint(__uint_as_float(old[u]) + b.v[u]));
-#pragma unroll
-        for (uint32_t u = 0; u < kRunAhead; ++u) again |= on[u] && got[u] != old[u];
-        if (!__any(again)) return;
-#pragma unroll
-        for (uint32_t u = 0; u < kRunAhead; ++u) {
-            if (!on[u] || got[u] == old[u]) continue;
-            if (!__hip_atomic_compare_exchange_strong(&bits[at[u]], &got[u], __float_as_uint(__uint_as_float(got[u]) + b.v[u]), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_WORKGROUP))
-                __hip_atomic_fetch_add(&acc[at[u]], b.v[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-    };
-    uint64_t todo = __ballot(my.count != 0);                      // windows to come
-    uint32_t w = 0, n = 0, first = 0, count = 0;
-    auto fetch = [&](RunBatch &b) {                              // past the last window: a batch of nothing
-        if (n >= count && todo != 0) {
-            w = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1ull;
-            n = 0;
-            first = of_lane(my.first, w);
-            count = of_lane(my.count, w);
-        }
-        const uint32_t left = n < count ? count - n : 0u;
-        load(b, w, first + (left ? n : 0u), left, of_lane(my.delta, w));
-        n += kRunAhead;
-        return left != 0;
-    };
-    RunBatch even, odd;
-    for (bool more = todo != 0 && fetch(even); more;) {
-        fetch(odd);
-        serve(even);
-        more = fetch(even);
-        serve(odd);
-    }
-    for (uint64_t wrapped = __ballot(my.over != 0); wrapped != 0; wrapped &= wrapped - 1ull) {
-        const uint32_t x = (uint32_t)__builtin_ctzll(wrapped), end = of_lane(my.over, x);
-        for (n = 0; n < end; n += kRunAhead) {
-            load(even, x, n, end - n, of_lane(my.delta, x) + 4u * p.m);
-            serve(even);
-        }
-    }
+    RunWalk k;
+    k.my = my;
+    k.my_base = my_base;
+    k.my_width = my_width;
+    k.wave = wave;
+    k.len4 = 4u * len;
+    k.last_tile = last_tile;
+    k.r_mask = l.place.r_mask;
+    // (short windows: the tiles after the first would mostly be requested in vain, and the walk is bound by what it issues.  208 K
+    // lookups, d = 128, tables of up to 100 K ids, 50 M slots, whole backward: Z = 1 204 -> 176 us, Z = 2 193 -> 169; 117 entries
+    // a window, 852 K lookups: 275, one at a time 278)
+    if (((uint64_t)used << kPlaceShift) <= (uint64_t)kRunShort * p.m) run_walk<1>(p, k, entries, tiles, acc);
+    else run_walk<kRunAhead>(p, k, entries, tiles, acc);
     __syncthreads();
     run_write_back<RULE>(s, acc, r0, len, dst, state, lr, eps, vec_ok);
 }

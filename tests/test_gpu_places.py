@@ -55,7 +55,7 @@ def test_served_rows_have_the_gathered_bits(m, d, Z, F, kind, sign):
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
 
 
-@pytest.mark.parametrize("m,d,Z,off,launches", [(2**23 - 1, 128, 1, 0, 5), (2**23, 100, 1, 0, 5), (2**23, 128, 4, 0, 5), (2**23, 128, 1, 1, 5), (2**28, 128, 1, 0, 5),
+@pytest.mark.parametrize("m,d,Z,off,launches", [(2**23 - 1, 128, 1, 0, 5), (2**23, 100, 1, 0, 5), (2**23, 128, 4, 0, 5), (2**23, 128, 1, 1, 5), (2**26, 128, 1, 0, 5),
                                                 (2**23, 128, 1, 4, 8)])
 def test_what_takes_the_route(m, d, Z, off, launches):
     F = 26
