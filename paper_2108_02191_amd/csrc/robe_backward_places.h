@@ -119,7 +119,8 @@ __global__ __launch_bounds__(kRunBlock) void run_turn_kernel(Params p, RegionPla
     __shared__ float turn[kRunTurn][65];
     __shared__ uint32_t src[64], tg[SIGN ? 64 : 1];
     const uint32_t used = runs_used(l.place), tile = blockIdx.x, t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    constexpr uint32_t kWaves = kRunBlock / 64u, kAhead = 8;
+    constexpr uint32_t kWaves = kRunBlock / 64u, kAhead = 16;
+    static_assert(64u % (kWaves * kAhead) == 0, "every step takes runs of the tile alone");
     if (tile * 64u >= used) return;
     const uint32_t count = min(64u, used - tile * 64u);
     if (t < 64u) {                                               // past the last run: its row, for the values 0

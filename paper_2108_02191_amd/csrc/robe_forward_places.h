@@ -21,8 +21,8 @@
 // The lists (two and a half words a lookup) lie in the last samples' rows until D4.  What has no room - ids that hardly
 // repeat leave few rows free - is gathered by F2 as before.
 //
-// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 588 -> 290 us (D1 30 instead
-// of 24, F1 8, F2 9, F3 95, F4 38, D3 73, D4 30 instead of 15, clearing 6, where the gather took 440).  F3 has three parts
+// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 588 -> 275 us (D1 30 instead
+// of 24, F1 8, F2 9, F3 85, F4 33, D3 72, D4 30 instead of 15, clearing 6, where the gather took 440).  F3 has three parts
 // that hardly overlap: its region's load 35, the walk 32, the stores 28 (161 MB, as a line's elements come from two windows).  A
 // hash and a page of its own for every entry instead of keys that compare packed and one page a tile: 112.  Regions of
 // 2^13 floats: 110; of 2^15, one workgroup per CU: 91 (short of entries for so long windows elsewhere); every
@@ -37,7 +37,7 @@ constexpr uint32_t kPlaceShift = 14;          // floats of a region: 64 KB of LD
 constexpr uint32_t kPlaceBlock = 1024;
 constexpr uint32_t kPlaceAhead = 3;           // tiles whose loads are requested together
 constexpr uint32_t kPlaceMostSegments = 32;
-constexpr uint32_t kPlaceTurn = 128;          // elements of a tile turned round at a time
+constexpr uint32_t kPlaceTurn = 64;           // elements of a tile turned round at a time (128, more LDS for fewer steps: 38 us instead of 33)
 constexpr uint32_t kPlaceMostD = 512;
 
 constexpr size_t kPlaceLds = ((size_t)4 << kPlaceShift) + 16;       // of F3: the region, and a float past it for blocks of two
