@@ -1,8 +1,10 @@
 // C ABI of the ROBE-Z library (see include/robe.h): argument validation,
 // launch geometry and kernel selection.  All device work is in robe_kernels.h
-// (forward, direct backward, update rules), robe_backward_dedup.h (sorted
+// (forward, direct backward, update rules), robe_forward_distinct.h and
+// robe_forward_places.h (forward of small blocks), robe_backward_dedup.h (sorted
 // backward with float atomics), robe_backward_regions.h (sorted backward
-// without them, fused Adagrad) and robe_radix_sort.h (the token sort).
+// without them, fused Adagrad), robe_backward_places.h (that of small blocks) and
+// robe_radix_sort.h (the token sort).
 //
 // Nothing here is process-wide state: every choice a call makes follows from
 // its arguments and its robe_options_t (NULL = all defaults).
@@ -933,7 +935,7 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
     pl.bytes = off;
 
     // Region-sorted scatter on top of the combined runs.
-    // Small blocks: the pairs of every element sorted by region, where nothing else is asked for.
+    // Small blocks: the runs by place, where nothing else is asked for.
     const uint64_t elem_regions = (h->m + (1u << robe::kPlaceShift) - 1) >> robe::kPlaceShift;
     const uint64_t elems = (uint64_t)n * h->d, room = elems < elem_room(h->m) ? elems : elem_room(h->m);
     const bool elements = h->Z <= kElemMostZ && !opt.reproducible && mixed_floats == 0 && route == ROBE_ROUTE_AUTO &&
@@ -1800,7 +1802,7 @@ int robe_backward_noalloc(const robe_hash_t *hash, const float *grad_out, const 
     if (int rc = robe_workspace_bytes(hash, batch, n_features, n_indices, options, &need)) return rc;
     // Where nothing is asked for, small calls scatter directly whatever sorting would gain: the buffer is
     // shared by all streams and threads of a GPU, and calls that use it must not overlap.  Larger ones
-    // sort, with atomics (the pairs of small blocks would not fit).
+    // sort, with atomics (the rows of small blocks' runs would not fit).
     robe_options_t routed;
     if (need > 0 && (options == nullptr || (options->backward_route == ROBE_ROUTE_AUTO && !options->reproducible))) {
         if (options != nullptr) routed = *options;
@@ -1927,7 +1929,7 @@ static bool fused_plan(const robe_hash_t *hash, const Opt &opt, int64_t rows, in
         if (pl->regions && (!pl->elements || pl->all_fit)) return true;
     }
     *pl = plan_backward(hash, opt, rows, n_indices, bags, grad_out);
-    // small blocks: the pairs' workgroups apply the rule, whatever the array size, if they are sure to get all pairs
+    // small blocks: the regions' workgroups apply the rule, whatever the array size, if they are sure to get all runs
     if (opt.fused_route == ROBE_ROUTE_AUTO && pl->elements && pl->all_fit) return true;
     if (!pl->elements) pl->regions = false;              // the two-step fallback adds onto a gradient array
     *scratch_bytes = align_up((size_t)hash->m * 4, 256);
