@@ -459,7 +459,8 @@ int allow_lds(K kernel, size_t bytes, const char *what)
 //   Z = 2, 25 M, 468 K 384 / 239 (610 / 630);  d = 64, 9 M, 520 K 345 / 243 (578 / 608);  d = 512, 25 M, 78 K 532 / 497 (744 / 762)
 // 26 tables, spaced evenly on a log scale, of 10 ids and up to 100 K, to 3 M, to 40 M:
 //   Z = 1, 10 M slots, 208 K 138 / 104, 169 / 108, 193 / 113;  25 M, 208 K 144 / 131, 180 / 135, 203 / 137, 852 K 323 / 224, 471 / 243,
-//   571 / 265;  50 M, 416 K 209 / 243, 288 / 228, 337 / 238;  Z = 2, 10 M, 468 K 151 / 131, 196 / 149, 224 / 164;  50 M, 858 K 238 / 270, 320 / 271
+//   571 / 265;  50 M, 414 K 210 / 219, 288 / 222, 337 / 232;  Z = 2, 10 M, 468 K 151 / 131, 196 / 149, 224 / 164;  50 M, 859 K 240 / 254, 323 / 262
+// (where the tables hold too few distinct tokens, 210 / 219 and 240 / 254, the lists are turned down: see PlacePlan::least)
 // Blocks of four (where this was not kept): 25 M, 852 K, to 40 M 311 / 242, never repeating 600 / 671; 520 K 191 / 174, 367 / 419.
 bool places_pay(const robe_hash_t *h, int64_t rows, const float *out)
 {
@@ -492,13 +493,14 @@ void plan_places(const robe_hash_t *h, int64_t rows, robe::PlacePlan *s, uint64_
     s->page_recip = (65536 + s->page_elems - 1) / s->page_elems;
     s->out_bytes = (uint32_t)(rows * (int64_t)h->d * 4);
     *list_words = (((uint64_t)s->buckets + 4) & ~3ull) + 4 + 2ull * s->most + (uint64_t)s->segments * s->segment_rows + 2 * robe::kPlacePad;
-    *count_words = (((uint64_t)s->buckets + 3) & ~3ull) + s->segments;
+    *count_words = (((uint64_t)s->buckets + 3) & ~3ull) + s->segments + 1;
 }
 
 void lay_out_places(uint32_t *counts, uint32_t *lists, robe::PlacePlan *s)
 {
     s->counts = counts;
     s->free_count = counts + (((uint64_t)s->buckets + 3) & ~3ull);
+    s->total = s->free_count + s->segments;
     s->starts = lists;
     s->used = lists + (((uint64_t)s->buckets + 4) & ~3ull);
     s->entries = s->used + 4;
@@ -523,7 +525,14 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
     const uint64_t skip = aligned(out, 8) ? 0 : 1;
     int64_t keep = 0;
     auto fits = [&] {
-        const int64_t last = ((int64_t)list_words + rows + h->d - 1) / h->d;
+        int64_t last = ((int64_t)list_words + rows + h->d - 1) / h->d;
+        if (by_place) {
+            // and those of tail_rep: as many workgroups of D4 as CUs, where there are rows enough (d = 512, 78 K lookups, D4
+            // with 32 words a row whatever their number 13 us, 10.5 so)
+            lists.tail_shift = log2u(robe::kLastMost);
+            while (lists.tail_shift > 3 && last >> lists.tail_shift < 256) --lists.tail_shift;
+            last += (last >> lists.tail_shift) + 1;
+        }
         keep = batch - (last + F - 1) / F;
         return keep >= 1 && skip + 2 * places + count_words <= (uint64_t)keep * F * h->d;
     };
@@ -544,7 +553,14 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
     uint32_t *lists_at = reinterpret_cast<uint32_t *>(out + (uint64_t)s.n * h->d);
     s.rep = lists_at + list_words;
     s.least_repeats = robe::distinct_least_repeats((uint64_t)batch);
-    if (by_place) lay_out_places(reinterpret_cast<uint32_t *>(s.table) + 2 * places, lists_at, &lists);
+    if (by_place) {
+        lay_out_places(reinterpret_cast<uint32_t *>(s.table) + 2 * places, lists_at, &lists);
+        const uint32_t past = (uint32_t)(rows - s.n);
+        lists.ends = (past + (1u << lists.tail_shift)) / ((1u << lists.tail_shift) + 1u);
+        lists.tail = past - lists.ends;
+        lists.tail_rep = reinterpret_cast<uint32_t *>(out + (uint64_t)(rows - lists.ends) * h->d);
+    }
+    const uint32_t F_recip = reciprocal(F);
     const bool sign = h->use_sign != 0;
     if (int rc = launch_fill(reinterpret_cast<uint32_t *>(s.table), 2 * places + count_words, 0u, stream, "forward (clear table)")) return rc;
     const dim3 tiles((s.n + robe::kDistinctTile - 1) / robe::kDistinctTile), find(robe::kDistinctBlock);
@@ -556,13 +572,17 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
     const uint32_t waves = (s.n + robe::kDistinctRows - 1) / robe::kDistinctRows;
     const dim3 grid(waves), block(robe::kRowBlock);
     if (by_place) {
-        robe::place_scan_kernel<<<dim3(1), dim3(robe::kScanThreads), 0, stream>>>(lists);
+        const dim3 sgrid(1 + (lists.tail + robe::kScanThreads - 1) / robe::kScanThreads), sblock(robe::kScanThreads);
+        if (sign) robe::place_scan_kernel<true><<<sgrid, sblock, 0, stream>>>(p, s, lists, F_recip, indices);
+        else robe::place_scan_kernel<false><<<sgrid, sblock, 0, stream>>>(p, s, lists, F_recip, indices);
         if (int rc = check_launch("forward (scan)")) return rc;
     }
-    const dim3 pgrid((s.n + robe::kRowBlock - 1) / robe::kRowBlock);
+    const uint32_t copy_g = h->d % 4 == 0 && aligned(out, 16) ? (log2u(h->d / 4) < 6 ? log2u(h->d / 4) : 6u) : (log2u(h->d) < 6 ? log2u(h->d) : 6u);
+    auto gather = [&](bool last) {
 #define ROBE_DISTINCT_S(V_, C_, S_)                                                                                   \
     do {                                                                                                              \
-        if (by_place) robe::place_tokens_kernel<V_, C_, S_, AT><<<pgrid, block, 0, stream>>>(p, q, s, lists, array, indices, out); \
+        if (last) robe::place_last_kernel<V_, C_, S_, AT><<<dim3(lists.ends), dim3((64u << lists.tail_shift) / robe::kLastRows), 0, stream>>>(p, q, s, lists, F_recip, copy_g, array, indices, out); \
+        else if (by_place) robe::place_tokens_kernel<V_, C_, S_, AT><<<grid, block, 0, stream>>>(p, q, s, lists, array, indices, out); \
         else robe::distinct_gather_kernel<V_, C_, S_, AT><<<grid, block, 0, stream>>>(p, q, s, array, indices, out);  \
     } while (0)
 #define ROBE_DISTINCT(V_, C_)                                                                                         \
@@ -570,24 +590,26 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
         if (sign) ROBE_DISTINCT_S(V_, C_, true);                                                                      \
         else ROBE_DISTINCT_S(V_, C_, false);                                                                          \
     } while (0)
-    if (lay.consec) {
-        switch (lay.V) {
-            case 1: ROBE_DISTINCT(1, true); break;
-            case 2: ROBE_DISTINCT(2, true); break;
-            default: ROBE_DISTINCT(4, true); break;
+        if (lay.consec) {
+            switch (lay.V) {
+                case 1: ROBE_DISTINCT(1, true); break;
+                case 2: ROBE_DISTINCT(2, true); break;
+                default: ROBE_DISTINCT(4, true); break;
+            }
+        } else {
+            switch (lay.V) {
+                case 1: ROBE_DISTINCT(1, false); break;
+                case 2: ROBE_DISTINCT(2, false); break;
+                case 3: ROBE_DISTINCT(3, false); break;
+                case 6: ROBE_DISTINCT(6, false); break;
+                case 8: ROBE_DISTINCT(8, false); break;
+                default: ROBE_DISTINCT(4, false); break;
+            }
         }
-    } else {
-        switch (lay.V) {
-            case 1: ROBE_DISTINCT(1, false); break;
-            case 2: ROBE_DISTINCT(2, false); break;
-            case 3: ROBE_DISTINCT(3, false); break;
-            case 6: ROBE_DISTINCT(6, false); break;
-            case 8: ROBE_DISTINCT(8, false); break;
-            default: ROBE_DISTINCT(4, false); break;
-        }
-    }
 #undef ROBE_DISTINCT
 #undef ROBE_DISTINCT_S
+    };
+    gather(false);
     if (int rc = check_launch("forward (distinct)")) return rc;
     if (by_place) {
         const size_t lds = robe::kPlaceLds;
@@ -603,20 +625,22 @@ int launch_distinct(const robe_hash_t *h, const Opt &opt, const Layout &lay, con
 #undef ROBE_PLACE_REGIONS
         if (int rc = check_launch("forward (regions)")) return rc;
         const dim3 turns(lists.most / 64u), turn(256);
-        if (sign) robe::place_rows_kernel<true><<<turns, turn, 0, stream>>>(p, lists, F, reciprocal(F), indices, out);
-        else robe::place_rows_kernel<false><<<turns, turn, 0, stream>>>(p, lists, F, reciprocal(F), indices, out);
+        if (sign) robe::place_rows_kernel<true><<<turns, turn, 0, stream>>>(p, lists, F, F_recip, indices, out);
+        else robe::place_rows_kernel<false><<<turns, turn, 0, stream>>>(p, lists, F, F_recip, indices, out);
         if (int rc = check_launch("forward (rows)")) return rc;
     }
     const uint32_t per_xcd = (waves + robe::kXcds - 1) / robe::kXcds;
     const dim3 spread(per_xcd * robe::kXcds);
     if (h->d % 4 == 0 && aligned(out, 16)) {
-        const uint32_t g = log2u(h->d / 4) < 6 ? log2u(h->d / 4) : 6u;
-        robe::distinct_copy_kernel<4><<<spread, block, 0, stream>>>(s, h->d, g, per_xcd, out);
+        robe::distinct_copy_kernel<4><<<spread, block, 0, stream>>>(s, h->d, copy_g, per_xcd, out);
     } else {
-        const uint32_t g = log2u(h->d) < 6 ? log2u(h->d) : 6u;
-        robe::distinct_copy_kernel<1><<<spread, block, 0, stream>>>(s, h->d, g, per_xcd, out);
+        robe::distinct_copy_kernel<1><<<spread, block, 0, stream>>>(s, h->d, copy_g, per_xcd, out);
     }
     if (int rc = check_launch("forward (copy)")) return rc;
+    if (by_place) {
+        gather(true);
+        return check_launch("forward (last)");
+    }
     // the last samples (a requested layout keeps this call off the path above)
     Opt plain = opt;
     plain.row_order = ROBE_ROWS_BY_TABLE;

@@ -65,11 +65,16 @@ struct PlacePlan {
     uint32_t segments, segment_shift;    // the free rows lie in so many lists (a power of two), by D1's workgroups in turn; tile t has the
     uint32_t segment_rows;               // next 64 of list t mod segments.  Room of each list, a multiple of 64
     uint32_t *free_count;                // [segments] rows of each list
+    uint32_t *total;                     // lookups that gather for themselves
     uint32_t *pages;                     // [tiles][64] the free rows, as multiples of 64 floats: row * page_elems
     uint32_t out_bytes;
     uint32_t page_elems, page_recip;     // d / 64; ceil(2^16 / page_elems): i / page_elems = i * page_recip >> 16 for i < 512
-    uint32_t *used;                      // entries that have room and whose tiles find free rows; the others' rows are gathered
+    uint32_t *used;                      // entries that have room and whose tiles find free rows; the others' rows are gathered.  Behind it: whether there are others
+    uint32_t tail, ends;                 // rows from n on that have a word in tail_rep; the rows after those, which hold the words
+    uint32_t *tail_rep;                  // [ends][d], 2^tail_shift words of each: see place_last_kernel
+    uint32_t tail_shift;
 };
+constexpr uint32_t kLastMost = 32;             // most words of such a row, 1 << tail_shift
 constexpr uint32_t kPlacePad = 256;            // words past the end of the lists that F3 may read
 constexpr uint32_t kPlaceSelf = 0x80000000u;   // in rep: the row gathers for itself, and the lower bits say which of its bucket it is
 
@@ -79,6 +84,9 @@ __device__ __forceinline__ uint32_t distinct_row(const DistinctPlan &s, uint32_t
     f = div_m(q, s.batch, s.batch_recip);
     return (q - f * s.batch) * s.F + f;
 }
+
+// Where a token's walk through the table in memory starts (modulo its places).
+__device__ __forceinline__ uint32_t table_place(uint32_t h, uint32_t g) { return ((h ^ (g << 7)) * 0x85EBCA6Bu) ^ (h >> 13); }
 
 template <bool SIGN, bool PLACES>
 __global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p, DistinctPlan s, PlacePlan lists, const int64_t *__restrict__ indices)
@@ -143,7 +151,7 @@ __global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p,
             continue;
         }
         const uint64_t entry = ((uint64_t)(h[i] + 1u) << 32) | row[i];
-        uint32_t at = ((h[i] ^ (g[i] << 7)) * 0x85EBCA6Bu) ^ (h[i] >> 13);
+        uint32_t at = table_place(h[i], g[i]);
         for (uint32_t tries = 0; tries < kDistinctProbes; ++tries, ++at) {
             uint64_t *slot = s.table + (at & s.mask);
             uint64_t there = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -195,7 +203,10 @@ __global__ __launch_bounds__(kDistinctBlock) void distinct_find_kernel(Params p,
                 if (k == i * (kDistinctBlock / 64u) + wave) mine[i] = all;
             all += free_n[k];
         }
-        if (t == 0) free_first = atomicAdd(&lists.free_count[seg], all);
+        if (t == 0) {
+            free_first = atomicAdd(&lists.free_count[seg], all);
+            atomicAdd(lists.total, min(kDistinctTile, s.n - base) - all);
+        }
         __syncthreads();
 #pragma unroll
         for (uint32_t i = 0; i < kDistinctPer; ++i) {
@@ -266,21 +277,14 @@ __global__ __launch_bounds__(kRowBlock) void distinct_gather_kernel(Params p, Ge
     gather_rows<V, CONSEC, SIGN>(p, q, self, __ballot(self), row, th, tg, array, out);
 }
 
-// W: floats per lane and access (4 where rows are aligned for it).  A row is G lanes' work, in several steps if longer.
+// The lanes with `copy`: row `from` of out to row `row`.  W: floats per lane and access (4 where rows are aligned for it).  A row
+// is G lanes' work, in several steps if longer.
 template <int W>
-__global__ __launch_bounds__(kRowBlock) void distinct_copy_kernel(DistinctPlan s, uint32_t d, uint32_t g_shift, uint32_t per_xcd, float *__restrict__ out)
+__device__ __forceinline__ void copy_rows(bool copy, uint32_t row, uint32_t from, uint32_t d, uint32_t g_shift, float *__restrict__ out)
 {
     typedef typename Vec<W>::A T;
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t block = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;      // an eighth of the tables' order per XCD, see RowWalk
-    const uint64_t at = (uint64_t)block * kDistinctRows + lane;
-    uint32_t f = 0, row = 0, from = 0, unused = 0;
-    bool copy = false;
-    if (lane < kDistinctRows && at < s.n) {
-        row = distinct_row(s, (uint32_t)at, f);
-        from = s.rep[at];
-        copy = from != row && from < s.n;                      // (rows of these samples are below n)
-    }
+    uint32_t unused = 0;
     const uint32_t n = to_front(copy, __ballot(copy), row, from, unused);
     const uint32_t G = 1u << g_shift, grp = lane & (G - 1u), sub = lane >> g_shift, step = 64u >> g_shift;
     for (uint32_t r = 0; r < n; r += step * kUnroll) {         // trip count uniform over the wavefront
@@ -302,6 +306,22 @@ __global__ __launch_bounds__(kRowBlock) void distinct_copy_kernel(DistinctPlan s
                 if (live[u]) __builtin_nontemporal_store(v[u], reinterpret_cast<T *>(out + (uint64_t)to[u] * d + i));
         }
     }
+}
+
+template <int W>
+__global__ __launch_bounds__(kRowBlock) void distinct_copy_kernel(DistinctPlan s, uint32_t d, uint32_t g_shift, uint32_t per_xcd, float *__restrict__ out)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t block = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;      // an eighth of the tables' order per XCD, see RowWalk
+    const uint64_t at = (uint64_t)block * kDistinctRows + lane;
+    uint32_t f = 0, row = 0, from = 0;
+    bool copy = false;
+    if (lane < kDistinctRows && at < s.n) {
+        row = distinct_row(s, (uint32_t)at, f);
+        from = s.rep[at];
+        copy = from != row && from < s.n;                      // (rows of these samples are below n)
+    }
+    copy_rows<W>(copy, row, from, d, g_shift, out);
 }
 
 }  // namespace robe

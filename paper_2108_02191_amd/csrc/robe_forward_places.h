@@ -10,20 +10,26 @@
 //
 //   D1 find     as in robe_forward_distinct.h; a lookup that gathers for itself also counts in a bucket of r (an
 //               integer atomic, which says how many were there before), the others' rows are listed as free.
-//   F1 scan     first entry of every bucket.
+//   F1 scan     first entry of every bucket, if there are entries enough.  Beside it the tokens of the last samples, which hold the
+//               lists, are looked up in D1's table.
 //   F2 place    the lookups that gather for themselves enter their key and row in the list.
 //   F3 regions  a workgroup per 2^14 slots.  What it finds leaves in tiles of 64 entries, element by element
 //               (consecutive lanes write consecutive words).  A tile lies in 64 of the free rows, which no one else
 //               needs before D3.
 //   F4 rows     a workgroup per tile turns it round and writes the tokens' rows.
-//   D3 copy, D4 as there.
+//   D3 copy     as there.
+//   D4 last     the last samples' rows: copied where F1 found the token, else gathered.
 //
 // The lists (two and a half words a lookup) lie in the last samples' rows until D4.  What has no room - ids that hardly
-// repeat leave few rows free - is gathered by F2 as before.
+// repeat leave few rows free - is gathered by F2 as D2 does there, and so are all where there are too few entries (PlacePlan::least):
+// such a call costs what F1, F3 and F4 take to start and D1's counts, 10 to 15 us more than one without lists.  It was a
+// quarter of the call and more while F2 gathered 64 rows a wavefront and D4 all of its rows: uniform ids, d = 128, gathered / by
+// place: Z = 1, 413 K lookups of 31 K distinct tokens, 53 M slots 192 / 274 us then, 189 / 202 now; Z = 2, 858 K of 62 K, 55 M 244 / 356,
+// 245 / 260; Z = 1, 780 K of 31 K, 100 M 228 / 344, 229 / 240.
 //
-// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 588 -> 275 us (D1 30 instead
-// of 24, F1 8, F2 9, F3 85, F4 33, D3 72, D4 30 instead of 15, clearing 6, where the gather took 440).  F3 has three parts
-// that hardly overlap: its region's load 35, the walk 32, the stores 28 (161 MB, as a line's elements come from two windows).  A
+// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 575 -> 258 us (D1 30 instead
+// of 24, F1 8, F2 9, F3 80, F4 35, D3 72 instead of 98, D4 17 instead of 14 (29 with all of its rows gathered), clearing 6, where
+// the gather took 434).  F3 (76 to 85 us in several runs, 85 beside the variants below) has three parts that hardly overlap: its region's load 35, the walk 32, the stores 28 (161 MB, as a line's elements come from two windows).  A
 // hash and a page of its own for every entry instead of keys that compare packed and one page a tile: 112.  Regions of
 // 2^13 floats: 110; of 2^15, one workgroup per CU: 91 (short of entries for so long windows elsewhere); every
 // workgroup three regions, the next loaded during the walk: 100 (the walk's loads then wait for it).
@@ -39,6 +45,7 @@ constexpr uint32_t kPlaceAhead = 3;           // tiles whose loads are requested
 constexpr uint32_t kPlaceMostSegments = 32;
 constexpr uint32_t kPlaceTurn = 64;           // elements of a tile turned round at a time (128, more LDS for fewer steps: 38 us instead of 33)
 constexpr uint32_t kPlaceMostD = 512;
+constexpr uint32_t kLastRows = 2;             // rows of a wavefront of D4: most are copied, all at once
 
 constexpr size_t kPlaceLds = ((size_t)4 << kPlaceShift) + 16;       // of F3: the region, and a float past it for blocks of two
 
@@ -59,32 +66,65 @@ __device__ __forceinline__ uint32_t places_used(const PlacePlan &s, uint32_t tot
     return used >= s.least ? used : 0u;
 }
 
-__global__ __launch_bounds__(kScanThreads) void place_scan_kernel(PlacePlan s)
+// The word of row n + i, i < tail: the row that has its token, or kPlaceSelf.
+__device__ __forceinline__ uint32_t *tail_word(const PlacePlan &s, uint32_t d, uint32_t i)
+{
+    return s.tail_rep + (uint64_t)(i >> s.tail_shift) * d + (i & ((1u << s.tail_shift) - 1u));
+}
+
+// Workgroup 0 scans, the others look the last samples' tokens up: the table is whole now, and still there.
+template <bool SIGN>
+__global__ __launch_bounds__(kScanThreads) void place_scan_kernel(Params p, DistinctPlan d, PlacePlan s, uint32_t F_recip, const int64_t *__restrict__ indices)
 {
     __shared__ uint32_t wave_sum[kScanThreads / 64u];
-    uint32_t c[kScanPer];
-    const uint32_t total = scan_counts(s.counts, s.starts, s.buckets, c, wave_sum);
-    const uint32_t used = places_used(s, total, threadIdx.x & 63u);
-    if (threadIdx.x == 0) *s.used = used;
+    if (blockIdx.x == 0) {
+        const uint32_t total = *s.total, used = places_used(s, total, threadIdx.x & 63u);
+        if (threadIdx.x == 0) {
+            s.used[0] = used;
+            s.used[1] = used < total;
+        }
+        uint32_t c[kScanPer];
+        if (used != 0) scan_counts(s.counts, s.starts, s.buckets, c, wave_sum);
+        return;
+    }
+    const uint32_t i = (blockIdx.x - 1u) * kScanThreads + threadIdx.x;
+    if (i >= s.tail) return;
+    const uint32_t row = d.n + i, f = mod_m(row, d.F, F_recip);
+    const int64_t x = indices[row];
+    const uint32_t th = staged_h(p, x, f), tg = SIGN ? staged_g(p, x, f) : 0u;
+    uint32_t found = kPlaceSelf, at = table_place(th, tg);
+    for (uint32_t tries = 0; tries < kDistinctProbes; ++tries, ++at) {
+        const uint64_t there = d.table[at & d.mask];
+        if (there == 0) break;
+        if ((uint32_t)(there >> 32) != th + 1u) continue;
+        const uint32_t first = (uint32_t)there;
+        if constexpr (SIGN) {
+            if (staged_g(p, indices[first], mod_m(first, d.F, F_recip)) != tg) continue;
+        }
+        found = first;
+        break;
+    }
+    *tail_word(s, p.d, i) = found;
 }
 
 template <int V, bool CONSEC, bool SIGN, typename AT>
 __global__ __launch_bounds__(kRowBlock) void place_tokens_kernel(Params p, Geom q, DistinctPlan d, PlacePlan s, const AT *__restrict__ array,
                                                                  const int64_t *__restrict__ indices, float *__restrict__ out)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t at = blockIdx.x * kRowBlock + lane;
-    const uint32_t used = *s.used;
+    const uint32_t lane = threadIdx.x & 63u, used = *s.used;
+    // nothing to gather: 64 positions a wavefront, and half the wavefronts have none; else as D2 of robe_forward_distinct.h
+    const uint32_t per = s.used[1] == 0 ? kRowBlock : kDistinctRows;
+    const uint64_t at = (uint64_t)blockIdx.x * per + lane;
     uint32_t f = 0, row = 0, th = 0, tg = 0;
     bool self = false;
-    if (at < d.n) {
-        row = distinct_row(d, at, f);
+    if (lane < per && at < d.n) {
+        row = distinct_row(d, (uint32_t)at, f);
         const uint32_t w = d.rep[at];
         self = (w & kPlaceSelf) != 0;
         if (self) {
             const int64_t x = indices[row];
             th = staged_h(p, x, f);
-            const uint32_t r = mod_m(th, p.m, p.m_recip), k = s.starts[r >> s.bucket_shift] + (w & ~kPlaceSelf);
+            const uint32_t r = mod_m(th, p.m, p.m_recip), k = used ? s.starts[r >> s.bucket_shift] + (w & ~kPlaceSelf) : 0u;
             if (k < used) {
                 s.entries[k] = place_entry(p, s, th, r);
                 s.row[k] = row;
@@ -301,6 +341,39 @@ __global__ __launch_bounds__(256) void place_rows_kernel(Params p, PlacePlan s, 
         }
         __syncthreads();
     }
+}
+
+// The rows past n, when all others are final: copied where F1 found who has the token, else gathered.  A workgroup's words lie in
+// one of the last rows, which it writes when all its wavefronts have read them.
+template <int V, bool CONSEC, bool SIGN, typename AT>
+__global__ __launch_bounds__(kLastMost * 64 / kLastRows) void place_last_kernel(Params p, Geom q, DistinctPlan d, PlacePlan s, uint32_t F_recip, uint32_t g_shift,
+                                                                                const AT *__restrict__ array, const int64_t *__restrict__ indices, float *__restrict__ out)
+{
+    __shared__ uint32_t words[kLastMost];
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, first = blockIdx.x << s.tail_shift;
+    const uint32_t live = min(1u << s.tail_shift, s.tail > first ? s.tail - first : 0u);
+    if (t < live) words[t] = *tail_word(s, p.d, first + t);
+    __syncthreads();
+    const uint32_t i = wave * kLastRows + lane;
+    uint32_t row = d.n + first + i, from = kPlaceSelf, th = 0, tg = 0;
+    bool self = false, copy = false;
+    if (lane < kLastRows && i < live) {
+        from = words[i];
+        self = from == kPlaceSelf;
+        copy = !self;
+    } else if (wave == 0 && lane == kLastRows) {
+        row = d.n + s.tail + blockIdx.x;
+        self = true;
+    }
+    if (self) {
+        const uint32_t f = mod_m(row, d.F, F_recip);
+        const int64_t x = indices[row];
+        th = staged_h(p, x, f);
+        if constexpr (SIGN) tg = staged_g(p, x, f);
+    }
+    copy_rows<4>(copy, row, from, p.d, g_shift, out);
+    const uint64_t plain = __ballot(self);
+    if (plain) gather_rows<V, CONSEC, SIGN>(p, q, self, plain, row, th, tg, array, out);
 }
 
 }  // namespace robe
