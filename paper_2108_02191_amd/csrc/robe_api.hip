@@ -482,8 +482,19 @@ void plan_places(const robe_hash_t *h, int64_t rows, robe::PlacePlan *s, uint64_
 {
     plan_buckets(h->m, s);
     s->most = (uint32_t)(rows / 2) & ~63u;
-    // fewer are gathered: a million lines take 19 us so, 4 by place, which costs some 35 before the first one at 25 M slots
-    s->least = (uint32_t)(h->m / 8 / (h->d / h->Z)) + 1;
+    // Fewer are gathered: a million lines take 19 us so, 4 by place, which costs some 35 before the first one at 25 M slots, a region's
+    // load and short windows of its chunks.  The line in entries a region and chunk, 16 being m / 1024 tokens: 16 with 128 chunks,
+    // twice that with 64.  With more chunks the array's load counts less, the windows stay: half of the 16 or a quarter, as the lines alone
+    // would have it, is where calls by place took up to half as long again.  Zipf ids, 26 tables spaced evenly on a log scale of 10 ids and
+    // up to 10 K .. 3 M, gathered / by place, us (tokens as a share of m / 1024):
+    //   d = 512, Z = 1  25 M slots, 78 K lookups 231 / 268 (0.53), 266 / 272 (0.71), 306 / 274 (0.91);  147 K 307 / 299 (0.59), 344 / 298 (0.78)
+    //                   50 M, 100 K 265 / 448 (0.31), 330 / 462 (0.45), 413 / 470 (0.65);  293 K 514 / 551 (0.58), 597 / 559 (0.76)
+    //   d = 256, Z = 1  25 M, 100 K 146 / 171 (0.62), 167 / 171 (0.84), 183 / 174 (1.00);  195 K 191 / 190 (0.67)
+    //                   50 M, 199 K 221 / 242 (0.46), 265 / 293 (0.67), 303 / 299 (0.83);  586 K 402 / 392 (0.82)
+    //   d = 512, Z = 2  25 M, 100 K 173 / 223 (0.62), 213 / 226 (1.00), 248 / 234 (1.30);  50 M, 586 K 542 / 564 (0.82), 594 / 573 (1.01)
+    const uint64_t C = h->d / h->Z;
+    if (C <= 128) s->least = (uint32_t)(h->m / 8 / C) + 1;
+    else s->least = (uint32_t)(h->Z == 1 ? h->m / 1024 * 5 / 8 + h->m * 3 / 64 / C : h->m / 1024) + 1;
     // a list for at least sixteen workgroups of D1, whose additions to a list's counter go one by one
     s->segments = 1;
     while (s->segments < robe::kPlaceMostSegments && (uint64_t)rows >= 32ull * s->segments * robe::kDistinctTile) s->segments <<= 1;

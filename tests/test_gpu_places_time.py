@@ -51,6 +51,12 @@ def test_lists_turned_down_cost_little(d, Z, F, B, each):
     assert _by_place_over_gathered(d, Z, F, B, _uniform(B, F, each)) < 1.2
 
 
+# (rows of 512 chunks: as many lines as would do with 128 lie in windows of few entries.  1.01, 1.03; served all the same 1.29, 1.50)
+@pytest.mark.parametrize("d,Z,F,B,each", [(512, 1, 26, 3840, 820), (512, 1, 26, 3840, 540)])
+def test_wide_rows_are_served_where_it_pays(d, Z, F, B, each):
+    assert _by_place_over_gathered(d, Z, F, B, _uniform(B, F, each)) < 1.2
+
+
 # (twice the ids that are worth it and more, each several times: 0.66, 0.76, 0.64)
 @pytest.mark.parametrize("d,Z,F,B,each", [(128, 1, 26, 15_900, 4000), (128, 2, 26, 33_000, 8000), (64, 1, 26, 34_000, 8000)])
 def test_lists_served_pay(d, Z, F, B, each):
