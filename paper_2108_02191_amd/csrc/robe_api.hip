@@ -849,7 +849,7 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 // since (below), against float atomics, us: forward + backward on the 100 MB array, d = 128, 852 K lookups, atomics / pairs
 // Z = 1 2353 / 1551, Z = 2 1266 / 1007, Z = 4 750 / 772; Z = 1 with 13 K, 52 K, 208 K lookups 140 / 188, 255 / 251, 725 / 486.
 // Backward alone, atomics / pairs:
-//   the last kernel has one workgroup per 2^14 slots: from 32 of them on.  Z = 2, 858 K lookups of d = 128,
+//   the last kernel had one workgroup per 2^14 slots: from 32 of them on.  Z = 2, 858 K lookups of d = 128,
 //   2^16, 2^18, 2^19, 2^22 slots: 672 / 1709, 672 / 688, 679 / 507, 675 / 332;
 //   few tokens leave its windows empty: from 2^16 tokens on.  Z = 1, d = 512, uniform ids, 17.6 K tokens 435 / 515, 78 K 1976 / 602;
 //   the sort and the walk cost by the token, atomics by the request: from eight blocks a row on, from four
@@ -865,6 +865,13 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 //   Z = 2, 852 K, 25 M 770 / 342 (2110 / 1435);  208 K, 25, 58 M 207 / 158 (264 / 185), 276 / 249 (384 / 265)
 //   d = 16, Z = 1, 852 K, 25 M 177 / 144 (207 / 175);  d = 8, 1.4 M 230 / 199 (252 / 229);  d = 512, 208 K 1615 / 437 (3662 / 2366)
 const uint32_t kElemMostZ = 2, kElemLeastRegions = 32, kElemMostRegions = 3600;
+// Regions of that route's last kernel, a workgroup each: 2^14 slots, fewer where those would leave CUs idle.  Backward, us, regions of 2^10,
+// 2^11, 2^12, 2^13, 2^14 slots (the pairs, always 2^14), 26 tables of 10 ids and up to 100 K:
+//   Z = 1, d = 128, 208 K lookups  0.5 M slots 103, 104, 117, 148, 211 (156);  1 M 112, 104, 105, 119, 152 (138);  2 M 133, 113, 104, 105, 120 (125);
+//   4 M 175, 134, 113, 105, 106 (119);  8 M 253, 176, 135, 116, 108 (123)
+//   Z = 2, d = 128, 858 K  0.5 M 232, 227, 280, 382, 594 (418);  1 M 232, 229, 227, 278, 385 (358);  2 M 241, 230, 227, 227, 282 (325);  4 M 278, 241, 230, 227, 225 (299)
+//   Z = 2, d = 16, 1300 K  0.5 M 138, 140, 156, 187, 251 (221);  2 M 146, 142, 140, 141, 157 (167)
+const uint32_t kRunLeastRegions = 192;
 const uint64_t kElemLeast = 1u << 23, kElemLeastTokens = 1u << 16;
 // Room for the runs' rows: two floats per array slot, or 2^26.  What does not fit goes by atomics.  Where all tokens differ,
 // little of a much larger problem would, and the walk is then in vain, so gradient elements may be eight times half of it at
@@ -1105,6 +1112,8 @@ BwdPlan plan_backward_with(bool tuned, const robe_hash_t *caller_hash, const Opt
         const uint64_t rows_fit = room * 2 / h->d & ~63ull, whole = (n + 63) & ~63ull;
         pl.runs.place.most = (uint32_t)(rows_fit < whole ? rows_fit : whole);
         pl.all_fit = n <= pl.runs.place.most;
+        pl.runs.shift = robe::kPlaceShift;
+        while (pl.runs.shift > 0 && h->m >> pl.runs.shift < kRunLeastRegions) --pl.runs.shift;
     }
     r.n = (uint32_t)n;
     r.rows = (uint32_t)rows;
@@ -1361,7 +1370,7 @@ int launch_dedup_backward(const robe_hash_t *h, const Opt &opt, const BwdPlan &p
             else robe::run_turn_kernel<false><<<tgrid, nblock, 0, stream>>>(p, r, l, grad_out);
             if (int rc = check_launch("backward (turn runs)")) return rc;
             if (int rc = probe(opt, ROBE_PROBE_REDUCE, false, stream)) return rc;
-            const dim3 pgrid((uint32_t)((h->m + (1u << robe::kPlaceShift) - 1) >> robe::kPlaceShift)), pblock(robe::kPlaceBlock);
+            const dim3 pgrid((uint32_t)((h->m + (1u << l.shift) - 1) >> l.shift)), pblock(robe::kPlaceBlock);
             const size_t lds = (size_t)4 * robe::kRunSlots;
             if (int rc = allow_lds(robe::run_reduce_kernel<0>, lds, "backward (reduce runs)")) return rc;
             if (int rc = allow_lds(robe::run_reduce_kernel<1>, lds, "backward (reduce runs)")) return rc;

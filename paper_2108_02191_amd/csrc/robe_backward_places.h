@@ -14,7 +14,7 @@
 //   S2 place    entry (see place_entry) and source row of every run.  Runs past the room for their rows (how many there will be
 //               is not known on the host) are added to the gradient array by float atomics here.
 //   S3 turn     tiles of 64 runs, element by element.
-//   S4 reduce   a workgroup per 2^14 slots: for every element and window, tile by tile, the entries' places, and the values of
+//   S4 reduce   a workgroup per region of up to 2^14 slots (RunPlan::shift): for every element and window, tile by tile, the entries' places, and the values of
 //               those that lie in the region, added to an LDS copy; then the rule applied to it.  ds_add_f32 runs at 0.33
 //               lanes per clock and CU on this GPU, a compare-and-swap at 2.2 (random places) to 4.7 (neighbours), but only one
 //               lane of those at a place gets through, so the few that do not try once more and then take the slow one.
@@ -41,6 +41,7 @@ struct RunPlan {
     uint32_t *rank;        // [n] at run starts: which of its bucket the run is
     uint32_t *tg;          // [most] token part of the sign hash (sign on only)
     float *tiles;          // [most / 64][d][64]
+    uint32_t shift;        // log2 of the slots of a region of S4
 };
 
 __device__ __forceinline__ uint32_t runs_used(const PlacePlan &s) { return min(s.starts[s.buckets], s.most); }
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
     const uint32_t t = threadIdx.x, lane = t & 63u, last_tile = (used - 1u) >> 6;
     constexpr uint32_t kWaves = kPlaceBlock / 64u;
     auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
-    for (uint32_t i = t; i < kRunSlots; i += kPlaceBlock) acc[i] = 0.0f;
+    for (uint32_t i = t; i < 1u << l.shift; i += kPlaceBlock) acc[i] = 0.0f;      // (the lanes' own words may hold anything)
     // a lane's window: element and class (see place_regions_kernel; every element has windows of its own, since a block may end in the next region)
     const uint32_t wave = uniform(t >> 6), my_w = wave + lane * kWaves, my_i = my_w >> 1;
     const bool my_live = my_w < 2u * p.d;
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
     const uint32_t my_base = my_w & 1u ? least : 0u, my_width = my_w & 1u ? 0u - least : least;
     uint32_t my_shift = wrap(mod_m(my_cc, p.m, p.m_recip) + (my_live ? my_i - my_c * p.Z : 0u), p.m);
     if (my_w & 1u) my_shift = wrap(my_shift + p.m - mod_m(kP, p.m, p.m_recip), p.m);
-    const uint32_t r0 = blockIdx.x << kPlaceShift, len = min(1u << kPlaceShift, p.m - r0);
+    const uint32_t r0 = blockIdx.x << l.shift, len = min(1u << l.shift, p.m - r0);
     const PlaceWindow my = place_window(p, l.place, used, r0, len, my_shift, my_live);
     if (!__syncthreads_or((int)(my.count | my.over))) return;     // nothing lands here
     RunWalk k;
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(kPlaceBlock, 8) void run_reduce_kernel(Params p, Re
     // (short windows: the tiles after the first would mostly be requested in vain, and the walk is bound by what it issues.  208 K
     // lookups, d = 128, tables of up to 100 K ids, 50 M slots, whole backward: Z = 1 204 -> 176 us, Z = 2 193 -> 169; 117 entries
     // a window, 852 K lookups: 275, one at a time 278)
-    if (((uint64_t)used << kPlaceShift) <= (uint64_t)kRunShort * p.m) run_walk<1>(p, k, entries, tiles, acc);
+    if (((uint64_t)used << l.shift) <= (uint64_t)kRunShort * p.m) run_walk<1>(p, k, entries, tiles, acc);
     else run_walk<kRunAhead>(p, k, entries, tiles, acc);
     __syncthreads();
     run_write_back<RULE>(s, acc, r0, len, dst, state, lr, eps, vec_ok);
