@@ -1,7 +1,7 @@
 """The fused step in two steps clears its gradient array beside the first kernel of the sort: parity with the oracle,
 exact on small integers, from a workspace full of NaN, for keys hashed in the sort and keys written before it, both
 sorts, arrays that are no whole number of vectors or shorter than a workgroup's share, mixed dimensions, and small
-blocks sorted by value whose pairs do not all fit."""
+blocks, the rows of whose runs do not all fit."""
 import numpy as np
 import pytest
 import torch
@@ -51,10 +51,10 @@ def test_two_steps_of_mixed_dimensions_clear_their_gradient():
     assert np.array_equal(state.cpu().numpy(), np.float32(ref) * np.float32(ref))       # (integers below 2^12: squares are exact)
 
 
-@pytest.mark.parametrize("n,d,bags", [(270_000, 128, False), (270_000, 128, True), (2**21 + 4, 32, False)])
-def test_pairs_without_room_clear_their_gradient(n, d, bags):
-    """More than 2^25 elements of blocks of one float on a small array: what finds no room among the pairs is added with
-    atomics, so the step goes through a gradient array."""
+@pytest.mark.parametrize("n,d,bags", [(540_000, 128, False), (540_000, 128, True), (2**21 + 2**17, 32, False)])
+def test_runs_without_room_clear_their_gradient(n, d, bags):
+    """More than 2^26 elements of blocks of one float on a small array, nearly every id another one: the runs whose rows find no
+    room are added with atomics, so the step goes through a gradient array."""
     m, F = 600_011, 2
     h, H = P.both_hashes(n, m, d, 1, 0)
     rng = np.random.default_rng(n)
@@ -64,7 +64,8 @@ def test_pairs_without_room_clear_their_gradient(n, d, bags):
     use = ids if bags else ids.reshape(B, F)
     G = rng.integers(-2, 3, size=(B, F, d)).astype(np.float32)
     need = robe.robe_fused_workspace_bytes(h, B, F, n)
-    assert need > robe.robe_fused_workspace_bytes(h, B, F, n, robe.options(backward_route=robe.ROUTE_COMBINE))      # the pairs' route
+    assert need > robe.robe_fused_workspace_bytes(h, B, F, n, robe.options(backward_route=robe.ROUTE_COMBINE))      # the route of small blocks
+    assert need >= robe.robe_workspace_bytes(h, B, F, n) + 4 * m and len(np.unique(ids)) * d > 2**26 + 2**20
     ref, _ = oracle.backward(H, G, use, off, B, F, threads=8)
     array = torch.zeros(m, device="cuda:0")
     robe.robe_backward_sgd(h, P.to_dev(G), P.to_dev(use), P.to_dev(off) if bags else None, B, F, array, 1.0, workspace=_nan(need))

@@ -1,4 +1,4 @@
-"""The backward of small blocks (Z <= 2 on large batches: the values sorted by region): parity with the
+"""The backward of small blocks (Z <= 2 on large batches: runs by the place they write): parity with the
 oracle slot by slot on small-integer gradients, whose float32 sums are exact in any order.  Cases cover
 row widths that are and are not powers of two, the widest and the narrowest rows of the route, blocks
 larger than embeddings, array lengths at both ends of its range and past it, tokens repeated thousands
@@ -61,12 +61,12 @@ def test_small_blocks_match_the_oracle(m, d, Z, sign, bags):
     assert np.array_equal(Md.cpu().numpy(), M - ref.astype(np.float32))
 
 
-# (m, d, Z, sign, bags): the fewest regions with a last one of five slots, the narrowest rows, and more
-# pairs than there is room for (2^25 on arrays this small): the rest is added with atomics
+# (m, d, Z, sign, bags, elements): the smallest array with a last region of five slots, the narrowest rows, and rows of more
+# runs than there is room for (2^26 floats on arrays this small): the rest is added with atomics
 MORE = [
     (31 * 2**14 + 5, 100, 1, 0, False, 2**23),
-    (31 * 2**14 + 5, 128, 1, 0, False, 2**25 + 2**22),
-    (600_007, 128, 2, 1, True, 2**25 + 2**22),
+    (31 * 2**14 + 5, 128, 1, 0, False, 2**26 + 2**22),
+    (600_007, 128, 2, 1, True, 2**26 + 2**22),
     (1_000_003, 4, 1, 0, False, 2**23),
     (1_000_003, 8, 2, 1, True, 2**23),
     (1_000_003, 16, 2, 1, False, 2**23),
@@ -79,7 +79,7 @@ def test_small_blocks_at_the_edges_of_their_room(m, d, Z, sign, bags, elems):
     rng = np.random.default_rng(m % 1009 + d)
     F = 3
     n = -(-(elems + 1000) // (d * F)) * F
-    ids = rng.permutation(n).astype(np.int64)               # all distinct: a pair for every gradient element
+    ids = rng.permutation(n).astype(np.int64)               # all distinct: a run for every token
     ids[:5000] = 7
     B, off = n // F, None
     if bags:
@@ -88,6 +88,8 @@ def test_small_blocks_at_the_edges_of_their_room(m, d, Z, sign, bags, elems):
         off[0], off[-1] = 0, n
     need = robe.robe_workspace_bytes(h, B, F, n)
     assert need > robe.robe_workspace_bytes(h, B, F, n, robe.options(backward_route=robe.ROUTE_COMBINE))
+    # (without room for all the fused step goes through a gradient array)
+    assert (robe.robe_fused_workspace_bytes(h, B, F, n) >= need + 4 * m) == (n * d - 5000 * d > 2**26)
     G = rng.integers(-2, 3, size=(B, F, d)).astype(np.float32)
     dG, dids, doff = P.to_dev(G), P.to_dev(ids), P.to_dev(off)
     ref, _ = oracle.backward(H, G, ids, off, B, F, threads=8)

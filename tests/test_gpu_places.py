@@ -55,6 +55,50 @@ def test_served_rows_have_the_gathered_bits(m, d, Z, F, kind, sign):
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
 
 
+def _least(m, d, Z):
+    """From how many distinct tokens on the lists are served."""
+    C = d // Z
+    if C <= 128:
+        return m // 8 // C + 1
+    return (m // 1024 * 5 // 8 + m * 3 // 64 // C if Z == 1 else m // 1024) + 1
+
+
+@pytest.mark.parametrize("m,d,Z,F,kind,sign", CASES)
+def test_the_cases_are_served_or_not(m, d, Z, F, kind, sign):
+    """What the device decides by, from the ids alone: distinct tokens enough, and as many free rows (of those before the last
+    samples, 5 words a lookup at the most)."""
+    B = _first_batch(d, Z, F) + 3
+    ids = _ids(kind, B, F)
+    keep = B - 5 * B // d - 2
+    tokens = len(np.unique(ids[:keep] % (2**31 - 1) + (np.arange(F) << 32)))
+    free = keep * F - tokens
+    assert (tokens >= _least(m, d, Z) and free >= _least(m, d, Z) + 64 * 32) == (kind not in ("same", "distinct")), (tokens, free)
+
+
+# arrays of more than 100 M slots and outputs past 2 GiB, where sizes in bytes have the top bit of 32 set, up to the last size of the route
+@pytest.mark.parametrize("m,d,Z,B,kind,sign", [(2**27 + 5, 128, 1, 170_000, "zipf", 1), (2**27 - 3, 128, 2, 165_000, "few", 0), (2**29 - 1, 128, 1, 322_638, "few", 0),
+                                               (2**23 + 77, 512, 1, 80_659, "few", 1)])
+def test_large_arrays_and_outputs(m, d, Z, B, kind, sign):
+    F = 26
+    n = B * F
+    assert 2**31 < n * d * 4 < 2**32
+    h, _ = P.both_hashes(d, m, d, Z, sign)
+    A = torch.randn(m, device=DEV)
+    if kind == "few":             # twice as many distinct tokens as are worth it, in most of the rows
+        I = torch.randint(0, 2 * _least(m, d, Z) // F, (B, F), device=DEV)
+    else:
+        I = P.to_dev(_ids(kind, B, F))
+    assert len(torch.unique(I + (torch.arange(F, device=DEV) << 32))) >= _least(m, d, Z)
+    room = torch.full((n * d + 8,), 7.0, device=DEV)
+    out = room[4:4 + n * d].view(B, F, d)
+    assert kernels(lambda: robe.robe_forward(h, A, I, None, B, F, out=out)) == 8
+    robe.robe_forward(h, A, I, None, B, F, out=out)
+    want = robe.robe_forward(h, A, I, None, B, F, options=robe.options(row_order=robe.ROWS_BY_TABLE))
+    for first in range(0, B, 50_000):                          # (a comparison holds copies)
+        assert torch.equal(out[first:first + 50_000].view(torch.int32), want[first:first + 50_000].view(torch.int32))
+    assert (room[:4] == 7.0).all() and (room[4 + n * d:] == 7.0).all()
+
+
 @pytest.mark.parametrize("m,d,Z,off,launches", [(2**23 - 1, 128, 1, 0, 5), (2**23, 100, 1, 0, 5), (2**23, 128, 4, 0, 5), (2**23, 128, 1, 1, 5), (2**26, 128, 1, 0, 5),
                                                 (2**23, 128, 1, 4, 8)])
 def test_what_takes_the_route(m, d, Z, off, launches):

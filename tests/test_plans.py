@@ -42,8 +42,8 @@ def test_the_default_sort_refuses_no_reproducible_call_that_a_longer_sort_takes(
     assert taken > 1000
 
 
-def test_small_blocks_are_sorted_by_value_only_where_it_pays():
-    """Arrays of 32 regions of 2^14 slots or more, rows of eight blocks (four if all is sure to fit), 2^16 tokens,
+def test_small_blocks_go_by_place_only_where_it_pays():
+    """The runs moved by the place they write: arrays of 32 times 2^14 slots or more, rows of eight blocks (four if all is sure to fit), 2^16 tokens,
     2^23 gradient elements."""
     took = 0
     for m in (5, 16_384, 2**19 - 2**14, 2**19 - 2**14 + 1, 1_000_003, 25_000_000, 3600 * 2**14, 3600 * 2**14 + 1):
