@@ -203,7 +203,9 @@ int robe_offsets(const robe_hash_t *hash, const int64_t *indices, int64_t n, int
  *              until the rows are written, with 64-bit atomics, and copy the rows of repeated tokens
  *              out of it: memory that is slow to read back, or takes no such atomics, wants a
  *              row_order other than ROBE_ROWS_AUTO, which gathers every row.  So do ids that hardly
- *              repeat, which pay up to a tenth for the lists
+ *              repeat, which pay up to a tenth for the lists (and on arrays of 2^23 slots or more, with
+ *              blocks of one or two floats, so do tables that hold few rows for the array, which pay
+ *              some 10 to 30 us)
  *   options    NULL or host robe_options_t (fwd_elems, fwd_strided, tile_lookups, row_order are read)
  * Errors: ROBE_EINVAL, ROBE_EHIP.  batch == 0 is a no-op.
  */
@@ -235,10 +237,11 @@ int robe_workspace_bytes(const robe_hash_t *hash, int64_t batch, int32_t n_featu
  * and issue the atomics once per run (ROBE_ROUTE_COMBINE); the largest (arrays of 2^26 slots or more
  * with 2^21 tokens or more) then collect the blocks by destination region and sum each region in LDS,
  * with no float atomic at all (ROBE_ROUTE_REGIONS; the route of the reproducible option).  Large
- * scatters of blocks of one or two floats, on arrays of half a million to 59 million slots, sort the
- * values themselves by region instead (nothing asks for that by name; beside the sort's buffers the
- * workspace then holds at most three floats per array slot or 384 MiB, whichever is more; what finds no
- * room there is added with atomics).  The
+ * scatters of blocks of one or two floats, on arrays of half a million to 59 million slots, order the
+ * combined rows by the place they write, move every row once and add it region by region instead
+ * (nothing asks for that by name; beside the sort's buffers the workspace then holds at most three
+ * floats per array slot or 384 MiB, whichever is more; rows that find no room there are added with
+ * atomics).  The
  * sorted routes need the workspace, rows and n_indices below 2^31 - 1 and d <= 512 (with Z > d,
  * Section 3.3, tokens are sorted by the array offset of their d slots instead of the token hash);
  * ROBE_ROUTE_REGIONS also needs d / Z and the lane group to be powers of two, at most 2^30 array

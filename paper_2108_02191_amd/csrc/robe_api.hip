@@ -455,12 +455,17 @@ int allow_lds(K kernel, size_t bytes, const char *what)
 // Whether the distinct tokens of such a lookup are served region by region of the array (robe_forward_places.h): where
 // one L2 does not hold much of it, and the lookups read as many blocks as it has slots, or reading it all is not worth it.
 // Forward, us, gathered / by place, d = 128, Zipf ids of 10 M a table and (ids that never repeat):
-//   Z = 1, 9 M slots, 208 K lookups 304 / 189 (460 / 474);  25 M, 198 K 316 / 249 (486 / 501), 852 K 1074 / 421 (2007 / 2057)
-//   Z = 2, 25 M, 468 K 384 / 239 (610 / 630);  d = 64, 9 M, 520 K 345 / 243 (578 / 608);  d = 512, 25 M, 78 K 532 / 497 (744 / 762)
+//   Z = 1, 9 M slots, 208 K lookups 304 / 186 (462 / 478);  25 M, 199 K 320 / 199 (489 / 502), 852 K 1072 / 391 (2008 / 2057);
+//   100 M, 797 K 1069 / 518 (1967 / 1999);  500 M, 4.0 M 5141 / 2868 (11913 / 12076)
+//   Z = 2, 25 M, 469 K 383 / 236 (612 / 637);  250 M, 4.0 M 2765 / 2159 (5822 / 5972)
+//   d = 64, Z = 1, 9 M, 520 K 345 / 159 (577 / 609);  d = 512, Z = 1, 25 M, 78 K 535 / 418 (747 / 761)
 // 26 tables, spaced evenly on a log scale, of 10 ids and up to 100 K, to 3 M, to 40 M:
-//   Z = 1, 10 M slots, 208 K 138 / 104, 169 / 108, 193 / 113;  25 M, 208 K 144 / 131, 180 / 135, 203 / 137, 852 K 323 / 224, 471 / 243,
-//   571 / 265;  50 M, 414 K 210 / 219, 288 / 222, 337 / 232;  Z = 2, 10 M, 468 K 151 / 131, 196 / 149, 224 / 164;  50 M, 859 K 240 / 254, 323 / 262
-// (where the tables hold too few distinct tokens, 210 / 219 and 240 / 254, the lists are turned down: see PlacePlan::least)
+//   Z = 1, 10 M slots, 208 K 139 / 102, 170 / 108, 193 / 111;  25 M, 199 K 134 / 127, 173 / 131, 196 / 135, 852 K 322 / 210, 471 / 228, 573 / 251;
+//   50 M, 414 K 209 / 220, 286 / 225, 337 / 231;  100 M, 1.6 M 541 / 546, 812 / 535, 998 / 581;  250 M, 2.0 M 665 / 676, 1023 / 1041, 1272 / 994;
+//   500 M, 7.8 M 1966 / 1916, 3254 / 2596, 4230 / 2973
+//   Z = 2, 10 M, 469 K 153 / 130, 196 / 148, 224 / 160;  33 M, 534 K 174 / 185, 228 / 185, 263 / 199;  50 M, 859 K 240 / 254, 322 / 264, 379 / 287;
+//   250 M, 4.0 M 908 / 927, 1265 / 1298, 1514 / 1353
+// (209 / 220, 240 / 254 and their like: too few distinct tokens, the lists are turned down, see PlacePlan::least)
 // Blocks of four (where this was not kept): 25 M, 852 K, to 40 M 311 / 242, never repeating 600 / 671; 520 K 191 / 174, 367 / 419.
 bool places_pay(const robe_hash_t *h, int64_t rows, const float *out)
 {
@@ -845,8 +850,8 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 }
 
 // Small blocks take the route of robe_backward_places.h up to this block size and from this many gradient elements on.
-// Its lines were drawn for the kernels it replaced, which sorted (place, value) pairs and were slower at every size measured
-// since (below), against float atomics, us: forward + backward on the 100 MB array, d = 128, 852 K lookups, atomics / pairs
+// Its lines were drawn for the kernels it replaced, which sorted (place, value) pairs, against float atomics, and were not drawn
+// anew (pairs against places: below), us: forward + backward on the 100 MB array, d = 128, 852 K lookups, atomics / pairs
 // Z = 1 2353 / 1551, Z = 2 1266 / 1007, Z = 4 750 / 772; Z = 1 with 13 K, 52 K, 208 K lookups 140 / 188, 255 / 251, 725 / 486.
 // Backward alone, atomics / pairs:
 //   the last kernel had one workgroup per 2^14 slots: from 32 of them on.  Z = 2, 858 K lookups of d = 128,
@@ -859,6 +864,10 @@ uint32_t pick_region_shift(const robe_hash_t *h, int requested)
 //   Z = 1, 208 K lookups, 10, 25, 50 M slots 124 / 111, 145 / 117; 142 / 135, 169 / 141; 176 / 176, 218 / 193;  852 K, 25 M 353 / 242, 434 / 275
 //   Z = 2, 208 K, 25, 50 M 137 / 131, 168 / 140; 162 / 169, 205 / 188;  858 K, 50 M 377 / 299, 495 / 337
 //   Z = 4 (atomics / places, where it was not kept), 25 M, 208 K 97 / 141, 153 / 149;  852 K 221 / 257, 403 / 277
+//   The pairs were the quicker ones where windows are nearly empty, from 50 M slots on with few tokens: 50 M, Z = 2, 66 K lookups, up to
+//   100 K, 400 K, 3 M ids 133 / 141, 137 / 142, 148 / 144;  208 K, up to 100 K, 200 K, 400 K 161 / 170, 170 / 174, 174 / 175;  59 M, Z = 1,
+//   208 K, up to 100 K, 400 K, 3 M 186 / 201, 199 / 209, 216 / 216; with ids of 1 K 117 / 149 (50 M, Z = 2, 208 K); and where narrow rows
+//   never repeat: d = 8, Z = 1, 1300 K on 2, 4, 8 M slots 212 / 235, 209 / 232, 214 / 227.  Regions of 2^15 slots there: 163 / 174 (50 M, Z = 2, 208 K).
 // Zipf ids of 10 M a table (and ids that never repeat):
 //   d = 128, Z = 1, 852 K lookups, 0.6, 2.1, 8.4, 25 (signs), 58 M slots 1449 / 934 (4387 / 3391), 1198 / 405 (3853 / 2527), 1163 / 333,
 //   1190 / 361 (3762 / 2401), 746 / 412 (2694 / 603);  104 K lookups, 4.2, 25 M 152 / 95 (178 / 102), 179 / 137 (205 / 133)

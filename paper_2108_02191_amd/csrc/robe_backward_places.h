@@ -20,7 +20,7 @@
 //               lane of those at a place gets through, so the few that do not try once more and then take the slow one.
 //
 // Backward of 852 K Zipf lookups, d = 128, Z = 1, 100 MB array: 405 -> 286 us (S1 9, R3 8, S2 8, S3 47, S4 106 instead of
-// the pairs' 294); with ids of 10 M a table, for whose pairs there was no room, 1190 -> 361.  S4 without its additions takes
+// the pairs' 294); with ids of 10 M a table, for whose pairs there was no room, 1182 -> 346.  S4 without its additions takes
 // 45 us less, without the write-back 43 (each measured in a copy); double words and their 64-bit additions, at half the
 // region or one workgroup per CU, 13 and 20 more; every compare-and-swap waited for by itself, 6 more.
 // The order of the additions is not fixed (the reproducible option keeps region_reduce_kernel).

@@ -27,12 +27,13 @@
 // place: Z = 1, 413 K lookups of 31 K distinct tokens, 53 M slots 192 / 274 us then, 189 / 202 now; Z = 2, 858 K of 62 K, 55 M 244 / 356,
 // 245 / 260; Z = 1, 780 K of 31 K, 100 M 228 / 344, 229 / 240.
 //
-// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 575 -> 258 us (D1 30 instead
-// of 24, F1 8, F2 9, F3 80, F4 35, D3 72 instead of 98, D4 17 instead of 14 (29 with all of its rows gathered), clearing 6, where
-// the gather took 434).  F3 (76 to 85 us in several runs, 85 beside the variants below) has three parts that hardly overlap: its region's load 35, the walk 32, the stores 28 (161 MB, as a line's elements come from two windows).  A
-// hash and a page of its own for every entry instead of keys that compare packed and one page a tile: 112.  Regions of
-// 2^13 floats: 110; of 2^15, one workgroup per CU: 91 (short of entries for so long windows elsewhere); every
-// workgroup three regions, the next loaded during the walk: 100 (the walk's loads then wait for it).
+// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 588 -> 261 us (D1 30 instead
+// of 24, F1 8, F2 10, F3 84, F4 34, D3 72 instead of 99, D4 17 instead of 15 (29 with all of its rows gathered), clearing 6, where
+// the gather took 440).  F3 has three parts that hardly overlap: its region's load 35, the walk 32, the stores 28 (161 MB, as a line's
+// elements come from two windows).  Forms tried beside an F3 of 95: a hash and a page of its own for every entry instead of keys that
+// compare packed and one page a tile 112; every workgroup three regions, the next loaded during the walk 100 (the walk's loads then wait
+// for it).  Beside one of 78 (the same lookups, the array in the last-level cache): regions of 2^13 floats 123; of 2^15, one workgroup
+// per CU, 81.  With short windows (d = 512, Z = 1, 78 K lookups) those take 348 and 127 us against 185.
 #pragma once
 #include "robe_backward_regions.h"
 #include "robe_forward_distinct.h"
