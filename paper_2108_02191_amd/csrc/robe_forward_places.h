@@ -22,12 +22,12 @@
 //
 // The lists (two and a half words a lookup) lie in the last samples' rows until D4.  What has no room - ids that hardly
 // repeat leave few rows free - is gathered by F2 as D2 does there, and so are all where there are too few entries (PlacePlan::least):
-// such a call costs what F1, F3 and F4 take to start and D1's counts, 10 to 15 us more than one without lists.  It was a
+// such a call costs what F1, F3 and F4 take to start and D1's counts, 10 to 15 us more than one without lists (up to 33 at 250 M slots).  It was a
 // quarter of the call and more while F2 gathered 64 rows a wavefront and D4 all of its rows: uniform ids, d = 128, gathered / by
 // place: Z = 1, 413 K lookups of 31 K distinct tokens, 53 M slots 192 / 274 us then, 189 / 202 now; Z = 2, 858 K of 62 K, 55 M 244 / 356,
 // 245 / 260; Z = 1, 780 K of 31 K, 100 M 228 / 344, 229 / 240.
 //
-// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 588 -> 261 us (D1 30 instead
+// 852 K Zipf lookups over 26 tables (178 K distinct tokens), d = 128, 100 MB array, Z = 1: 588 -> some 262 us (D1 30 instead
 // of 24, F1 8, F2 10, F3 84, F4 34, D3 72 instead of 99, D4 17 instead of 15 (29 with all of its rows gathered), clearing 6, where
 // the gather took 440).  F3 has three parts that hardly overlap: its region's load 35, the walk 32, the stores 28 (161 MB, as a line's
 // elements come from two windows).  Forms tried beside an F3 of 95: a hash and a page of its own for every entry instead of keys that
